@@ -45,17 +45,34 @@ __device__ inline int find_segment(const DevSeg* segs, int n_segs, int64_t b, F 
     return lo;
 }
 
-// Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2).  Virtual index
-// v in [0, 8 ceil(total/8)) maps to item (v % 8) * ceil(total/8) + v / 8, so XCD x works through
-// the contiguous eighth [x ceil(total/8), (x+1) ceil(total/8)) of the item list and the tiles of
-// one execution unit share one L2.  Items >= total are skipped.
+// Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2).  Items are dealt to
+// the XCDs in runs of 2^lg consecutive ones: virtual index v in [0, xcd_span) maps to item
+// ((v / 8 / 2^lg) * 8 + v % 8) * 2^lg + (v / 8) % 2^lg, so that the tiles of one execution unit
+// mostly share one L2 while every XCD sees units from the whole range.  (One contiguous eighth of
+// the list per XCD left CUs idle 31 % of the density launches of a 100-atom block and 38 % of
+// the basis launches: eighths at the rim of a structure hold shorter lists.)  Items >= total are
+// skipped.
 constexpr int N_XCD = 8;
-__host__ __device__ inline int64_t xcd_span(int64_t total) { return N_XCD * ((total + N_XCD - 1) / N_XCD); }
-__device__ inline int64_t xcd_item(int64_t v, int64_t total)
+__host__ __device__ inline int64_t xcd_span(int64_t total, int lg)
 {
-    const int64_t per = (total + N_XCD - 1) / N_XCD;
-    return (v % N_XCD) * per + v / N_XCD;
+    const int64_t run = (int64_t)N_XCD << lg;
+    return (total + run - 1) / run * run;
 }
+__device__ inline int64_t xcd_item(int64_t v, int lg)
+{
+    const int64_t q = v / N_XCD;
+    return ((((q >> lg) * N_XCD) + v % N_XCD) << lg) + (q & ((1 << lg) - 1));
+}
+// Runs of at most 2^most items, shorter ones where the launch would otherwise have fewer than
+// eight runs per XCD to even out.
+static int xcd_run(int64_t total, int most)
+{
+    int lg = 0;
+    while (lg < most && total >> (lg + 7) > 0) ++lg;
+    return lg;
+}
+constexpr int HRUN = 5;  // tile pairs (28 of a unit with 7 tiles): 16 to 64 measure alike, 512 a few percent slower
+constexpr int NRUN = 4;  // column tiles (7 to 11 of a unit): runs of 4 cost the 375-atom slab 4 %, 64 gain nothing
 
 // (dx*dx + dy*dy) + dz*dz without contraction: the same arithmetic that decides relevance.
 __device__ inline double dist2_exact(double dx, double dy, double dz)
@@ -160,7 +177,7 @@ constexpr int BASIS_WIN = 16;      // values per pair staged at a time for the r
 // parameters) are staged in LDS first, so that a pair's chain of table lookups stays on chip;
 // a unit or system larger than the staging arrays reads them from global memory instead.
 template <typename T, bool SPLINE_LDS, int EX>
-__global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict__ segs, int n_segs, int64_t total,
+__global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg,
                                                        int spline_lds)
 {
     extern __shared__ double lds_spline[];
@@ -180,8 +197,8 @@ __global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict_
     (void)spline_lds;  // the launcher sized the dynamic LDS for the table
     const int tid = threadIdx.x;
     const DevSys* table_of = nullptr;  // the system whose spline table is in LDS
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total); v_ += gridDim.x) {
-        const int64_t bi = xcd_item(v_, total);
+    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
+        const int64_t bi = xcd_item(v_, lg);
         if (bi >= total) continue;
         // item = (unit, slice): BASIS_SLICES consecutive items split one unit's points
         const int64_t b = bi / BASIS_SLICES;
@@ -547,9 +564,9 @@ __global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict_
     }
 }
 
-static unsigned grid_for(int64_t n, int64_t max_grid)
+static unsigned grid_for(int64_t n, int lg, int64_t max_grid)
 {
-    const int64_t span = xcd_span(n);
+    const int64_t span = xcd_span(n, lg);
     if (max_grid > 0) {
         const int64_t cap = std::max<int64_t>(N_XCD, max_grid / N_XCD * N_XCD);
         if (span > cap) return (unsigned)cap;
@@ -578,7 +595,7 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
         }
         max_grid = 2 * (int64_t)std::max(1, n_cu.load());
     }
-    const dim3 g(grid_for(n_items, max_grid)), b(256);
+    const dim3 g(grid_for(n_items, 2, max_grid)), b(256);
     const bool staged = spline_lds > 0;
     const size_t lds = (size_t)spline_lds * sizeof(double);
     // dynamic LDS above 64 KiB must be allowed per kernel, once per device
@@ -608,8 +625,8 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
     }
 #define NAO_BASIS_LAUNCH(TT, EE)                                                                                 \
     do {                                                                                                       \
-        if (staged) hipLaunchKernelGGL((basis_kernel<TT, true, EE>), g, b, lds, st, segs_dev, n_segs, n_items, spline_lds); \
-        else hipLaunchKernelGGL((basis_kernel<TT, false, EE>), g, b, lds, st, segs_dev, n_segs, n_items, 0);  \
+        if (staged) hipLaunchKernelGGL((basis_kernel<TT, true, EE>), g, b, lds, st, segs_dev, n_segs, n_items, 2, spline_lds); \
+        else hipLaunchKernelGGL((basis_kernel<TT, false, EE>), g, b, lds, st, segs_dev, n_segs, n_items, 2, 0);  \
     } while (0)
 #define NAO_BASIS_EXTRA(TT)                                           \
     do {                                                              \
@@ -687,7 +704,7 @@ template <> struct Mma<float> {
 // w v once per value as it is stashed) is faster than the directly-loaded form; FP64 uses the
 // latter.
 template <typename T>
-__global__ __launch_bounds__(256, 4) void h_kernel(const DevSeg* __restrict__ segs, int n_segs, int64_t total)
+__global__ __launch_bounds__(256, 4) void h_kernel(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     typedef Mma<T> M;
     constexpr int HK = KCHUNK;              // points per chunk
@@ -700,8 +717,8 @@ __global__ __launch_bounds__(256, 4) void h_kernel(const DevSeg* __restrict__ se
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave >> 1, wc = wave & 1;
     const int lr = lane & 15, lk = lane >> 4;
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total); v_ += gridDim.x) {
-        const int64_t b = xcd_item(v_, total);
+    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
+        const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
@@ -814,7 +831,7 @@ __global__ __launch_bounds__(256, 4) void h_kernel(const DevSeg* __restrict__ se
 // into the upper triangle of H.  The 16-byte loads need 16-byte aligned rows: every
 // basis-value block starts on a 64-value boundary of its buffer and ld is a multiple of 64.
 template <typename T, int KC, int S>
-__global__ __launch_bounds__(256) void h_kernel_dma(const DevSeg* __restrict__ segs, int n_segs, int64_t total)
+__global__ __launch_bounds__(256) void h_kernel_dma(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     typedef Mma<T> M;
     constexpr int ROW_SLOTS = TILE * (int)sizeof(T) / 16;     // 16-byte slots per tile row
@@ -828,8 +845,8 @@ __global__ __launch_bounds__(256) void h_kernel_dma(const DevSeg* __restrict__ s
     const int lr = lane & 15, lk = lane >> 4;
     // this lane's slot of every wave load: tile row (within the load's rows) and 16-byte column slot
     const int slot_row = lane / ROW_SLOTS, slot_col = (lane % ROW_SLOTS) * (16 / (int)sizeof(T));
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total); v_ += gridDim.x) {
-        const int64_t b = xcd_item(v_, total);
+    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
+        const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
@@ -955,7 +972,7 @@ __global__ __launch_bounds__(256) void h_kernel_dma(const DevSeg* __restrict__ s
 // K = points in double-buffered chunks of 8 (two products per chunk), four waves of 32x32, FP64
 // atomics into the upper triangle.
 template <typename T>
-__global__ __launch_bounds__(256, 4) void h_kernel_gga(const DevSeg* __restrict__ segs, int n_segs, int64_t total)
+__global__ __launch_bounds__(256, 4) void h_kernel_gga(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     typedef Mma<T> M;
     constexpr int GK = 8;  // points per chunk: half the LDS of 16-point chunks, so that four
@@ -966,8 +983,8 @@ __global__ __launch_bounds__(256, 4) void h_kernel_gga(const DevSeg* __restrict_
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave >> 1, wc = wave & 1;
     const int lr = lane & 15, lk = lane >> 4;
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total); v_ += gridDim.x) {
-        const int64_t b = xcd_item(v_, total);
+    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
+        const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
@@ -1078,7 +1095,7 @@ __global__ __launch_bounds__(256, 4) void h_kernel_gga(const DevSeg* __restrict_
 constexpr int WTILE = 128;
 
 template <typename T>
-__global__ __launch_bounds__(512) void h_kernel_wide(const DevSeg* __restrict__ segs, int n_segs, int64_t total)
+__global__ __launch_bounds__(512) void h_kernel_wide(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     typedef Mma<T> M;
     __shared__ T As[2][KCHUNK][WTILE + 2];
@@ -1086,8 +1103,8 @@ __global__ __launch_bounds__(512) void h_kernel_wide(const DevSeg* __restrict__ 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave >> 1, wc = wave & 1;  // rows 32 wr .. 32 wr + 31, columns 64 wc .. 64 wc + 63
     const int lr = lane & 15, lk = lane >> 4;
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total); v_ += gridDim.x) {
-        const int64_t b = xcd_item(v_, total);
+    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
+        const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
@@ -1195,7 +1212,7 @@ __global__ __launch_bounds__(512) void h_kernel_wide(const DevSeg* __restrict__ 
 // sums, f_j += sum_p grad phi_pj M_pj, into the per-function accumulator fb[N_b][3].
 enum NKind { NK_DENSITY = 0, NK_GRADIENT = 1, NK_FORCE = 2 };
 template <typename T, int NW, int KC, bool DB, int KIND = NK_DENSITY>
-__global__ __launch_bounds__(64 * NW) void n_kernel(const DevSeg* __restrict__ segs, int n_segs, int64_t total)
+__global__ __launch_bounds__(64 * NW) void n_kernel(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     typedef Mma<T> M;
     constexpr bool GRAD = KIND == NK_GRADIENT;
@@ -1232,8 +1249,8 @@ __global__ __launch_bounds__(64 * NW) void n_kernel(const DevSeg* __restrict__ s
     const int lr = lane & 15, lk = lane >> 4;
     // staged position of slot j of row `row` within a buffer (SLOT)
     auto a_slot = [](int row, int j) { return row * KC + ((j ^ ((row / ROWS_128B) & (SPR - 1))) * VPS); };
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total); v_ += gridDim.x) {
-        const int64_t b = xcd_item(v_, total);
+    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
+        const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
@@ -1530,7 +1547,7 @@ constexpr int BKP = BK + 8;  // padded LDS row (80 bytes: keeps 16-byte alignmen
 // after every chunk; FP64 atomics into the upper triangle of H.  At least three waves per SIMD
 // (the two-part form then fits three workgroups per CU: 9 % faster than two).
 template <int NS>
-__global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total)
+__global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     constexpr int NQ = BK * TILE / 256;  // values per thread per chunk and operand
     __shared__ __attribute__((aligned(16))) __bf16 As[2][NS][TILE][BKP];
@@ -1538,8 +1555,8 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave >> 1, wc = wave & 1;
     const int lr = lane & 15, lk = lane >> 4;
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total); v_ += gridDim.x) {
-        const int64_t b = xcd_item(v_, total);
+    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
+        const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
@@ -1671,7 +1688,7 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
 // sums move into FP64 after every 64-function tile; the row dot and the sums over tiles and
 // units are FP64.
 template <int NS, int NB>
-__global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total)
+__global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     constexpr int NT = 1024, RB = 4, RS = 4;
     constexpr int NA = MAX_UNIT_POINTS * BK / NT;  // basis values per thread per chunk (8)
@@ -1683,8 +1700,8 @@ __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int cb = wave & 3, rh = wave >> 2;
     const int lr = lane & 15, lk = lane >> 4;
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total); v_ += gridDim.x) {
-        const int64_t b = xcd_item(v_, total);
+    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
+        const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
@@ -1834,20 +1851,22 @@ hipError_t launch_h(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n_ite
     if (h_tile == WTILE && (mode == MODE_FP64 || mode == MODE_FP32)) {
         if (n_items <= 0 || n_segs <= 0) return hipSuccess;
         if (n_items > 0x7ffffff0) return hipErrorInvalidValue;
-        const dim3 g(grid_for(n_items, max_grid)), b(512);
-        if (mode == MODE_FP64) hipLaunchKernelGGL(h_kernel_wide<double>, g, b, 0, st, segs_dev, n_segs, n_items);
-        else hipLaunchKernelGGL(h_kernel_wide<float>, g, b, 0, st, segs_dev, n_segs, n_items);
+        const int lg = xcd_run(n_items, HRUN);
+        const dim3 g(grid_for(n_items, lg, max_grid)), b(512);
+        if (mode == MODE_FP64) hipLaunchKernelGGL(h_kernel_wide<double>, g, b, 0, st, segs_dev, n_segs, n_items, lg);
+        else hipLaunchKernelGGL(h_kernel_wide<float>, g, b, 0, st, segs_dev, n_segs, n_items, lg);
         return hipGetLastError();
     }
     if (h_tile != TILE) return hipErrorInvalidValue;
     if (n_items <= 0 || n_segs <= 0) return hipSuccess;
     if (n_items > 0x7ffffff0) return hipErrorInvalidValue;
-    const dim3 g(grid_for(n_items, max_grid)), b(256);
+    const int lg = xcd_run(n_items, HRUN);
+    const dim3 g(grid_for(n_items, lg, max_grid)), b(256);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL((h_kernel_dma<double, 16, 3>), g, b, 0, st, segs_dev, n_segs, n_items); break;
-    case MODE_FP32: hipLaunchKernelGGL(h_kernel<float>, g, b, 0, st, segs_dev, n_segs, n_items); break;
-    case MODE_BF16X3: hipLaunchKernelGGL(h_kernel_bf16<2>, g, b, 0, st, segs_dev, n_segs, n_items); break;
-    case MODE_BF16X6: hipLaunchKernelGGL(h_kernel_bf16<3>, g, b, 0, st, segs_dev, n_segs, n_items); break;
+    case MODE_FP64: hipLaunchKernelGGL((h_kernel_dma<double, 16, 3>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL(h_kernel<float>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_BF16X3: hipLaunchKernelGGL(h_kernel_bf16<2>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_BF16X6: hipLaunchKernelGGL(h_kernel_bf16<3>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1858,12 +1877,13 @@ hipError_t launch_n(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n_ite
 {
     if (n_items <= 0 || n_segs <= 0) return hipSuccess;
     if (n_items > 0x7ffffff0) return hipErrorInvalidValue;
-    const dim3 g(grid_for(n_items, max_grid)), b(1024);
+    const int lg = xcd_run(n_items, NRUN);
+    const dim3 g(grid_for(n_items, lg, max_grid)), b(1024);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL((n_kernel<double, 16, 16, true>), g, b, 0, st, segs_dev, n_segs, n_items); break;
-    case MODE_FP32: hipLaunchKernelGGL((n_kernel<float, 16, 16, true>), g, b, 0, st, segs_dev, n_segs, n_items); break;
-    case MODE_BF16X3: hipLaunchKernelGGL((n_kernel_bf16<2, 2>), g, b, 0, st, segs_dev, n_segs, n_items); break;
-    case MODE_BF16X6: hipLaunchKernelGGL((n_kernel_bf16<3, 1>), g, b, 0, st, segs_dev, n_segs, n_items); break;
+    case MODE_FP64: hipLaunchKernelGGL((n_kernel<double, 16, 16, true>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL((n_kernel<float, 16, 16, true>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_BF16X3: hipLaunchKernelGGL((n_kernel_bf16<2, 2>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_BF16X6: hipLaunchKernelGGL((n_kernel_bf16<3, 1>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1873,10 +1893,11 @@ hipError_t launch_n_grad(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t 
 {
     if (n_items <= 0 || n_segs <= 0) return hipSuccess;
     if (n_items > 0x7ffffff0) return hipErrorInvalidValue;
-    const dim3 g(grid_for(n_items, 0)), b(1024);
+    const int lg = xcd_run(n_items, NRUN);
+    const dim3 g(grid_for(n_items, lg, 0)), b(1024);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL((n_kernel<double, 16, 16, true, NK_GRADIENT>), g, b, 0, st, segs_dev, n_segs, n_items); break;
-    case MODE_FP32: hipLaunchKernelGGL((n_kernel<float, 16, 16, true, NK_GRADIENT>), g, b, 0, st, segs_dev, n_segs, n_items); break;
+    case MODE_FP64: hipLaunchKernelGGL((n_kernel<double, 16, 16, true, NK_GRADIENT>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL((n_kernel<float, 16, 16, true, NK_GRADIENT>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1886,10 +1907,11 @@ hipError_t launch_n_force(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t
 {
     if (n_items <= 0 || n_segs <= 0) return hipSuccess;
     if (n_items > 0x7ffffff0) return hipErrorInvalidValue;
-    const dim3 g(grid_for(n_items, 0)), b(1024);
+    const int lg = xcd_run(n_items, NRUN);
+    const dim3 g(grid_for(n_items, lg, 0)), b(1024);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL((n_kernel<double, 16, 16, true, NK_FORCE>), g, b, 0, st, segs_dev, n_segs, n_items); break;
-    case MODE_FP32: hipLaunchKernelGGL((n_kernel<float, 16, 16, true, NK_FORCE>), g, b, 0, st, segs_dev, n_segs, n_items); break;
+    case MODE_FP64: hipLaunchKernelGGL((n_kernel<double, 16, 16, true, NK_FORCE>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL((n_kernel<float, 16, 16, true, NK_FORCE>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1899,10 +1921,11 @@ hipError_t launch_h_gga(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n
 {
     if (n_items <= 0 || n_segs <= 0) return hipSuccess;
     if (n_items > 0x7ffffff0) return hipErrorInvalidValue;
-    const dim3 g(grid_for(n_items, 0)), b(256);
+    const int lg = xcd_run(n_items, HRUN);
+    const dim3 g(grid_for(n_items, lg, 0)), b(256);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL(h_kernel_gga<double>, g, b, 0, st, segs_dev, n_segs, n_items); break;
-    case MODE_FP32: hipLaunchKernelGGL(h_kernel_gga<float>, g, b, 0, st, segs_dev, n_segs, n_items); break;
+    case MODE_FP64: hipLaunchKernelGGL(h_kernel_gga<double>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL(h_kernel_gga<float>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
