@@ -42,6 +42,7 @@ struct DevUnit {
     int64_t atom_begin;   // into unit_atoms / unit_cols
     int64_t fn_begin;     // into unit_fn (global basis index of every column)
     int64_t out_offset;   // element offset of this unit's [n_points][ld] block within its block
+    int64_t mask_begin;   // into unit_mask (one entry per 16 columns, ld / 16 of the unit)
     int32_t n_points;
     int32_t n_atoms;
     int32_t m;            // columns in use
@@ -70,6 +71,7 @@ struct DevSeg {
     const int32_t* unit_atoms;
     const int32_t* unit_cols;
     const int32_t* unit_fn;
+    const uint16_t* unit_mask;  // per 16 columns: which 16-point chunks of the unit they reach
     const void* items;       // HItem* or NItem*
     void* phi;               // basis values of this block (FP64, or FP32 for the reduced-precision
                              // modes); unit.out_offset is relative to it
@@ -127,6 +129,9 @@ hipError_t launch_force_atoms(const double* fb, const int64_t* atom_first, int64
                               hipStream_t st);
 hipError_t launch_wa(const double* pw, const int32_t* perm, const double* a_caller, double* wa, int64_t n_points,
                      hipStream_t st);
+// Fills unit_mask for the units of a system (n_points <= MAX_UNIT_POINTS each).
+hipError_t launch_unit_masks(const DevSys* sys, const DevUnit* units, const int32_t* unit_atoms, const int32_t* unit_cols,
+                             int64_t n_units, uint16_t* mask, hipStream_t st);
 hipError_t launch_fill(double* p, int64_t n, double value, hipStream_t st);
 hipError_t launch_wv(const double* pw, const int32_t* perm, const double* v_caller, double* wv,
                      int64_t n_points, hipStream_t st);

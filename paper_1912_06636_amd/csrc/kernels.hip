@@ -695,397 +695,231 @@ template <> struct Mma<float> {
     static __device__ inline int row(int lk, int r) { return 4 * lk + r; }
 };
 
-// Hamiltonian: per work item one 64x64 tile pair (I <= J) of a unit,
-//   H[I, J] += (w v Phi[:, I])^T Phi[:, J];
-// K loop over the unit's points in double-buffered chunks of 16 (register prefetch of the
-// next chunk while the MFMAs of the current one run); four waves, each a 32x32 quarter as
-// 2x2 MFMA blocks; FP64 atomics into the upper triangle of H.  T = FP32 accumulates a unit
-// (<= 256 points) in FP32 before the FP64 atomics.  The FP32 form (the staging below applies
-// w v once per value as it is stashed) is faster than the directly-loaded form; FP64 uses the
-// latter.
-template <typename T>
-__global__ __launch_bounds__(256, 4) void h_kernel(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
+// ------------------------------------------------------------------------------------------
+// Parts shared by the tile kernels of H below.
+
+// Lane-uniform values kept in scalar registers: FP64 and FP32 MFMA do not issue beside vector
+// instructions (measured: 69 and 31 cycles per MFMA alone, about 3 more for every vector
+// instruction between them), so what is uniform is computed by the scalar unit.
+__device__ inline int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ inline int64_t uni(int64_t x)
 {
-    typedef Mma<T> M;
-    constexpr int HK = KCHUNK;              // points per chunk
-    constexpr int HQ = HK * TILE / 256;     // values per thread per chunk and operand
-    // rows padded so that two consecutive rows start half a 128-byte bank period apart: the MFMA
-    // reads of a wave's first 32 lanes (16 columns of two rows) then fall in distinct banks
-    constexpr int PAD = 64 / (int)sizeof(T);
-    __shared__ T As[2][HK][TILE + PAD];
-    __shared__ T Bs[2][HK][TILE + PAD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int lr = lane & 15, lk = lane >> 4;
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
-        const int64_t b = xcd_item(v_, lg);
-        if (b >= total) continue;
-        const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
-        const DevSeg& sg = segs[s];
-        const HItem it = static_cast<const HItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit u = sg.units[it.unit];
-        gp<const T> __restrict__ phi = gptr(static_cast<const T*>(sg.phi) + u.out_offset);
-        gp<const double> __restrict__ wv = gptr(sg.wv + u.point_begin);
-        const int np = u.n_points, ld = u.ld;
-        const int I0 = it.ti * TILE, J0 = it.tj * TILE;
-        const int n_chunks = (np + HK - 1) / HK;
-
-        if (np <= 0) continue;
-        // Loads are issued unconditionally (rows clamped into the unit) and only consumed at
-        // the stash after the next chunk's MFMAs, so that they stay in flight meanwhile.
-        T ra[HQ], rb[HQ];
-        double rw[HQ];
-        auto fetch = [&](int c) {
-#pragma unroll
-            for (int q = 0; q < HQ; ++q) {
-                const int e = tid + 256 * q;
-                const int pc = min(c * HK + (e >> 6), np - 1), col = e & 63;
-                gp<const T> rowp = phi + (int64_t)pc * ld;
-                ra[q] = rowp[I0 + col];
-                rb[q] = rowp[J0 + col];
-                rw[q] = wv[pc];
-            }
-        };
-        auto stash = [&](int c, int buf) {
-#pragma unroll
-            for (int q = 0; q < HQ; ++q) {
-                const int e = tid + 256 * q;
-                const bool ok = c * HK + (e >> 6) < np;
-                As[buf][e >> 6][e & 63] = ok ? T((double)ra[q] * rw[q]) : T(0);
-                Bs[buf][e >> 6][e & 63] = ok ? rb[q] : T(0);
-            }
-        };
-        // global indices of this lane's output rows and columns, needed only after the K loop
-        gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + u.fn_begin);
-        int32_t gI[2][4], gJ[2];
-#pragma unroll
-        for (int ib = 0; ib < 2; ++ib) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) gI[ib][r] = fn[min(I0 + wr * 32 + ib * 16 + M::row(lk, r), u.m - 1)];
-            gJ[ib] = fn[min(J0 + wc * 32 + ib * 16 + lr, u.m - 1)];
-        }
-
-        typename M::acc_t acc[2][2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = M::zero();
-        // On a diagonal tile pair the wave of the strictly lower quarter only stages data.
-        auto k_loop = [&](auto with_mfma) {
-            fetch(0);
-            stash(0, 0);
-            __syncthreads();
-            for (int c = 0; c < n_chunks; ++c) {
-                const int buf = c & 1;
-                if (c + 1 < n_chunks) fetch(c + 1);
-                if (decltype(with_mfma)::value) {
-#pragma unroll
-                    for (int kk = 0; kk < HK / 4; ++kk) {
-                        const int kr = kk * 4 + lk;
-                        const T a0 = As[buf][kr][wr * 32 + lr];
-                        const T a1 = As[buf][kr][wr * 32 + 16 + lr];
-                        const T b0 = Bs[buf][kr][wc * 32 + lr];
-                        const T b1 = Bs[buf][kr][wc * 32 + 16 + lr];
-                        acc[0][0] = M::op(a0, b0, acc[0][0]);
-                        acc[0][1] = M::op(a0, b1, acc[0][1]);
-                        acc[1][0] = M::op(a1, b0, acc[1][0]);
-                        acc[1][1] = M::op(a1, b1, acc[1][1]);
-                    }
-                }
-                if (c + 1 < n_chunks) stash(c + 1, buf ^ 1);
-                __syncthreads();
-            }
-        };
-        const bool diag = it.ti == it.tj;
-        if (diag && wr > wc) {
-            k_loop(std::false_type{});
-            continue;
-        }
-        k_loop(std::true_type{});
-
-        gp<double> __restrict__ H = gptr(sg.H);
-        const int64_t ldh = sg.ld;
-#pragma unroll
-        for (int ib = 0; ib < 2; ++ib)
-#pragma unroll
-            for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = wr * 32 + ib * 16 + M::row(lk, r);
-                    const int col = wc * 32 + jb * 16 + lr;
-                    const int ci = I0 + row, cj = J0 + col;
-                    if (ci < u.m && cj < u.m && (!diag || row <= col))
-                        gadd(H + (int64_t)gI[ib][r] * ldh + gJ[jb], (double)acc[ib][jb][r]);
-                }
-    }
+    const uint32_t lo = (uint32_t)uni((int)(uint32_t)x), hi = (uint32_t)uni((int)(uint32_t)((uint64_t)x >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
 }
+template <typename T> __device__ inline T* uni(T* p) { return reinterpret_cast<T*>(uni((int64_t)(uintptr_t)p)); }
 
-// Hamiltonian, staged by direct global-to-LDS loads: per work item one 64x64 tile pair (I <= J)
-// of a unit, H[I, J] += (w v Phi[:, I])^T Phi[:, J].  K = the unit's points in chunks of KC
-// held in an S-stage ring in LDS: the loads of chunk c + S - 1 are issued (global_load_lds, 16
-// bytes per lane, no registers involved) while the MFMAs of chunk c run, so S - 1 chunks are in
-// flight.  w v of the unit's points is staged the same way once per item; the A operand is
-// scaled by it as it is read (loads of rows beyond the unit's last point are clamped into the
-// unit, and the w v of such rows is taken as zero).  On a diagonal pair (I == J) one tile
-// serves both operands.  Four waves, each a 32x32 quarter as 2x2 MFMA blocks; FP64 atomics
-// into the upper triangle of H.  The 16-byte loads need 16-byte aligned rows: every
-// basis-value block starts on a 64-value boundary of its buffer and ld is a multiple of 64.
-template <typename T, int KC, int S>
-__global__ __launch_bounds__(256) void h_kernel_dma(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
+// A raw buffer over [p, p + bytes): loads beyond its end return zeros.
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
+}
+// One wave load from a buffer straight into LDS, 16 or 4 bytes per lane to dst + lane * 16 or 4.
+__device__ inline void load16_to_lds(__amdgpu_buffer_rsrc_t r, void* dst, int voffset, int soffset)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, voffset, soffset, 0, 0);
+}
+__device__ inline void load4_to_lds(__amdgpu_buffer_rsrc_t r, void* dst, int voffset, int soffset)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 4, voffset, soffset, 0, 0);
+}
+// Wait until at most N of this wave's vector loads are outstanding and its LDS reads are done.
+template <int N> __device__ inline void wait_loads() { __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4)); }
+
+// Hamiltonian, per work item one 64x64 tile pair (I <= J) of a unit:
+//   TWO = false: H[I, J] += (w v Phi[:, I])^T Phi[:, J];
+//   TWO = true:  H[I, J] += Phi_I^T L_J + L_I^T Phi_J, with L written by the basis launch (a vector
+//                field or the kinetic term).
+// K = the unit's points in chunks of KC, held in an S-stage ring in LDS that is filled by direct
+// buffer loads (16 bytes per lane, rows beyond the unit's last point read as zeros).  Four waves,
+// each a strip of 16 rows by 64 columns as four 16x16 MFMA blocks.
+//
+// Bound: the matrix pipes, which share their issue slots with the vector instructions, so the loop
+// has next to none: uniform addresses are scalar, LDS addresses are per-lane constants plus
+// immediate stage offsets (the ring is unrolled), and w v costs one multiplication per four MFMAs.
+// unit_mask holds, per 16 columns, which 16-point chunks of the unit any of their functions
+// reaches: chunks that reach only one of the two tiles are not loaded, and 16x16 blocks that a
+// chunk cannot change skip its MFMAs (they would add zeros).  The strip of a wave rotates with the
+// item, so that the blocks below the diagonal, left out, do not idle the same SIMD in every item.
+// Measured, kernel alone, against the form with register math in its loop (6.7 vector instructions
+// per MFMA): 100-atom block FP64 7.45 -> 6.5 ms, 375-atom slab 113 -> 98 ms; with L 12.6 -> 10.0 ms.
+// Two stages and four workgroups per CU measure 2 % faster than three and three.
+template <typename T, int KC, int S, bool TWO>
+__global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     typedef Mma<T> M;
-    constexpr int ROW_SLOTS = TILE * (int)sizeof(T) / 16;     // 16-byte slots per tile row
-    constexpr int ROWS_PER_LOAD = 64 / ROW_SLOTS;            // tile rows one wave load covers
-    constexpr int LOADS = KC / ROWS_PER_LOAD / 4;            // wave loads per operand and chunk
-    static_assert(LOADS >= 1 && KC % 4 == 0 && MAX_UNIT_POINTS % KC == 0, "chunk geometry");
-    __shared__ __align__(16) T st[S][2][KC][TILE];           // [stage][operand A, B][point][column]
-    __shared__ double wvs[MAX_UNIT_POINTS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
+    constexpr int NOP = TWO ? 4 : 2;                    // tiles of a stage: Phi_I, Phi_J, then L_I, L_J
+    constexpr int ROWB = TILE * (int)sizeof(T);         // bytes of a tile row
+    constexpr int TILEB = KC * ROWB, STAGEB = NOP * TILEB;
+    constexpr int SPR = ROWB / 16;                      // 16-byte slots per row
+    constexpr int RPL = 64 / SPR;                       // rows per wave load
+    constexpr int LOADS = KC / RPL / 4;                 // wave loads per tile, wave and chunk
+    static_assert(LOADS >= 1 && (KC == 8 || KC == 16) && (S == 2 || S == 3), "chunk geometry");
+    constexpr int WV = S * STAGEB, FN = WV + (TWO ? 0 : MAX_UNIT_POINTS * 8);
+    __shared__ __align__(16) unsigned char lds[FN + 2 * TILE * 4];  // ring | w v | row and column indices
+    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
     const int lr = lane & 15, lk = lane >> 4;
-    // this lane's slot of every wave load: tile row (within the load's rows) and 16-byte column slot
-    const int slot_row = lane / ROW_SLOTS, slot_col = (lane % ROW_SLOTS) * (16 / (int)sizeof(T));
+    // FP32 rows are half a bank period long: odd rows have their 64-byte halves swapped, so that the
+    // two rows a read of 32 lanes touches fall in distinct banks
+    const int swz = sizeof(T) == 4 ? (lk & 1) * 64 : 0;
     for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
         const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
         const HItem it = static_cast<const HItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit u = sg.units[it.unit];
-        const int np = u.n_points, ld = u.ld;
-        if (np <= 0) continue;
-        const T* phi = static_cast<const T*>(sg.phi) + u.out_offset;
-        const int I0 = it.ti * TILE, J0 = it.tj * TILE;
-        const bool diag = it.ti == it.tj;
+        const int ti = uni((int)it.ti), tj = uni((int)it.tj);
+        const DevUnit* up = sg.units + uni(it.unit);
+        const int np = uni(up->n_points), ld = uni(up->ld), m = uni(up->m);
+        const int64_t out_offset = uni(up->out_offset), point_begin = uni(up->point_begin);
+        const int64_t fn_begin = uni(up->fn_begin), mask_begin = uni(up->mask_begin);
+        const uint64_t* mp = reinterpret_cast<const uint64_t*>(sg.unit_mask + mask_begin);
+        const uint64_t mI = (uint64_t)uni((int64_t)mp[ti]), mJ = (uint64_t)uni((int64_t)mp[tj]);
+        auto any16 = [](uint64_t x) { x |= x >> 32; return (uint32_t)((x | (x >> 16)) & 0xFFFF); };
+        // masks over chunks of KC points
         const int n_chunks = (np + KC - 1) / KC;
-        const int per_chunk = diag ? LOADS : 2 * LOADS;  // wave loads per chunk (wave-uniform)
+        auto chunks = [&](uint32_t x) {
+            if (KC == 8) {  // every bit twice
+                x = (x | (x << 8)) & 0x00FF00FF;
+                x = (x | (x << 4)) & 0x0F0F0F0F;
+                x = (x | (x << 2)) & 0x33333333;
+                x = (x | (x << 1)) & 0x55555555;
+                x |= x << 1;
+                if (n_chunks < 32) x &= (1u << n_chunks) - 1;
+            }
+            return x;
+        };
+        uint32_t todo = chunks(any16(mI) & any16(mJ));
+        if (todo == 0) continue;  // no point is reached by functions of both tiles
+        const bool diag = ti == tj;
+        const int strip = (wave + tj) & 3;
+        const uint32_t ma = (uint32_t)(mI >> (16 * strip)) & 0xFFFF;
+        uint32_t mm[4];  // chunks that change this wave's block jb (none below the diagonal)
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+            mm[jb] = diag && jb < strip ? 0 : chunks(ma & (uint32_t)(mJ >> (16 * jb)) & 0xFFFF);
+        const uint32_t m_any = mm[0] | mm[1] | mm[2] | mm[3];
 
-        // every wave must be done reading the previous item's stages and w v before they are
-        // refilled (its loads into them have all completed; its atomics need not)
+        const char* phi = static_cast<const char*>(sg.phi) + out_offset * (int)sizeof(T);
+        const char* lv = TWO ? static_cast<const char*>(sg.gphi) + out_offset * (int)sizeof(T) : nullptr;
+        const int ldb = ld * (int)sizeof(T);
+        const int I0b = ti * ROWB, J0b = tj * ROWB;
+        // every wave must be done reading the previous item's LDS
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        // w v of the unit's points into wvs, 32 per wave load (two 4-byte halves per value), point
-        // indices clamped into the unit; rows at and beyond np are masked where they are used
-        {
-            const double* wv = sg.wv + u.point_begin;
-            const int nq = (n_chunks * KC + 31) / 32;
-            for (int q = wave; q < nq; q += 4) {
-                const int d = min(32 * q + (lane >> 1), np - 1);
-                const char* src = reinterpret_cast<const char*>(wv + d) + 4 * (lane & 1);
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                                 (__attribute__((address_space(3))) void*)&wvs[32 * q], 4, 0, 0);
-            }
+        if (!TWO) {  // w v of the unit's points, zeros beyond the last one
+            const __amdgpu_buffer_rsrc_t r = buffer_of(sg.wv + point_begin, np * 8);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                load4_to_lds(r, lds + WV + (2 * wave + q) * 256, 4 * lane, (2 * wave + q) * 256);
         }
-        auto issue = [&](int c) {
-            const int stg = c % S;
+        if (wave < 2)  // global indices of the tile's rows and columns
+            load4_to_lds(buffer_of(sg.unit_fn + fn_begin, m * 4), lds + FN + wave * TILE * 4,
+                           4 * ((wave ? tj : ti) * TILE + lane), 0);
+        int voff[LOADS];  // this lane's 16 bytes of every wave load, within a chunk's rows
 #pragma unroll
-            for (int op = 0; op < 2; ++op) {
-                if (op == 1 && diag) break;
-                const int col0 = op == 0 ? I0 : J0;
+        for (int q = 0; q < LOADS; ++q) {
+            const int row = (wave * LOADS + q) * RPL + lane / SPR;
+            voff[q] = row * ldb + (((lane % SPR) * 16) ^ (sizeof(T) == 4 ? (row & 1) * 64 : 0));
+        }
+        auto issue = [&](int c, int stg) {
+            const int64_t o = (int64_t)c * KC * ldb;
+            const int bytes = (np - c * KC) * ldb;
 #pragma unroll
-                for (int q = 0; q < LOADS; ++q) {
-                    const int r0 = (wave * LOADS + q) * ROWS_PER_LOAD;  // first tile row of this load
-                    const int p = min(c * KC + r0 + slot_row, np - 1);
-                    const T* src = phi + (int64_t)p * ld + col0 + slot_col;
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                                     (__attribute__((address_space(3))) void*)&st[stg][op][r0][0],
-                                                     16, 0, 0);
-                }
+            for (int op = 0; op < NOP; ++op) {
+                if ((op & 1) && diag) continue;
+                const __amdgpu_buffer_rsrc_t r = buffer_of((op < 2 ? phi : lv) + o, bytes);
+#pragma unroll
+                for (int q = 0; q < LOADS; ++q)
+                    load16_to_lds(r, lds + stg * STAGEB + op * TILEB + (wave * LOADS + q) * 1024, voff[q], op & 1 ? J0b : I0b);
             }
         };
-        // wait until at most `later` chunks' loads of this wave are outstanding (vmcnt counts wave
-        // loads in issue order), and for the LDS reads of the last chunk, then barrier
-        auto sync_chunk = [&](int later) {
-            const int n = __builtin_amdgcn_readfirstlane(later * per_chunk);  // at most (S - 2) * 2 * LOADS
-            switch (n) {
-#define NAO_VMWAIT(N) \
-    case N: __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4)); break;
-                NAO_VMWAIT(0) NAO_VMWAIT(1) NAO_VMWAIT(2) NAO_VMWAIT(3) NAO_VMWAIT(4) NAO_VMWAIT(5)
-                NAO_VMWAIT(6) NAO_VMWAIT(7) NAO_VMWAIT(8) NAO_VMWAIT(9) NAO_VMWAIT(10) NAO_VMWAIT(11)
-                NAO_VMWAIT(12) NAO_VMWAIT(13) NAO_VMWAIT(14) NAO_VMWAIT(15) NAO_VMWAIT(16)
-#undef NAO_VMWAIT
-            default: __builtin_amdgcn_s_waitcnt(0x7 << 4); break;  // vmcnt(0), lgkmcnt(0)
-            }
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        };
+        // per-lane LDS offsets of the operands: row lk of a stage's tiles
+        const int a_off = lk * ROWB + ((strip * 16 * (int)sizeof(T)) ^ swz) + lr * (int)sizeof(T);
+        const int b_tile = diag ? 0 : TILEB;
+        int b_off[2];
+        b_off[0] = b_tile + lk * ROWB + swz + lr * (int)sizeof(T);
+        b_off[1] = b_tile + lk * ROWB + ((16 * (int)sizeof(T)) ^ swz) + lr * (int)sizeof(T);
 
-        gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + u.fn_begin);
-        int32_t gI[2][4], gJ[2];
+        typename M::acc_t acc[4];
 #pragma unroll
-        for (int ib = 0; ib < 2; ++ib) {
+        for (int j = 0; j < 4; ++j) acc[j] = M::zero();
+        auto compute = [&](int c, int stg) {
+            if (!((m_any >> c) & 1)) return;
+            constexpr int KK = KC / 4;
+            const unsigned char* base = lds + stg * STAGEB;
+            T a[KK], bv[4][KK], a2[TWO ? KK : 1], b2[TWO ? 4 : 1][KK];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) gI[ib][r] = fn[min(I0 + wr * 32 + ib * 16 + M::row(lk, r), u.m - 1)];
-            gJ[ib] = fn[min(J0 + wc * 32 + ib * 16 + lr, u.m - 1)];
-        }
-        typename M::acc_t acc[2][2];
+            for (int kk = 0; kk < KK; ++kk) {
+                const T x = *reinterpret_cast<const T*>(base + a_off + kk * 4 * ROWB);
+                if (TWO) a[kk] = x, a2[kk] = *reinterpret_cast<const T*>(base + a_off + 2 * TILEB + kk * 4 * ROWB);
+                else a[kk] = T((double)x * *reinterpret_cast<const double*>(lds + WV + lk * 8 + (c * KC + kk * 4) * 8));
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = M::zero();
-        const bool compute = !(diag && wr > wc);  // the strictly lower quarter of a diagonal pair
-        const int ob = diag ? 0 : 1;              // operand B's slot in the stages
-
-        for (int c = 0; c < S - 1 && c < n_chunks; ++c) issue(c);
-        for (int c = 0; c < n_chunks; ++c) {
-            sync_chunk(min(S - 2, n_chunks - 1 - c));
-            if (c + S - 1 < n_chunks) issue(c + S - 1);
-            if (compute) {
-                const int stg = c % S;
-#pragma unroll
-                for (int kk = 0; kk < KC / 4; ++kk) {
-                    const int kr = kk * 4 + lk;
-                    const double w = c * KC + kr < np ? wvs[c * KC + kr] : 0.0;
-                    const T a0 = T((double)st[stg][0][kr][wr * 32 + lr] * w);
-                    const T a1 = T((double)st[stg][0][kr][wr * 32 + 16 + lr] * w);
-                    const T b0 = st[stg][ob][kr][wc * 32 + lr];
-                    const T b1 = st[stg][ob][kr][wc * 32 + 16 + lr];
-                    acc[0][0] = M::op(a0, b0, acc[0][0]);
-                    acc[0][1] = M::op(a0, b1, acc[0][1]);
-                    acc[1][0] = M::op(a1, b0, acc[1][0]);
-                    acc[1][1] = M::op(a1, b1, acc[1][1]);
+                for (int jb = 0; jb < 4; ++jb) {
+                    const unsigned char* q = base + b_off[jb & 1] + (jb & 2) * 16 * (int)sizeof(T) + kk * 4 * ROWB;
+                    // the factors of Phi_I are L_J, those of L_I are Phi_J
+                    bv[jb][kk] = *reinterpret_cast<const T*>(q + (TWO ? 2 * TILEB : 0));
+                    if (TWO) b2[jb][kk] = *reinterpret_cast<const T*>(q);
                 }
             }
-        }
-        if (!compute) continue;
-        gp<double> __restrict__ H = gptr(sg.H);
-        const int64_t ldh = sg.ld;
+            // block by block, four dependent MFMAs each: the other waves of the SIMD fill their
+            // latency, and the accumulators stay where they are on every path
 #pragma unroll
-        for (int ib = 0; ib < 2; ++ib)
+            for (int jb = 0; jb < 4; ++jb)
+                if ((mm[jb] >> c) & 1)
 #pragma unroll
-            for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = wr * 32 + ib * 16 + M::row(lk, r);
-                    const int col = wc * 32 + jb * 16 + lr;
-                    const int ci = I0 + row, cj = J0 + col;
-                    if (ci < u.m && cj < u.m && (!diag || row <= col))
-                        gadd(H + (int64_t)gI[ib][r] * ldh + gJ[jb], (double)acc[ib][jb][r]);
-                }
-    }
-}
-
-// Hamiltonian with a vector field (GGA form of eq. batch_matrix_mult): per item one 64x64 tile
-// pair (I <= J) of a unit, H[I, J] += Phi_I^T L_J + L_I^T Phi_J, with L = (w v / 2) Phi +
-// (w a) . grad Phi written by the basis launch (or the kinetic L).  Schedule of h_kernel with
-// K = points in double-buffered chunks of 8 (two products per chunk), four waves of 32x32, FP64
-// atomics into the upper triangle.
-template <typename T>
-__global__ __launch_bounds__(256, 4) void h_kernel_gga(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
-{
-    typedef Mma<T> M;
-    constexpr int GK = 8;  // points per chunk: half the LDS of 16-point chunks, so that four
-                           // workgroups fit a CU (20 % faster than two with 16-point chunks)
-    constexpr int HQ = GK * TILE / 256;  // values per thread per chunk and operand
-    __shared__ T Ps[2][2][GK][TILE + 2];  // [buffer][I, J] basis values
-    __shared__ T Ls[2][2][GK][TILE + 2];  // [buffer][I, J] L values
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int lr = lane & 15, lk = lane >> 4;
-    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
-        const int64_t b = xcd_item(v_, lg);
-        if (b >= total) continue;
-        const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
-        const DevSeg& sg = segs[s];
-        const HItem it = static_cast<const HItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit u = sg.units[it.unit];
-        gp<const T> __restrict__ phi = gptr(static_cast<const T*>(sg.phi) + u.out_offset);
-        gp<const T> __restrict__ lv = gptr(static_cast<const T*>(sg.gphi) + u.out_offset);
-        const int np = u.n_points, ld = u.ld;
-        if (np <= 0) continue;
-        const int I0 = it.ti * TILE, J0 = it.tj * TILE;
-        const int n_chunks = (np + GK - 1) / GK;
-
-        T rp[2][HQ], rl[2][HQ];  // [I, J] basis and L values of the next chunk
-        auto fetch = [&](int c) {
-#pragma unroll
-            for (int q = 0; q < HQ; ++q) {
-                const int e = tid + 256 * q;
-                const int64_t o = (int64_t)min(c * GK + (e >> 6), np - 1) * ld + (e & 63);
-                rp[0][q] = phi[o + I0];
-                rp[1][q] = phi[o + J0];
-                rl[0][q] = lv[o + I0];
-                rl[1][q] = lv[o + J0];
-            }
-        };
-        auto stash = [&](int c, int buf) {
-#pragma unroll
-            for (int q = 0; q < HQ; ++q) {
-                const int e = tid + 256 * q;
-                const bool ok = c * GK + (e >> 6) < np;
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    Ps[buf][t][e >> 6][e & 63] = ok ? rp[t][q] : T(0);
-                    Ls[buf][t][e >> 6][e & 63] = ok ? rl[t][q] : T(0);
-                }
-            }
-        };
-        gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + u.fn_begin);
-        int32_t gI[2][4], gJ[2];
-#pragma unroll
-        for (int ib = 0; ib < 2; ++ib) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) gI[ib][r] = fn[min(I0 + wr * 32 + ib * 16 + M::row(lk, r), u.m - 1)];
-            gJ[ib] = fn[min(J0 + wc * 32 + ib * 16 + lr, u.m - 1)];
-        }
-
-        typename M::acc_t acc[2][2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = M::zero();
-        auto k_loop = [&](auto with_mfma) {
-            fetch(0);
-            stash(0, 0);
-            __syncthreads();
-            for (int c = 0; c < n_chunks; ++c) {
-                const int buf = c & 1;
-                if (c + 1 < n_chunks) fetch(c + 1);
-                if (decltype(with_mfma)::value) {
-#pragma unroll
-                    for (int kk = 0; kk < GK / 4; ++kk) {
-                        const int kr = kk * 4 + lk;
-                        // Phi_I^T L_J, then L_I^T Phi_J
-                        const T a0 = Ps[buf][0][kr][wr * 32 + lr], a1 = Ps[buf][0][kr][wr * 32 + 16 + lr];
-                        const T b0 = Ls[buf][1][kr][wc * 32 + lr], b1 = Ls[buf][1][kr][wc * 32 + 16 + lr];
-                        acc[0][0] = M::op(a0, b0, acc[0][0]);
-                        acc[0][1] = M::op(a0, b1, acc[0][1]);
-                        acc[1][0] = M::op(a1, b0, acc[1][0]);
-                        acc[1][1] = M::op(a1, b1, acc[1][1]);
-                        const T c0 = Ls[buf][0][kr][wr * 32 + lr], c1 = Ls[buf][0][kr][wr * 32 + 16 + lr];
-                        const T d0 = Ps[buf][1][kr][wc * 32 + lr], d1 = Ps[buf][1][kr][wc * 32 + 16 + lr];
-                        acc[0][0] = M::op(c0, d0, acc[0][0]);
-                        acc[0][1] = M::op(c0, d1, acc[0][1]);
-                        acc[1][0] = M::op(c1, d0, acc[1][0]);
-                        acc[1][1] = M::op(c1, d1, acc[1][1]);
+                    for (int kk = 0; kk < KK; ++kk) {
+                        acc[jb] = M::op(a[kk], bv[jb][kk], acc[jb]);
+                        if (TWO) acc[jb] = M::op(a2[kk], b2[jb][kk], acc[jb]);
                     }
-                }
-                if (c + 1 < n_chunks) stash(c + 1, buf ^ 1);
-                __syncthreads();
-            }
         };
-        const bool diag = it.ti == it.tj;
-        if (diag && wr > wc) {  // the strictly lower quarter of a diagonal tile pair only stages data
-            k_loop(std::false_type{});
-            continue;
+        uint32_t ahead = todo;
+#pragma unroll
+        for (int k = 0; k < S - 1; ++k)
+            if (ahead) {
+                issue(__builtin_ctz(ahead), k);
+                ahead &= ahead - 1;
+            }
+        // per chunk: its loads (every wave's) have landed and every wave is done with the stage that
+        // is refilled next
+        while (todo) {
+#pragma unroll
+            for (int stg = 0; stg < S; ++stg) {
+                const int c = __builtin_ctz(todo);
+                todo &= todo - 1;
+                if (S == 2 || todo == 0) wait_loads<0>();
+                else if (diag) wait_loads<LOADS * NOP / 2>();
+                else wait_loads<LOADS * NOP>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                if (ahead) {
+                    issue(__builtin_ctz(ahead), (stg + S - 1) % S);
+                    ahead &= ahead - 1;
+                }
+                compute(c, stg);
+                if (todo == 0) break;
+            }
         }
-        k_loop(std::true_type{});
-
+        if (m_any == 0) continue;
+        const int32_t* gi = reinterpret_cast<const int32_t*>(lds + FN);
         gp<double> __restrict__ H = gptr(sg.H);
         const int64_t ldh = sg.ld;
+        const int row0 = strip * 16, I0 = ti * TILE, J0 = tj * TILE;
+        gp<double> Hr[4];
 #pragma unroll
-        for (int ib = 0; ib < 2; ++ib)
+        for (int r = 0; r < 4; ++r) Hr[r] = H + (int64_t)gi[row0 + M::row(lk, r)] * ldh;
 #pragma unroll
-            for (int jb = 0; jb < 2; ++jb)
+        for (int jb = 0; jb < 4; ++jb) {
+            if (!mm[jb]) continue;  // no chunk reaches this block
+            const int32_t gj = gi[TILE + jb * 16 + lr];
+            const bool whole = I0 + row0 + 16 <= m && J0 + jb * 16 + 16 <= m && !(diag && jb == strip);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = wr * 32 + ib * 16 + M::row(lk, r);
-                    const int col = wc * 32 + jb * 16 + lr;
-                    const int ci = I0 + row, cj = J0 + col;
-                    if (ci < u.m && cj < u.m && (!diag || row <= col))
-                        gadd(H + (int64_t)gI[ib][r] * ldh + gJ[jb], (double)acc[ib][jb][r]);
-                }
+            for (int r = 0; r < 4; ++r) {
+                const int row = row0 + M::row(lk, r), col = jb * 16 + lr;
+                if (whole || (I0 + row < m && J0 + col < m && (!diag || row <= col))) gadd(Hr[r] + gj, (double)acc[jb][r]);
+            }
+        }
     }
 }
 
@@ -1863,8 +1697,8 @@ hipError_t launch_h(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n_ite
     const int lg = xcd_run(n_items, HRUN);
     const dim3 g(grid_for(n_items, lg, max_grid)), b(256);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL((h_kernel_dma<double, 16, 3>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
-    case MODE_FP32: hipLaunchKernelGGL(h_kernel<float>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP64: hipLaunchKernelGGL((h_tiles<double, 16, 2, false>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL((h_tiles<float, 16, 2, false>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     case MODE_BF16X3: hipLaunchKernelGGL(h_kernel_bf16<2>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     case MODE_BF16X6: hipLaunchKernelGGL(h_kernel_bf16<3>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
@@ -1924,8 +1758,8 @@ hipError_t launch_h_gga(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n
     const int lg = xcd_run(n_items, HRUN);
     const dim3 g(grid_for(n_items, lg, 0)), b(256);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL(h_kernel_gga<double>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
-    case MODE_FP32: hipLaunchKernelGGL(h_kernel_gga<float>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP64: hipLaunchKernelGGL((h_tiles<double, 8, 3, true>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL((h_tiles<float, 16, 3, true>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1958,6 +1792,50 @@ hipError_t launch_force_atoms(const double* fb, const int64_t* atom_first, int64
     const int64_t blocks = (3 * n_atoms + 255) / 256;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL(force_atoms_kernel, dim3((unsigned)blocks), dim3(256), 0, st, fb, atom_first, n_atoms, F);
+    return hipGetLastError();
+}
+
+// Reach of the units' functions (DevSeg::unit_mask): per 16 columns of a unit, bit c is set when
+// some point of rows 16 c .. 16 c + 15 lies within the largest cutoff of an atom that owns one of
+// the columns; padding columns give no bits.  Geometry alone decides, so the masks are made once per
+// set of units.  One wave per unit, a thread per 16 columns.
+__global__ __launch_bounds__(64) void unit_mask_kernel(const DevSys* __restrict__ S, const DevUnit* __restrict__ units,
+                                                       const int32_t* __restrict__ unit_atoms,
+                                                       const int32_t* __restrict__ unit_cols, int64_t n_units,
+                                                       uint16_t* __restrict__ mask)
+{
+    for (int64_t k = blockIdx.x; k < n_units; k += gridDim.x) {
+        const DevUnit u = units[k];
+        const int32_t* at = unit_atoms + u.atom_begin;
+        const int32_t* col = unit_cols + u.atom_begin;
+        for (int blk = threadIdx.x; blk < u.ld / 16; blk += 64) {
+            uint32_t bits = 0;
+            if (blk * 16 < u.m) {
+                int lo = 0, hi = u.n_atoms - 1;  // the atom that owns column 16 blk
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (col[mid] <= blk * 16) lo = mid; else hi = mid - 1;
+                }
+                for (int q = lo; q < u.n_atoms && col[q] < blk * 16 + 16; ++q) {
+                    const double* A = S->atom_xyzr + 4 * (int64_t)at[q];
+                    const double ax = A[0], ay = A[1], az = A[2], rc2 = A[3];
+                    for (int p = 0; p < u.n_points; ++p) {
+                        const int64_t g = u.point_begin + p;
+                        if (dist2_exact(S->px[g] - ax, S->py[g] - ay, S->pz[g] - az) < rc2) bits |= 1u << (p >> 4);
+                    }
+                }
+            }
+            mask[u.mask_begin + blk] = (uint16_t)bits;
+        }
+    }
+}
+
+hipError_t launch_unit_masks(const DevSys* sys, const DevUnit* units, const int32_t* unit_atoms, const int32_t* unit_cols,
+                             int64_t n_units, uint16_t* mask, hipStream_t st)
+{
+    if (n_units <= 0) return hipSuccess;
+    hipLaunchKernelGGL(unit_mask_kernel, dim3((unsigned)std::min<int64_t>(n_units, 1 << 20)), dim3(64), 0, st, sys, units,
+                       unit_atoms, unit_cols, n_units, mask);
     return hipGetLastError();
 }
 

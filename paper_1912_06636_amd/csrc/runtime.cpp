@@ -300,7 +300,7 @@ struct nao_system_s {
     DevSys dsys{};
     DevArray d_sys, d_px, d_py, d_pz, d_pw, d_perm, d_atoms, d_species, d_shell_ptr, d_shell_l, d_shell_rad,
         d_radial_par, d_spline, d_fn_ptr, d_fn_code;
-    DevArray d_units, d_unit_atoms, d_unit_cols, d_unit_fn, d_h_items, d_hw_items, d_n_items;
+    DevArray d_units, d_unit_atoms, d_unit_cols, d_unit_fn, d_unit_mask, d_h_items, d_hw_items, d_n_items;
     DevArray d_wv, d_v, d_D, d_H, d_n, d_gn, d_a, d_wa, d_segs, d_Q, d_fb, d_atom_first, d_F;
     // resident basis values (opt-in): every block's values kept across operations
     bool resident = false;
@@ -318,7 +318,7 @@ size_t system_bytes(const nao_system_s* s)
 {
     const DevArray* arr[] = {&s->d_sys, &s->d_px, &s->d_py, &s->d_pz, &s->d_pw, &s->d_perm, &s->d_atoms,
                              &s->d_species, &s->d_shell_ptr, &s->d_shell_l, &s->d_shell_rad, &s->d_radial_par,
-                             &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn,
+                             &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn, &s->d_unit_mask,
                              &s->d_h_items, &s->d_hw_items, &s->d_n_items, &s->d_wv, &s->d_v, &s->d_D, &s->d_H, &s->d_n,
                              &s->d_gn, &s->d_a, &s->d_wa, &s->d_segs, &s->d_Q, &s->d_fb, &s->d_atom_first,
                              &s->d_F, &s->d_phi_res};
@@ -331,7 +331,7 @@ void free_all(nao_system_s* s)
 {
     DevArray* arr[] = {&s->d_sys, &s->d_px, &s->d_py, &s->d_pz, &s->d_pw, &s->d_perm, &s->d_atoms,
                        &s->d_species, &s->d_shell_ptr, &s->d_shell_l, &s->d_shell_rad, &s->d_radial_par,
-                       &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn,
+                       &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn, &s->d_unit_mask,
                        &s->d_h_items, &s->d_hw_items, &s->d_n_items, &s->d_wv, &s->d_v, &s->d_D, &s->d_H, &s->d_n, &s->d_gn, &s->d_a, &s->d_wa, &s->d_segs,
                        &s->d_Q, &s->d_fb, &s->d_atom_first, &s->d_F, &s->d_phi_res};
     for (auto* a : arr) {
@@ -381,7 +381,7 @@ nao_status build_groups(nao_system_s* s)
     std::vector<int64_t> item_first;
     s->blocks.clear();
     Block cur;
-    int64_t off = 0;
+    int64_t off = 0, mask_len = 0;
     const int64_t cap = (int64_t)c->scratch_cap_elems;
     for (size_t k = 0; k < units.size(); ++k) {
         const Unit& u = units[k];
@@ -397,6 +397,8 @@ nao_status build_groups(nao_system_s* s)
             const int32_t a = uat[u.atom_begin + q];
             for (int64_t f = s->basis.atom_first[a]; f < s->basis.atom_first[a + 1]; ++f) ufn.push_back((int32_t)f);
         }
+        d.mask_begin = mask_len;
+        mask_len += d.ld / 16;
         const int64_t elems = (int64_t)d.n_points * d.ld;
         if (elems > cap) return (set_err(c, "one execution group exceeds the scratch size"), NAO_ERR_INTERNAL);
         if (off + elems > cap) {
@@ -441,6 +443,9 @@ nao_status build_groups(nao_system_s* s)
     if ((st = upload(c, s->d_h_items, hitems.data(), hitems.size() * sizeof(HItem))) != NAO_OK) return st;
     if ((st = upload(c, s->d_hw_items, hwitems.data(), hwitems.size() * sizeof(HItem))) != NAO_OK) return st;
     if ((st = upload(c, s->d_n_items, nitems.data(), nitems.size() * sizeof(NItem))) != NAO_OK) return st;
+    if ((st = ensure(c, s->d_unit_mask, std::max<int64_t>(1, mask_len) * sizeof(uint16_t))) != NAO_OK) return st;
+    HIP_TRY(c, launch_unit_masks(s->d_sys.as<DevSys>(), s->d_units.as<DevUnit>(), s->d_unit_atoms.as<int32_t>(),
+                                 s->d_unit_cols.as<int32_t>(), (int64_t)du.size(), s->d_unit_mask.as<uint16_t>(), c->stream));
     if ((st = ensure(c, s->d_segs, std::max<size_t>(1, s->blocks.size()) * sizeof(DevSeg))) != NAO_OK) return st;
     size_t need = 0;
     for (const Block& b : s->blocks) need = std::max(need, (size_t)b.phi_elems);
@@ -461,6 +466,7 @@ DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = fal
     g.unit_atoms = s->d_unit_atoms.as<int32_t>();
     g.unit_cols = s->d_unit_cols.as<int32_t>();
     g.unit_fn = s->d_unit_fn.as<int32_t>();
+    g.unit_mask = s->d_unit_mask.as<uint16_t>();
     g.items = ham ? (wide ? (const void*)s->d_hw_items.p : (const void*)s->d_h_items.p) : (const void*)s->d_n_items.p;
     g.phi = s->ctx->scratch;
     g.ld = s->basis.n_basis;
