@@ -10,6 +10,8 @@ namespace nao {
 constexpr int TILE = 64;              // basis-function tile of the contraction kernels
 constexpr int KCHUNK = 16;            // points (Hamiltonian) / functions (density) per LDS stage
 constexpr int MAX_UNIT_POINTS = 256;  // largest execution group the contraction kernels take
+constexpr int MAX_CLUSTER_ROWS = 960; // largest Hamiltonian cluster (60 chunks: masks have 64 bits, and
+                                      // four FP64 workgroups with w v of 960 rows fill a CU's LDS)
 constexpr int MAX_SPLINE_LDS = 8192;  // doubles of spline table staged in LDS (64 KiB)
 
 // One structure's resident device state, as seen by the kernels.
@@ -36,17 +38,25 @@ struct DevSys {
     int64_t n_points;
 };
 
-// A run of batch-ordered points evaluated against one list of atoms.
+// A run of batch-ordered points evaluated against one list of atoms: an execution unit, or one
+// unit of a Hamiltonian cluster (over the cluster's list; its values are rows of the cluster's
+// block), or a whole cluster (then n_points = n_rows, and point_begin is unused).
 struct DevUnit {
     int64_t point_begin;  // into the system's batch-ordered points
     int64_t atom_begin;   // into unit_atoms / unit_cols
     int64_t fn_begin;     // into unit_fn (global basis index of every column)
-    int64_t out_offset;   // element offset of this unit's [n_points][ld] block within its block
+    int64_t out_offset;   // element offset of this unit's [n_rows][ld] block within its block
     int64_t mask_begin;   // into unit_mask (one entry per 16 columns, ld / 16 of the unit)
+    int64_t row_begin;    // into the row-ordered w*v (execution units: point_begin)
+    uint64_t sub_first;   // clusters: bit c is set when 16-row chunk c starts another unit
     int32_t n_points;
+    int32_t n_rows;       // n_points, in clusters rounded up to 16 (zero rows)
     int32_t n_atoms;
     int32_t m;            // columns in use
     int32_t ld;           // row stride of the basis block (>= m)
+    int32_t sub_begin;    // its units, in the unit array that the basis launch takes
+    int32_t sub_count;
+    int32_t pad_;
 };
 
 // Work item of the Hamiltonian kernel: one tile pair (ti <= tj) of one unit.
@@ -67,15 +77,16 @@ struct NItem {
 // to the segment whose prefix range contains it.
 struct DevSeg {
     const DevSys* sys;
-    const DevUnit* units;
+    const DevUnit* units;       // what the basis launch evaluates
+    const DevUnit* item_units;  // what the items index: the same units, or their clusters
     const int32_t* unit_atoms;
     const int32_t* unit_cols;
     const int32_t* unit_fn;
-    const uint16_t* unit_mask;  // per 16 columns: which 16-point chunks of the unit they reach
+    const uint64_t* unit_mask;  // per 16 columns: which 16-row chunks of the unit (cluster) they reach
     const void* items;       // HItem* or NItem*
     void* phi;               // basis values of this block (FP64, or FP32 for the reduced-precision
                              // modes); unit.out_offset is relative to it
-    const double* wv;        // batch-ordered w*v (Hamiltonian)
+    const double* wv;        // w*v in row order (plain Hamiltonian) or batch order
     const double* D;         // density matrix (density), row-major, ld = n_basis
     double* H;               // Hamiltonian, row-major, ld = n_basis
     double* n;               // density, caller order
@@ -129,9 +140,12 @@ hipError_t launch_force_atoms(const double* fb, const int64_t* atom_first, int64
                               hipStream_t st);
 hipError_t launch_wa(const double* pw, const int32_t* perm, const double* a_caller, double* wa, int64_t n_points,
                      hipStream_t st);
-// Fills unit_mask for the units of a system (n_points <= MAX_UNIT_POINTS each).
-hipError_t launch_unit_masks(const DevSys* sys, const DevUnit* units, const int32_t* unit_atoms, const int32_t* unit_cols,
-                             int64_t n_units, uint16_t* mask, hipStream_t st);
+// Fills unit_mask for `units` (or clusters), whose rows are those of `subs`.
+hipError_t launch_unit_masks(const DevSys* sys, const DevUnit* units, const DevUnit* subs, const int32_t* unit_atoms,
+                             const int32_t* unit_cols, int64_t n_units, uint64_t* mask, hipStream_t st);
+// Row-ordered w*v of n_subs units: wv[row_begin + r] = w v of their point r, 0 in padding rows.
+hipError_t launch_wv_rows(const DevUnit* subs, int64_t n_subs, const double* pw, const int32_t* perm, const double* v_caller,
+                          double* wv, hipStream_t st);
 hipError_t launch_fill(double* p, int64_t n, double value, hipStream_t st);
 hipError_t launch_wv(const double* pw, const int32_t* perm, const double* v_caller, double* wv,
                      int64_t n_points, hipStream_t st);

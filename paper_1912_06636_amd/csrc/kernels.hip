@@ -550,6 +550,14 @@ __global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict_
             if (staged) pairs(std::true_type{});
             else pairs(std::false_type{});
         }
+        if (slice == BASIS_SLICES - 1 && u.n_rows > u.n_points) {  // padding rows of a cluster's unit
+            const int64_t z0 = (int64_t)u.n_points * u.ld, z1 = (int64_t)u.n_rows * u.ld;
+            for (int64_t q = z0 + tid; q < z1; q += blockDim.x) {
+                out[q] = T(0);
+                if (EX != EXTRA_NONE)
+                    for (int c = 0; c < XW; ++c) gout[XW * q + c] = T(0);
+            }
+        }
         const int pad = u.ld - u.m;
         if (pad > 0) {
             const int64_t ne = (int64_t)(row1 - row0) * pad;
@@ -755,7 +763,7 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
     constexpr int RPL = 64 / SPR;                       // rows per wave load
     constexpr int LOADS = KC / RPL / 4;                 // wave loads per tile, wave and chunk
     static_assert(LOADS >= 1 && (KC == 8 || KC == 16) && (S == 2 || S == 3), "chunk geometry");
-    constexpr int WV = S * STAGEB, FN = WV + (TWO ? 0 : MAX_UNIT_POINTS * 8);
+    constexpr int WV = S * STAGEB, FN = WV + (TWO ? 0 : MAX_CLUSTER_ROWS * 8);
     __shared__ __align__(16) unsigned char lds[FN + 2 * TILE * 4];  // ring | w v | row and column indices
     const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
     const int lr = lane & 15, lk = lane >> 4;
@@ -769,36 +777,28 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
         const DevSeg& sg = segs[s];
         const HItem it = static_cast<const HItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
         const int ti = uni((int)it.ti), tj = uni((int)it.tj);
-        const DevUnit* up = sg.units + uni(it.unit);
-        const int np = uni(up->n_points), ld = uni(up->ld), m = uni(up->m);
-        const int64_t out_offset = uni(up->out_offset), point_begin = uni(up->point_begin);
+        const DevUnit* up = sg.item_units + uni(it.unit);
+        const int np = uni(up->n_rows), ld = uni(up->ld), m = uni(up->m);
+        const int64_t out_offset = uni(up->out_offset), row_begin = uni(up->row_begin);
         const int64_t fn_begin = uni(up->fn_begin), mask_begin = uni(up->mask_begin);
-        const uint64_t* mp = reinterpret_cast<const uint64_t*>(sg.unit_mask + mask_begin);
-        const uint64_t mI = (uint64_t)uni((int64_t)mp[ti]), mJ = (uint64_t)uni((int64_t)mp[tj]);
-        auto any16 = [](uint64_t x) { x |= x >> 32; return (uint32_t)((x | (x >> 16)) & 0xFFFF); };
-        // masks over chunks of KC points
-        const int n_chunks = (np + KC - 1) / KC;
-        auto chunks = [&](uint32_t x) {
-            if (KC == 8) {  // every bit twice
-                x = (x | (x << 8)) & 0x00FF00FF;
-                x = (x | (x << 4)) & 0x0F0F0F0F;
-                x = (x | (x << 2)) & 0x33333333;
-                x = (x | (x << 1)) & 0x55555555;
-                x |= x << 1;
-                if (n_chunks < 32) x &= (1u << n_chunks) - 1;
-            }
-            return x;
-        };
-        uint32_t todo = chunks(any16(mI) & any16(mJ));
-        if (todo == 0) continue;  // no point is reached by functions of both tiles
+        uint64_t sub_first = sizeof(T) == 4 ? (uint64_t)uni((int64_t)up->sub_first) : 0;
+        const uint64_t* mI = sg.unit_mask + mask_begin + 4 * ti;
+        const uint64_t* mJ = sg.unit_mask + mask_begin + 4 * tj;
+        uint64_t any_i = 0, any_j = 0, mj[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            any_i |= (uint64_t)uni((int64_t)mI[q]);
+            any_j |= mj[q] = (uint64_t)uni((int64_t)mJ[q]);
+        }
+        uint64_t todo = any_i & any_j;  // 16-row chunks both tiles reach
+        if (todo == 0) continue;        // none
         const bool diag = ti == tj;
         const int strip = (wave + tj) & 3;
-        const uint32_t ma = (uint32_t)(mI >> (16 * strip)) & 0xFFFF;
-        uint32_t mm[4];  // chunks that change this wave's block jb (none below the diagonal)
+        const uint64_t ma = (uint64_t)uni((int64_t)mI[strip]);
+        uint64_t mm[4];  // chunks that change this wave's block jb (none below the diagonal)
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb)
-            mm[jb] = diag && jb < strip ? 0 : chunks(ma & (uint32_t)(mJ >> (16 * jb)) & 0xFFFF);
-        const uint32_t m_any = mm[0] | mm[1] | mm[2] | mm[3];
+        for (int jb = 0; jb < 4; ++jb) mm[jb] = diag && jb < strip ? 0 : ma & mj[jb];
+        const uint64_t m_any = mm[0] | mm[1] | mm[2] | mm[3];
 
         const char* phi = static_cast<const char*>(sg.phi) + out_offset * (int)sizeof(T);
         const char* lv = TWO ? static_cast<const char*>(sg.gphi) + out_offset * (int)sizeof(T) : nullptr;
@@ -808,11 +808,9 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (!TWO) {  // w v of the unit's points, zeros beyond the last one
-            const __amdgpu_buffer_rsrc_t r = buffer_of(sg.wv + point_begin, np * 8);
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-                load4_to_lds(r, lds + WV + (2 * wave + q) * 256, 4 * lane, (2 * wave + q) * 256);
+        if (!TWO) {  // w v of the rows, zeros beyond the last one
+            const __amdgpu_buffer_rsrc_t r = buffer_of(sg.wv + row_begin, np * 8);
+            for (int q = wave; 32 * q < np; q += 4) load4_to_lds(r, lds + WV + q * 256, 4 * lane + q * 256, 0);
         }
         if (wave < 2)  // global indices of the tile's rows and columns
             load4_to_lds(buffer_of(sg.unit_fn + fn_begin, m * 4), lds + FN + wave * TILE * 4,
@@ -823,9 +821,12 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
             const int row = (wave * LOADS + q) * RPL + lane / SPR;
             voff[q] = row * ldb + (((lane % SPR) * 16) ^ (sizeof(T) == 4 ? (row & 1) * 64 : 0));
         }
-        auto issue = [&](int c, int stg) {
-            const int64_t o = (int64_t)c * KC * ldb;
-            const int bytes = (np - c * KC) * ldb;
+        // a chunk of 16 rows is taken in steps of KC: step h of chunk c
+        constexpr int STEPS = 16 / KC;
+        auto issue = [&](int c, int h, int stg) {
+            const int row = c * 16 + h * KC;
+            const int64_t o = (int64_t)row * ldb;
+            const int bytes = max(0, np - row) * ldb;
 #pragma unroll
             for (int op = 0; op < NOP; ++op) {
                 if ((op & 1) && diag) continue;
@@ -845,8 +846,26 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
         typename M::acc_t acc[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = M::zero();
-        auto compute = [&](int c, int stg) {
+        // FP32: the sums of a unit move to FP64 when the next one starts
+        d4 acc64[sizeof(T) == 4 ? 4 : 1] = {};
+        auto flush = [&]() {
+            if constexpr (sizeof(T) == 4)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc64[j][r] += (double)acc[j][r];
+                    acc[j] = M::zero();
+                }
+        };
+        auto compute = [&](int c, int h, int stg) {
             if (!((m_any >> c) & 1)) return;
+            if (sizeof(T) == 4) {
+                const uint64_t past = sub_first & ((2ull << c) - 1);
+                if (past) {
+                    flush();
+                    sub_first &= ~past;
+                }
+            }
             constexpr int KK = KC / 4;
             const unsigned char* base = lds + stg * STAGEB;
             T a[KK], bv[4][KK], a2[TWO ? KK : 1], b2[TWO ? 4 : 1][KK];
@@ -854,7 +873,7 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
             for (int kk = 0; kk < KK; ++kk) {
                 const T x = *reinterpret_cast<const T*>(base + a_off + kk * 4 * ROWB);
                 if (TWO) a[kk] = x, a2[kk] = *reinterpret_cast<const T*>(base + a_off + 2 * TILEB + kk * 4 * ROWB);
-                else a[kk] = T((double)x * *reinterpret_cast<const double*>(lds + WV + lk * 8 + (c * KC + kk * 4) * 8));
+                else a[kk] = T((double)x * *reinterpret_cast<const double*>(lds + WV + lk * 8 + (c * 16 + h * KC + kk * 4) * 8));
 #pragma unroll
                 for (int jb = 0; jb < 4; ++jb) {
                     const unsigned char* q = base + b_off[jb & 1] + (jb & 2) * 16 * (int)sizeof(T) + kk * 4 * ROWB;
@@ -874,34 +893,41 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
                         if (TWO) acc[jb] = M::op(a2[kk], b2[jb][kk], acc[jb]);
                     }
         };
-        uint32_t ahead = todo;
-#pragma unroll
-        for (int k = 0; k < S - 1; ++k)
-            if (ahead) {
-                issue(__builtin_ctz(ahead), k);
+        uint64_t ahead = todo;
+        int ah = 0, th = 0;  // steps of the chunks at the front of ahead and todo
+        auto issue_next = [&](int stg) {
+            issue(__builtin_ctzll(ahead), ah, stg);
+            if (++ah == STEPS) {
+                ah = 0;
                 ahead &= ahead - 1;
             }
-        // per chunk: its loads (every wave's) have landed and every wave is done with the stage that
+        };
+#pragma unroll
+        for (int k = 0; k < S - 1; ++k)
+            if (ahead) issue_next(k);
+        // per step: its loads (every wave's) have landed and every wave is done with the stage that
         // is refilled next
         while (todo) {
 #pragma unroll
             for (int stg = 0; stg < S; ++stg) {
-                const int c = __builtin_ctz(todo);
-                todo &= todo - 1;
+                const int c = __builtin_ctzll(todo), h = th;
+                if (++th == STEPS) {
+                    th = 0;
+                    todo &= todo - 1;
+                }
                 if (S == 2 || todo == 0) wait_loads<0>();
                 else if (diag) wait_loads<LOADS * NOP / 2>();
                 else wait_loads<LOADS * NOP>();
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                if (ahead) {
-                    issue(__builtin_ctz(ahead), (stg + S - 1) % S);
-                    ahead &= ahead - 1;
-                }
-                compute(c, stg);
+                if (ahead) issue_next((stg + S - 1) % S);
+                compute(c, h, stg);
                 if (todo == 0) break;
             }
         }
         if (m_any == 0) continue;
+        // pairs of a cluster's columns are not ordered by their global indices, so a pair's sum may
+        // go above or below the diagonal of H; the mirror adds the two
         const int32_t* gi = reinterpret_cast<const int32_t*>(lds + FN);
         gp<double> __restrict__ H = gptr(sg.H);
         const int64_t ldh = sg.ld;
@@ -917,7 +943,7 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = row0 + M::row(lk, r), col = jb * 16 + lr;
-                if (whole || (I0 + row < m && J0 + col < m && (!diag || row <= col))) gadd(Hr[r] + gj, (double)acc[jb][r]);
+                if (whole || (I0 + row < m && J0 + col < m && (!diag || row <= col))) gadd(Hr[r] + gj, sizeof(T) == 4 ? acc64[sizeof(T) == 4 ? jb : 0][r] + (double)acc[jb][r] : (double)acc[jb][r]);
             }
         }
     }
@@ -943,7 +969,7 @@ __global__ __launch_bounds__(512) void h_kernel_wide(const DevSeg* __restrict__ 
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
         const HItem it = static_cast<const HItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit u = sg.units[it.unit];
+        const DevUnit u = sg.item_units[it.unit];
         gp<const T> __restrict__ phi = gptr(static_cast<const T*>(sg.phi) + u.out_offset);
         gp<const double> __restrict__ wv = gptr(sg.wv + u.point_begin);
         const int np = u.n_points, ld = u.ld;
@@ -1089,7 +1115,7 @@ __global__ __launch_bounds__(64 * NW) void n_kernel(const DevSeg* __restrict__ s
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
         const NItem it = static_cast<const NItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit u = sg.units[it.unit];
+        const DevUnit u = sg.item_units[it.unit];
         gp<const T> __restrict__ phi = gptr(static_cast<const T*>(sg.phi) + u.out_offset);
         gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + u.fn_begin);
         gp<const double> __restrict__ D = gptr(sg.D);
@@ -1395,7 +1421,7 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
         const HItem it = static_cast<const HItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit u = sg.units[it.unit];
+        const DevUnit u = sg.item_units[it.unit];
         gp<const float> __restrict__ phi = gptr(static_cast<const float*>(sg.phi) + u.out_offset);
         gp<const double> __restrict__ wv = gptr(sg.wv + u.point_begin);
         const int np = u.n_points, ld = u.ld;
@@ -1540,7 +1566,7 @@ __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
         const NItem it = static_cast<const NItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit u = sg.units[it.unit];
+        const DevUnit u = sg.item_units[it.unit];
         gp<const float> __restrict__ phi = gptr(static_cast<const float*>(sg.phi) + u.out_offset);
         gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + u.fn_begin);
         gp<const double> __restrict__ D = gptr(sg.D);
@@ -1795,21 +1821,22 @@ hipError_t launch_force_atoms(const double* fb, const int64_t* atom_first, int64
     return hipGetLastError();
 }
 
-// Reach of the units' functions (DevSeg::unit_mask): per 16 columns of a unit, bit c is set when
-// some point of rows 16 c .. 16 c + 15 lies within the largest cutoff of an atom that owns one of
-// the columns; padding columns give no bits.  Geometry alone decides, so the masks are made once per
-// set of units.  One wave per unit, a thread per 16 columns.
+// Reach of the units' functions (DevSeg::unit_mask): per 16 columns of a unit or cluster, bit c is
+// set when some point of rows 16 c .. 16 c + 15 lies within the largest cutoff of an atom that owns
+// one of the columns; padding columns give no bits.  Geometry alone decides, so the masks are made
+// once per set of units.  One wave per unit or cluster, a thread per 16 columns.
 __global__ __launch_bounds__(64) void unit_mask_kernel(const DevSys* __restrict__ S, const DevUnit* __restrict__ units,
+                                                       const DevUnit* __restrict__ subs,
                                                        const int32_t* __restrict__ unit_atoms,
                                                        const int32_t* __restrict__ unit_cols, int64_t n_units,
-                                                       uint16_t* __restrict__ mask)
+                                                       uint64_t* __restrict__ mask)
 {
     for (int64_t k = blockIdx.x; k < n_units; k += gridDim.x) {
         const DevUnit u = units[k];
         const int32_t* at = unit_atoms + u.atom_begin;
         const int32_t* col = unit_cols + u.atom_begin;
         for (int blk = threadIdx.x; blk < u.ld / 16; blk += 64) {
-            uint32_t bits = 0;
+            uint64_t bits = 0;
             if (blk * 16 < u.m) {
                 int lo = 0, hi = u.n_atoms - 1;  // the atom that owns column 16 blk
                 while (lo < hi) {
@@ -1819,23 +1846,45 @@ __global__ __launch_bounds__(64) void unit_mask_kernel(const DevSys* __restrict_
                 for (int q = lo; q < u.n_atoms && col[q] < blk * 16 + 16; ++q) {
                     const double* A = S->atom_xyzr + 4 * (int64_t)at[q];
                     const double ax = A[0], ay = A[1], az = A[2], rc2 = A[3];
-                    for (int p = 0; p < u.n_points; ++p) {
-                        const int64_t g = u.point_begin + p;
-                        if (dist2_exact(S->px[g] - ax, S->py[g] - ay, S->pz[g] - az) < rc2) bits |= 1u << (p >> 4);
+                    for (int t = u.sub_begin; t < u.sub_begin + u.sub_count; ++t) {
+                        const int64_t p0 = subs[t].point_begin, r0 = subs[t].row_begin - u.row_begin;
+                        for (int p = 0; p < subs[t].n_points; ++p)
+                            if (dist2_exact(S->px[p0 + p] - ax, S->py[p0 + p] - ay, S->pz[p0 + p] - az) < rc2)
+                                bits |= 1ull << ((r0 + p) >> 4);
                     }
                 }
             }
-            mask[u.mask_begin + blk] = (uint16_t)bits;
+            mask[u.mask_begin + blk] = bits;
         }
     }
 }
 
-hipError_t launch_unit_masks(const DevSys* sys, const DevUnit* units, const int32_t* unit_atoms, const int32_t* unit_cols,
-                             int64_t n_units, uint16_t* mask, hipStream_t st)
+hipError_t launch_unit_masks(const DevSys* sys, const DevUnit* units, const DevUnit* subs, const int32_t* unit_atoms,
+                             const int32_t* unit_cols, int64_t n_units, uint64_t* mask, hipStream_t st)
 {
     if (n_units <= 0) return hipSuccess;
     hipLaunchKernelGGL(unit_mask_kernel, dim3((unsigned)std::min<int64_t>(n_units, 1 << 20)), dim3(64), 0, st, sys, units,
-                       unit_atoms, unit_cols, n_units, mask);
+                       subs, unit_atoms, unit_cols, n_units, mask);
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void wv_rows_kernel(const DevUnit* __restrict__ subs, int64_t n_subs,
+                                                      const double* __restrict__ pw, const int32_t* __restrict__ perm,
+                                                      const double* __restrict__ v, double* __restrict__ wv)
+{
+    for (int64_t k = blockIdx.x; k < n_subs; k += gridDim.x) {
+        const int64_t p0 = subs[k].point_begin, r0 = subs[k].row_begin;
+        const int np = subs[k].n_points, nr = subs[k].n_rows;
+        for (int r = threadIdx.x; r < nr; r += blockDim.x) wv[r0 + r] = r < np ? pw[p0 + r] * v[perm[p0 + r]] : 0.0;
+    }
+}
+
+hipError_t launch_wv_rows(const DevUnit* subs, int64_t n_subs, const double* pw, const int32_t* perm, const double* v_caller,
+                          double* wv, hipStream_t st)
+{
+    if (n_subs <= 0) return hipSuccess;
+    hipLaunchKernelGGL(wv_rows_kernel, dim3((unsigned)std::min<int64_t>(n_subs, 65536)), dim3(256), 0, st, subs, n_subs, pw,
+                       perm, v_caller, wv);
     return hipGetLastError();
 }
 
@@ -1883,21 +1932,24 @@ hipError_t launch_wa(const double* pw, const int32_t* perm, const double* a_call
     return hipGetLastError();
 }
 
-// H[j][i] = H[i][j] for i < j, through 32x32 LDS tiles (coalesced on both sides).
+// H[i][j] = H[j][i] = H[i][j] + H[j][i] for i < j, through 32x32 LDS tiles (coalesced on both
+// sides): the contractions add a pair's sums to either of the two.
 __global__ __launch_bounds__(256) void mirror_kernel(double* __restrict__ H, int64_t n)
 {
-    __shared__ double t[32][33];
+    __shared__ double up[32][33], lo[32][33];
     const int64_t bi = blockIdx.y, bj = blockIdx.x;
     if (bi > bj) return;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
     for (int r = ty; r < 32; r += 8) {
-        const int64_t i = bi * 32 + r, j = bj * 32 + tx;
-        t[r][tx] = (i < n && j < n) ? H[i * n + j] : 0.0;
+        const int64_t i = bi * 32 + r, j = bj * 32 + tx, k = bj * 32 + r, l = bi * 32 + tx;
+        up[r][tx] = (i < n && j < n) ? H[i * n + j] : 0.0;
+        lo[r][tx] = (k < n && l < n) ? H[k * n + l] : 0.0;
     }
     __syncthreads();
     for (int r = ty; r < 32; r += 8) {
-        const int64_t i = bj * 32 + r, j = bi * 32 + tx;  // lower-triangle target (i > j)
-        if (i < n && j < n && i > j) H[i * n + j] = t[tx][r];
+        const int64_t i = bi * 32 + r, j = bj * 32 + tx, k = bj * 32 + r, l = bi * 32 + tx;
+        if (i < n && j < n && i < j) H[i * n + j] = up[r][tx] + lo[tx][r];
+        if (k < n && l < n && k > l) H[k * n + l] = up[tx][r] + lo[r][tx];
     }
 }
 

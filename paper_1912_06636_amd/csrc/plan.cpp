@@ -497,6 +497,73 @@ void make_groups(const HostBasis& b, const std::vector<int64_t>& batch_ptr,
     flush();
 }
 
+void make_clusters(const HostBasis& b, const std::vector<int64_t>& batch_ptr, const std::vector<int64_t>& atom_ptr,
+                   const std::vector<int32_t>& atoms, const std::vector<Unit>& units, const std::vector<int32_t>& unit_atoms,
+                   int32_t max_rows, int32_t tile, int64_t max_elems, std::vector<Cluster>& clusters,
+                   std::vector<int32_t>& cl_atoms, std::vector<int32_t>& cl_cols, std::vector<int32_t>& asc_atoms,
+                   std::vector<int32_t>& asc_cols)
+{
+    asc_atoms.clear();
+    asc_cols.clear();
+    clusters.clear();
+    cl_atoms.clear();
+    cl_cols.clear();
+    auto rows_of = [](const Unit& u) { return (u.n_points + 15) / 16 * 16; };
+    auto padded = [&](int64_t m) { return (m + tile - 1) / tile * tile; };
+    std::vector<int32_t> cur, merged;
+    std::vector<std::pair<int64_t, int32_t>> reach;  // (points in batches the atom reaches, atom), by atom
+    std::vector<int64_t> points(b.n_atoms, 0);       // of the atoms of the current cluster
+    size_t k = 0;
+    while (k < units.size()) {
+        auto list = [&](size_t q) {
+            return std::make_pair(unit_atoms.begin() + units[q].atom_begin,
+                                  unit_atoms.begin() + units[q].atom_begin + units[q].n_atoms);
+        };
+        cur.assign(list(k).first, list(k).second);
+        int64_t rows = rows_of(units[k]), apart = rows * units[k].m;
+        size_t e = k + 1;
+        for (; e < units.size() && rows + rows_of(units[e]) <= max_rows; ++e) {
+            merged.clear();
+            std::set_union(cur.begin(), cur.end(), list(e).first, list(e).second, std::back_inserter(merged));
+            const int64_t r = rows + rows_of(units[e]), a = apart + (int64_t)rows_of(units[e]) * units[e].m;
+            const int64_t mu = list_size(b, merged);
+            if (4 * r * mu > 5 * a || r * padded(mu) > max_elems) break;
+            cur.swap(merged);
+            rows = r;
+            apart = a;
+        }
+        for (int32_t a : cur) points[a] = 0;
+        for (size_t q = k; q < e; ++q) {
+            const int64_t p1 = units[q].point_begin + units[q].n_points;
+            for (int64_t bi = units[q].batch; bi + 1 < (int64_t)batch_ptr.size() && batch_ptr[bi] < p1; ++bi) {
+                const int64_t np = std::min(batch_ptr[bi + 1], p1) - std::max(batch_ptr[bi], units[q].point_begin);
+                for (int64_t t = atom_ptr[bi]; t < atom_ptr[bi + 1]; ++t) points[atoms[t]] += np;
+            }
+        }
+        reach.clear();
+        for (int32_t a : cur) reach.push_back({points[a], a});
+        std::stable_sort(reach.begin(), reach.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+        Cluster c;
+        c.unit_begin = (int32_t)k;
+        c.unit_count = (int32_t)(e - k);
+        c.n_rows = (int32_t)rows;
+        c.n_atoms = (int32_t)cur.size();
+        c.atom_begin = (int64_t)cl_atoms.size();
+        auto place = [&](int32_t a, int32_t col, std::vector<int32_t>& at, std::vector<int32_t>& cols) {
+            at.push_back(a);
+            cols.push_back(col);
+            return col + (int32_t)(b.atom_first[a + 1] - b.atom_first[a]);
+        };
+        int32_t col = 0;
+        for (int32_t a : cur) col = place(a, col, asc_atoms, asc_cols);
+        col = 0;
+        for (const auto& x : reach) col = place(x.second, col, cl_atoms, cl_cols);
+        c.m = col;
+        clusters.push_back(c);
+        k = e;
+    }
+}
+
 void batch_units(const HostBasis& b, const std::vector<int64_t>& batch_ptr,
                  const std::vector<int64_t>& atom_ptr, const std::vector<int32_t>& atoms,
                  int64_t batch_begin, int64_t batch_end, std::vector<Unit>& units,

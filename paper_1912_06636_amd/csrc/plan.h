@@ -76,6 +76,27 @@ void make_groups(const HostBasis& b, const std::vector<int64_t>& batch_ptr,
                  int32_t group_max, std::vector<Unit>& units, std::vector<int32_t>& unit_atoms,
                  std::vector<int32_t>& unit_cols);
 
+// Hamiltonian clusters: runs of consecutive units contracted as one, over the union of their
+// atoms.  Every unit's rows start at a multiple of 16 within its cluster (row_off), the last ones up
+// to the next multiple are padding.
+struct Cluster {
+    int32_t unit_begin, unit_count;
+    int32_t n_rows;       // a multiple of 16
+    int32_t n_atoms, m;
+    int64_t atom_begin;   // into cluster atom arrays
+};
+
+// Packs consecutive units into clusters of at most max_rows rows while the values to evaluate
+// (rows times columns) grow by at most a quarter and fit max_elems (columns rounded up to tile).
+// cl_atoms / cl_cols as make_groups, the atoms of a cluster ordered by the number of its points in
+// batches they reach, most first, so that columns which few points reach share tiles; asc_atoms /
+// asc_cols the same in ascending order.
+void make_clusters(const HostBasis& b, const std::vector<int64_t>& batch_ptr, const std::vector<int64_t>& atom_ptr,
+                   const std::vector<int32_t>& atoms, const std::vector<Unit>& units, const std::vector<int32_t>& unit_atoms,
+                   int32_t max_rows, int32_t tile, int64_t max_elems, std::vector<Cluster>& clusters,
+                   std::vector<int32_t>& cl_atoms, std::vector<int32_t>& cl_cols, std::vector<int32_t>& asc_atoms,
+                   std::vector<int32_t>& asc_cols);
+
 // One unit per batch (used for basis output per batch).
 void batch_units(const HostBasis& b, const std::vector<int64_t>& batch_ptr,
                  const std::vector<int64_t>& atom_ptr, const std::vector<int32_t>& atoms,

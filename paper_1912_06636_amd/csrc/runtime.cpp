@@ -301,6 +301,10 @@ struct nao_system_s {
     DevArray d_sys, d_px, d_py, d_pz, d_pw, d_perm, d_atoms, d_species, d_shell_ptr, d_shell_l, d_shell_rad,
         d_radial_par, d_spline, d_fn_ptr, d_fn_code;
     DevArray d_units, d_unit_atoms, d_unit_cols, d_unit_fn, d_unit_mask, d_h_items, d_hw_items, d_n_items;
+    // Hamiltonian clusters (FP64 and FP32 with 64-wide tiles; cl_blocks is empty when there are none)
+    std::vector<Block> cl_blocks;
+    int64_t n_cl_subs = 0, n_cl_rows = 0, n_cl_atoms = 0, n_cl_fn = 0, n_cl_mask = 0;
+    DevArray d_cl_units, d_cl_subs, d_cl_atoms, d_cl_cols, d_cl_fn, d_cl_mask, d_cl_items;
     DevArray d_wv, d_v, d_D, d_H, d_n, d_gn, d_a, d_wa, d_segs, d_Q, d_fb, d_atom_first, d_F;
     // resident basis values (opt-in): every block's values kept across operations
     bool resident = false;
@@ -318,7 +322,8 @@ size_t system_bytes(const nao_system_s* s)
 {
     const DevArray* arr[] = {&s->d_sys, &s->d_px, &s->d_py, &s->d_pz, &s->d_pw, &s->d_perm, &s->d_atoms,
                              &s->d_species, &s->d_shell_ptr, &s->d_shell_l, &s->d_shell_rad, &s->d_radial_par,
-                             &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn, &s->d_unit_mask,
+                             &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn, &s->d_unit_mask, &s->d_cl_units, &s->d_cl_subs,
+                             &s->d_cl_atoms, &s->d_cl_cols, &s->d_cl_fn, &s->d_cl_mask, &s->d_cl_items,
                              &s->d_h_items, &s->d_hw_items, &s->d_n_items, &s->d_wv, &s->d_v, &s->d_D, &s->d_H, &s->d_n,
                              &s->d_gn, &s->d_a, &s->d_wa, &s->d_segs, &s->d_Q, &s->d_fb, &s->d_atom_first,
                              &s->d_F, &s->d_phi_res};
@@ -331,7 +336,8 @@ void free_all(nao_system_s* s)
 {
     DevArray* arr[] = {&s->d_sys, &s->d_px, &s->d_py, &s->d_pz, &s->d_pw, &s->d_perm, &s->d_atoms,
                        &s->d_species, &s->d_shell_ptr, &s->d_shell_l, &s->d_shell_rad, &s->d_radial_par,
-                       &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn, &s->d_unit_mask,
+                       &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn, &s->d_unit_mask, &s->d_cl_units, &s->d_cl_subs,
+                             &s->d_cl_atoms, &s->d_cl_cols, &s->d_cl_fn, &s->d_cl_mask, &s->d_cl_items,
                        &s->d_h_items, &s->d_hw_items, &s->d_n_items, &s->d_wv, &s->d_v, &s->d_D, &s->d_H, &s->d_n, &s->d_gn, &s->d_a, &s->d_wa, &s->d_segs,
                        &s->d_Q, &s->d_fb, &s->d_atom_first, &s->d_F, &s->d_phi_res};
     for (auto* a : arr) {
@@ -340,6 +346,8 @@ void free_all(nao_system_s* s)
         a->bytes = 0;
     }
 }
+
+constexpr int64_t CLUSTER_ITEMS = 6144;  // tile pairs that one operation keeps at least
 
 int32_t round_up(int32_t x, int32_t m) { return (x + m - 1) / m * m; }
 
@@ -367,6 +375,131 @@ nao_status resident_layout(nao_system_s* s)
     return st;
 }
 
+void drop_clusters(nao_system_s* s)
+{
+    for (DevArray* a : {&s->d_cl_units, &s->d_cl_subs, &s->d_cl_atoms, &s->d_cl_cols, &s->d_cl_fn, &s->d_cl_mask, &s->d_cl_items}) {
+        dev_free(s->ctx, a->p, a->bytes);
+        a->p = nullptr;
+        a->bytes = 0;
+    }
+    s->cl_blocks.clear();
+    s->n_cl_subs = s->n_cl_rows = 0;
+}
+
+// Clusters of the execution units for the Hamiltonian (FP64 and FP32, 64-wide tiles): a tile pair
+// of a cluster adds its 4,096 sums to H once for two to four units, whose sums would otherwise
+// each cost as many atomics (they bound the FP32 kernel: a 100-atom slab's 14.4 ms fell to 7.5
+// without them).  Columns of the same cluster differ in how many points reach them, which the
+// masks turn into work left out.  Only while enough items remain to fill the chip: 256 CUs take
+// 1,024 tile pairs at a time.
+nao_status build_clusters(nao_system_s* s, const std::vector<Unit>& units, const std::vector<int32_t>& uat)
+{
+    nao_ctx c = s->ctx;
+    drop_clusters(s);
+    const int32_t rows = s->n_h_items >= 4 * CLUSTER_ITEMS ? MAX_CLUSTER_ROWS : 2 * MAX_UNIT_POINTS;
+    if (s->group_max == 0 || s->h_tile != TILE || s->n_h_items < 2 * CLUSTER_ITEMS) return NAO_OK;
+    const int64_t cap = (int64_t)c->scratch_cap_elems;
+    std::vector<Cluster> cl;
+    std::vector<int32_t> cat, ccol, cfn, aat, acol, afn;
+    make_clusters(s->basis, s->batch_ptr, s->atom_ptr, s->atoms, units, uat, rows, TILE, cap, cl, cat, ccol, aat, acol);
+    std::vector<DevUnit> dc(cl.size()), ds;
+    std::vector<HItem> items;
+    std::vector<Block> blocks;
+    Block cur;
+    int64_t off = 0, mask_len = 0, row = 0;
+    for (size_t k = 0; k < cl.size(); ++k) {
+        const Cluster& q = cl[k];
+        DevUnit d{};
+        d.atom_begin = q.atom_begin;
+        d.fn_begin = (int64_t)cfn.size();
+        d.mask_begin = mask_len;
+        d.row_begin = row;
+        d.n_points = d.n_rows = q.n_rows;
+        d.n_atoms = q.n_atoms;
+        d.m = q.m;
+        d.ld = round_up(q.m, TILE);
+        d.sub_begin = (int32_t)ds.size();
+        d.sub_count = q.unit_count;
+        mask_len += d.ld / 16;
+        auto functions = [&](const std::vector<int32_t>& at, std::vector<int32_t>& fn) {
+            for (int32_t t = 0; t < q.n_atoms; ++t)
+                for (int64_t f = s->basis.atom_first[at[q.atom_begin + t]]; f < s->basis.atom_first[at[q.atom_begin + t] + 1]; ++f)
+                    fn.push_back((int32_t)f);
+        };
+        functions(cat, cfn);
+        functions(aat, afn);
+        const int64_t elems = (int64_t)d.n_rows * d.ld;
+        if (elems > cap) return NAO_OK;  // only the padding rows take it past the scratch: no clusters
+        if (off + elems > cap) {
+            blocks.push_back(cur);
+            cur = Block();
+            cur.unit_begin = (int64_t)ds.size();
+            cur.h_begin = (int64_t)items.size();
+            off = 0;
+        }
+        d.out_offset = off;
+        for (int32_t t = 0; t < q.unit_count; ++t) {
+            const Unit& u = units[q.unit_begin + t];
+            DevUnit b = d;
+            b.point_begin = u.point_begin;
+            b.n_points = u.n_points;
+            b.n_rows = round_up(u.n_points, 16);
+            b.row_begin = row;
+            b.out_offset = off + (row - d.row_begin) * d.ld;
+            if (t) d.sub_first |= 1ull << ((row - d.row_begin) / 16);
+            row += b.n_rows;
+            ds.push_back(b);
+        }
+        dc[k] = d;
+        off += elems;
+        cur.phi_elems = off;
+        cur.unit_count += q.unit_count;
+        const int nt = d.ld / TILE;
+        for (int tj = 0; tj < nt; ++tj)
+            for (int ti = 0; ti <= tj; ++ti) items.push_back(HItem{(int32_t)k, (int16_t)ti, (int16_t)tj});
+        cur.h_count = (int64_t)items.size() - cur.h_begin;
+    }
+    if (cur.unit_count) blocks.push_back(cur);
+    // both orders of every list, the ascending one in the second half
+    s->n_cl_atoms = (int64_t)cat.size();
+    s->n_cl_fn = (int64_t)cfn.size();
+    s->n_cl_mask = mask_len;
+    cat.insert(cat.end(), aat.begin(), aat.end());
+    ccol.insert(ccol.end(), acol.begin(), acol.end());
+    cfn.insert(cfn.end(), afn.begin(), afn.end());
+    nao_status st;
+    if ((st = upload(c, s->d_cl_units, dc.data(), dc.size() * sizeof(DevUnit))) != NAO_OK) return st;
+    if ((st = upload(c, s->d_cl_subs, ds.data(), ds.size() * sizeof(DevUnit))) != NAO_OK) return st;
+    if ((st = upload(c, s->d_cl_atoms, cat.data(), cat.size() * sizeof(int32_t))) != NAO_OK) return st;
+    if ((st = upload(c, s->d_cl_cols, ccol.data(), ccol.size() * sizeof(int32_t))) != NAO_OK) return st;
+    if ((st = upload(c, s->d_cl_fn, cfn.data(), cfn.size() * sizeof(int32_t))) != NAO_OK) return st;
+    if ((st = upload(c, s->d_cl_items, items.data(), items.size() * sizeof(HItem))) != NAO_OK) return st;
+    if ((st = ensure(c, s->d_cl_mask, std::max<int64_t>(1, 2 * mask_len) * sizeof(uint64_t))) != NAO_OK) return st;
+    for (int k = 0; k < 2; ++k)
+        HIP_TRY(c, launch_unit_masks(s->d_sys.as<DevSys>(), s->d_cl_units.as<DevUnit>(), s->d_cl_subs.as<DevUnit>(),
+                                     s->d_cl_atoms.as<int32_t>() + k * s->n_cl_atoms,
+                                     s->d_cl_cols.as<int32_t>() + k * s->n_cl_atoms, (int64_t)dc.size(),
+                                     s->d_cl_mask.as<uint64_t>() + k * s->n_cl_mask, c->stream));
+    size_t need = 0;
+    for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
+    if ((st = grow_scratch(c, need)) != NAO_OK) return st;
+    if ((st = ensure(c, s->d_wv, std::max(s->n_points, row) * sizeof(double))) != NAO_OK) return st;
+    if ((st = ensure(c, s->d_segs, std::max(s->blocks.size(), blocks.size()) * sizeof(DevSeg))) != NAO_OK) return st;
+    HIP_TRY(c, hipStreamSynchronize(c->stream));  // host vectors above go out of scope
+    s->cl_blocks = std::move(blocks);
+    s->n_cl_subs = (int64_t)ds.size();
+    s->n_cl_rows = row;
+    return NAO_OK;
+}
+
+// Whether (and in which column order, see make_seg) a Hamiltonian of this precision runs over the
+// system's clusters.
+int use_clusters(const nao_system_s* s, nao_precision prec)
+{
+    if (s->cl_blocks.empty()) return 0;
+    return prec == NAO_FP64 ? 1 : prec == NAO_FP32 ? 2 : 0;
+}
+
 // Build execution groups, split them into scratch-sized blocks and upload units and items.
 nao_status build_groups(nao_system_s* s)
 {
@@ -389,8 +522,12 @@ nao_status build_groups(nao_system_s* s)
         d.point_begin = u.point_begin;
         d.atom_begin = u.atom_begin;
         d.fn_begin = (int64_t)ufn.size();
-        d.n_points = u.n_points;
+        d.row_begin = u.point_begin;
+        d.sub_first = 0;
+        d.n_points = d.n_rows = u.n_points;
         d.n_atoms = u.n_atoms;
+        d.sub_begin = (int32_t)k;
+        d.sub_count = 1;
         d.m = u.m;
         d.ld = round_up(u.m, std::max<int32_t>(TILE, s->h_tile));
         for (int32_t q = 0; q < u.n_atoms; ++q) {
@@ -443,9 +580,10 @@ nao_status build_groups(nao_system_s* s)
     if ((st = upload(c, s->d_h_items, hitems.data(), hitems.size() * sizeof(HItem))) != NAO_OK) return st;
     if ((st = upload(c, s->d_hw_items, hwitems.data(), hwitems.size() * sizeof(HItem))) != NAO_OK) return st;
     if ((st = upload(c, s->d_n_items, nitems.data(), nitems.size() * sizeof(NItem))) != NAO_OK) return st;
-    if ((st = ensure(c, s->d_unit_mask, std::max<int64_t>(1, mask_len) * sizeof(uint16_t))) != NAO_OK) return st;
-    HIP_TRY(c, launch_unit_masks(s->d_sys.as<DevSys>(), s->d_units.as<DevUnit>(), s->d_unit_atoms.as<int32_t>(),
-                                 s->d_unit_cols.as<int32_t>(), (int64_t)du.size(), s->d_unit_mask.as<uint16_t>(), c->stream));
+    if ((st = ensure(c, s->d_unit_mask, std::max<int64_t>(1, mask_len) * sizeof(uint64_t))) != NAO_OK) return st;
+    HIP_TRY(c, launch_unit_masks(s->d_sys.as<DevSys>(), s->d_units.as<DevUnit>(), s->d_units.as<DevUnit>(),
+                                 s->d_unit_atoms.as<int32_t>(), s->d_unit_cols.as<int32_t>(), (int64_t)du.size(),
+                                 s->d_unit_mask.as<uint64_t>(), c->stream));
     if ((st = ensure(c, s->d_segs, std::max<size_t>(1, s->blocks.size()) * sizeof(DevSeg))) != NAO_OK) return st;
     size_t need = 0;
     for (const Block& b : s->blocks) need = std::max(need, (size_t)b.phi_elems);
@@ -453,20 +591,46 @@ nao_status build_groups(nao_system_s* s)
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     s->h_units = std::move(du);
     s->h_item_first = std::move(item_first);
+    if ((st = build_clusters(s, units, uat)) != NAO_OK) {
+        drop_clusters(s);  // they are not needed: the Hamiltonian then runs over the units
+        if (st != NAO_ERR_BUDGET && st != NAO_ERR_OUT_OF_MEMORY) return st;
+        if ((st = grow_scratch(c, need)) != NAO_OK) return st;
+    }
     return resident_layout(s);
 }
 
 // Hamiltonian segments use the 128-wide items when wide is set (FP64 / FP32 on systems with
 // h_tile 128), else the 64-wide ones.
-DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = false)
+// clusters: over the system's clusters, 1 with columns by reach (FP64), 2 with ascending columns: a
+// pair's w v goes to the column that comes first and FP32 rounds the product, so FP32 keeps the order
+// that the units have.
+DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = false, int clusters = 0)
 {
     DevSeg g{};
+    if (clusters) {
+        g.sys = s->d_sys.as<DevSys>();
+        g.units = s->d_cl_subs.as<DevUnit>();
+        g.item_units = s->d_cl_units.as<DevUnit>();
+        const int64_t k = clusters - 1;
+        g.unit_atoms = s->d_cl_atoms.as<int32_t>() + k * s->n_cl_atoms;
+        g.unit_cols = s->d_cl_cols.as<int32_t>() + k * s->n_cl_atoms;
+        g.unit_fn = s->d_cl_fn.as<int32_t>() + k * s->n_cl_fn;
+        g.unit_mask = s->d_cl_mask.as<uint64_t>() + k * s->n_cl_mask;
+        g.items = s->d_cl_items.p;
+        g.phi = s->ctx->scratch;
+        g.ld = s->basis.n_basis;
+        g.unit_begin = b.unit_begin;
+        g.unit_count = b.unit_count;
+        g.item_begin = b.h_begin;
+        g.item_count = b.h_count;
+        return g;
+    }
     g.sys = s->d_sys.as<DevSys>();
-    g.units = s->d_units.as<DevUnit>();
+    g.units = g.item_units = s->d_units.as<DevUnit>();
     g.unit_atoms = s->d_unit_atoms.as<int32_t>();
     g.unit_cols = s->d_unit_cols.as<int32_t>();
     g.unit_fn = s->d_unit_fn.as<int32_t>();
-    g.unit_mask = s->d_unit_mask.as<uint16_t>();
+    g.unit_mask = s->d_unit_mask.as<uint64_t>();
     g.items = ham ? (wide ? (const void*)s->d_hw_items.p : (const void*)s->d_h_items.p) : (const void*)s->d_n_items.p;
     g.phi = s->ctx->scratch;
     g.ld = s->basis.n_basis;
@@ -673,7 +837,7 @@ nao_status many_build(nao_ctx c, const nao_work* work, int64_t n_work, nao_preci
     int64_t wv_total = 0;
     for (const nao_work& w : m->entries) {
         m->wv_off.push_back(wv_total);
-        if (w.op == 0) wv_total += w.sys->n_points;
+        if (w.op == 0) wv_total += use_clusters(w.sys, prec) ? w.sys->n_cl_rows : w.sys->n_points;
     }
     nao_status st = pool_take(c, m->d_wv, std::max<int64_t>(1, wv_total) * sizeof(double));
     if (st != NAO_OK) return st;
@@ -681,7 +845,8 @@ nao_status many_build(nao_ctx c, const nao_work* work, int64_t n_work, nao_preci
     // contexts on this device)
     int64_t need = 0;
     for (const nao_work& w : m->entries)
-        for (const Block& b : w.sys->blocks) need = std::max(need, b.phi_elems);
+        for (const Block& b : w.op == 0 && use_clusters(w.sys, prec) ? w.sys->cl_blocks : w.sys->blocks)
+            need = std::max(need, b.phi_elems);
     if ((st = grow_scratch(c, (size_t)need)) != NAO_OK) return st;
     // one segment per (entry, block); consecutive segments share a chunk while their basis
     // values fit the scratch
@@ -692,13 +857,14 @@ nao_status many_build(nao_ctx c, const nao_work* work, int64_t n_work, nao_preci
         const nao_work& w = m->entries[e];
         nao_system_s* s = w.sys;
         const bool ham = w.op == 0;
-        for (const Block& b : s->blocks) {
+        const int cl = ham ? use_clusters(s, prec) : 0;
+        for (const Block& b : cl ? s->cl_blocks : s->blocks) {
             if (off + b.phi_elems > (int64_t)c->scratch_elems && off > 0) {
                 chunks.emplace_back();
                 off = 0;
             }
             const bool wide = ham && s->h_tile == 128 && (prec == NAO_FP64 || prec == NAO_FP32);
-            DevSeg g = make_seg(s, b, ham, wide);
+            DevSeg g = make_seg(s, b, ham, wide, cl);
             if (ham) {
                 g.wv = m->d_wv.as<double>() + m->wv_off[e];
                 g.H = const_cast<double*>(w.out);
@@ -772,8 +938,11 @@ nao_status many_enqueue(nao_ctx c, ManyPlan* m)
         nao_system_s* s = w.sys;
         if (w.op == 0) {
             LAUNCH(c, "fill", launch_fill(w.out, s->basis.n_basis * s->basis.n_basis, 0.0, c->stream));
-            LAUNCH(c, "wv", launch_wv(s->d_pw.as<double>(), s->d_perm.as<int32_t>(), w.in,
-                                      m->d_wv.as<double>() + m->wv_off[e], s->n_points, c->stream));
+            LAUNCH(c, "wv", use_clusters(s, m->prec)
+                                ? launch_wv_rows(s->d_cl_subs.as<DevUnit>(), s->n_cl_subs, s->d_pw.as<double>(),
+                                                 s->d_perm.as<int32_t>(), w.in, m->d_wv.as<double>() + m->wv_off[e], c->stream)
+                                : launch_wv(s->d_pw.as<double>(), s->d_perm.as<int32_t>(), w.in,
+                                            m->d_wv.as<double>() + m->wv_off[e], s->n_points, c->stream));
         } else {
             LAUNCH(c, "fill", launch_fill(w.out, s->n_points, 0.0, c->stream));
         }
@@ -1497,7 +1666,7 @@ nao_status nao_eval_basis(nao_system s, int64_t b0, int64_t b1, double* phi, nao
         d.atom_begin = u.atom_begin;
         d.fn_begin = 0;
         d.out_offset = phi_ptr[k];
-        d.n_points = u.n_points;
+        d.n_points = d.n_rows = u.n_points;
         d.n_atoms = u.n_atoms;
         d.m = u.m;
         d.ld = u.m;
@@ -1564,11 +1733,13 @@ static nao_status run_blocks(nao_system s, bool ham, nao_precision prec, const d
     const bool res = s->resident && s->d_phi_res.p && s->res_off.size() == s->blocks.size();
     const int kind = f32 ? 1 : 0;
     const bool evaluate = !res || s->res_kind != kind;
+    const int cl = ham && !res ? use_clusters(s, prec) : 0;  // resident values are laid out by units
+    const std::vector<Block>& blocks = cl ? s->cl_blocks : s->blocks;
     size_t need = 0;
-    for (const Block& b : s->blocks) need = std::max(need, (size_t)b.phi_elems);
-    const bool ovl = !res && s->blocks.size() > 1 && overlap_ready(c, need);
-    for (size_t k = 0; k < s->blocks.size(); ++k) {
-        DevSeg g = make_seg(s, s->blocks[k], ham, wide);
+    for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
+    const bool ovl = !res && blocks.size() > 1 && overlap_ready(c, need);
+    for (size_t k = 0; k < blocks.size(); ++k) {
+        DevSeg g = make_seg(s, blocks[k], ham, wide, cl);
         if (ovl && (k & 1)) g.phi = c->scratch2;
         if (res) g.phi = static_cast<char*>(s->d_phi_res.p) + s->res_off[k] * (f32 ? sizeof(float) : sizeof(double));
         g.wv = wv;
@@ -1618,7 +1789,10 @@ nao_status nao_integrate_h(nao_system s, const double* v, nao_memspace v_space, 
         Hd = s->d_H.as<double>();
     }
     LAUNCH(c, "fill", launch_fill(Hd, nb * nb, 0.0, c->stream));
-    LAUNCH(c, "wv", launch_wv(s->d_pw.as<double>(), s->d_perm.as<int32_t>(), vd, s->d_wv.as<double>(), n, c->stream));
+    const bool cl = use_clusters(s, prec) && !(s->resident && s->d_phi_res.p && s->res_off.size() == s->blocks.size());
+    LAUNCH(c, "wv", cl ? launch_wv_rows(s->d_cl_subs.as<DevUnit>(), s->n_cl_subs, s->d_pw.as<double>(), s->d_perm.as<int32_t>(),
+                                        vd, s->d_wv.as<double>(), c->stream)
+                       : launch_wv(s->d_pw.as<double>(), s->d_perm.as<int32_t>(), vd, s->d_wv.as<double>(), n, c->stream));
     if ((st = run_blocks(s, true, prec, s->d_wv.as<double>(), nullptr, Hd, nullptr)) != NAO_OK) return st;
     LAUNCH(c, "mirror", launch_mirror(Hd, nb, c->stream));
     if (H_space == NAO_MEM_HOST) {
@@ -1744,20 +1918,20 @@ nao_status nao_update_density(nao_system s, const double* D, nao_memspace D_spac
 // Extra per-block scratch beside the basis values: `per_value` FP64 slots per basis value.
 // Both second buffers for an overlapped extended operation whose extra block holds per_value
 // values per basis value (call after ensure_gscratch).
-static bool overlap_ext(nao_system s, int per_value)
+static bool overlap_ext(nao_system s, int per_value, const std::vector<Block>& blocks)
 {
     nao_ctx c = s->ctx;
-    if (s->blocks.size() < 2) return false;
+    if (blocks.size() < 2) return false;
     size_t need = 0;
-    for (const Block& b : s->blocks) need = std::max(need, (size_t)b.phi_elems);
+    for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
     return overlap_ready(c, need) && overlap_gscratch(c, need * per_value * sizeof(double));
 }
 
-static nao_status ensure_gscratch(nao_system s, int per_value)
+static nao_status ensure_gscratch(nao_system s, int per_value, const std::vector<Block>& blocks)
 {
     nao_ctx c = s->ctx;
     size_t need = 0;
-    for (const Block& b : s->blocks) need = std::max(need, (size_t)b.phi_elems * per_value * sizeof(double));
+    for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems * per_value * sizeof(double));
     if (need <= c->gscratch_bytes) return NAO_OK;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     dev_free(c, c->gscratch, c->gscratch_bytes);
@@ -1780,7 +1954,9 @@ static nao_status integrate_h_with_l(nao_system s, const double* v, const double
     if ((in_space != NAO_MEM_HOST && in_space != NAO_MEM_DEVICE) || (H_space != NAO_MEM_HOST && H_space != NAO_MEM_DEVICE))
         return (set_err(c, "bad memspace"), NAO_ERR_INVALID_ARG);
     nao_status st;
-    if ((st = ensure_gscratch(s, 1)) != NAO_OK) return st;  // L: one value per basis value
+    const int cl = use_clusters(s, prec);
+    const std::vector<Block>& blocks = cl ? s->cl_blocks : s->blocks;
+    if ((st = ensure_gscratch(s, 1, blocks)) != NAO_OK) return st;  // L: one value per basis value
     const bool has_a = a != nullptr && n > 0;
     const double* vd = v;
     const double* ad = a;
@@ -1806,10 +1982,10 @@ static nao_status integrate_h_with_l(nao_system s, const double* v, const double
         LAUNCH(c, "wa", launch_wa(s->d_pw.as<double>(), s->d_perm.as<int32_t>(), ad, s->d_wa.as<double>(), n, c->stream));
     const Mode mode = exec_mode(c, prec);
     const bool f32 = prec != NAO_FP64;
-    const bool ovl = overlap_ext(s, 1);
+    const bool ovl = overlap_ext(s, 1, blocks);
     std::vector<DevSeg> segs;
-    for (const Block& b : s->blocks) {
-        DevSeg g = make_seg(s, b, true, false);
+    for (const Block& b : blocks) {
+        DevSeg g = make_seg(s, b, true, false, cl);
         g.wv = s->d_wv.as<double>();
         g.wa = has_a ? s->d_wa.as<double>() : nullptr;
         g.H = Hd;
@@ -1879,7 +2055,7 @@ nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspa
     if ((D_space != NAO_MEM_HOST && D_space != NAO_MEM_DEVICE) || (out_space != NAO_MEM_HOST && out_space != NAO_MEM_DEVICE))
         return (set_err(c, "bad memspace"), NAO_ERR_INVALID_ARG);
     // gradients of one block's basis values: 3 per value
-    if ((st = ensure_gscratch(s, 3)) != NAO_OK) return st;
+    if ((st = ensure_gscratch(s, 3, s->blocks)) != NAO_OK) return st;
     const double* Dd = D;
     if (D_space == NAO_MEM_HOST && nb > 0) {
         if ((st = ensure(c, s->d_D, nb * nb * sizeof(double))) != NAO_OK) return st;
@@ -1898,7 +2074,7 @@ nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspa
     LAUNCH(c, "fill", launch_fill(gd, 3 * n, 0.0, c->stream));
     const Mode mode = exec_mode(c, prec);
     const bool f32 = prec != NAO_FP64;
-    const bool ovl = overlap_ext(s, 3);
+    const bool ovl = overlap_ext(s, 3, s->blocks);
     std::vector<DevSeg> segs;
     for (const Block& b : s->blocks) {
         DevSeg g = make_seg(s, b, false);
@@ -1945,7 +2121,7 @@ nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, cons
     if (!F || (nb > 0 && (!D || !Q)) || (n > 0 && !v)) return (set_err(c, "NULL D, Q, v or F"), NAO_ERR_INVALID_ARG);
     if ((in_space != NAO_MEM_HOST && in_space != NAO_MEM_DEVICE) || (F_space != NAO_MEM_HOST && F_space != NAO_MEM_DEVICE))
         return (set_err(c, "bad memspace"), NAO_ERR_INVALID_ARG);
-    if ((st = ensure_gscratch(s, 4)) != NAO_OK) return st;  // gradient and lap phi: 4 per basis value
+    if ((st = ensure_gscratch(s, 4, s->blocks)) != NAO_OK) return st;  // gradient and lap phi: 4 per basis value
     const double* Dd = D;
     const double* Qd = Q;
     const double* vd = v;
@@ -1977,7 +2153,7 @@ nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, cons
     LAUNCH(c, "wv", launch_wv(s->d_pw.as<double>(), s->d_perm.as<int32_t>(), vd, s->d_wv.as<double>(), n, c->stream));
     const Mode mode = exec_mode(c, prec);
     const bool f32 = prec != NAO_FP64;
-    const bool ovl = overlap_ext(s, 4);
+    const bool ovl = overlap_ext(s, 4, s->blocks);
     std::vector<DevSeg> segs;
     for (const Block& b : s->blocks) {
         DevSeg g = make_seg(s, b, false);
