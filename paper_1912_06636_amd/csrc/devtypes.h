@@ -10,6 +10,7 @@ namespace nao {
 constexpr int TILE = 64;              // basis-function tile of the contraction kernels
 constexpr int KCHUNK = 16;            // points (Hamiltonian) / functions (density) per LDS stage
 constexpr int MAX_UNIT_POINTS = 256;  // largest execution group the contraction kernels take
+constexpr int NTILE_ROWS = 128;       // rows of a density item (8 row blocks)
 constexpr int MAX_CLUSTER_ROWS = 960; // largest Hamiltonian cluster (60 chunks: masks have 64 bits, and
                                       // four FP64 workgroups with w v of 960 rows fill a CU's LDS)
 constexpr int MAX_SPLINE_LDS = 8192;  // doubles of spline table staged in LDS (64 KiB)
@@ -66,10 +67,22 @@ struct HItem {
     int16_t tj;
 };
 
-// Work item of the density kernel: one column tile of one unit.
+// Work item of the split-BF16 density kernel and the FP32 forces: one column tile of one unit.
 struct NItem {
     int32_t unit;
     int32_t tj;
+};
+
+// Work item of n_tiles: rows of one unit (at most NTILE_ROWS, whole row blocks of 16) and one column
+// tile.  It carries what the kernel needs of the unit, so that an item starts with one load.
+struct NTile {
+    int64_t out_offset;   // of the first row within the block
+    int64_t point_begin;  // of the first row
+    int64_t fn_begin, mask_begin;
+    int32_t n_rows;
+    int32_t row_block;    // first row block within the unit
+    int32_t ld, m, tj;
+    int32_t pad_[3];
 };
 
 // One segment of a launch: a block of one system's units (and their work items) whose
@@ -83,7 +96,7 @@ struct DevSeg {
     const int32_t* unit_cols;
     const int32_t* unit_fn;
     const uint64_t* unit_mask;  // per 16 columns: which 16-row chunks of the unit (cluster) they reach
-    const void* items;       // HItem* or NItem*
+    const void* items;       // HItem*, NTile* or NItem*
     void* phi;               // basis values of this block (FP64, or FP32 for the reduced-precision
                              // modes); unit.out_offset is relative to it
     const double* wv;        // w*v in row order (plain Hamiltonian) or batch order
@@ -91,7 +104,8 @@ struct DevSeg {
     double* H;               // Hamiltonian, row-major, ld = n_basis
     double* n;               // density, caller order
     void* gphi;              // gradients of the basis values of this block, 3 per value (x, y, z
-                             // interleaved; density-gradient launches only)
+                             // interleaved; gradient and force launches), or L (1 per value)
+    void* hphi;              // w h_KS phi of this block (force launches)
     double* gn;              // density gradient [n_points][3], caller order
     const double* wa;        // batch-ordered w*a, 3 per point (Hamiltonian with a vector field)
     const double* Q;         // energy-weighted density matrix (forces), row-major, ld = n_basis
@@ -115,8 +129,7 @@ enum Mode { MODE_FP64 = 0, MODE_FP32 = 1, MODE_BF16X3 = 2, MODE_BF16X6 = 3 };
 // extra: also write, to the segments' gphi, the gradient of every basis value (EXTRA_GRAD, 3 per
 // value), L = (w v / 2) phi + (w a) . grad phi (EXTRA_GGA_L, 1 per value; needs wv and wa) or
 // L = (w v / 2) phi - (w / 4) lap phi [+ (w a) . grad phi when wa is set] (EXTRA_KS_L, 1 per value),
-// or the gradient and w h_KS phi = (w v) phi - (w / 2) lap phi (EXTRA_GRAD_H, 4 per value: x, y, z,
-// w h_KS phi; needs wv).
+// or the gradient, and to hphi w h_KS phi = (w v) phi - (w / 2) lap phi (EXTRA_GRAD_H, needs wv).
 enum BasisExtra { EXTRA_NONE = 0, EXTRA_GRAD = 1, EXTRA_GGA_L = 2, EXTRA_KS_L = 3, EXTRA_GRAD_H = 4 };
 hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int spline_lds, bool fp32_out,
                         hipStream_t st, int64_t max_grid = 0, int extra = EXTRA_NONE);
@@ -132,8 +145,8 @@ hipError_t launch_n_grad(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t 
 // 64-wide tile pairs I <= J, L from the basis launch with EXTRA_GGA_L.
 hipError_t launch_h_gga(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n_items, hipStream_t st);
 // Local Pulay forces (FP64 or FP32 modes), density items walked over the whole list twice:
-// fb[j] += sum_p grad phi_pj [((w v Phi - w lap Phi / 2) D)_pj - w_p (Phi Q)_pj]; gphi from the
-// basis launch with EXTRA_GRAD_H, wv batch-ordered w*v.
+// fb[j] += sum_p grad phi_pj [((w v Phi - w lap Phi / 2) D)_pj - w_p (Phi Q)_pj]; gphi and hphi
+// from the basis launch with EXTRA_GRAD_H, wv batch-ordered w*v.
 hipError_t launch_n_force(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n_items, hipStream_t st);
 // F[a] = 2 sum over the functions i of atom a (atom_first[a] <= i < atom_first[a + 1]) of fb[i].
 hipError_t launch_force_atoms(const double* fb, const int64_t* atom_first, int64_t n_atoms, double* F,

@@ -263,13 +263,14 @@ __global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict_
         // EX = EXTRA_GRAD: 3 gradient values per basis value; EX = EXTRA_GGA_L: L = (w v / 2) phi +
         // (w a) . grad phi, one per basis value; EX = EXTRA_KS_L: L = (w v / 2) phi - (w / 4) lap phi
         // (+ (w a) . grad phi when the segment has a field); same element order as the basis values
-        // EX = EXTRA_GRAD_H: the 3 gradient values and w h_KS phi = (w v) phi - (w / 2) lap phi, 4 per
-        // basis value
+        // EX = EXTRA_GRAD_H: the 3 gradient values, and w h_KS phi = (w v) phi - (w / 2) lap phi in a
+        // plane of its own (hphi)
         constexpr bool LAPL = EX == EXTRA_GRAD_H;
         constexpr bool GRAD = EX == EXTRA_GRAD || LAPL, GGA = EX == EXTRA_GGA_L, KS = EX == EXTRA_KS_L;
         const bool field = GGA || (KS && sg.wa != nullptr);  // uniform
-        constexpr int XW = GRAD ? (LAPL ? 4 : 3) : 1;  // extra values per basis value
+        constexpr int XW = GRAD ? 3 : 1;  // extra values per basis value in gphi
         gp<T> __restrict__ gout = EX != EXTRA_NONE ? gptr(static_cast<T*>(sg.gphi) + XW * u.out_offset) : nullptr;
+        gp<T> __restrict__ hout = LAPL ? gptr(static_cast<T*>(sg.hphi) + u.out_offset) : nullptr;
         const int64_t npairs = (int64_t)(row1 - row0) * na;
         const double tmax = (double)(nk - 1);
 
@@ -304,6 +305,8 @@ __global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict_
                         for (int f = 0; f < nf; ++f) row[col + f] = T(0);
                         if (EX != EXTRA_NONE)
                             for (int f = 0; f < XW * nf; ++f) grow[XW * col + f] = T(0);
+                        if (LAPL)
+                            for (int f = 0; f < nf; ++f) hout[(int64_t)pl * u.ld + col + f] = T(0);
                         col += nf;
                     }
                     continue;
@@ -389,7 +392,7 @@ __global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict_
                                 dst[0] = T(g0);
                                 dst[1] = T(g1);
                                 dst[2] = T(g2);
-                                if (LAPL) dst[3] = T(hwv * (R * yv) - qw * (lap * yv));
+                                if (LAPL) hout[(int64_t)pl * u.ld + col + f] = T(hwv * (R * yv) - qw * (lap * yv));
                             } else {
                                 grow[col + f] = T((hwv * (R * yv) - qw * (lap * yv)) + ((wax * g0 + way * g1) + waz * g2));
                             }
@@ -567,6 +570,7 @@ __global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict_
                 out[pl * u.ld + u.m + cpad] = T(0);
                 if (EX != EXTRA_NONE)
                     for (int c = 0; c < XW; ++c) gout[XW * (pl * u.ld + u.m + cpad) + c] = T(0);
+                if (LAPL) hout[pl * u.ld + u.m + cpad] = T(0);
             }
         }
     }
@@ -731,6 +735,12 @@ __device__ inline void load4_to_lds(__amdgpu_buffer_rsrc_t r, void* dst, int vof
 {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 4, voffset, soffset, 0, 0);
 }
+// One FP64 or FP32 value per lane from a buffer.
+template <typename T> __device__ inline T load_value(__amdgpu_buffer_rsrc_t r, int voffset)
+{
+    if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, voffset, 0, 0));
+    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, voffset, 0, 0));
+}
 // Wait until at most N of this wave's vector loads are outstanding and its LDS reads are done.
 template <int N> __device__ inline void wait_loads() { __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4)); }
 
@@ -858,7 +868,7 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
                 }
         };
         auto compute = [&](int c, int h, int stg) {
-            if (!((m_any >> c) & 1)) return;
+            if (__builtin_expect(!((m_any >> c) & 1), 0)) return;
             if (sizeof(T) == 4) {
                 const uint64_t past = sub_first & ((2ull << c) - 1);
                 if (past) {
@@ -886,7 +896,7 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
             // latency, and the accumulators stay where they are on every path
 #pragma unroll
             for (int jb = 0; jb < 4; ++jb)
-                if ((mm[jb] >> c) & 1)
+                if (__builtin_expect((mm[jb] >> c) & 1, 1))
 #pragma unroll
                     for (int kk = 0; kk < KK; ++kk) {
                         acc[jb] = M::op(a[kk], bv[jb][kk], acc[jb]);
@@ -920,7 +930,7 @@ __global__ __launch_bounds__(256, TWO ? 3 : 4) void h_tiles(const DevSeg* __rest
                 else wait_loads<LOADS * NOP>();
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                if (ahead) issue_next((stg + S - 1) % S);
+                if (__builtin_expect(ahead != 0, 1)) issue_next((stg + S - 1) % S);
                 compute(c, h, stg);
                 if (todo == 0) break;
             }
@@ -1054,61 +1064,390 @@ __global__ __launch_bounds__(512) void h_kernel_wide(const DevSeg* __restrict__ 
     }
 }
 
-// Density: per work item one 64-wide column tile J of a unit,
-//   T[:, J] = sum_{I <= J} c_IJ Phi[:, I] D[I, J]   (c = 2 off the diagonal tile, 1 on it,
-//             the diagonal tile read from the upper triangle of D),
-//   n_p += sum_{j in J} T[p, j] Phi[p, j].
-// Rows = the unit's points (<= 256: 16 row blocks), K = basis functions in chunks of KC staged
-// through LDS (two buffers when DB, else one buffer and a second barrier per chunk); the next
-// chunk is prefetched into registers while the MFMAs of the current one run.  NW waves: wave w
-// owns column block w % 4 and row blocks w / 4, w / 4 + NW / 4, ...  T = FP32 accumulates the
-// whole column tile in FP32; the row dot and the sum over tiles and units are FP64.
+// Density, its gradient and the local Pulay forces: per work item up to 128 rows (8 row blocks) of an
+// execution unit and one 64-wide column tile J,
+//   NK_DENSITY:  T[:, J] = sum over the list up to J of Phi D[:, J],  n_p += sum_{j in J} T_pj Phi_pj
+//                (every pair of tiles once, doubled; the diagonal tile once);
+//   NK_GRADIENT: T[:, J] = Phi D[:, J] over the whole list, and four row dots, n and
+//                grad n = 2 T . grad Phi;
+//   NK_FORCE:    M[:, J] = (w h_KS Phi) D[:, J] - diag(w) Phi Q[:, J] over the whole list, and column
+//                sums f_j += sum_p grad phi_pj M_pj into fb[N_b][3].
+// Only upper triangles of D and Q are read: rows i of D for tiles I < J, columns of D (rows j of the
+// matrix) for I > J, and the diagonal tile element by element.
 //
-// KIND = NK_GRADIENT: T[:, J] = Phi D[:, J] over the whole list (coefficient 1, the lower
-// triangle read transposed) and four row dots, n and grad n = 2 T . grad Phi.
-// KIND = NK_FORCE: the list is walked twice, M[:, J] = diag(w) (h_KS Phi) D[:, J] - diag(w) Phi
-// Q[:, J] with h_KS phi = v phi - lap phi / 2 (w h_KS phi written by the basis launch beside the
-// gradients, four values per basis value: x, y, z, w h_KS phi), and the epilogue takes column
-// sums, f_j += sum_p grad phi_pj M_pj, into the per-function accumulator fb[N_b][3].
+// K = the list in steps of KC functions through two LDS stages filled by direct loads: 128 x KC
+// basis values (rows of 64 bytes, their 16-byte slots XOR-swizzled by row so that reads meet distinct
+// banks) and KC x 64 values of D (16 bytes per lane and two matrix rows per wave load where the
+// tile's columns come in neighbouring pairs, else 4 bytes and half a row; right of the diagonal rows
+// of the tile).  Four waves, a 16-column block each, with D as the first
+// MFMA operand, so that a lane's results belong to one point and the row dots are sums within a lane
+// and over four lanes.
+//
+// Bound: the matrix pipes; as in h_tiles there are next to no vector instructions in the loop.  Four
+// workgroups of four waves share a CU, so that three compute while one starts, ends or waits at a
+// barrier.  unit_mask leaves out the MFMAs of row blocks that either side does not reach, and the
+// FP64 density contracts the diagonal tile's upper triangle alone (its diagonal halved, everything
+// doubled at the end); FP32 keeps the order and the rounding of full diagonal tiles.
+// Measured, kernel alone, against sixteen waves per 256 rows with staging through registers (4.9 vector
+// instructions per MFMA): FP64 density 7.9 -> 5.5 ms (100-atom block), 117 -> 83 ms (375-atom slab),
+// FP32 13.3 -> 8.8 ms (100-atom slab), gradient 16.0 -> 12.7 ms, forces 33 -> 26 ms.  Eight waves per
+// 256 rows took 6.6 ms, loads of D by 4 bytes alone 6.4, a third stage gains nothing.
 enum NKind { NK_DENSITY = 0, NK_GRADIENT = 1, NK_FORCE = 2 };
-template <typename T, int NW, int KC, bool DB, int KIND = NK_DENSITY>
-__global__ __launch_bounds__(64 * NW) void n_kernel(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
+constexpr int NWIN = 512;   // functions whose indices and masks are in LDS at a time
+template <typename T, int KIND>
+__global__ __launch_bounds__(256, 4) void n_tiles(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     typedef Mma<T> M;
-    constexpr bool GRAD = KIND == NK_GRADIENT;
-    constexpr bool FORCE = KIND == NK_FORCE;
-    constexpr bool FULL = KIND != NK_DENSITY;  // contraction over the whole list
-    constexpr int NT = 64 * NW;                              // threads
-    constexpr int RB = 64 / NW;                              // row blocks per wave (16 row x 4 column blocks)
-    constexpr int RS = NW / 4;                               // row-block stride between the waves of a column
-    constexpr int NA = MAX_UNIT_POINTS * KC / NT;            // basis values per thread per chunk
-    constexpr int ND = KC * TILE / NT;                       // D values per thread per chunk
-    constexpr int NB = DB ? 2 : 1;                           // LDS buffers
-    static_assert(ND >= 1 && NA % 2 == 0 && RB % 4 == 0 && NT % TILE == 0 && TILE % KC == 0 && KC % 4 == 0,
-                  "tile geometry");
-    static_assert(!FORCE || RS * TILE * 3 <= 4 * MAX_UNIT_POINTS, "force partials fit in red");
-    // SLOT (density, gradient): basis values move as 16-byte slots (VPS values of one row), are
-    // staged in rows of KC values whose slots are XOR-swizzled by row, and are read back a whole
-    // slot per lane, so that the rows one 128-byte pass of a read touches fall in distinct banks
-    // (the MFMA steps take the chunk's columns in slot order, A and B alike).  The forces, whose D
-    // pass stages every fourth value of the basis launch's extra block, keep rows padded to KC + 1,
-    // and so does FP32 (faster so: its slots hold four columns, its rows half the bytes).
-    constexpr bool SLOT = !FORCE && sizeof(T) == 8;
-    constexpr int VPS = 16 / (int)sizeof(T);                 // values per slot
-    constexpr int SPR = KC / VPS;                            // slots per staged row
-    constexpr int ROWS_128B = 128 / (KC * (int)sizeof(T));   // staged rows per 128 bytes (the bank period)
-    constexpr int AW = SLOT ? KC : KC + 1;                   // staged row length
-    static_assert(!SLOT || (SPR >= 4 && SPR % 4 == 0 && ROWS_128B >= 1 && (SPR & (SPR - 1)) == 0), "slot geometry");
-    typedef T slot_t __attribute__((ext_vector_type(VPS)));
-    __shared__ __align__(16) T As[NB][MAX_UNIT_POINTS][AW];
-    __shared__ T Bs[NB][KC][TILE + 2];
-    constexpr int NQ = GRAD ? 4 : 1;                         // row dots: n, or n and the three gradient components
-    __shared__ double red[NQ][4][MAX_UNIT_POINTS];
+    constexpr bool F64 = sizeof(T) == 8;
+    constexpr bool FULL = KIND != NK_DENSITY, TRI = F64 && !FULL;
+    constexpr int KC = 64 / (int)sizeof(T);             // functions per step: 8 (FP64), 16 (FP32)
+    constexpr int KR = KC / 4;                          // D rows per wave and step
+    constexpr int AB = NTILE_ROWS * 64, BB = KC * TILE * 8, STAGEB = AB + BB;
+    constexpr int FN = 2 * STAGEB, MK = FN + NWIN * 4;
+    __shared__ __align__(16) unsigned char lds[MK + 64 * 4];  // (the masks' wave load fills 64 entries)
+    typedef T slot_t __attribute__((ext_vector_type(16 / sizeof(T))));
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+    const int lr = lane & 15, lk = lane >> 4;
+    for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
+        const int64_t b = xcd_item(v_, lg);
+        if (b >= total) continue;
+        const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
+        const DevSeg& sg = segs[s];
+        const NTile* it = static_cast<const NTile*>(sg.items) + (sg.item_begin + (b - sg.item_prefix));
+        const int tj = uni(it->tj), np = uni(it->n_rows), ld = uni(it->ld), m = uni(it->m), rb0 = uni(it->row_block);
+        const int64_t out_offset = uni(it->out_offset), point_begin = uni(it->point_begin);
+        const int64_t fn_begin = uni(it->fn_begin), mask_begin = uni(it->mask_begin);
+        const int64_t ldd = uni(sg.ld);
+        const uint64_t* mp = sg.unit_mask + mask_begin;
+        const int J0 = tj * TILE, cb = (wave + tj) & 3;
+        uint32_t any_j = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) any_j |= (uint32_t)uni((int)mp[4 * tj + q]);
+        const uint32_t own = (1u << ((np + 15) / 16)) - 1;  // the item's row blocks
+        any_j = (any_j >> rb0) & own;
+        if (any_j == 0) continue;
+        const uint32_t col_rows = ((uint32_t)uni((int)mp[4 * tj + cb]) >> rb0) & own;  // row blocks this wave's columns reach
+        const int32_t* fn = sg.unit_fn + fn_begin;
+        const int ldb = ld * (int)sizeof(T);
+        // D by 16 bytes per lane, a wave load for two of its rows: the tile's columns have to come in
+        // pairs of neighbours (atoms with an even number of functions) and D to lie within 32-bit offsets
+        const int ldd8 = (int)(ldd * 8);
+        const int cp = J0 + 2 * (lane & 31), gp0 = fn[min(cp, m - 1)], gp1 = fn[min(cp + 1, m - 1)];
+        const bool pairs = ldd <= 23170 && __all(cp + 1 >= m || gp1 == gp0 + 1);
+        const int voff_p = gp0 * 8;
+        // else by 4 bytes per lane, half of a row per wave load: columns J0 + 32 q + lane / 2
+        int voff_d[2];
+        int64_t row_j[FULL || !F64 ? 2 : 1];  // byte offsets of those columns' own rows (diagonal tile)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int g = fn[min(J0 + 32 * q + (lane >> 1), m - 1)];
+            voff_d[q] = g * 8 + 4 * (lane & 1);
+            if (FULL || !F64) row_j[q] = ((int64_t)g * ldd) * 8 + 4 * (lane & 1);
+        }
+        // right of the diagonal a wave load takes rows j of D, 64 / (2 KC) of them
+        constexpr int JPL = 32 / KC, NLOW = FULL ? 2 * KR : 1;
+        int64_t low_j[NLOW];
+        int low_k[NLOW];
+        if (FULL)
+#pragma unroll
+            for (int q = 0; q < NLOW; ++q) {
+                const int j = (wave * 2 * KR + q) * JPL + lane / (2 * KC), d = lane % (2 * KC);
+                low_j[q] = ((int64_t)fn[min(J0 + j, m - 1)] * ldd) * 8 + 4 * (d & 1);
+                low_k[q] = 2 * ((d >> 2) ^ (F64 ? (j >> 1) & 3 : j & 7)) + ((d >> 1) & 1);
+            }
+        int voff_a[2];  // row blocks wave and wave + 4
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            voff_a[q] = ((wave + 4 * q) * 16 + (lane >> 2)) * ldb + (((lane & 3) ^ ((lane >> 3) & 3)) * 16);
+        // per-lane LDS offsets: rows lr of this wave's row blocks, D columns cb * 16 + lr
+        const int a_sw = (lr >> 1) & 3;
+        const int a_off = lr * 64 + (F64 ? (lk ^ a_sw) * 16 : lk * 4);
+        const int b_col = cb * 16 + lr;
+        const int b_up = AB + (F64 ? 2 * lk : lk) * 512 + b_col * 8;
+        const int b_low = AB + b_col * (KC * 8) + (F64 ? (lk ^ ((b_col >> 1) & 3)) * 16 : 0);
+
+        typename M::acc_t acc[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[q] = M::zero();
+
+        // acc += A[:, list] mat[list, J] over the functions k < K (A: rows of ldb bytes)
+        auto contract = [&](const T* A, const double* mat, int K) {
+            const char* a_base = reinterpret_cast<const char*>(A);
+            const char* d_base = reinterpret_cast<const char*>(mat);
+            for (int w0 = 0; w0 < K; w0 += NWIN) {
+                const int k_end = min(K, w0 + NWIN);
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // every wave is done with the LDS of the step before
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                const __amdgpu_buffer_rsrc_t rf = buffer_of(fn, m * 4);  // past the list: its last function
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    load4_to_lds(rf, lds + FN + q * 1024 + wave * 256, min(w0 + q * 256 + wave * 64 + lane, m - 1) * 4, 0);
+                if (wave == 0)
+                    load4_to_lds(buffer_of(mp, ld / 16 * 8), lds + MK, (w0 / 16 + (lane & 31)) * 8, 0);
+                wait_loads<0>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                const int32_t* fnw = reinterpret_cast<const int32_t*>(lds + FN) - w0;
+                const uint32_t* mkw = reinterpret_cast<const uint32_t*>(lds + MK) - w0 / 16;
+                const __amdgpu_buffer_rsrc_t ra = buffer_of(a_base, np * ldb);
+                const __amdgpu_buffer_rsrc_t rd = buffer_of(d_base, (int)(uint32_t)(pairs ? ldd * ldd8 : 0));
+                // list indices and mask of the step that is issued next, read a step ahead: this
+                // wave's D rows are KR wave .. KR wave + KR - 1 of the step's, two per wave load
+                int nx_k[KR / 2], nx_low[NLOW];
+                uint32_t nx_m;
+                auto peek = [&](int k0) {
+                    nx_m = mkw[k0 >> 4];
+#pragma unroll
+                    for (int t = 0; t < KR / 2; ++t) nx_k[t] = fnw[k0 + KR * wave + 2 * t + (lane >> 5)];
+                    if (FULL)
+#pragma unroll
+                        for (int q = 0; q < NLOW; ++q) nx_low[q] = fnw[k0 + low_k[q]];
+                };
+                auto tile_diag = [&](int k0) { return (k0 >> 6) == tj; };
+                auto tile_low = [&](int k0) { return FULL && (k0 >> 6) > tj; };
+                uint32_t mk[2];  // masks of the steps in the two stages
+                auto issue = [&](int k0, int stg) {
+                    unsigned char* st = lds + stg * STAGEB;
+                    mk[stg] = (uint32_t)uni((int)nx_m) >> rb0;
+                    // rows past the last one lie past the buffer's end by their voffset alone
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        load16_to_lds(ra, st + (wave + 4 * q) * 1024, voff_a[q], k0 * (int)sizeof(T));
+                    unsigned char* bt = st + AB + KR * wave * 512;
+                    if (tile_low(k0)) {
+#pragma unroll
+                        for (int q = 0; q < NLOW; ++q) {
+                            const char* src = d_base + (low_j[q] + (int64_t)nx_low[q] * 8);
+                            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                                             (__attribute__((address_space(3))) void*)(st + AB + (wave * 2 * KR + q) * 256),
+                                                             4, 0, 0);
+                        }
+                    } else if (pairs && (TRI || !tile_diag(k0))) {
+#pragma unroll
+                        for (int t = 0; t < KR / 2; ++t) load16_to_lds(rd, bt + t * 1024, nx_k[t] * ldd8 + voff_p, 0);
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < KR; ++t) {
+                            const int gk = __builtin_amdgcn_readlane(nx_k[t / 2], 32 * (t & 1));
+                            const char* row = d_base + (int64_t)gk * ldd * 8;
+                            const __amdgpu_buffer_rsrc_t r = buffer_of(row, ldd8);
+#pragma unroll
+                            for (int q = 0; q < 2; ++q) {
+                                unsigned char* dst = bt + t * 512 + q * 256;
+                                if (!TRI && tile_diag(k0)) {  // below the diagonal: the transposed element
+                                    const bool below = k0 + KR * wave + t > J0 + 32 * q + (lane >> 1);
+                                    const char* src = below ? d_base + (row_j[FULL || !F64 ? q : 0] + (int64_t)gk * 8) : row + voff_d[q];
+                                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                                                     (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
+                                } else {
+                                    load4_to_lds(r, dst, voff_d[q], 0);
+                                }
+                            }
+                        }
+                    }
+                };
+                // one step: its operands are read, the next step is issued while they come, and then the
+                // MFMAs run
+                auto step = [&](int k0, int stg, int ki) {
+                    const uint32_t act = mk[stg] & col_rows;
+                    const bool at_diag = tile_diag(k0), low = tile_low(k0);
+                    const int kb = (k0 >> 4) & 3;  // 16-function block within its tile
+                    const unsigned char* st = lds + stg * STAGEB;
+                    auto next = [&]() {
+                        if (ki >= k_end) return;
+                        issue(ki, stg ^ 1);
+                        peek(ki + KC);
+                    };
+                    if constexpr (F64) {
+                        slot_t a[8];
+                        double b0, b1;
+                        if (low) {
+                            const d2 x = *reinterpret_cast<const d2*>(st + b_low);
+                            b0 = x[0], b1 = x[1];
+                        } else {
+                            b0 = *reinterpret_cast<const double*>(st + b_up);
+                            b1 = *reinterpret_cast<const double*>(st + b_up + 512);
+                        }
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            if (!FULL) a[q] = *reinterpret_cast<const slot_t*>(st + a_off + q * 1024);
+                        next();
+                        if (!act || (TRI && at_diag && kb > cb)) return;
+                        if (TRI && at_diag && kb == cb) {
+                            const int k = (k0 & 15) + 2 * lk;
+                            b0 = k < lr ? b0 : k == lr ? 0.5 * b0 : 0.0;
+                            b1 = k + 1 < lr ? b1 : k + 1 == lr ? 0.5 * b1 : 0.0;
+                        }
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            if ((act >> q) & 1) {
+                                if (FULL) a[q] = *reinterpret_cast<const slot_t*>(st + a_off + q * 1024);  // fewer registers
+                                acc[q] = M::op(b0, a[q][0], acc[q]);
+                                acc[q] = M::op(b1, a[q][1], acc[q]);
+                            }
+                    } else {
+                        double bd[4];
+#pragma unroll
+                        for (int kk = 0; kk < 4; ++kk) {
+                            const int k = kk * 4 + lk;
+                            bd[kk] = low ? *reinterpret_cast<const double*>(st + b_low + (((k >> 1) ^ (b_col & 7)) * 16) + (k & 1) * 8)
+                                         : *reinterpret_cast<const double*>(st + b_up + kk * 2048);
+                        }
+                        next();
+                        if (KIND == NK_DENSITY && k0 == J0)  // the tiles before the diagonal count twice
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) acc[q] += acc[q];
+                        if (!act) return;
+                        T bv[4];
+#pragma unroll
+                        for (int kk = 0; kk < 4; ++kk) bv[kk] = T(bd[kk]);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            if ((act >> q) & 1) {
+                                T a[4];
+#pragma unroll
+                                for (int kk = 0; kk < 4; ++kk)
+                                    a[kk] = *reinterpret_cast<const T*>(st + a_off + q * 1024 + ((kk ^ a_sw) * 16));
+#pragma unroll
+                                for (int kk = 0; kk < 4; ++kk) acc[q] = M::op(bv[kk], a[kk], acc[q]);
+                            }
+                    }
+                };
+                peek(w0);
+                issue(w0, 0);
+                peek(w0 + KC);
+                int kc = w0;
+                while (kc < k_end) {
+#pragma unroll
+                    for (int stg = 0; stg < 2; ++stg) {
+                        wait_loads<0>();
+                        __builtin_amdgcn_s_barrier();
+                        asm volatile("" ::: "memory");
+                        step(kc, stg, kc + KC);
+                        kc += KC;
+                        if (kc >= k_end) break;
+                    }
+                }
+            }
+        };
+
+        const T* phi = static_cast<const T*>(sg.phi) + out_offset;
+        if constexpr (KIND == NK_FORCE) {
+            contract(phi, sg.Q, m);
+            gp<const double> pw = gptr(sg.sys->pw + point_begin);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[q] *= -pw[min(q * 16 + lr, np - 1)];
+            contract(static_cast<const T*>(sg.hphi) + out_offset, sg.D, m);
+        } else {
+            contract(phi, sg.D, FULL ? m : min(J0 + TILE, m));
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();  // the ring is free
+        asm volatile("" ::: "memory");
+        // acc[q][r] belongs to row 16 q + lr and column J0 + 16 cb + row(lk, r)
+        double* red = reinterpret_cast<double*>(lds);
+        const int c0 = J0 + cb * 16;
+        // columns past the list (the last one's values of D, not zeros, were loaded for them)
+        if (c0 + 16 > m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (c0 + M::row(lk, r) >= m)
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) acc[q][r] = T(0);
+        constexpr int SZ = (int)sizeof(T);
+        const int voff_e = lr * ldb + c0 * SZ;  // row lr of a row block, first column of this wave
+        if constexpr (KIND == NK_FORCE) {
+            const char* g = static_cast<const char*>(sg.gphi) + 3 * out_offset * SZ;
+            double f[4][3] = {};
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int rb = q;
+                if (!((col_rows >> rb) & 1)) continue;
+                const __amdgpu_buffer_rsrc_t rg = buffer_of(g + (int64_t)rb * 48 * ldb, max(0, np - rb * 16) * 3 * ldb);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+                        f[r][k] += (double)acc[q][r] * (double)load_value<T>(rg, 3 * voff_e + (3 * M::row(lk, r) + k) * SZ);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const double x = row_sum16(f[r][k]);
+                    if (lr == 0) red[k * TILE + cb * 16 + M::row(lk, r)] = x;
+                }
+            __syncthreads();
+            const int k = threadIdx.x / TILE, col = threadIdx.x % TILE;
+            if (k < 3 && J0 + col < m)
+                gadd(gptr(sg.fb) + 3 * (int64_t)fn[J0 + col] + k, red[k * TILE + col]);
+        } else {
+            constexpr int NQ = KIND == NK_GRADIENT ? 4 : 1;
+            const char* ph = reinterpret_cast<const char*>(phi);
+            const char* g = KIND == NK_GRADIENT ? static_cast<const char*>(sg.gphi) + 3 * out_offset * SZ : nullptr;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int rb = q, p = rb * 16 + lr;
+                double dot[NQ] = {};
+                if ((col_rows >> rb) & 1) {
+                    const int rows = max(0, np - rb * 16);
+                    const __amdgpu_buffer_rsrc_t rp = buffer_of(ph + (int64_t)rb * 16 * ldb, rows * ldb);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        dot[0] += (double)acc[q][r] * (double)load_value<T>(rp, voff_e + M::row(lk, r) * SZ);
+                    if constexpr (KIND == NK_GRADIENT) {
+                        const __amdgpu_buffer_rsrc_t rg = buffer_of(g + (int64_t)rb * 48 * ldb, rows * 3 * ldb);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+#pragma unroll
+                            for (int k = 1; k < NQ; ++k)
+                                dot[k] += (double)acc[q][r] * (double)load_value<T>(rg, 3 * voff_e + (3 * M::row(lk, r) + k - 1) * SZ);
+                    }
+#pragma unroll
+                    for (int k = 0; k < NQ; ++k) {
+                        dot[k] += __shfl_xor(dot[k], 16);
+                        dot[k] += __shfl_xor(dot[k], 32);
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < NQ; ++k)
+                    if (lk == 0) red[(k * 4 + cb) * NTILE_ROWS + p] = dot[k];
+            }
+            __syncthreads();
+            const int p = threadIdx.x;
+            if (p < np) {
+                const int32_t pc = gptr(sg.sys->perm)[point_begin + p];
+#pragma unroll
+                for (int k = 0; k < NQ; ++k) {
+                    const double* x = red + k * 4 * NTILE_ROWS + p;
+                    const double v = (x[0] + x[NTILE_ROWS]) + (x[2 * NTILE_ROWS] + x[3 * NTILE_ROWS]);
+                    if (k == 0) gadd(gptr(sg.n) + pc, TRI ? 2.0 * v : v);
+                    else gadd(gptr(sg.gn) + 3 * (int64_t)pc + k - 1, 2.0 * v);
+                }
+            }
+        }
+    }
+}
+
+// Local Pulay forces in FP32: as n_tiles NK_FORCE with every -w phi rounded to FP32 before the
+// second product (direct loads cannot scale what they stage, so basis values and D go through
+// registers: rows padded to 17 values, double-buffered chunks of 16 functions, the next chunk
+// prefetched while the MFMAs of the current one run).  Sixteen waves: wave w owns column block w % 4
+// and row blocks w / 4 + 4 q.
+__global__ __launch_bounds__(1024) void n_force_f32(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
+{
+    typedef float T;
+    typedef Mma<T> M;
+    constexpr int KC = 16, NT = 1024, RB = 4, RS = 4;
+    constexpr int NA = MAX_UNIT_POINTS * KC / NT;  // basis values per thread per chunk
+    __shared__ T As[2][MAX_UNIT_POINTS][KC + 1];
+    __shared__ T Bs[2][KC][TILE + 2];
+    __shared__ double red[3][RS][TILE];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int cb = wave & 3, rh = wave >> 2;  // column block; row blocks rh, rh + RS, ...
     const int lr = lane & 15, lk = lane >> 4;
-    // staged position of slot j of row `row` within a buffer (SLOT)
-    auto a_slot = [](int row, int j) { return row * KC + ((j ^ ((row / ROWS_128B) & (SPR - 1))) * VPS); };
     for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
         const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
@@ -1117,244 +1456,101 @@ __global__ __launch_bounds__(64 * NW) void n_kernel(const DevSeg* __restrict__ s
         const NItem it = static_cast<const NItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
         const DevUnit u = sg.item_units[it.unit];
         gp<const T> __restrict__ phi = gptr(static_cast<const T*>(sg.phi) + u.out_offset);
+        gp<const T> __restrict__ hphi = gptr(static_cast<const T*>(sg.hphi) + u.out_offset);
         gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + u.fn_begin);
-        gp<const double> __restrict__ D = gptr(sg.D);
         const int64_t ldd = sg.ld;
         const int np = u.n_points, ld = u.ld, m = u.m;
         if (np <= 0 || m <= 0) continue;
         const int P = (np + 15) >> 4;
         const int J0 = it.tj * TILE;
-        // this wave's 16 output columns hold list entries (the last tile of a unit is padded)
-        const bool col_live = __builtin_amdgcn_readfirstlane(J0 + cb * 16 < m);
-        // chunk c covers columns KC c .. KC c + KC - 1: the tiles I <= J, or all tiles for the
-        // gradient (T = Phi D over the whole list); the forces walk the list once against D and
-        // once against Q (chunk c + half covers the columns of chunk c).  Chunks that start at
-        // or beyond m hold only the zero padding of the basis values and are left out.
-        const int half = min(FULL ? (m + TILE - 1) / TILE * (TILE / KC) : (it.tj + 1) * (TILE / KC), (m + KC - 1) / KC);
-        const int n_chunks = FORCE ? 2 * half : half;
-        auto col0 = [&](int c) { return KC * (FORCE && c >= half ? c - half : c); };
-        const int cjd = J0 + (tid & (TILE - 1));              // this thread's D column in every chunk
+        // chunks 0 .. half - 1 run the list against D, half .. 2 half - 1 against Q
+        const int half = (m + KC - 1) / KC, n_chunks = 2 * half;
+        auto col0 = [&](int c) { return KC * (c >= half ? c - half : c); };
+        const int cjd = J0 + (tid & (TILE - 1));  // this thread's D column in every chunk
         const int64_t gjd = fn[min(cjd, m - 1)];
-
-        // F = rows staged (RB row blocks per wave's share, or RB / 2 when the unit has at most
-        // 128 points); R = this wave's row blocks below the unit's last one (the waves of one
-        // SIMD share a column block and split the rows, so a SIMD issues MFMAs for exactly the
-        // unit's row blocks).  Loads are issued with clamped (in-bounds) addresses and consumed
-        // only at the stash after the current chunk's MFMAs.
-        auto run = [&](auto rows_staged, auto rows_own) {
+        // F = row blocks staged per wave's share (RB, or RB / 2 for at most 128 points)
+        auto run = [&](auto rows_staged) {
             constexpr int F = decltype(rows_staged)::value;
-            constexpr int R = decltype(rows_own)::value;
             constexpr int NAR = NA * F / RB;
-            constexpr int ROWS = F * RS * 16;                           // rows staged
-            constexpr int NSL = SLOT ? (ROWS * SPR + NT - 1) / NT : 1;  // slots per thread
-            constexpr bool SL_ALL = ROWS * SPR % NT == 0;               // every thread takes NSL slots
-            T pa[SLOT ? 1 : NAR];
-            slot_t ps[NSL];
-            double pd[ND];
-            // list indices of the D rows: those of chunk c + 1 are loaded during chunk c
-            int32_t gcur[ND], gnxt[ND];
-            auto load_idx = [&](int c, int32_t* g) {
+            T pa[NAR];
+            double pd;
+            int32_t gcur, gnxt;
+            auto load_idx = [&](int c) { return fn[min(col0(c) + (tid >> 6), m - 1)]; };
+            double sw[NAR];  // -w of this thread's staged rows, for the Q pass
+            gp<const double> pw = gptr(sg.sys->pw + u.point_begin);
 #pragma unroll
-                for (int q = 0; q < ND; ++q) g[q] = fn[min(col0(c) + (tid >> 6) + (NT / TILE) * q, m - 1)];
-            };
-            // forces: weights of this thread's staged rows, -w for the Q pass
-            double sw[FORCE ? NAR : 1];
-            if constexpr (FORCE) {
-                gp<const double> pw = gptr(sg.sys->pw + u.point_begin);
-#pragma unroll
-                for (int q = 0; q < NAR; ++q) sw[q] = -pw[min((tid + NT * q) / KC, np - 1)];
-            }
+            for (int q = 0; q < NAR; ++q) sw[q] = -pw[min((tid + NT * q) / KC, np - 1)];
             auto fetch = [&](int c) {
-                if constexpr (SLOT) {
 #pragma unroll
-                    for (int q = 0; q < NSL; ++q) {
-                        const int e = tid + NT * q;  // slot e % SPR of row e / SPR
-                        if (SL_ALL || e < ROWS * SPR)
-                            ps[q] = *reinterpret_cast<gp<const slot_t>>(
-                                phi + (int64_t)min(e / SPR, np - 1) * ld + col0(c) + (e % SPR) * VPS);
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < (SLOT ? 0 : NAR); ++q) {
+                for (int q = 0; q < NAR; ++q) {
                     const int e = tid + NT * q;
                     const int64_t el = (int64_t)min(e / KC, np - 1) * ld + col0(c) + (e % KC);
-                    // forces: the D pass takes w h_KS phi (fourth value of the basis launch's
-                    // gradient block), the Q pass phi
-                    if (FORCE && c < half) pa[q] = gptr(static_cast<const T*>(sg.gphi) + 4 * u.out_offset)[4 * el + 3];
-                    else pa[q] = phi[el];
+                    pa[q] = c < half ? hphi[el] : phi[el];
                 }
-                const bool diag = c / (TILE / KC) == it.tj;
-                gp<const double> src = FORCE && c >= half ? gptr(sg.Q) : D;
-#pragma unroll
-                for (int q = 0; q < ND; ++q) {
-                    const int ci = col0(c) + (tid >> 6) + (NT / TILE) * q;
-                    // upper triangle only: the diagonal tile's lower part (every tile's, for the
-                    // gradient and the forces) is read transposed
-                    const bool lower = (FULL || diag) && ci > cjd;
-                    pd[q] = src[lower ? gjd * ldd + gcur[q] : (int64_t)gcur[q] * ldd + gjd];
-                }
-                load_idx(c + 1, gnxt);
+                gp<const double> src = gptr(c >= half ? sg.Q : sg.D);
+                const bool lower = col0(c) + (tid >> 6) > cjd;  // only the upper triangle is read
+                pd = src[lower ? gjd * ldd + gcur : (int64_t)gcur * ldd + gjd];
+                gnxt = load_idx(c + 1);
             };
             auto stash = [&](int c, int buf) {
+                gcur = gnxt;
 #pragma unroll
-                for (int q = 0; q < ND; ++q) gcur[q] = gnxt[q];
-                const bool diag = c / (TILE / KC) == it.tj;
-                if constexpr (SLOT) {
-#pragma unroll
-                    for (int q = 0; q < NSL; ++q) {
-                        const int e = tid + NT * q;
-                        if (SL_ALL || e < ROWS * SPR)
-                            *reinterpret_cast<slot_t*>(&As[buf][0][0] + a_slot(e / SPR, e % SPR)) =
-                                e / SPR < np ? ps[q] : slot_t(T(0));
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < (SLOT ? 0 : NAR); ++q) {
+                for (int q = 0; q < NAR; ++q) {
                     const int e = tid + NT * q;
-                    T x = pa[q];
-                    if constexpr (FORCE) {  // Q pass: -w phi (the D pass staged w h_KS phi as it is)
-                        if (c >= half) x = T((double)x * sw[q]);
-                    }
+                    const T x = c >= half ? T((double)pa[q] * sw[q]) : pa[q];
                     As[buf][e / KC][e % KC] = (e / KC) < np ? x : T(0);
                 }
-#pragma unroll
-                for (int q = 0; q < ND; ++q) {
-                    const int e = tid + NT * q;
-                    const bool ok = col0(c) + (e >> 6) < m && cjd < m;
-                    Bs[buf][e >> 6][e & 63] = ok ? T((FULL || diag) ? pd[q] : 2.0 * pd[q]) : T(0);
-                }
+                Bs[buf][tid >> 6][tid & 63] = col0(c) + (tid >> 6) < m && cjd < m ? T(pd) : T(0);
             };
-
-            typename M::acc_t acc[R > 0 ? R : 1];
+            M::acc_t acc[F];
 #pragma unroll
-            for (int i = 0; i < R; ++i) acc[i] = M::zero();
-            load_idx(0, gcur);
+            for (int i = 0; i < F; ++i) acc[i] = M::zero();
+            gcur = load_idx(0);
             fetch(0);
             stash(0, 0);
             __syncthreads();
-            auto mfma_chunk = [&](int buf) {
-                if (!col_live) return;  // this wave's 16 columns lie in the tile's padding
-                if constexpr (SLOT) {
-                    // lane group lk reads slots lk + 4 h of its rows; step (h, e) takes column
-                    // VPS (lk + 4 h) + e of the chunk
+            for (int c = 0; c < n_chunks; ++c) {
+                const int buf = c & 1;
+                if (c + 1 < n_chunks) fetch(c + 1);
 #pragma unroll
-                    for (int h = 0; h < SPR / 4; ++h) {
-                        slot_t a[R > 0 ? R : 1];
+                for (int kk = 0; kk < KC / 4; ++kk) {
+                    const T bv = Bs[buf][kk * 4 + lk][cb * 16 + lr];
 #pragma unroll
-                        for (int q = 0; q < R; ++q)
-                            a[q] = *reinterpret_cast<const slot_t*>(&As[buf][0][0] + a_slot((RS * q + rh) * 16 + lr, lk + 4 * h));
-#pragma unroll
-                        for (int e = 0; e < VPS; ++e) {
-                            const T bv = Bs[buf][VPS * (lk + 4 * h) + e][cb * 16 + lr];
-#pragma unroll
-                            for (int q = 0; q < R; ++q) acc[q] = M::op(a[q][e], bv, acc[q]);
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int kk = 0; kk < KC / 4; ++kk) {
-                        const T bv = Bs[buf][kk * 4 + lk][cb * 16 + lr];
-#pragma unroll
-                        for (int q = 0; q < R; ++q) acc[q] = M::op(As[buf][(RS * q + rh) * 16 + lr][kk * 4 + lk], bv, acc[q]);
-                    }
+                    for (int q = 0; q < F; ++q) acc[q] = M::op(As[buf][(RS * q + rh) * 16 + lr][kk * 4 + lk], bv, acc[q]);
                 }
-            };
-            // straight-line body (the last chunk peeled off) so that the scheduler can
-            // interleave the next chunk's stash with this chunk's MFMAs
-            for (int c = 0; c + 1 < n_chunks; ++c) {
-                const int buf = DB ? (c & 1) : 0;
-                fetch(c + 1);
-                mfma_chunk(buf);
-                if (!DB) __syncthreads();  // every wave is done with the only buffer
-                stash(c + 1, DB ? (buf ^ 1) : 0);
+                if (c + 1 < n_chunks) stash(c + 1, buf ^ 1);
                 __syncthreads();
             }
-            mfma_chunk(DB ? ((n_chunks - 1) & 1) : 0);
-
+            // f_j += sum_p grad phi_pj M_pj: this wave's rows, then the lanes of one column
             const int cj = J0 + cb * 16 + lr;
-            if constexpr (FORCE) {
-                // f_j += sum_p grad phi_pj M_pj: this wave's rows, then the lanes of one column
-                gp<const T> gph = gptr(static_cast<const T*>(sg.gphi) + 4 * u.out_offset);  // x, y, z, lap
-                double f[3] = {0.0, 0.0, 0.0};
+            gp<const T> gph = gptr(static_cast<const T*>(sg.gphi) + 3 * u.out_offset);
+            double f[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-                for (int q = 0; q < R; ++q) {
-                    const int pblk = RS * q + rh;
-                    if (pblk < P) {
+            for (int q = 0; q < F; ++q)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int p = pblk * 16 + M::row(lk, r);
-                            const int64_t e = (int64_t)min(p, np - 1) * ld + cj;
-                            const double a = p < np && cj < m ? (double)acc[q][r] : 0.0;
+                for (int r = 0; r < 4; ++r) {
+                    const int p = (RS * q + rh) * 16 + M::row(lk, r);
+                    const int64_t e = (int64_t)min(p, np - 1) * ld + cj;
+                    const double a = p < np && cj < m ? (double)acc[q][r] : 0.0;
 #pragma unroll
-                            for (int k = 0; k < 3; ++k) f[k] += a * (double)gph[4 * e + k];
-                        }
-                    }
+                    for (int k = 0; k < 3; ++k) f[k] += a * (double)gph[3 * e + k];
                 }
-                double(*fred)[RS][TILE] = reinterpret_cast<double(*)[RS][TILE]>(&red[0][0][0]);
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    double v = f[k];
-                    v += __shfl_xor(v, 16);
-                    v += __shfl_xor(v, 32);
-                    if (lk == 0) fred[k][rh][cb * 16 + lr] = v;
-                }
-                return;
-            }
-            // n_p += sum_j T[p][j] Phi[p][j]
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int pblk = RS * q + rh;
-                if (pblk < P) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int p = pblk * 16 + M::row(lk, r);
-                        const int64_t e = (int64_t)min(p, np - 1) * ld + cj;
-                        const bool live = p < np && cj < m;
-#pragma unroll
-                        for (int qq = 0; qq < NQ; ++qq) {
-                            const double f = qq == 0 ? (double)phi[e]
-                                                     : (double)gptr(static_cast<const T*>(sg.gphi) + 3 * u.out_offset)[3 * e + qq - 1];
-                            const double v = row_sum16(live ? (double)acc[q][r] * f : 0.0);
-                            if (lr == 0) red[qq][cb][p] = v;
-                        }
-                    }
-                }
+            for (int k = 0; k < 3; ++k) {
+                double v = f[k];
+                v += __shfl_xor(v, 16);
+                v += __shfl_xor(v, 32);
+                if (lk == 0) red[k][rh][cb * 16 + lr] = v;
             }
         };
-        // R is the smallest of RB, 3 RB / 4, RB / 2, RB / 4, 0 that covers this wave's blocks
-        typedef std::integral_constant<int, RB> Full;
-        typedef std::integral_constant<int, RB / 2> Half;
-        const int own = min(RB, (P - rh + RS - 1) / RS);  // wave-uniform
-        if (P > RB / 2 * RS) {  // rows beyond 128: every wave owns more than RB / 2 - 1 blocks
-            if (own > RB * 3 / 4) run(Full{}, Full{});
-            else if (own > RB / 2) run(Full{}, std::integral_constant<int, RB * 3 / 4>{});
-            else run(Full{}, Half{});
-        } else {
-            if (own > RB / 4) run(Half{}, Half{});
-            else if (own > 0) run(Half{}, std::integral_constant<int, RB / 4>{});
-            else run(Half{}, std::integral_constant<int, 0>{});
-        }
+        if (P > RB / 2 * RS) run(std::integral_constant<int, RB>{});
+        else run(std::integral_constant<int, RB / 2>{});
         __syncthreads();
-        if constexpr (FORCE) {
-            if (tid < 3 * TILE) {
-                const int k = tid / TILE, col = tid % TILE;
-                if (J0 + col < m) {
-                    double(*fred)[RS][TILE] = reinterpret_cast<double(*)[RS][TILE]>(&red[0][0][0]);
-                    double v = 0.0;
-#pragma unroll
-                    for (int h = 0; h < RS; ++h) v += fred[k][h][col];
-                    gadd(gptr(sg.fb) + 3 * (int64_t)fn[J0 + col] + k, v);
-                }
-            }
-        } else if (tid < np) {
-            const int32_t pc = gptr(sg.sys->perm)[u.point_begin + tid];
-            const double v = (red[0][0][tid] + red[0][1][tid]) + (red[0][2][tid] + red[0][3][tid]);
-            gadd(gptr(sg.n) + pc, v);
-            if (GRAD)  // grad n = 2 sum_j T_pj grad phi_pj
-#pragma unroll
-                for (int qq = 1; qq < NQ; ++qq)
-                    gadd(gptr(sg.gn) + 3 * (int64_t)pc + qq - 1,
-                         2.0 * ((red[qq][0][tid] + red[qq][1][tid]) + (red[qq][2][tid] + red[qq][3][tid])));
+        if (tid < 3 * TILE) {
+            const int k = tid / TILE, col = tid % TILE;
+            if (J0 + col < m)
+                gadd(gptr(sg.fb) + 3 * (int64_t)fn[J0 + col] + k,
+                     (red[k][0][col] + red[k][1][col]) + (red[k][2][col] + red[k][3][col]));
         }
         __syncthreads();  // red is rewritten by the next item
     }
@@ -1740,8 +1936,8 @@ hipError_t launch_n(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n_ite
     const int lg = xcd_run(n_items, NRUN);
     const dim3 g(grid_for(n_items, lg, max_grid)), b(1024);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL((n_kernel<double, 16, 16, true>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
-    case MODE_FP32: hipLaunchKernelGGL((n_kernel<float, 16, 16, true>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP64: hipLaunchKernelGGL((n_tiles<double, NK_DENSITY>), g, dim3(256), 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL((n_tiles<float, NK_DENSITY>), g, dim3(256), 0, st, segs_dev, n_segs, n_items, lg); break;
     case MODE_BF16X3: hipLaunchKernelGGL((n_kernel_bf16<2, 2>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     case MODE_BF16X6: hipLaunchKernelGGL((n_kernel_bf16<3, 1>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
@@ -1754,10 +1950,10 @@ hipError_t launch_n_grad(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t 
     if (n_items <= 0 || n_segs <= 0) return hipSuccess;
     if (n_items > 0x7ffffff0) return hipErrorInvalidValue;
     const int lg = xcd_run(n_items, NRUN);
-    const dim3 g(grid_for(n_items, lg, 0)), b(1024);
+    const dim3 g(grid_for(n_items, lg, 0)), b(256);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL((n_kernel<double, 16, 16, true, NK_GRADIENT>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
-    case MODE_FP32: hipLaunchKernelGGL((n_kernel<float, 16, 16, true, NK_GRADIENT>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP64: hipLaunchKernelGGL((n_tiles<double, NK_GRADIENT>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL((n_tiles<float, NK_GRADIENT>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1770,8 +1966,8 @@ hipError_t launch_n_force(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t
     const int lg = xcd_run(n_items, NRUN);
     const dim3 g(grid_for(n_items, lg, 0)), b(1024);
     switch (mode) {
-    case MODE_FP64: hipLaunchKernelGGL((n_kernel<double, 16, 16, true, NK_FORCE>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
-    case MODE_FP32: hipLaunchKernelGGL((n_kernel<float, 16, 16, true, NK_FORCE>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP64: hipLaunchKernelGGL((n_tiles<double, NK_FORCE>), g, dim3(256), 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_FP32: hipLaunchKernelGGL(n_force_f32, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

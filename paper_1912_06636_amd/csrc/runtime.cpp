@@ -271,7 +271,8 @@ struct Block {
     int64_t unit_begin = 0, unit_count = 0;
     int64_t h_begin = 0, h_count = 0;    // Hamiltonian items over 64-wide tiles
     int64_t hw_begin = 0, hw_count = 0;  // ... over 128-wide tiles (systems with h_tile 128)
-    int64_t n_begin = 0, n_count = 0;
+    int64_t n_begin = 0, n_count = 0;    // column tiles
+    int64_t nt_begin = 0, nt_count = 0;  // column tiles times row parts (n_tiles)
     int64_t phi_elems = 0;
 };
 
@@ -300,7 +301,7 @@ struct nao_system_s {
     DevSys dsys{};
     DevArray d_sys, d_px, d_py, d_pz, d_pw, d_perm, d_atoms, d_species, d_shell_ptr, d_shell_l, d_shell_rad,
         d_radial_par, d_spline, d_fn_ptr, d_fn_code;
-    DevArray d_units, d_unit_atoms, d_unit_cols, d_unit_fn, d_unit_mask, d_h_items, d_hw_items, d_n_items;
+    DevArray d_units, d_unit_atoms, d_unit_cols, d_unit_fn, d_unit_mask, d_h_items, d_hw_items, d_n_items, d_nt_items;
     // Hamiltonian clusters (FP64 and FP32 with 64-wide tiles; cl_blocks is empty when there are none)
     std::vector<Block> cl_blocks;
     int64_t n_cl_subs = 0, n_cl_rows = 0, n_cl_atoms = 0, n_cl_fn = 0, n_cl_mask = 0;
@@ -324,7 +325,7 @@ size_t system_bytes(const nao_system_s* s)
                              &s->d_species, &s->d_shell_ptr, &s->d_shell_l, &s->d_shell_rad, &s->d_radial_par,
                              &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn, &s->d_unit_mask, &s->d_cl_units, &s->d_cl_subs,
                              &s->d_cl_atoms, &s->d_cl_cols, &s->d_cl_fn, &s->d_cl_mask, &s->d_cl_items,
-                             &s->d_h_items, &s->d_hw_items, &s->d_n_items, &s->d_wv, &s->d_v, &s->d_D, &s->d_H, &s->d_n,
+                             &s->d_h_items, &s->d_hw_items, &s->d_n_items, &s->d_nt_items, &s->d_wv, &s->d_v, &s->d_D, &s->d_H, &s->d_n,
                              &s->d_gn, &s->d_a, &s->d_wa, &s->d_segs, &s->d_Q, &s->d_fb, &s->d_atom_first,
                              &s->d_F, &s->d_phi_res};
     size_t t = 0;
@@ -338,7 +339,7 @@ void free_all(nao_system_s* s)
                        &s->d_species, &s->d_shell_ptr, &s->d_shell_l, &s->d_shell_rad, &s->d_radial_par,
                        &s->d_spline, &s->d_fn_ptr, &s->d_fn_code, &s->d_units, &s->d_unit_atoms, &s->d_unit_cols, &s->d_unit_fn, &s->d_unit_mask, &s->d_cl_units, &s->d_cl_subs,
                              &s->d_cl_atoms, &s->d_cl_cols, &s->d_cl_fn, &s->d_cl_mask, &s->d_cl_items,
-                       &s->d_h_items, &s->d_hw_items, &s->d_n_items, &s->d_wv, &s->d_v, &s->d_D, &s->d_H, &s->d_n, &s->d_gn, &s->d_a, &s->d_wa, &s->d_segs,
+                       &s->d_h_items, &s->d_hw_items, &s->d_n_items, &s->d_nt_items, &s->d_wv, &s->d_v, &s->d_D, &s->d_H, &s->d_n, &s->d_gn, &s->d_a, &s->d_wa, &s->d_segs,
                        &s->d_Q, &s->d_fb, &s->d_atom_first, &s->d_F, &s->d_phi_res};
     for (auto* a : arr) {
         dev_free(s->ctx, a->p, a->bytes);
@@ -511,6 +512,7 @@ nao_status build_groups(nao_system_s* s)
     std::vector<int32_t> ufn;
     std::vector<HItem> hitems, hwitems;
     std::vector<NItem> nitems;
+    std::vector<NTile> ntiles;
     std::vector<int64_t> item_first;
     s->blocks.clear();
     Block cur;
@@ -545,6 +547,7 @@ nao_status build_groups(nao_system_s* s)
             cur.h_begin = (int64_t)hitems.size();
             cur.hw_begin = (int64_t)hwitems.size();
             cur.n_begin = (int64_t)nitems.size();
+            cur.nt_begin = (int64_t)ntiles.size();
             off = 0;
         }
         d.out_offset = off;
@@ -557,6 +560,23 @@ nao_status build_groups(nao_system_s* s)
             for (int ti = 0; ti <= tj; ++ti) hitems.push_back(HItem{(int32_t)k, (int16_t)ti, (int16_t)tj});
             nitems.push_back(NItem{(int32_t)k, tj});
         }
+        // row parts: all row blocks, or two halves of more than NTILE_ROWS / 16; longest items first
+        const int row_blocks = (d.n_points + 15) / 16, parts = row_blocks > NTILE_ROWS / 16 ? 2 : 1;
+        for (int tj = nt - 1; tj >= 0; --tj)
+            for (int q = 0; q < parts; ++q) {
+                const int r0 = q ? (row_blocks + 1) / 2 : 0, r1 = q + 1 < parts ? (row_blocks + 1) / 2 : row_blocks;
+                NTile t{};
+                t.out_offset = d.out_offset + (int64_t)r0 * 16 * d.ld;
+                t.point_begin = d.point_begin + r0 * 16;
+                t.fn_begin = d.fn_begin;
+                t.mask_begin = d.mask_begin;
+                t.n_rows = std::min(r1 * 16, d.n_points) - r0 * 16;
+                t.row_block = r0;
+                t.ld = d.ld;
+                t.m = d.m;
+                t.tj = tj;
+                ntiles.push_back(t);
+            }
         if (s->h_tile == 128) {
             const int ntw = (d.m + 127) / 128;
             for (int tj = 0; tj < ntw; ++tj)
@@ -565,6 +585,7 @@ nao_status build_groups(nao_system_s* s)
         cur.h_count = (int64_t)hitems.size() - cur.h_begin;
         cur.hw_count = (int64_t)hwitems.size() - cur.hw_begin;
         cur.n_count = (int64_t)nitems.size() - cur.n_begin;
+        cur.nt_count = (int64_t)ntiles.size() - cur.nt_begin;
     }
     if (cur.unit_count) s->blocks.push_back(cur);
     item_first.push_back((int64_t)hitems.size());
@@ -580,6 +601,7 @@ nao_status build_groups(nao_system_s* s)
     if ((st = upload(c, s->d_h_items, hitems.data(), hitems.size() * sizeof(HItem))) != NAO_OK) return st;
     if ((st = upload(c, s->d_hw_items, hwitems.data(), hwitems.size() * sizeof(HItem))) != NAO_OK) return st;
     if ((st = upload(c, s->d_n_items, nitems.data(), nitems.size() * sizeof(NItem))) != NAO_OK) return st;
+    if ((st = upload(c, s->d_nt_items, ntiles.data(), ntiles.size() * sizeof(NTile))) != NAO_OK) return st;
     if ((st = ensure(c, s->d_unit_mask, std::max<int64_t>(1, mask_len) * sizeof(uint64_t))) != NAO_OK) return st;
     HIP_TRY(c, launch_unit_masks(s->d_sys.as<DevSys>(), s->d_units.as<DevUnit>(), s->d_units.as<DevUnit>(),
                                  s->d_unit_atoms.as<int32_t>(), s->d_unit_cols.as<int32_t>(), (int64_t)du.size(),
@@ -604,7 +626,7 @@ nao_status build_groups(nao_system_s* s)
 // clusters: over the system's clusters, 1 with columns by reach (FP64), 2 with ascending columns: a
 // pair's w v goes to the column that comes first and FP32 rounds the product, so FP32 keeps the order
 // that the units have.
-DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = false, int clusters = 0)
+DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = false, int clusters = 0, bool tiles = false)
 {
     DevSeg g{};
     if (clusters) {
@@ -637,6 +659,12 @@ DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = fal
     g.unit_begin = b.unit_begin;
     g.unit_count = b.unit_count;
     g.unit_prefix = 0;
+    if (tiles) {  // n_tiles items
+        g.items = s->d_nt_items.p;
+        g.item_begin = b.nt_begin;
+        g.item_count = b.nt_count;
+        return g;
+    }
     g.item_begin = ham ? (wide ? b.hw_begin : b.h_begin) : b.n_begin;
     g.item_count = ham ? (wide ? b.hw_count : b.h_count) : b.n_count;
     g.item_prefix = 0;
@@ -864,7 +892,7 @@ nao_status many_build(nao_ctx c, const nao_work* work, int64_t n_work, nao_preci
                 off = 0;
             }
             const bool wide = ham && s->h_tile == 128 && (prec == NAO_FP64 || prec == NAO_FP32);
-            DevSeg g = make_seg(s, b, ham, wide, cl);
+            DevSeg g = make_seg(s, b, ham, wide, cl, !ham && (prec == NAO_FP64 || prec == NAO_FP32));
             if (ham) {
                 g.wv = m->d_wv.as<double>() + m->wv_off[e];
                 g.H = const_cast<double*>(w.out);
@@ -1739,7 +1767,7 @@ static nao_status run_blocks(nao_system s, bool ham, nao_precision prec, const d
     for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
     const bool ovl = !res && blocks.size() > 1 && overlap_ready(c, need);
     for (size_t k = 0; k < blocks.size(); ++k) {
-        DevSeg g = make_seg(s, blocks[k], ham, wide, cl);
+        DevSeg g = make_seg(s, blocks[k], ham, wide, cl, !ham && (prec == NAO_FP64 || prec == NAO_FP32));
         if (ovl && (k & 1)) g.phi = c->scratch2;
         if (res) g.phi = static_cast<char*>(s->d_phi_res.p) + s->res_off[k] * (f32 ? sizeof(float) : sizeof(double));
         g.wv = wv;
@@ -2077,7 +2105,7 @@ nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspa
     const bool ovl = overlap_ext(s, 3, s->blocks);
     std::vector<DevSeg> segs;
     for (const Block& b : s->blocks) {
-        DevSeg g = make_seg(s, b, false);
+        DevSeg g = make_seg(s, b, false, false, 0, true);
         g.D = Dd;
         g.n = nd;
         g.gn = gd;
@@ -2156,7 +2184,7 @@ nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, cons
     const bool ovl = overlap_ext(s, 4, s->blocks);
     std::vector<DevSeg> segs;
     for (const Block& b : s->blocks) {
-        DevSeg g = make_seg(s, b, false);
+        DevSeg g = make_seg(s, b, false, false, 0, prec == NAO_FP64);
         g.D = Dd;
         g.Q = Qd;
         g.wv = s->d_wv.as<double>();
@@ -2166,6 +2194,8 @@ nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, cons
             g.phi = c->scratch2;
             g.gphi = c->gscratch2;
         }
+        // the block's extra buffer: gradients (3 per value), then w h_KS phi
+        g.hphi = static_cast<char*>(g.gphi) + 3 * b.phi_elems * (f32 ? sizeof(float) : sizeof(double));
         segs.push_back(g);
     }
     if (!segs.empty()) {
