@@ -74,6 +74,17 @@ static int xcd_run(int64_t total, int most)
 constexpr int HRUN = 5;  // tile pairs (28 of a unit with 7 tiles): 16 to 64 measure alike, 512 a few percent slower
 constexpr int NRUN = 4;  // column tiles (7 to 11 of a unit): runs of 4 cost the 375-atom slab 4 %, 64 gain nothing
 
+// Lane-uniform values kept in scalar registers: FP64 and FP32 MFMA do not issue beside vector
+// instructions (measured: 69 and 31 cycles per MFMA alone, about 3 more for every vector
+// instruction between them), so what is uniform is computed by the scalar unit.
+__device__ inline int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ inline int64_t uni(int64_t x)
+{
+    const uint32_t lo = (uint32_t)uni((int)(uint32_t)x), hi = (uint32_t)uni((int)(uint32_t)((uint64_t)x >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+template <typename T> __device__ inline T* uni(T* p) { return reinterpret_cast<T*>(uni((int64_t)(uintptr_t)p)); }
+
 // (dx*dx + dy*dy) + dz*dz without contraction: the same arithmetic that decides relevance.
 __device__ inline double dist2_exact(double dx, double dy, double dz)
 {
@@ -163,52 +174,78 @@ __device__ inline void ylm_grad_one(int lm, double x, double y, double z, double
 
 // ------------------------------------------------------------------------------------------
 // Basis evaluation
-constexpr size_t BASIS_LDS_BYTES = (size_t)MAX_SPLINE_LDS * sizeof(double);
-
 constexpr int BASIS_ATOMS = 192;   // atoms of a unit staged in LDS
 constexpr int BASIS_SHELLS = 128;  // shells of a system staged in LDS
-constexpr int BASIS_SLICES = 4;    // work items per unit (point slices) of the basis kernel
-constexpr int BASIS_WIN = 16;      // values per pair staged at a time for the row writes
-
-// Basis values of execution units: BASIS_SLICES workgroups per unit, each taking a contiguous
-// slice of the unit's points (more workgroups in flight than one per unit, and shorter tails);
-// threads over (point, atom) pairs with the atom fastest, each writing all functions of its atom.  The unit's atoms (position,
-// cutoff, species, first column) and the system's shell tables (l, radial function and its
-// parameters) are staged in LDS first, so that a pair's chain of table lookups stays on chip;
-// a unit or system larger than the staging arrays reads them from global memory instead.
-template <typename T, bool SPLINE_LDS, int EX>
-__global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg,
-                                                       int spline_lds)
+constexpr int BASIS_SLICES = 2, BASIS_SLICES_PAIRS = 4;  // work items per unit (point slices), rows staged or not
+// waves of a workgroup, as many as its registers allow a CU
+constexpr int basis_waves(int extra)
 {
-    extern __shared__ double lds_spline[];
-    // plain FP64 basis values (EX = EXTRA_NONE): per wave, BASIS_WIN values of each of its 64
-    // pairs, and per pair the unit-local offset of its first value and its value count (FP32
-    // values, half the bytes, are faster stored per pair directly)
-    constexpr bool STAGE = EX == EXTRA_NONE && sizeof(T) == 8;
-    __shared__ double s_win[STAGE ? 4 * 64 * (BASIS_WIN + 1) : 1];
-    __shared__ __align__(8) int32_t s_pair[STAGE ? 4 * 64 * 2 : 2];
-    constexpr int SPT = MAX_UNIT_POINTS / BASIS_SLICES;  // points of a slice staged at a time
-    __shared__ double s_pt[STAGE ? SPT : 1][3];  // the slice's points (a run of SPT at a time)
+    return extra == EXTRA_NONE ? 16 : extra == EXTRA_GRAD ? 12 : 8;
+}
+constexpr int BASIS_LDS = 160 * 1024, BASIS_STATIC = 13312;  // LDS of a CU, and the kernel's static arrays
+constexpr int64_t BASIS_ROWS_UNITS = 512;
+constexpr int BASIS_ROWS_BYTES = 96;
+
+// N consecutive values of one lane, 16 bytes per store (values are only aligned to their own size).
+template <int N, typename T> __device__ inline void store_run(gp<T> dst, const T* v)
+{
+    constexpr int V = 16 / (int)sizeof(T);
+    typedef T vec __attribute__((ext_vector_type(V)));
+    typedef vec uvec __attribute__((aligned(sizeof(T))));
+    typedef T two __attribute__((ext_vector_type(2)));
+    typedef two utwo __attribute__((aligned(sizeof(T))));
+    int k = 0;
+#pragma unroll
+    for (; k + V <= N; k += V) {
+        vec x;
+#pragma unroll
+        for (int j = 0; j < V; ++j) x[j] = v[k + j];
+        *reinterpret_cast<gp<uvec>>(dst + k) = x;
+    }
+    if (V == 4 && k + 2 <= N) {
+        *reinterpret_cast<gp<utwo>>(dst + k) = two{v[k], v[k + 1]};
+        k += 2;
+    }
+    if (k < N) dst[k] = v[k];
+}
+
+// Basis values of execution units: `slices` workgroups per unit, each taking a contiguous slice of the
+// unit's points.  The unit's atoms (position, cutoff, species, first column) and the system's shell
+// tables (l, radial function and its parameters) are staged in LDS first, so that a pair's chain of
+// table lookups stays on chip; a unit or system larger than the staging arrays reads them from global
+// memory instead.  Two ways to the rows of the block:
+//   rows_staged: the values go to LDS first, in the place that they have in the row, and leave in full
+//   64-byte segments.  A lane that stores its own pair's values makes an L2 request of 12 to 22 bytes
+//   out of every 16-byte store, and the L2s, not HBM, bound the launch (100-atom block, FP64, a value
+//   and three gradients: 9.7 ms at 2.9 TB/s; staged 5.1 ms at 5.4 TB/s, a fill writes 6.4).  One plane at
+//   a time, a wave's LDS being 64 pairs of one plane, which recomputes the radial functions per plane
+//   (8 % VALU before, the arithmetic is not what bounds).  Values alone: 3.9 to 3.0 ms (FP64, 14
+//   functions per atom), 7.0 to 4.4 ms (slab of 100, FP32, 29 functions).
+//   pairs: every lane stores its own.  Less work per value where the runs are short, see launch_basis.
+template <typename T, bool SPLINE_LDS, int EX>
+__global__ __launch_bounds__(64 * basis_waves(EX), basis_waves(EX) / 4) void basis_kernel(const DevSeg* __restrict__ segs, int n_segs,
+                                                                                           int64_t total, int lg, int slices, int spline_lds, int run)
+{
+    extern __shared__ __align__(16) double lds_spline[];  // spline table, then four rows of run values per wave
     __shared__ double s_atom[BASIS_ATOMS][4];  // x, y, z, (largest cutoff)^2
     __shared__ int32_t s_aspc[BASIS_ATOMS][2];  // species, first column in the unit
     __shared__ double s_par[BASIS_SHELLS][4];  // rmin, rcut^2, 1/Delta, ln rmin of the shell's radial
-    __shared__ int32_t s_shell[BASIS_SHELLS][2];  // l, radial function
+    __shared__ int32_t s_shell[BASIS_SHELLS];  // l + 4 (same radial grid as the shell before) + 8 radial function
     __shared__ int32_t s_shptr[BASIS_SHELLS + 1];
-    (void)spline_lds;  // the launcher sized the dynamic LDS for the table
     const int tid = threadIdx.x;
     const DevSys* table_of = nullptr;  // the system whose spline table is in LDS
     for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
         const int64_t bi = xcd_item(v_, lg);
         if (bi >= total) continue;
-        // item = (unit, slice): BASIS_SLICES consecutive items split one unit's points
-        const int64_t b = bi / BASIS_SLICES;
-        const int slice = (int)(bi - b * BASIS_SLICES);
+        // item = (unit, slice): consecutive items split one unit's points
+        const int64_t b = bi / slices;
+        const int slice = (int)(bi - b * slices);
         __syncthreads();  // the previous item may still read LDS
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.unit_prefix; });
         const DevSeg& sg = segs[s];
         const DevUnit u = sg.units[sg.unit_begin + (b - sg.unit_prefix)];
-        const int row0 = (int)(((int64_t)u.n_points * slice) / BASIS_SLICES);
-        const int row1 = (int)(((int64_t)u.n_points * (slice + 1)) / BASIS_SLICES);
+        const int row0 = (int)(((int64_t)u.n_points * slice) / slices);
+        const int row1 = (int)(((int64_t)u.n_points * (slice + 1)) / slices);
         if (row1 <= row0) continue;
         const DevSys* S = sg.sys;
         const int nk = S->n_knots;
@@ -231,16 +268,6 @@ __global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict_
             for (int i = tid; i < nsp; i += blockDim.x) lds_spline[i] = spl[i];
             table_of = S;
         }
-        // points of rows r0 .. r1 - 1 of the unit into s_pt
-        auto stage_points = [&](int r0, int r1) {
-            for (int i = tid; i < r1 - r0; i += blockDim.x) {
-                const int64_t p = u.point_begin + r0 + i;
-                s_pt[i][0] = gptr(S->px)[p];
-                s_pt[i][1] = gptr(S->py)[p];
-                s_pt[i][2] = gptr(S->pz)[p];
-            }
-        };
-        if (STAGE) stage_points(row0, min(row1, row0 + SPT));
         if (staged) {
             for (int ai = tid; ai < na; ai += blockDim.x) {
                 const int atom = uat[ai];
@@ -250,327 +277,266 @@ __global__ __launch_bounds__(256, 2) void basis_kernel(const DevSeg* __restrict_
                 s_aspc[ai][1] = ucol[ai];
             }
             for (int j = tid; j < n_sh; j += blockDim.x) {
-                const int rr = shell_rad[j];
-                s_shell[j][0] = shell_l[j];
-                s_shell[j][1] = rr;
+                const int rr = shell_rad[j], r0 = shell_rad[max(j - 1, 0)];
+                const bool same = rpar[4 * rr] == rpar[4 * r0] && rpar[4 * rr + 2] == rpar[4 * r0 + 2] && rpar[4 * rr + 3] == rpar[4 * r0 + 3];
+                s_shell[j] = shell_l[j] + 4 * same + 8 * rr;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) s_par[j][k] = rpar[4 * rr + k];
             }
             for (int k = tid; k <= n_sp; k += blockDim.x) s_shptr[k] = shell_ptr[k];
         }
-        if (restage || staged || STAGE) __syncthreads();
+        if (restage || staged) __syncthreads();
         gp<T> __restrict__ out = gptr(static_cast<T*>(sg.phi) + u.out_offset);
-        // EX = EXTRA_GRAD: 3 gradient values per basis value; EX = EXTRA_GGA_L: L = (w v / 2) phi +
-        // (w a) . grad phi, one per basis value; EX = EXTRA_KS_L: L = (w v / 2) phi - (w / 4) lap phi
-        // (+ (w a) . grad phi when the segment has a field); same element order as the basis values
-        // EX = EXTRA_GRAD_H: the 3 gradient values, and w h_KS phi = (w v) phi - (w / 2) lap phi in a
-        // plane of its own (hphi)
+        // EX = EXTRA_GRAD: the gradient, a plane of values per component; EX = EXTRA_GGA_L: L =
+        // (w v / 2) phi + (w a) . grad phi; EX = EXTRA_KS_L: L = (w v / 2) phi - (w / 4) lap phi
+        // (+ (w a) . grad phi when the segment has a field); EX = EXTRA_GRAD_H: the gradient, and
+        // w h_KS phi = (w v) phi - (w / 2) lap phi (hphi).  All planes are laid out as the values are.
         constexpr bool LAPL = EX == EXTRA_GRAD_H;
         constexpr bool GRAD = EX == EXTRA_GRAD || LAPL, GGA = EX == EXTRA_GGA_L, KS = EX == EXTRA_KS_L;
         const bool field = GGA || (KS && sg.wa != nullptr);  // uniform
-        constexpr int XW = GRAD ? 3 : 1;  // extra values per basis value in gphi
-        gp<T> __restrict__ gout = EX != EXTRA_NONE ? gptr(static_cast<T*>(sg.gphi) + XW * u.out_offset) : nullptr;
-        gp<T> __restrict__ hout = LAPL ? gptr(static_cast<T*>(sg.hphi) + u.out_offset) : nullptr;
+        constexpr int NP = 1 + (GRAD ? 3 : EX != EXTRA_NONE) + LAPL;  // planes: values, gradient or L, h phi
+        auto plane = [&](int k) {
+            return k == 0 ? out : gptr(static_cast<T*>(k == 4 ? sg.hphi : sg.gphi) + (k == 4 ? 0 : (k - 1) * sg.plane) + u.out_offset);
+        };
         const int64_t npairs = (int64_t)(row1 - row0) * na;
         const double tmax = (double)(nk - 1);
 
-        // Gradient and L values (EX != EXTRA_NONE): threads over (point, atom) pairs, each writing
-        // every value of its pair directly.
-        auto pairs = [&](auto on_chip) {
-            constexpr bool ST = decltype(on_chip)::value;
-            for (int64_t q = tid; q < npairs; q += blockDim.x) {
-                const int ql = (int)q;
-                const int pq = ql / na;
-                const int ai = ql - pq * na;
-                const int pl = row0 + pq;
-                const int atom = ST ? 0 : uat[ai];
-                int col = ST ? s_aspc[ai][1] : ucol[ai];
-                const int64_t p = u.point_begin + pl;
-                const double ax = ST ? s_atom[ai][0] : axyz[4 * (int64_t)atom];
-                const double ay = ST ? s_atom[ai][1] : axyz[4 * (int64_t)atom + 1];
-                const double az = ST ? s_atom[ai][2] : axyz[4 * (int64_t)atom + 2];
-                const double arc2 = ST ? s_atom[ai][3] : axyz[4 * (int64_t)atom + 3];
-                const double dx = gptr(S->px)[p] - ax;
-                const double dy = gptr(S->py)[p] - ay;
-                const double dz = gptr(S->pz)[p] - az;
-                const double d2 = dist2_exact(dx, dy, dz);
-                const int sp = ST ? s_aspc[ai][0] : aspecies[atom];
-                const int sh0 = ST ? s_shptr[sp] : shell_ptr[sp];
-                const int sh1 = ST ? s_shptr[sp + 1] : shell_ptr[sp + 1];
-                gp<T> row = out + (int64_t)pl * u.ld;
-                gp<T> grow = EX != EXTRA_NONE ? gout + XW * (int64_t)pl * u.ld : nullptr;
-                if (d2 >= arc2) {
-                    for (int j = sh0; j < sh1; ++j) {
-                        const int nf = 2 * (ST ? s_shell[j][0] : shell_l[j]) + 1;
-                        for (int f = 0; f < nf; ++f) row[col + f] = T(0);
-                        if (EX != EXTRA_NONE)
-                            for (int f = 0; f < XW * nf; ++f) grow[XW * col + f] = T(0);
-                        if (LAPL)
-                            for (int f = 0; f < nf; ++f) hout[(int64_t)pl * u.ld + col + f] = T(0);
-                        col += nf;
-                    }
-                    continue;
+        // One (point, atom) pair: what its shells share
+        struct Pair {
+            double d2, r, ir, lnr, x, y, z;
+            double hwv, wax, way, waz, qw;
+            bool near;
+        };
+        auto pair_at = [&](int64_t p, double ax, double ay, double az, double arc2) {
+            Pair q{};
+            const double dx = gptr(S->px)[p] - ax, dy = gptr(S->py)[p] - ay, dz = gptr(S->pz)[p] - az;
+            q.d2 = dist2_exact(dx, dy, dz);
+            if (GGA || KS) q.hwv = 0.5 * gptr(sg.wv)[p];
+            if (field) {
+                gp<const double> wa = gptr(sg.wa) + 3 * p;
+                q.wax = wa[0], q.way = wa[1], q.waz = wa[2];
+            }
+            if (KS) q.qw = 0.25 * gptr(S->pw)[p];
+            if (LAPL) {
+                q.hwv = gptr(sg.wv)[p];
+                q.qw = 0.5 * gptr(S->pw)[p];
+            }
+            q.near = q.d2 < arc2;  // else every value of the pair is zero
+            q.z = 1.0;
+            if (q.near) {
+                q.r = sqrt(q.d2);
+                if (q.r > 0.0) {
+                    q.ir = 1.0 / q.r;
+                    q.x = dx * q.ir;
+                    q.y = dy * q.ir;
+                    q.z = dz * q.ir;
+                    q.lnr = log(q.r);
                 }
-                const double r = sqrt(d2);
-                double ux = 0.0, uy = 0.0, uz = 1.0;
-                if (r > 0.0) {
-                    const double ir = 1.0 / r;
-                    ux = dx * ir;
-                    uy = dy * ir;
-                    uz = dz * ir;
+            }
+            return q;
+        };
+        // phi = R Y, grad phi = R'(r) u Y + (R / r) (G - u (u . G)) with G = dY/du (zero where the
+        // function is cut off or r <= rmin), lap phi = lap Y
+        struct Radial {
+            double R, dR, Rr, lap;
+        };
+        // place on a radial grid: knots k and k + 1 with weights v and w
+        struct Knot {
+            int k;
+            double v, w;
+        };
+        auto knot_of = [&](const Pair& q, double rmin, double idel, double lnmin) {
+            double t = q.r > rmin ? (q.lnr - lnmin) * idel : 0.0;
+            t = fmin(fmax(t, 0.0), tmax);
+            Knot g;
+            g.k = min((int)t, nk - 2);
+            g.w = t - (double)g.k;
+            g.v = 1.0 - g.w;
+            return g;
+        };
+        auto radial_of = [&](const Pair& q, const Knot& g, int l, int rr, double rmin, double rc2, double idel) {
+            Radial f{};
+            if (q.near && q.d2 < rc2) {
+                const double w = g.w, v = g.v;
+                // (y_k, M_k / 6, y_{k+1}, M_{k+1} / 6), 32 contiguous bytes
+                const int ci = (rr * nk + g.k) * 2;
+                double ya, pa, yb, pb;
+                if (SPLINE_LDS) {
+                    ya = lds_spline[ci], pa = lds_spline[ci + 1], yb = lds_spline[ci + 2], pb = lds_spline[ci + 3];
+                } else {
+                    gp<const double> c = spl + ((int64_t)rr * nk + g.k) * 2;
+                    ya = c[0], pa = c[1], yb = c[2], pb = c[3];
                 }
-                double Y[16];
-                int lmax = 0;
-                for (int j = sh0; j < sh1; ++j) lmax = max(lmax, ST ? s_shell[j][0] : shell_l[j]);
-                real_ylm(ux, uy, uz, lmax, Y);
-                const double lnr = r > 0.0 ? log(r) : 0.0;
-                for (int j = sh0; j < sh1; ++j) {
-                    const int l = ST ? s_shell[j][0] : shell_l[j];
-                    const int rr = ST ? s_shell[j][1] : shell_rad[j];
-                    const double rmin = ST ? s_par[j][0] : rpar[4 * rr];
-                    const double rc2 = ST ? s_par[j][1] : rpar[4 * rr + 1];
-                    const double idel = ST ? s_par[j][2] : rpar[4 * rr + 2];
-                    const double lnmin = ST ? s_par[j][3] : rpar[4 * rr + 3];
-                    double R = 0.0, dR = 0.0, dS = 0.0, d2S = 0.0;
-                    if (d2 < rc2) {
-                        double t = r > rmin ? (lnr - lnmin) * idel : 0.0;
-                        t = fmin(fmax(t, 0.0), tmax);
-                        const int k = min((int)t, nk - 2);
-                        const double w = t - (double)k, v = 1.0 - w;
-                        // knots k and k + 1: (y_k, M_k / 6, y_{k+1}, M_{k+1} / 6), 32 contiguous bytes
-                        const int64_t ci = ((int64_t)rr * nk + k) * 2;
-                        double ya, pa, yb, pb;
-                        if (SPLINE_LDS) {
-                            ya = lds_spline[ci], pa = lds_spline[ci + 1], yb = lds_spline[ci + 2], pb = lds_spline[ci + 3];
-                        } else {
-                            gp<const double> c = spl + ci;
-                            ya = c[0], pa = c[1], yb = c[2], pb = c[3];
-                        }
-                        R = v * (ya + (v * v - 1.0) * pa) + w * (yb + (w * w - 1.0) * pb);
-                        // dR/dr = dR/dw dt/dr with dt/dr = 1 / (r Delta); the clamped part r <= rmin is constant
-                        const double dRdw = (yb - ya) - (3.0 * v * v - 1.0) * pa + (3.0 * w * w - 1.0) * pb;
-                        if (EX != EXTRA_NONE && r > rmin) dR = dRdw * idel / r;
-                        if (KS || LAPL) {
-                            dS = dRdw;                    // dR/dt
-                            d2S = 6.0 * (v * pa + w * pb);  // d2R/dt2
-                        }
-                    }
-                    if (EX != EXTRA_NONE) {
-                        // grad phi = R'(r) u Y + (R / r) (G - u (u . G)), G = dY/du; zero where the
-                        // function is cut off or r <= rmin
-                        const bool live = d2 < rc2 && r > rmin;
-                        const double ir = live ? 1.0 / r : 0.0;
-                        double hwv = 0.0, wax = 0.0, way = 0.0, waz = 0.0, qw = 0.0;
-                        if (GGA || KS) hwv = 0.5 * gptr(sg.wv)[p];
-                        if (field) {
-                            gp<const double> wa = gptr(sg.wa) + 3 * p;
-                            wax = wa[0], way = wa[1], waz = wa[2];
-                        }
-                        // lap phi = (S''/Delta^2 + S'/Delta - l(l+1) S) Y / r^2 in the spline variable
-                        double lap = 0.0;
-                        if (KS || LAPL)
-                            lap = live ? ((d2S * idel + dS) * idel - (double)(l * (l + 1)) * R) * ir * ir : 0.0;
-                        if (KS) qw = 0.25 * gptr(S->pw)[p];
-                        if (LAPL) {
-                            hwv = gptr(sg.wv)[p];
-                            qw = 0.5 * gptr(S->pw)[p];
-                        }
-                        for (int f = 0; f < 2 * l + 1; ++f) {
-                            const int lm = l * l + f;
-                            const double yv = Y[lm];
-                            double g0 = 0.0, g1 = 0.0, g2 = 0.0;
-                            if (GRAD || field) {
-                                double gv[3];
-                                ylm_grad_one(lm, ux, uy, uz, gv);
-                                const double ug = (ux * gv[0] + uy * gv[1]) + uz * gv[2];
-                                g0 = live ? dR * ux * yv + R * ir * (gv[0] - ux * ug) : 0.0;
-                                g1 = live ? dR * uy * yv + R * ir * (gv[1] - uy * ug) : 0.0;
-                                g2 = live ? dR * uz * yv + R * ir * (gv[2] - uz * ug) : 0.0;
-                            }
-                            if (GRAD) {
-                                gp<T> dst = grow + XW * (int64_t)(col + f);
-                                dst[0] = T(g0);
-                                dst[1] = T(g1);
-                                dst[2] = T(g2);
-                                if (LAPL) hout[(int64_t)pl * u.ld + col + f] = T(hwv * (R * yv) - qw * (lap * yv));
-                            } else {
-                                grow[col + f] = T((hwv * (R * yv) - qw * (lap * yv)) + ((wax * g0 + way * g1) + waz * g2));
-                            }
-                        }
-                    }
-                    auto put = [&](auto deg) {
-                        constexpr int L = decltype(deg)::value;
+                f.R = v * (ya + (v * v - 1.0) * pa) + w * (yb + (w * w - 1.0) * pb);
+                if (EX != EXTRA_NONE && q.r > rmin) {
+                    // dR/dr = dR/dt dt/dr with dt/dr = 1 / (r Delta); the clamped part r <= rmin is constant
+                    const double dS = (yb - ya) - (3.0 * v * v - 1.0) * pa + (3.0 * w * w - 1.0) * pb;  // dR/dt
+                    f.dR = dS * idel * q.ir;
+                    f.Rr = f.R * q.ir;
+                    // lap phi = (S''/Delta^2 + S'/Delta - l(l+1) S) Y / r^2 in the spline variable
+                    const double d2S = 6.0 * (v * pa + w * pb);  // d2R/dt2
+                    if (KS || LAPL) f.lap = ((d2S * idel + dS) * idel - (double)(l * (l + 1)) * f.R) * q.ir * q.ir;
+                }
+            }
+            return f;
+        };
+        // the 2 L + 1 values of plane P of a shell
+        auto shell_values = [&](auto which, auto deg, const Pair& q, const Radial& f, T* val) {
+            constexpr int P = decltype(which)::value, L = decltype(deg)::value, NF = 2 * L + 1;
+            // harmonics and their derivatives per shell: left to itself the compiler takes those of
+            // all degrees out of the loop over the shells, some 60 values that then spill
+            double x = q.x, y = q.y, z = q.z;
+            asm volatile("" : "+v"(x), "+v"(y), "+v"(z));
+            double Y[NF];
+            ylm_l<L>(x, y, z, Y);
 #pragma unroll
-                        for (int f = 0; f < 2 * L + 1; ++f) row[col + f] = T(R * Y[L * L + f]);
-                        col += 2 * L + 1;
-                    };
-                    switch (l) {
-                    case 0: put(std::integral_constant<int, 0>{}); break;
-                    case 1: put(std::integral_constant<int, 1>{}); break;
-                    case 2: put(std::integral_constant<int, 2>{}); break;
-                    default: put(std::integral_constant<int, 3>{}); break;
+            for (int i = 0; i < NF; ++i) {
+                if constexpr (P == 0) {
+                    val[i] = T(f.R * Y[i]);
+                } else if constexpr (P == 4) {
+                    val[i] = T(q.hwv * (f.R * Y[i]) - q.qw * (f.lap * Y[i]));
+                } else {
+                    double g[3] = {};
+                    if (GRAD || field) {
+                        double gv[3];
+                        ylm_grad_one(L * L + i, x, y, z, gv);
+                        const double ug = (x * gv[0] + y * gv[1]) + z * gv[2];
+                        g[0] = f.dR * x * Y[i] + f.Rr * (gv[0] - x * ug);
+                        g[1] = f.dR * y * Y[i] + f.Rr * (gv[1] - y * ug);
+                        g[2] = f.dR * z * Y[i] + f.Rr * (gv[2] - z * ug);
                     }
+                    if constexpr (GRAD) val[i] = T(g[P - 1]);
+                    else val[i] = T((q.hwv * (f.R * Y[i]) - q.qw * (f.lap * Y[i])) + ((q.wax * g[0] + q.way * g[1]) + q.waz * g[2]));
                 }
             }
         };
-        // Plain values: a wave's 64 pairs are consecutive atoms of one or a few points, whose
-        // columns are consecutive in the row, so the values are staged in LDS, BASIS_WIN per pair
-        // at a time, and written as contiguous runs of the rows (a store per value and lane would
-        // touch a separate cache line per lane).
-        // the rows of the run in s_pt (a slice longer than SPT rows, which only a unit of more
-        // than MAX_UNIT_POINTS points has, is taken in several runs)
-        int run_row0 = row0;
-        int64_t run_pairs = (int64_t)(min(row1, row0 + SPT) - row0) * na;
-        auto pairs_staged = [&](auto on_chip) {
+        // planes 0 .. NP - 1, h phi being plane 4
+        auto each_plane = [&](auto&& fn) {
+            fn(std::integral_constant<int, 0>{});
+            if constexpr (NP > 1) fn(std::integral_constant<int, 1>{});
+            if constexpr (NP > 3) fn(std::integral_constant<int, 2>{});
+            if constexpr (NP > 3) fn(std::integral_constant<int, 3>{});
+            if constexpr (NP > 4) fn(std::integral_constant<int, 4>{});
+        };
+        auto by_degree = [&](int l, auto&& fn) {
+            switch (l) {
+            case 0: fn(std::integral_constant<int, 0>{}); break;
+            case 1: fn(std::integral_constant<int, 1>{}); break;
+            case 2: fn(std::integral_constant<int, 2>{}); break;
+            default: fn(std::integral_constant<int, 3>{}); break;
+            }
+        };
+        // Threads over pairs, each storing its own values (units or systems past the staging arrays,
+        // and functions per atom past the row stage)
+        auto pairs = [&](auto on_chip) {
             constexpr bool ST = decltype(on_chip)::value;
-            constexpr int BW = BASIS_WIN, BWP = BASIS_WIN + 1;
-            const int lane = tid & 63, wave = tid >> 6;
-            double* win = &s_win[wave * 64 * BWP];
-            int32_t* pinfo = &s_pair[wave * 64 * 2];
-            for (int64_t qb = tid - lane; qb < run_pairs; qb += blockDim.x) {  // wave-uniform trip count
-                const int64_t q = qb + lane;
-                const bool valid = q < run_pairs;
-                const int ql = (int)(valid ? q : qb);  // lanes past the end redo the wave's first pair
-                const int pq = ql / na;
-                const int ai = ql - pq * na;
-                const int pl = run_row0 + pq;
+            for (int64_t e = tid; e < npairs; e += blockDim.x) {
+                const int pq = (int)e / na;
+                const int ai = (int)e - pq * na;
+                const int pl = row0 + pq;
                 const int atom = ST ? 0 : uat[ai];
-                const int col = ST ? s_aspc[ai][1] : ucol[ai];
-                const double ax = ST ? s_atom[ai][0] : axyz[4 * (int64_t)atom];
-                const double ay = ST ? s_atom[ai][1] : axyz[4 * (int64_t)atom + 1];
-                const double az = ST ? s_atom[ai][2] : axyz[4 * (int64_t)atom + 2];
-                const double arc2 = ST ? s_atom[ai][3] : axyz[4 * (int64_t)atom + 3];
-                const double dx = s_pt[pq][0] - ax;
-                const double dy = s_pt[pq][1] - ay;
-                const double dz = s_pt[pq][2] - az;
-                const double d2 = dist2_exact(dx, dy, dz);
+                gp<const double> xyzr = axyz + 4 * (int64_t)atom;
+                const Pair q = ST ? pair_at(u.point_begin + pl, s_atom[ai][0], s_atom[ai][1], s_atom[ai][2], s_atom[ai][3])
+                                  : pair_at(u.point_begin + pl, xyzr[0], xyzr[1], xyzr[2], xyzr[3]);
                 const int sp = ST ? s_aspc[ai][0] : aspecies[atom];
                 const int sh0 = ST ? s_shptr[sp] : shell_ptr[sp];
                 const int sh1 = ST ? s_shptr[sp + 1] : shell_ptr[sp + 1];
-                const bool near = d2 < arc2;  // else every value of the pair is zero
-                const double r = near ? sqrt(d2) : 0.0;
-                double ux = 0.0, uy = 0.0, uz = 1.0;
-                if (r > 0.0) {
-                    const double ir = 1.0 / r;
-                    ux = dx * ir;
-                    uy = dy * ir;
-                    uz = dz * ir;
+                int64_t at = (int64_t)pl * u.ld + (ST ? s_aspc[ai][1] : ucol[ai]);
+                for (int j = sh0; j < sh1; ++j) {
+                    const int l = ST ? s_shell[j] & 3 : shell_l[j];
+                    const int rr = ST ? s_shell[j] >> 3 : shell_rad[j];
+                    const double rmin = ST ? s_par[j][0] : rpar[4 * rr], rc2 = ST ? s_par[j][1] : rpar[4 * rr + 1];
+                    const double idel = ST ? s_par[j][2] : rpar[4 * rr + 2], lnmin = ST ? s_par[j][3] : rpar[4 * rr + 3];
+                    const Radial f = radial_of(q, knot_of(q, rmin, idel, lnmin), l, rr, rmin, rc2, idel);
+                    by_degree(l, [&](auto deg) {
+                        constexpr int NF = 2 * decltype(deg)::value + 1;
+                        each_plane([&](auto which) {
+                            T val[NF];
+                            shell_values(which, deg, q, f, val);
+                            store_run<NF>(plane(decltype(which)::value) + at, val);
+                        });
+                        at += NF;
+                    });
                 }
-                const double lnr = r > 0.0 ? log(r) : 0.0;
-                int nval = 0;
-                for (int j = sh0; j < sh1; ++j) nval += 2 * (ST ? s_shell[j][0] : shell_l[j]) + 1;
-                pinfo[2 * lane] = valid ? pl * u.ld + col : -1;
-                pinfo[2 * lane + 1] = nval;
-                int nmax = valid ? nval : 0;  // the wave's largest value count
+            }
+        };
+        // A wave takes 16 neighbouring atoms of four points, plane by plane: every lane puts the values
+        // of its pair where they belong in the run of columns that the 16 atoms have in each row, and
+        // the runs are copied out by 16 bytes per lane from 64-byte boundaries
+        auto rows_staged = [&]() {
+            constexpr int V = 16 / (int)sizeof(T), SEG = 64 / (int)sizeof(T);
+            typedef T vec __attribute__((ext_vector_type(V)));
+            const int lane = tid & 63, wave = uni(tid >> 6), waves = (int)blockDim.x >> 6;
+            T* win = reinterpret_cast<T*>(lds_spline + spline_lds) + wave * 4 * run;
+            const int parts = (na + 15) >> 4, tasks = (row1 - row0 + 3) / 4 * parts;
+            for (int task = wave; task < tasks; task += waves) {
+                const int part = task % parts, rowb = row0 + 4 * (task / parts);
+                const int c0 = uni(s_aspc[16 * part][1]), c1 = part + 1 < parts ? uni(s_aspc[16 * part + 16][1]) : u.m;
+                const int ai = 16 * part + (lane & 15), rl = lane >> 4;
+                const bool mine = ai < na && rowb + rl < row1;
+                const int pl = min(rowb + rl, row1 - 1), aj = min(ai, na - 1);
+                const Pair q = pair_at(u.point_begin + pl, s_atom[aj][0], s_atom[aj][1], s_atom[aj][2], s_atom[aj][3]);
+                const int sp = s_aspc[aj][0];
+                const bool any = __any(mine && q.near);  // else zeros throughout
+                const int sh0 = s_shptr[sp], sh1 = mine && any ? s_shptr[sp + 1] : sh0;
+                each_plane([&](auto which) {
+                    gp<T> dst = plane(decltype(which)::value) + (int64_t)rowb * u.ld + c0;
+                    // values by which a row's run starts past a 64-byte boundary
+                    auto past = [&](int r) { return (int)(reinterpret_cast<uintptr_t>(dst + (int64_t)r * u.ld) / sizeof(T)) & (SEG - 1); };
+                    T* at = win + rl * run + past(rl) + (s_aspc[aj][1] - c0);
+                    Knot g{};
+                    for (int j = sh0; j < sh1; ++j) {
+                        const int sh = s_shell[j], l = sh & 3;
+                        if (j == sh0 || !(sh & 4)) g = knot_of(q, s_par[j][0], s_par[j][2], s_par[j][3]);
+                        const Radial f = radial_of(q, g, l, sh >> 3, s_par[j][0], s_par[j][1], s_par[j][2]);
+                        by_degree(l, [&](auto deg) {
+                            constexpr int NF = 2 * decltype(deg)::value + 1;
+                            T val[NF];
+                            shell_values(which, deg, q, f, val);
 #pragma unroll
-                for (int o = 1; o < 64; o <<= 1) nmax = max(nmax, __shfl_xor(nmax, o));
-                for (int w0 = 0; w0 < nmax; w0 += BW) {
-                    // this pair's values w0 .. w0 + BW - 1 into its row of the window
-                    int off = 0;
-                    for (int j = sh0; j < sh1 && off < w0 + BW; ++j) {
-                        const int l = ST ? s_shell[j][0] : shell_l[j];
-                        const int nf = 2 * l + 1;
-                        if (off + nf > w0) {
-                            const int rr = ST ? s_shell[j][1] : shell_rad[j];
-                            const double rmin = ST ? s_par[j][0] : rpar[4 * rr];
-                            const double rc2 = ST ? s_par[j][1] : rpar[4 * rr + 1];
-                            const double idel = ST ? s_par[j][2] : rpar[4 * rr + 2];
-                            const double lnmin = ST ? s_par[j][3] : rpar[4 * rr + 3];
-                            double R = 0.0;
-                            if (near && d2 < rc2) {
-                                double t = r > rmin ? (lnr - lnmin) * idel : 0.0;
-                                t = fmin(fmax(t, 0.0), tmax);
-                                const int k = min((int)t, nk - 2);
-                                const double w = t - (double)k, v = 1.0 - w;
-                                const int64_t ci = ((int64_t)rr * nk + k) * 2;
-                                double ya, pa, yb, pb;
-                                if (SPLINE_LDS) {
-                                    ya = lds_spline[ci], pa = lds_spline[ci + 1], yb = lds_spline[ci + 2], pb = lds_spline[ci + 3];
-                                } else {
-                                    gp<const double> c = spl + ci;
-                                    ya = c[0], pa = c[1], yb = c[2], pb = c[3];
-                                }
-                                R = v * (ya + (v * v - 1.0) * pa) + w * (yb + (w * w - 1.0) * pb);
-                            }
-                            auto put = [&](auto deg) {
-                                constexpr int L = decltype(deg)::value;
-                                double Yl[2 * L + 1];
-                                ylm_l<L>(ux, uy, uz, Yl);
-#pragma unroll
-                                for (int f = 0; f < 2 * L + 1; ++f) {
-                                    const int slot = off + f - w0;
-                                    if (slot >= 0 && slot < BW) win[lane * BWP + slot] = R * Yl[f];
-                                }
-                            };
-                            switch (l) {
-                            case 0: put(std::integral_constant<int, 0>{}); break;
-                            case 1: put(std::integral_constant<int, 1>{}); break;
-                            case 2: put(std::integral_constant<int, 2>{}); break;
-                            default: put(std::integral_constant<int, 3>{}); break;
-                            }
-                        }
-                        off += nf;
+                            for (int i = 0; i < NF; ++i) at[i] = val[i];
+                            at += NF;
+                        });
                     }
                     // the wave's own LDS writes are performed before its later reads (in order)
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                    // element e = k 64 + lane of the 64 x BW window: pair e / BW, value e % BW;
-                    // the LDS reads of four elements are issued before their stores
-                    const int2* pinfo2 = reinterpret_cast<const int2*>(pinfo);
+                    __builtin_amdgcn_wave_barrier();
+                    const int n_rows = min(4, row1 - rowb);
+                    for (int r = 0; r < n_rows; ++r) {
+                        const int b0 = past(r), b1 = b0 + c1 - c0;
+                        const T* src = win + r * run;
+                        gp<T> to = dst + (int64_t)r * u.ld - b0;
+                        for (int i = lane * V; i < b1; i += 64 * V) {
+                            vec x = *reinterpret_cast<const vec*>(src + i);
+                            if (!any) x = vec(T(0));
+                            if (i >= b0 && i + V <= b1) {
+                                *reinterpret_cast<gp<vec>>(to + i) = x;
+                            } else {
 #pragma unroll
-                    for (int kb = 0; kb < BW; kb += 4) {
-                        int2 pi[4];
-                        double val[4];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const int e = (kb + j) * 64 + lane;
-                            pi[j] = pinfo2[e / BW];
-                            val[j] = win[(e / BW) * BWP + e % BW];
-                        }
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const int f = ((kb + j) * 64 + lane) % BW;
-                            if (pi[j].x >= 0 && w0 + f < pi[j].y) out[(int64_t)pi[j].x + w0 + f] = T(val[j]);
+                                for (int k = 0; k < V; ++k)
+                                    if (i + k >= b0 && i + k < b1) to[i + k] = x[k];
+                            }
                         }
                     }
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                }
+                    __builtin_amdgcn_wave_barrier();
+                });
             }
         };
-        if constexpr (STAGE) {
-            for (int r0 = row0; r0 < row1; r0 += SPT) {
-                const int r1 = min(row1, r0 + SPT);
-                if (r0 != row0) {
-                    __syncthreads();  // every wave is done with the previous run's points
-                    stage_points(r0, r1);
-                    __syncthreads();
-                }
-                run_row0 = r0;
-                run_pairs = (int64_t)(r1 - r0) * na;
-                if (staged) pairs_staged(std::true_type{});
-                else pairs_staged(std::false_type{});
-            }
-        } else {
-            if (staged) pairs(std::true_type{});
-            else pairs(std::false_type{});
-        }
-        if (slice == BASIS_SLICES - 1 && u.n_rows > u.n_points) {  // padding rows of a cluster's unit
+        if (run > 0 && staged) rows_staged();
+        else if (staged) pairs(std::true_type{});
+        else pairs(std::false_type{});
+        if (slice == slices - 1 && u.n_rows > u.n_points) {  // padding rows of a cluster's unit
             const int64_t z0 = (int64_t)u.n_points * u.ld, z1 = (int64_t)u.n_rows * u.ld;
-            for (int64_t q = z0 + tid; q < z1; q += blockDim.x) {
-                out[q] = T(0);
-                if (EX != EXTRA_NONE)
-                    for (int c = 0; c < XW; ++c) gout[XW * q + c] = T(0);
-            }
+            for (int64_t q = z0 + tid; q < z1; q += blockDim.x) each_plane([&](auto which) { plane(decltype(which)::value)[q] = T(0); });
         }
         const int pad = u.ld - u.m;
         if (pad > 0) {
             const int64_t ne = (int64_t)(row1 - row0) * pad;
             for (int64_t q = tid; q < ne; q += blockDim.x) {
                 const int64_t pl = row0 + q / pad;
-                const int64_t cpad = q - (pl - row0) * pad;
-                out[pl * u.ld + u.m + cpad] = T(0);
-                if (EX != EXTRA_NONE)
-                    for (int c = 0; c < XW; ++c) gout[XW * (pl * u.ld + u.m + cpad) + c] = T(0);
-                if (LAPL) hout[pl * u.ld + u.m + cpad] = T(0);
+                const int64_t at = pl * u.ld + u.m + (q - (pl - row0) * pad);
+                each_plane([&](auto which) { plane(decltype(which)::value)[at] = T(0); });
             }
         }
     }
@@ -586,30 +552,43 @@ static unsigned grid_for(int64_t n, int lg, int64_t max_grid)
     return (unsigned)span;
 }
 
-hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int spline_lds, bool fp32_out,
-                        hipStream_t st, int64_t max_grid, int extra)
+hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int spline_lds, int max_fn, double mean_fn,
+                        bool fp32_out, hipStream_t st, int64_t max_grid, int extra)
 {
     if (n_units <= 0 || n_segs <= 0) return hipSuccess;
-    if (n_units > 0x7ffffff0 / BASIS_SLICES || spline_lds < 0 || spline_lds > MAX_SPLINE_LDS) return hipErrorInvalidValue;
+    if (n_units > 0x7ffffff0 / BASIS_SLICES_PAIRS || spline_lds < 0 || spline_lds > MAX_SPLINE_LDS || max_fn < 0)
+        return hipErrorInvalidValue;
     if (extra != EXTRA_NONE && extra != EXTRA_GRAD && extra != EXTRA_GGA_L && extra != EXTRA_KS_L &&
         extra != EXTRA_GRAD_H)
         return hipErrorInvalidValue;
-    const int64_t n_items = n_units * BASIS_SLICES;
-    // two workgroups per CU fit (LDS); a grid of that size takes many items per workgroup, which
-    // stages its spline table once
-    if (max_grid <= 0) {
-        static std::atomic<int> n_cu{0};
-        if (n_cu.load() == 0) {
-            int dev = 0, cu = 0;
-            if (hipGetDevice(&dev) == hipSuccess &&
-                hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cu > 0)
-                n_cu.store(cu);
-        }
-        max_grid = 2 * (int64_t)std::max(1, n_cu.load());
+    static std::atomic<int> n_cu{0};
+    if (n_cu.load() == 0) {
+        int dev = 0, cu = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cu > 0)
+            n_cu.store(cu);
     }
-    const dim3 g(grid_for(n_items, 2, max_grid)), b(256);
+    const int cus = std::max(1, n_cu.load());
+    // Rows are staged where the LDS left by the spline table holds those of four waves or more, and
+    // where their longer way pays: not in launches too small to fill the chip (8 atoms, 130 units: 14 us
+    // by pairs, 20 staged), not for short runs (9.5 FP64 functions per atom: 0.25 against 0.28 ms; 14
+    // FP32 ones: 0.72 against 0.77; 14 FP64 ones: 1.5 by rows against 2.2), and not for L in FP32, two
+    // planes with the arithmetic of four (2.0 against 2.3 ms).
+    const int size = fp32_out ? sizeof(float) : sizeof(double), most = basis_waves(extra);
+    const int64_t table = 8 * (int64_t)spline_lds, room = BASIS_LDS - BASIS_STATIC - table;
+    const int64_t run = 16 * (int64_t)max_fn + 64 / size;
+    const int fit = (int)std::min<int64_t>(most, room / (4 * run * size));
+    const bool rows = fit >= 4 && n_units >= BASIS_ROWS_UNITS && mean_fn * size >= BASIS_ROWS_BYTES &&
+                      !(fp32_out && (extra == EXTRA_GGA_L || extra == EXTRA_KS_L));
+    const int waves = rows ? fit : 4, slices = rows ? BASIS_SLICES : BASIS_SLICES_PAIRS;
+    const int64_t n_items = n_units * slices;
+    const size_t lds = (size_t)(table + (rows ? waves * 4 * run * size : 0));
+    // as many workgroups as fit the chip at once (LDS and registers): each takes many items and
+    // stages its spline table once
+    if (max_grid <= 0)
+        max_grid = cus * std::max<int64_t>(1, std::min<int64_t>(most / waves, BASIS_LDS / ((int64_t)lds + BASIS_STATIC)));
+    const dim3 g(grid_for(n_items, 2, max_grid)), b(64 * waves);
     const bool staged = spline_lds > 0;
-    const size_t lds = (size_t)spline_lds * sizeof(double);
     // dynamic LDS above 64 KiB must be allowed per kernel, once per device
     static std::atomic<uint64_t> attrs_set{0};
     int dev = 0;
@@ -630,15 +609,15 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
         const void* fns[] = {NAO_BASIS_FNS(float), NAO_BASIS_FNS(double)};
 #undef NAO_BASIS_FNS
         for (const void* f : fns) {
-            const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BASIS_LDS_BYTES);
+            const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, BASIS_LDS - BASIS_STATIC);
             if (e != hipSuccess) return e;
         }
         attrs_set.fetch_or(bit);
     }
 #define NAO_BASIS_LAUNCH(TT, EE)                                                                                 \
     do {                                                                                                       \
-        if (staged) hipLaunchKernelGGL((basis_kernel<TT, true, EE>), g, b, lds, st, segs_dev, n_segs, n_items, 2, spline_lds); \
-        else hipLaunchKernelGGL((basis_kernel<TT, false, EE>), g, b, lds, st, segs_dev, n_segs, n_items, 2, 0);  \
+        if (staged) hipLaunchKernelGGL((basis_kernel<TT, true, EE>), g, b, lds, st, segs_dev, n_segs, n_items, 2, slices, spline_lds, rows ? (int)run : 0); \
+        else hipLaunchKernelGGL((basis_kernel<TT, false, EE>), g, b, lds, st, segs_dev, n_segs, n_items, 2, slices, 0, rows ? (int)run : 0);  \
     } while (0)
 #define NAO_BASIS_EXTRA(TT)                                           \
     do {                                                              \
@@ -709,17 +688,6 @@ template <> struct Mma<float> {
 
 // ------------------------------------------------------------------------------------------
 // Parts shared by the tile kernels of H below.
-
-// Lane-uniform values kept in scalar registers: FP64 and FP32 MFMA do not issue beside vector
-// instructions (measured: 69 and 31 cycles per MFMA alone, about 3 more for every vector
-// instruction between them), so what is uniform is computed by the scalar unit.
-__device__ inline int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ inline int64_t uni(int64_t x)
-{
-    const uint32_t lo = (uint32_t)uni((int)(uint32_t)x), hi = (uint32_t)uni((int)(uint32_t)((uint64_t)x >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-template <typename T> __device__ inline T* uni(T* p) { return reinterpret_cast<T*>(uni((int64_t)(uintptr_t)p)); }
 
 // A raw buffer over [p, p + bytes): loads beyond its end return zeros.
 __device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes)
@@ -1359,18 +1327,18 @@ __global__ __launch_bounds__(256, 4) void n_tiles(const DevSeg* __restrict__ seg
         constexpr int SZ = (int)sizeof(T);
         const int voff_e = lr * ldb + c0 * SZ;  // row lr of a row block, first column of this wave
         if constexpr (KIND == NK_FORCE) {
-            const char* g = static_cast<const char*>(sg.gphi) + 3 * out_offset * SZ;
+            const char* g = static_cast<const char*>(sg.gphi) + out_offset * SZ;
             double f[4][3] = {};
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 const int rb = q;
                 if (!((col_rows >> rb) & 1)) continue;
-                const __amdgpu_buffer_rsrc_t rg = buffer_of(g + (int64_t)rb * 48 * ldb, max(0, np - rb * 16) * 3 * ldb);
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
+                for (int k = 0; k < 3; ++k) {
+                    const __amdgpu_buffer_rsrc_t rg = buffer_of(g + k * sg.plane * SZ + (int64_t)rb * 16 * ldb, max(0, np - rb * 16) * ldb);
 #pragma unroll
-                    for (int k = 0; k < 3; ++k)
-                        f[r][k] += (double)acc[q][r] * (double)load_value<T>(rg, 3 * voff_e + (3 * M::row(lk, r) + k) * SZ);
+                    for (int r = 0; r < 4; ++r) f[r][k] += (double)acc[q][r] * (double)load_value<T>(rg, voff_e + M::row(lk, r) * SZ);
+                }
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -1386,7 +1354,7 @@ __global__ __launch_bounds__(256, 4) void n_tiles(const DevSeg* __restrict__ seg
         } else {
             constexpr int NQ = KIND == NK_GRADIENT ? 4 : 1;
             const char* ph = reinterpret_cast<const char*>(phi);
-            const char* g = KIND == NK_GRADIENT ? static_cast<const char*>(sg.gphi) + 3 * out_offset * SZ : nullptr;
+            const char* g = KIND == NK_GRADIENT ? static_cast<const char*>(sg.gphi) + out_offset * SZ : nullptr;
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 const int rb = q, p = rb * 16 + lr;
@@ -1398,12 +1366,13 @@ __global__ __launch_bounds__(256, 4) void n_tiles(const DevSeg* __restrict__ seg
                     for (int r = 0; r < 4; ++r)
                         dot[0] += (double)acc[q][r] * (double)load_value<T>(rp, voff_e + M::row(lk, r) * SZ);
                     if constexpr (KIND == NK_GRADIENT) {
-                        const __amdgpu_buffer_rsrc_t rg = buffer_of(g + (int64_t)rb * 48 * ldb, rows * 3 * ldb);
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
+                        for (int k = 1; k < NQ; ++k) {
+                            const __amdgpu_buffer_rsrc_t rg = buffer_of(g + (k - 1) * sg.plane * SZ + (int64_t)rb * 16 * ldb, rows * ldb);
 #pragma unroll
-                            for (int k = 1; k < NQ; ++k)
-                                dot[k] += (double)acc[q][r] * (double)load_value<T>(rg, 3 * voff_e + (3 * M::row(lk, r) + k - 1) * SZ);
+                            for (int r = 0; r < 4; ++r)
+                                dot[k] += (double)acc[q][r] * (double)load_value<T>(rg, voff_e + M::row(lk, r) * SZ);
+                        }
                     }
 #pragma unroll
                     for (int k = 0; k < NQ; ++k) {
@@ -1523,7 +1492,7 @@ __global__ __launch_bounds__(1024) void n_force_f32(const DevSeg* __restrict__ s
             }
             // f_j += sum_p grad phi_pj M_pj: this wave's rows, then the lanes of one column
             const int cj = J0 + cb * 16 + lr;
-            gp<const T> gph = gptr(static_cast<const T*>(sg.gphi) + 3 * u.out_offset);
+            gp<const T> gph = gptr(static_cast<const T*>(sg.gphi) + u.out_offset);
             double f[3] = {0.0, 0.0, 0.0};
 #pragma unroll
             for (int q = 0; q < F; ++q)
@@ -1533,7 +1502,7 @@ __global__ __launch_bounds__(1024) void n_force_f32(const DevSeg* __restrict__ s
                     const int64_t e = (int64_t)min(p, np - 1) * ld + cj;
                     const double a = p < np && cj < m ? (double)acc[q][r] : 0.0;
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) f[k] += a * (double)gph[3 * e + k];
+                    for (int k = 0; k < 3; ++k) f[k] += a * (double)gph[k * sg.plane + e];
                 }
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
