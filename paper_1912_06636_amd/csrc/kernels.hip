@@ -1598,7 +1598,7 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
         // that every part is stashed as one 16-byte run of a column (loads: a wave reads 64
         // consecutive columns of one point)
         static_assert(NQ == 8, "eight points per thread");
-        const int col = tid & 63, p0 = NQ * (tid >> 6);
+        const int col = tid & 63, p0 = NQ * uni(tid >> 6);  // the points are the wave's: scalar addresses and w v
         float ra[NQ], rb[NQ];
         double rw[NQ];
         auto fetch = [&](int c) {
@@ -1707,164 +1707,154 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
 }
 
 // Density, split-BF16 MFMA: per item one 64-wide column tile J of a unit, K = 32 functions per
-// chunk; sixteen waves as in n_kernel (wave w: column block w % 4, row blocks w / 4 + 4 q).  A
-// (points x functions) in LDS as [part][point][function], B (functions x columns) as
-// [part][column][function]; NB LDS buffers (one buffer adds a barrier per chunk).  The FP32
-// sums move into FP64 after every 64-function tile; the row dot and the sums over tiles and
+// chunk; sixteen waves, wave w takes column block w % 4 and row blocks w / 4 + 4 q.  A (points x
+// functions) in LDS as [part][point][function], B (functions x columns) as [part][column][function],
+// rows of 64 bytes with their 16-byte slots permuted by row (no bank conflicts), two buffers.  The
+// FP32 sums move into FP64 after every 64-function tile; the row dot and the sums over tiles and
 // units are FP64.
-template <int NS, int NB>
+// @NBF@
+template <int NS>
 __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
-    constexpr int NT = 1024, RB = 4, RS = 4;
-    constexpr int NA = MAX_UNIT_POINTS * BK / NT;  // basis values per thread per chunk (8)
-    constexpr int ND = BK * TILE / NT;             // D values per thread per chunk (2)
-    constexpr int CPT = TILE / BK;                 // chunks per tile (2)
-    __shared__ __attribute__((aligned(16))) __bf16 As[NB][NS][MAX_UNIT_POINTS][BKP];
-    __shared__ __attribute__((aligned(16))) __bf16 Bs[NB][NS][TILE][BKP];
+    constexpr int RB = 4, RS = 4;
+    constexpr int CPT = TILE / BK;  // chunks per tile (2)
+    __shared__ __attribute__((aligned(16))) __bf16 As[2][NS][MAX_UNIT_POINTS][BK];
+    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NS][TILE][BK];
     __shared__ double red[4][MAX_UNIT_POINTS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     const int cb = wave & 3, rh = wave >> 2;
     const int lr = lane & 15, lk = lane >> 4;
+    auto slot = [](int row, int g) { return 8 * (g ^ ((row >> 1) & 3)); };  // first of the functions 8 g .. 8 g + 7
     for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
         const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
         const NItem it = static_cast<const NItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit u = sg.item_units[it.unit];
-        gp<const float> __restrict__ phi = gptr(static_cast<const float*>(sg.phi) + u.out_offset);
-        gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + u.fn_begin);
-        gp<const double> __restrict__ D = gptr(sg.D);
-        const int64_t ldd = sg.ld;
-        const int np = u.n_points, ld = u.ld, m = u.m;
+        const DevUnit& u = sg.item_units[uni(it.unit)];
+        const int tj = uni(it.tj), np = uni(u.n_points), ld = uni(u.ld), m = uni(u.m);
         if (np <= 0 || m <= 0) continue;
+        const int64_t out_offset = uni(u.out_offset), point_begin = uni(u.point_begin);
+        gp<const float> __restrict__ phi = gptr(static_cast<const float*>(sg.phi) + out_offset);
+        gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + uni(u.fn_begin));
+        gp<const double> __restrict__ D = gptr(sg.D);
+        const int64_t ldd = uni(sg.ld);
         const int P = (np + 15) >> 4;
-        const int J0 = it.tj * TILE;
-        const int n_chunks = (it.tj + 1) * CPT;  // chunk c covers functions 32 c .. 32 c + 31
-        const int cjd = J0 + (tid & (TILE - 1));
+        const int J0 = tj * TILE, n_chunks = (tj + 1) * CPT;  // chunk c covers functions 32 c .. 32 c + 31
+        // staged by this thread: functions 8 (tid % 4) .. of row tid / 4, and functions 2 wave and
+        // 2 wave + 1 of column tid % 64
+        const int ar = tid >> 2, ag = tid & 3;
+        const bool stages_a = wave < P;  // wave-uniform: 16 rows per wave
+        gp<const float> a_row = phi + (int64_t)min(ar, np - 1) * ld + 8 * ag;
+        const int cjd = J0 + lane;
         const int64_t gjd = fn[min(cjd, m - 1)];
-
-        auto run = [&](auto rows_staged, auto rows_own) {
-            constexpr int F = decltype(rows_staged)::value;
-            constexpr int R = decltype(rows_own)::value;
-            constexpr int NAR = NA * F / RB;
-            float pa[NAR];
-            double pd[ND];
-            int32_t gcur[ND], gnxt[ND];
-            auto load_idx = [&](int c, int32_t* g) {
+        f4 pa[2];
+        double pd[2];
+        int32_t gcur[2], gnxt[2];
+        auto load_idx = [&](int c, int32_t* g) {
 #pragma unroll
-                for (int q = 0; q < ND; ++q) g[q] = fn[min(BK * c + (tid >> 6) + (NT / TILE) * q, m - 1)];
-            };
-            auto fetch = [&](int c) {
-#pragma unroll
-                for (int q = 0; q < NAR; ++q) {
-                    const int e = tid + NT * q;
-                    pa[q] = phi[(int64_t)min(e / BK, np - 1) * ld + BK * c + (e % BK)];
-                }
-                const bool diag = c / CPT == it.tj;
-#pragma unroll
-                for (int q = 0; q < ND; ++q) {
-                    const int ci = BK * c + (tid >> 6) + (NT / TILE) * q;
-                    const bool lower = diag && ci > cjd;
-                    pd[q] = D[lower ? gjd * ldd + gcur[q] : (int64_t)gcur[q] * ldd + gjd];
-                }
-                load_idx(c + 1, gnxt);
-            };
-            auto stash = [&](int c, int buf) {
-#pragma unroll
-                for (int q = 0; q < ND; ++q) gcur[q] = gnxt[q];
-                const bool diag = c / CPT == it.tj;
-#pragma unroll
-                for (int q = 0; q < NAR; ++q) {
-                    const int e = tid + NT * q;
-                    __bf16 px[NS];
-                    split_bf16<NS>((e / BK) < np ? pa[q] : 0.f, px);
-#pragma unroll
-                    for (int t = 0; t < NS; ++t) As[buf][t][e / BK][e % BK] = px[t];
-                }
-#pragma unroll
-                for (int q = 0; q < ND; ++q) {
-                    const int e = tid + NT * q;
-                    const int i = e >> 6, j = e & 63;
-                    const bool ok = BK * c + i < m && cjd < m;
-                    __bf16 pv[NS];
-                    split_bf16<NS>(ok ? (float)(diag ? pd[q] : 2.0 * pd[q]) : 0.f, pv);
-#pragma unroll
-                    for (int t = 0; t < NS; ++t) Bs[buf][t][j][i] = pv[t];
-                }
-            };
-
-            f4 acc[R > 0 ? R : 1];
-            d4 acc64[R > 0 ? R : 1];
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                acc[i] = f4{0.f, 0.f, 0.f, 0.f};
-                acc64[i] = d4{0.0, 0.0, 0.0, 0.0};
+            for (int q = 0; q < 2; ++q) g[q] = uni(fn[min(BK * c + 2 * wave + q, m - 1)]);
+        };
+        auto fetch = [&](int c) {
+            if (stages_a) {
+                pa[0] = *reinterpret_cast<gp<const f4>>(a_row + BK * c);
+                pa[1] = *reinterpret_cast<gp<const f4>>(a_row + BK * c + 4);
             }
-            load_idx(0, gcur);
-            fetch(0);
-            stash(0, 0);
-            __syncthreads();
-            for (int c = 0; c < n_chunks; ++c) {
-                const int buf = NB == 2 ? (c & 1) : 0;
-                if (c + 1 < n_chunks) fetch(c + 1);
-                if (R > 0) {
-                    bf8 bv[NS];
+            const bool diag = c / CPT == tj;
 #pragma unroll
-                    for (int t = 0; t < NS; ++t) bv[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][cb * 16 + lr][lk * 8]);
-#pragma unroll
-                    for (int q = 0; q < R; ++q) {
-                        bf8 av[NS];
-#pragma unroll
-                        for (int t = 0; t < NS; ++t)
-                            av[t] = *reinterpret_cast<const bf8*>(&As[buf][t][(RS * q + rh) * 16 + lr][lk * 8]);
-                        acc[q] = mfma_split<NS>(av, bv, acc[q]);
-                    }
-                    if (c % CPT == CPT - 1) {  // end of a 64-function tile
-#pragma unroll
-                        for (int q = 0; q < R; ++q)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                acc64[q][r] += (double)acc[q][r];
-                                acc[q][r] = 0.f;
-                            }
-                    }
-                }
-                if (NB == 1) __syncthreads();
-                if (c + 1 < n_chunks) stash(c + 1, NB == 2 ? (buf ^ 1) : 0);
-                __syncthreads();
+            for (int q = 0; q < 2; ++q) {
+                const bool lower = diag && BK * c + 2 * wave + q > cjd;
+                pd[q] = D[lower ? gjd * ldd + gcur[q] : (int64_t)gcur[q] * ldd + gjd];
             }
-            const int cj = J0 + cb * 16 + lr;
+            load_idx(c + 1, gnxt);
+        };
+        auto stash = [&](int c, int buf) {
 #pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int pblk = RS * q + rh;
-                if (pblk < P) {
+            for (int q = 0; q < 2; ++q) gcur[q] = gnxt[q];
+            if (stages_a) {
+                bf8 part[NS];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    __bf16 x[NS];
+                    split_bf16<NS>(ar < np ? pa[k >> 2][k & 3] : 0.f, x);
+#pragma unroll
+                    for (int t = 0; t < NS; ++t) part[t][k] = x[t];
+                }
+#pragma unroll
+                for (int t = 0; t < NS; ++t) *reinterpret_cast<bf8*>(&As[buf][t][ar][slot(ar, ag)]) = part[t];
+            }
+            typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+            bf2 part[NS];
+            const bool diag = c / CPT == tj;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const bool ok = BK * c + 2 * wave + q < m && cjd < m;
+                __bf16 x[NS];
+                split_bf16<NS>(ok ? (float)(diag ? pd[q] : 2.0 * pd[q]) : 0.f, x);
+#pragma unroll
+                for (int t = 0; t < NS; ++t) part[t][q] = x[t];
+            }
+#pragma unroll
+            for (int t = 0; t < NS; ++t)
+                *reinterpret_cast<bf2*>(&Bs[buf][t][lane][slot(lane, wave >> 2) + 2 * (wave & 3)]) = part[t];
+        };
+
+        f4 acc[RB];
+        d4 acc64[RB];
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+            acc[q] = f4{0.f, 0.f, 0.f, 0.f};
+            acc64[q] = d4{0.0, 0.0, 0.0, 0.0};
+        }
+        load_idx(0, gcur);
+        fetch(0);
+        stash(0, 0);
+        __syncthreads();
+        for (int c = 0; c < n_chunks; ++c) {
+            const int buf = c & 1;
+            if (c + 1 < n_chunks) fetch(c + 1);
+            bf8 bv[NS];
+#pragma unroll
+            for (int t = 0; t < NS; ++t) bv[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][cb * 16 + lr][slot(lr, lk)]);
+#pragma unroll
+            for (int q = 0; q < RB; ++q)
+                if (RS * q + rh < P) {
+                    bf8 av[NS];
+#pragma unroll
+                    for (int t = 0; t < NS; ++t)
+                        av[t] = *reinterpret_cast<const bf8*>(&As[buf][t][(RS * q + rh) * 16 + lr][slot(lr, lk)]);
+                    acc[q] = mfma_split<NS>(av, bv, acc[q]);
+                }
+            if (c % CPT == CPT - 1) {  // end of a 64-function tile
+#pragma unroll
+                for (int q = 0; q < RB; ++q)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int p = pblk * 16 + lk * 4 + r;
-                        const double f = (double)phi[(int64_t)min(p, np - 1) * ld + cj];
-                        const double v = row_sum16((p < np && cj < m) ? acc64[q][r] * f : 0.0);
-                        if (lr == 0) red[cb][p] = v;
+                        acc64[q][r] += (double)acc[q][r];
+                        acc[q][r] = 0.f;
                     }
+            }
+            if (c + 1 < n_chunks) stash(c + 1, buf ^ 1);
+            __syncthreads();
+        }
+        const int cj = J0 + cb * 16 + lr;
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+            const int pblk = RS * q + rh;
+            if (pblk < P) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int p = pblk * 16 + lk * 4 + r;
+                    const double f = (double)phi[(int64_t)min(p, np - 1) * ld + cj];
+                    const double v = row_sum16((p < np && cj < m) ? acc64[q][r] * f : 0.0);
+                    if (lr == 0) red[cb][p] = v;
                 }
             }
-        };
-        typedef std::integral_constant<int, RB> Full;
-        typedef std::integral_constant<int, RB / 2> Half;
-        const int own = min(RB, (P - rh + RS - 1) / RS);
-        if (P > RB / 2 * RS) {
-            if (own > RB * 3 / 4) run(Full{}, Full{});
-            else if (own > RB / 2) run(Full{}, std::integral_constant<int, RB * 3 / 4>{});
-            else run(Full{}, Half{});
-        } else {
-            if (own > RB / 4) run(Half{}, Half{});
-            else if (own > 0) run(Half{}, std::integral_constant<int, RB / 4>{});
-            else run(Half{}, std::integral_constant<int, 0>{});
         }
         __syncthreads();
         if (tid < np) {
             const double v = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
-            gadd(gptr(sg.n) + gptr(sg.sys->perm)[u.point_begin + tid], v);
+            gadd(gptr(sg.n) + gptr(sg.sys->perm)[point_begin + tid], v);
         }
         __syncthreads();  // red is rewritten by the next item
     }
@@ -1907,8 +1897,8 @@ hipError_t launch_n(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n_ite
     switch (mode) {
     case MODE_FP64: hipLaunchKernelGGL((n_tiles<double, NK_DENSITY>), g, dim3(256), 0, st, segs_dev, n_segs, n_items, lg); break;
     case MODE_FP32: hipLaunchKernelGGL((n_tiles<float, NK_DENSITY>), g, dim3(256), 0, st, segs_dev, n_segs, n_items, lg); break;
-    case MODE_BF16X3: hipLaunchKernelGGL((n_kernel_bf16<2, 2>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
-    case MODE_BF16X6: hipLaunchKernelGGL((n_kernel_bf16<3, 1>), g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_BF16X3: hipLaunchKernelGGL(n_kernel_bf16<2>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
+    case MODE_BF16X6: hipLaunchKernelGGL(n_kernel_bf16<3>, g, b, 0, st, segs_dev, n_segs, n_items, lg); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
