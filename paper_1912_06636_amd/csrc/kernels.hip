@@ -1531,21 +1531,20 @@ __global__ __launch_bounds__(1024) void n_force_f32(const DevSeg* __restrict__ s
 // into FP64 accumulators and reach H and n through FP64 atomics.
 
 
-
-
-
-
-// Split of an FP32 value into NS bf16 parts: x ~ x0 + x1 (+ x2), each part the rounding to
-// nearest of what the previous parts leave.
+// Split of two FP32 values into NS bf16 parts each: x ~ x0 + x1 (+ x2), each part the rounding to
+// nearest of what the previous parts leave.  part[s]: the two values' part s, packed.
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 template <int NS>
-__device__ inline void split_bf16(float x, __bf16* part)
+__device__ inline void split_bf16(float x, float y, uint32_t* part)
 {
-    float r = x;
+    typedef float f2 __attribute__((ext_vector_type(2)));
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        const __bf16 h = (__bf16)r;
+        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x, y}, bf2));
         part[s] = h;
-        r -= (float)h;
+        x -= __builtin_bit_cast(float, h << 16);
+        y -= __builtin_bit_cast(float, h & 0xffff0000u);
     }
 }
 
@@ -1561,8 +1560,10 @@ __device__ inline f4 mfma_split(const bf8* a, const bf8* b, f4 acc)
     return acc;
 }
 
-constexpr int BK = 32;       // K per bf16 MFMA step
-constexpr int BKP = BK + 8;  // padded LDS row (80 bytes: keeps 16-byte alignment)
+constexpr int BK = 32;  // K per bf16 MFMA step
+// LDS rows are 64 bytes, their four 16-byte slots permuted by row (no bank conflicts, no padding):
+// first of the elements 8 g .. 8 g + 7 of a row
+__device__ inline int bf16_slot(int row, int g) { return 8 * (g ^ ((row >> 1) & 3)); }
 
 // Hamiltonian, split-BF16 MFMA (v_mfma_f32_16x16x32_bf16): per item one 64x64 tile pair of a
 // unit, K = 32 points per chunk, four waves of 32x32.  LDS holds [buffer][part][column][point]
@@ -1575,9 +1576,9 @@ template <int NS>
 __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
     constexpr int NQ = BK * TILE / 256;  // values per thread per chunk and operand
-    __shared__ __attribute__((aligned(16))) __bf16 As[2][NS][TILE][BKP];
-    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NS][TILE][BKP];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ __attribute__((aligned(16))) __bf16 As[2][NS][TILE][BK];
+    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NS][TILE][BK];
+    const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     const int wr = wave >> 1, wc = wave & 1;
     const int lr = lane & 15, lk = lane >> 4;
     for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
@@ -1586,72 +1587,64 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
         const HItem it = static_cast<const HItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit u = sg.item_units[it.unit];
-        gp<const float> __restrict__ phi = gptr(static_cast<const float*>(sg.phi) + u.out_offset);
-        gp<const double> __restrict__ wv = gptr(sg.wv + u.point_begin);
-        const int np = u.n_points, ld = u.ld;
+        const DevUnit& u = sg.item_units[uni(it.unit)];
+        const int np = uni(u.n_points), ld = uni(u.ld), m = uni(u.m);
+        gp<const float> __restrict__ phi = gptr(static_cast<const float*>(sg.phi) + uni(u.out_offset));
+        gp<const double> __restrict__ wv = gptr(sg.wv + uni(u.point_begin));
         if (np <= 0) continue;
-        const int I0 = it.ti * TILE, J0 = it.tj * TILE;
+        const int ti = uni((int)it.ti), tj = uni((int)it.tj), I0 = ti * TILE, J0 = tj * TILE;
         const int n_chunks = (np + BK - 1) / BK;
 
         // this thread's column of both operands and its NQ = 8 consecutive points of a chunk, so
         // that every part is stashed as one 16-byte run of a column (loads: a wave reads 64
         // consecutive columns of one point)
         static_assert(NQ == 8, "eight points per thread");
-        const int col = tid & 63, p0 = NQ * uni(tid >> 6);  // the points are the wave's: scalar addresses and w v
+        const int col = lane, p0 = NQ * wave;  // the points are the wave's: scalar addresses and w v
         float ra[NQ], rb[NQ];
         double rw[NQ];
+        // points past the last: w v = 0 makes their products zero
         auto fetch = [&](int c) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
-                const int pc = min(c * BK + p0 + q, np - 1);
+                const int p = c * BK + p0 + q, pc = min(p, np - 1);
                 gp<const float> rowp = phi + (int64_t)pc * ld;
                 ra[q] = rowp[I0 + col];
                 rb[q] = rowp[J0 + col];
-                rw[q] = wv[pc];
+                rw[q] = p < np ? wv[pc] : 0.0;
             }
         };
-        auto stash = [&](int c, int buf) {
-            bf8 pa[NS], pb[NS];
+        auto stash = [&](int buf) {
+            u4 pa[NS], pb[NS];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const bool ok = c * BK + p0 + q < np;
-                __bf16 xa[NS], xb[NS];
-                split_bf16<NS>(ok ? (float)((double)ra[q] * rw[q]) : 0.f, xa);
-                split_bf16<NS>(ok ? rb[q] : 0.f, xb);
+            for (int q = 0; q < NQ; q += 2) {
+                uint32_t xa[NS], xb[NS];
+                split_bf16<NS>((float)((double)ra[q] * rw[q]), (float)((double)ra[q + 1] * rw[q + 1]), xa);
+                split_bf16<NS>(rb[q], rb[q + 1], xb);
 #pragma unroll
                 for (int t = 0; t < NS; ++t) {
-                    pa[t][q] = xa[t];
-                    pb[t][q] = xb[t];
+                    pa[t][q / 2] = xa[t];
+                    pb[t][q / 2] = xb[t];
                 }
             }
 #pragma unroll
             for (int t = 0; t < NS; ++t) {
-                *reinterpret_cast<bf8*>(&As[buf][t][col][p0]) = pa[t];
-                *reinterpret_cast<bf8*>(&Bs[buf][t][col][p0]) = pb[t];
+                *reinterpret_cast<u4*>(&As[buf][t][col][bf16_slot(col, wave)]) = pa[t];
+                *reinterpret_cast<u4*>(&Bs[buf][t][col][bf16_slot(col, wave)]) = pb[t];
             }
         };
-        gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + u.fn_begin);
+        gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + uni(u.fn_begin));
         int32_t gI[2][4], gJ[2];
 #pragma unroll
         for (int ib = 0; ib < 2; ++ib) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) gI[ib][r] = fn[min(I0 + wr * 32 + ib * 16 + lk * 4 + r, u.m - 1)];
-            gJ[ib] = fn[min(J0 + wc * 32 + ib * 16 + lr, u.m - 1)];
+            for (int r = 0; r < 4; ++r) gI[ib][r] = fn[min(I0 + wr * 32 + ib * 16 + lk * 4 + r, m - 1)];
+            gJ[ib] = fn[min(J0 + wc * 32 + ib * 16 + lr, m - 1)];
         }
 
-        f4 acc[2][2];
-        d4 acc64[2][2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-                acc64[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-            }
+        d4 acc64[2][2] = {};
         auto k_loop = [&](auto with_mfma) {
             fetch(0);
-            stash(0, 0);
+            stash(0);
             __syncthreads();
             for (int c = 0; c < n_chunks; ++c) {
                 const int buf = c & 1;
@@ -1660,31 +1653,28 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
                     bf8 a0[NS], a1[NS], b0[NS], b1[NS];
 #pragma unroll
                     for (int t = 0; t < NS; ++t) {
-                        a0[t] = *reinterpret_cast<const bf8*>(&As[buf][t][wr * 32 + lr][lk * 8]);
-                        a1[t] = *reinterpret_cast<const bf8*>(&As[buf][t][wr * 32 + 16 + lr][lk * 8]);
-                        b0[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][wc * 32 + lr][lk * 8]);
-                        b1[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][wc * 32 + 16 + lr][lk * 8]);
+                        const int k = bf16_slot(lr, lk);
+                        a0[t] = *reinterpret_cast<const bf8*>(&As[buf][t][wr * 32 + lr][k]);
+                        a1[t] = *reinterpret_cast<const bf8*>(&As[buf][t][wr * 32 + 16 + lr][k]);
+                        b0[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][wc * 32 + lr][k]);
+                        b1[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][wc * 32 + 16 + lr][k]);
                     }
-                    acc[0][0] = mfma_split<NS>(a0, b0, acc[0][0]);
-                    acc[0][1] = mfma_split<NS>(a0, b1, acc[0][1]);
-                    acc[1][0] = mfma_split<NS>(a1, b0, acc[1][0]);
-                    acc[1][1] = mfma_split<NS>(a1, b1, acc[1][1]);
-                    // every chunk of 32 points: move the FP32 sums into FP64
+                    // every chunk of 32 points: its FP32 sums move into FP64
+                    const f4 zero{0.f, 0.f, 0.f, 0.f};
+                    const f4 x[2][2] = {{mfma_split<NS>(a0, b0, zero), mfma_split<NS>(a0, b1, zero)},
+                                        {mfma_split<NS>(a1, b0, zero), mfma_split<NS>(a1, b1, zero)}};
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
 #pragma unroll
                         for (int j = 0; j < 2; ++j)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                acc64[i][j][r] += (double)acc[i][j][r];
-                                acc[i][j][r] = 0.f;
-                            }
+                            for (int r = 0; r < 4; ++r) acc64[i][j][r] += (double)x[i][j][r];
                 }
-                if (c + 1 < n_chunks) stash(c + 1, buf ^ 1);
+                if (c + 1 < n_chunks) stash(buf ^ 1);
                 __syncthreads();
             }
         };
-        const bool diag = it.ti == it.tj;
+        const bool diag = ti == tj;
         if (diag && wr > wc) {  // the strictly lower quarter of a diagonal tile pair only stages data
             k_loop(std::false_type{});
             continue;
@@ -1700,7 +1690,7 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
                 for (int r = 0; r < 4; ++r) {
                     const int row = wr * 32 + ib * 16 + lk * 4 + r, col = wc * 32 + jb * 16 + lr;
                     const int ci = I0 + row, cj = J0 + col;
-                    if (ci < u.m && cj < u.m && (!diag || row <= col))
+                    if (ci < m && cj < m && (!diag || row <= col))
                         gadd(H + (int64_t)gI[ib][r] * ldh + gJ[jb], acc64[ib][jb][r]);
                 }
     }
@@ -1709,7 +1699,7 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
 // Density, split-BF16 MFMA: per item one 64-wide column tile J of a unit, K = 32 functions per
 // chunk; sixteen waves, wave w takes column block w % 4 and row blocks w / 4 + 4 q.  A (points x
 // functions) in LDS as [part][point][function], B (functions x columns) as [part][column][function],
-// rows of 64 bytes with their 16-byte slots permuted by row (no bank conflicts), two buffers.  The
+// two buffers.  The
 // FP32 sums move into FP64 after every 64-function tile; the row dot and the sums over tiles and
 // units are FP64.
 // @NBF@
@@ -1724,7 +1714,6 @@ __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     const int cb = wave & 3, rh = wave >> 2;
     const int lr = lane & 15, lk = lane >> 4;
-    auto slot = [](int row, int g) { return 8 * (g ^ ((row >> 1) & 3)); };  // first of the functions 8 g .. 8 g + 7
     for (int64_t v_ = blockIdx.x; v_ < xcd_span(total, lg); v_ += gridDim.x) {
         const int64_t b = xcd_item(v_, lg);
         if (b >= total) continue;
@@ -1772,31 +1761,26 @@ __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__
 #pragma unroll
             for (int q = 0; q < 2; ++q) gcur[q] = gnxt[q];
             if (stages_a) {
-                bf8 part[NS];
+                u4 part[NS];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    __bf16 x[NS];
-                    split_bf16<NS>(ar < np ? pa[k >> 2][k & 3] : 0.f, x);
+                for (int k = 0; k < 8; k += 2) {
+                    uint32_t x[NS];
+                    split_bf16<NS>(ar < np ? pa[k >> 2][k & 3] : 0.f, ar < np ? pa[k >> 2][(k & 3) + 1] : 0.f, x);
 #pragma unroll
-                    for (int t = 0; t < NS; ++t) part[t][k] = x[t];
+                    for (int t = 0; t < NS; ++t) part[t][k / 2] = x[t];
                 }
 #pragma unroll
-                for (int t = 0; t < NS; ++t) *reinterpret_cast<bf8*>(&As[buf][t][ar][slot(ar, ag)]) = part[t];
+                for (int t = 0; t < NS; ++t) *reinterpret_cast<u4*>(&As[buf][t][ar][bf16_slot(ar, ag)]) = part[t];
             }
-            typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-            bf2 part[NS];
+            uint32_t part[NS];
             const bool diag = c / CPT == tj;
+            float d[2];
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const bool ok = BK * c + 2 * wave + q < m && cjd < m;
-                __bf16 x[NS];
-                split_bf16<NS>(ok ? (float)(diag ? pd[q] : 2.0 * pd[q]) : 0.f, x);
-#pragma unroll
-                for (int t = 0; t < NS; ++t) part[t][q] = x[t];
-            }
+            for (int q = 0; q < 2; ++q) d[q] = BK * c + 2 * wave + q < m && cjd < m ? (float)(diag ? pd[q] : 2.0 * pd[q]) : 0.f;
+            split_bf16<NS>(d[0], d[1], part);
 #pragma unroll
             for (int t = 0; t < NS; ++t)
-                *reinterpret_cast<bf2*>(&Bs[buf][t][lane][slot(lane, wave >> 2) + 2 * (wave & 3)]) = part[t];
+                *reinterpret_cast<uint32_t*>(&Bs[buf][t][lane][bf16_slot(lane, wave >> 2) + 2 * (wave & 3)]) = part[t];
         };
 
         f4 acc[RB];
@@ -1815,14 +1799,14 @@ __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__
             if (c + 1 < n_chunks) fetch(c + 1);
             bf8 bv[NS];
 #pragma unroll
-            for (int t = 0; t < NS; ++t) bv[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][cb * 16 + lr][slot(lr, lk)]);
+            for (int t = 0; t < NS; ++t) bv[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][cb * 16 + lr][bf16_slot(lr, lk)]);
 #pragma unroll
             for (int q = 0; q < RB; ++q)
                 if (RS * q + rh < P) {
                     bf8 av[NS];
 #pragma unroll
                     for (int t = 0; t < NS; ++t)
-                        av[t] = *reinterpret_cast<const bf8*>(&As[buf][t][(RS * q + rh) * 16 + lr][slot(lr, lk)]);
+                        av[t] = *reinterpret_cast<const bf8*>(&As[buf][t][(RS * q + rh) * 16 + lr][bf16_slot(lr, lk)]);
                     acc[q] = mfma_split<NS>(av, bv, acc[q]);
                 }
             if (c % CPT == CPT - 1) {  // end of a 64-function tile
