@@ -1565,13 +1565,16 @@ constexpr int BK = 32;  // K per bf16 MFMA step
 // first of the elements 8 g .. 8 g + 7 of a row
 __device__ inline int bf16_slot(int row, int g) { return 8 * (g ^ ((row >> 1) & 3)); }
 
-// Hamiltonian, split-BF16 MFMA (v_mfma_f32_16x16x32_bf16): per item one 64x64 tile pair of a
-// unit, K = 32 points per chunk, four waves of 32x32.  LDS holds [buffer][part][column][point]
-// so that every lane reads its 8 consecutive points as one 16-byte vector; the next chunk's
-// FP32 basis values and FP64 w v are prefetched into registers while the MFMAs of the current
-// one run and are split into bf16 parts at the stash.  The FP32 tile sums move into FP64
-// after every chunk; FP64 atomics into the upper triangle of H.  At least three waves per SIMD
-// (the two-part form then fits three workgroups per CU: 9 % faster than two).
+// Hamiltonian, split-BF16 MFMA (v_mfma_f32_16x16x32_bf16): per item one 64x64 tile pair of a unit or
+// a cluster, in chunks of 32 points of one unit, four waves of 32x32.  LDS holds
+// [buffer][part][column][point] so that every lane reads its 8 consecutive points as one 16-byte
+// vector; the next chunk's FP32 basis values and w v are prefetched while the MFMAs of the current
+// one run and are split into bf16 parts at the stash.  The FP32 sums move into FP64 after every
+// chunk, so that a cluster's sums are those of its units and reach H by a half to a quarter of the
+// atomics; chunks that one of the tiles does not reach are left out.  FP64 atomics into the upper
+// triangle of H.  The splitting binds it (19 instructions beside every MFMA), then the atomics: three
+// workgroups per CU, two values per conversion, scalar row addresses and w v; 64-atom block, three
+// parts, units alone 3.03 ms before and 2.81 after, over clusters 2.10 (MFMA busy 15 % at 2.81).
 template <int NS>
 __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
@@ -1588,12 +1591,35 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
         const DevSeg& sg = segs[s];
         const HItem it = static_cast<const HItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
         const DevUnit& u = sg.item_units[uni(it.unit)];
-        const int np = uni(u.n_points), ld = uni(u.ld), m = uni(u.m);
+        const int ld = uni(u.ld), m = uni(u.m), n_sub = uni(u.sub_count);
+        const DevUnit* sub = sg.units + uni(u.sub_begin);
+        const int64_t row_begin = uni(u.row_begin);
         gp<const float> __restrict__ phi = gptr(static_cast<const float*>(sg.phi) + uni(u.out_offset));
-        gp<const double> __restrict__ wv = gptr(sg.wv + uni(u.point_begin));
-        if (np <= 0) continue;
+        gp<const double> __restrict__ wv = gptr(sg.wv + row_begin);
         const int ti = uni((int)it.ti), tj = uni((int)it.tj), I0 = ti * TILE, J0 = tj * TILE;
-        const int n_chunks = (np + BK - 1) / BK;
+        const uint64_t* mI = sg.unit_mask + uni(u.mask_begin) + 4 * ti;
+        const uint64_t* mJ = sg.unit_mask + uni(u.mask_begin) + 4 * tj;
+        uint64_t any_i = 0, any_j = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            any_i |= (uint64_t)uni((int64_t)mI[q]);
+            any_j |= (uint64_t)uni((int64_t)mJ[q]);
+        }
+        const uint64_t todo = any_i & any_j;  // 16-row chunks both tiles reach
+        if (todo == 0) continue;
+        // the next chunk: rows p .. p + 31 of the np rows that unit k has from row r0 on
+        int k, r0, np, p;
+        auto unit_at = [&]() {
+            r0 = (int)(uni(sub[k].row_begin) - row_begin);
+            np = uni(sub[k].n_points);
+            p = 0;
+        };
+        auto seek = [&]() {  // to one that both tiles reach, or k = n_sub
+            while (k < n_sub && (p >= np || !((todo >> ((r0 + p) >> 4)) & 3))) {
+                if (p < np) p += BK;
+                else if (++k < n_sub) unit_at();
+            }
+        };
 
         // this thread's column of both operands and its NQ = 8 consecutive points of a chunk, so
         // that every part is stashed as one 16-byte run of a column (loads: a wave reads 64
@@ -1602,16 +1628,18 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
         const int col = lane, p0 = NQ * wave;  // the points are the wave's: scalar addresses and w v
         float ra[NQ], rb[NQ];
         double rw[NQ];
-        // points past the last: w v = 0 makes their products zero
-        auto fetch = [&](int c) {
+        // points past the unit's last: w v = 0 makes their products zero
+        auto fetch = [&]() {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
-                const int p = c * BK + p0 + q, pc = min(p, np - 1);
-                gp<const float> rowp = phi + (int64_t)pc * ld;
+                const int pc = min(p + p0 + q, np - 1);
+                gp<const float> rowp = phi + (int64_t)(r0 + pc) * ld;
                 ra[q] = rowp[I0 + col];
                 rb[q] = rowp[J0 + col];
-                rw[q] = p < np ? wv[pc] : 0.0;
+                rw[q] = p + p0 + q < np ? wv[r0 + pc] : 0.0;
             }
+            p += BK;
+            seek();
         };
         auto stash = [&](int buf) {
             u4 pa[NS], pb[NS];
@@ -1643,21 +1671,25 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
 
         d4 acc64[2][2] = {};
         auto k_loop = [&](auto with_mfma) {
-            fetch(0);
+            k = 0;
+            unit_at();
+            seek();
+            if (k >= n_sub) return;
+            fetch();
             stash(0);
             __syncthreads();
-            for (int c = 0; c < n_chunks; ++c) {
-                const int buf = c & 1;
-                if (c + 1 < n_chunks) fetch(c + 1);
+            for (int buf = 0;; buf ^= 1) {
+                const bool more = k < n_sub;
+                if (more) fetch();
                 if (decltype(with_mfma)::value) {
                     bf8 a0[NS], a1[NS], b0[NS], b1[NS];
 #pragma unroll
                     for (int t = 0; t < NS; ++t) {
-                        const int k = bf16_slot(lr, lk);
-                        a0[t] = *reinterpret_cast<const bf8*>(&As[buf][t][wr * 32 + lr][k]);
-                        a1[t] = *reinterpret_cast<const bf8*>(&As[buf][t][wr * 32 + 16 + lr][k]);
-                        b0[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][wc * 32 + lr][k]);
-                        b1[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][wc * 32 + 16 + lr][k]);
+                        const int sl = bf16_slot(lr, lk);
+                        a0[t] = *reinterpret_cast<const bf8*>(&As[buf][t][wr * 32 + lr][sl]);
+                        a1[t] = *reinterpret_cast<const bf8*>(&As[buf][t][wr * 32 + 16 + lr][sl]);
+                        b0[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][wc * 32 + lr][sl]);
+                        b1[t] = *reinterpret_cast<const bf8*>(&Bs[buf][t][wc * 32 + 16 + lr][sl]);
                     }
                     // every chunk of 32 points: its FP32 sums move into FP64
                     const f4 zero{0.f, 0.f, 0.f, 0.f};
@@ -1670,8 +1702,9 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
 #pragma unroll
                             for (int r = 0; r < 4; ++r) acc64[i][j][r] += (double)x[i][j][r];
                 }
-                if (c + 1 < n_chunks) stash(buf ^ 1);
+                if (more) stash(buf ^ 1);
                 __syncthreads();
+                if (!more) break;
             }
         };
         const bool diag = ti == tj;
@@ -1702,7 +1735,9 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
 // two buffers.  The
 // FP32 sums move into FP64 after every 64-function tile; the row dot and the sums over tiles and
 // units are FP64.
-// @NBF@
+// Sixteen waves share one stage of A, split once for the 64 columns; parts are stored by 16 bytes
+// (they were stored by 2, to one buffer of padded rows: 64-atom block, three parts, 4.4 to 2.35 ms,
+// MFMA busy 18 %, VALU 39 %).
 template <int NS>
 __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {

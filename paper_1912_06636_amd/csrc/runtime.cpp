@@ -302,7 +302,7 @@ struct nao_system_s {
     DevArray d_sys, d_px, d_py, d_pz, d_pw, d_perm, d_atoms, d_species, d_shell_ptr, d_shell_l, d_shell_rad,
         d_radial_par, d_spline, d_fn_ptr, d_fn_code;
     DevArray d_units, d_unit_atoms, d_unit_cols, d_unit_fn, d_unit_mask, d_h_items, d_hw_items, d_n_items, d_nt_items;
-    // Hamiltonian clusters (FP64 and FP32 with 64-wide tiles; cl_blocks is empty when there are none)
+    // Hamiltonian clusters (64-wide tiles; cl_blocks is empty when there are none)
     std::vector<Block> cl_blocks;
     int64_t n_cl_subs = 0, n_cl_rows = 0, n_cl_atoms = 0, n_cl_fn = 0, n_cl_mask = 0;
     DevArray d_cl_units, d_cl_subs, d_cl_atoms, d_cl_cols, d_cl_fn, d_cl_mask, d_cl_items;
@@ -389,7 +389,7 @@ void drop_clusters(nao_system_s* s)
     s->n_cl_subs = s->n_cl_rows = 0;
 }
 
-// Clusters of the execution units for the Hamiltonian (FP64 and FP32, 64-wide tiles): a tile pair
+// Clusters of the execution units for the Hamiltonian (64-wide tiles): a tile pair
 // of a cluster adds its 4,096 sums to H once for two to four units, whose sums would otherwise
 // each cost as many atomics (they bound the FP32 kernel: a 100-atom slab's 14.4 ms fell to 7.5
 // without them).  Columns of the same cluster differ in how many points reach them, which the
@@ -500,7 +500,7 @@ nao_status build_clusters(nao_system_s* s, const std::vector<Unit>& units, const
 int use_clusters(const nao_system_s* s, nao_precision prec)
 {
     if (s->cl_blocks.empty()) return 0;
-    return prec == NAO_FP64 ? 1 : prec == NAO_FP32 ? 2 : 0;
+    return prec == NAO_FP64 ? 1 : 2;
 }
 
 // Build execution groups, split them into scratch-sized blocks and upload units and items.
@@ -626,8 +626,8 @@ nao_status build_groups(nao_system_s* s)
 // Hamiltonian segments use the 128-wide items when wide is set (FP64 / FP32 on systems with
 // h_tile 128), else the 64-wide ones.
 // clusters: over the system's clusters, 1 with columns by reach (FP64), 2 with ascending columns: a
-// pair's w v goes to the column that comes first and FP32 rounds the product, so FP32 keeps the order
-// that the units have.
+// pair's w v goes to the column that comes first and FP32 rounds the product, so FP32 and split-BF16
+// keep the order that the units have.
 DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = false, int clusters = 0, bool tiles = false)
 {
     DevSeg g{};

@@ -94,3 +94,26 @@ def test_clusters_dropped_when_they_do_not_fit():
         small.synchronize()
         assert rel_max(Hd.cpu().numpy(), H) <= 1e-12
         small.close()
+
+
+# The split-BF16 sums of 32 points are the units' own, and what is above them is FP64: 1e-12.
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["bf16x3", "bf16x6"])
+@pytest.mark.parametrize("n_atoms,n_r,n_ang,max_batch,batcher", [(34, 44, 194, 200, "octree"), (64, 44, 194, 256, "cutplane")])
+def test_clusters_equal_units_bf16(prec, n_atoms, n_r, n_ang, max_batch, batcher):
+    from paper_1912_06636_amd import nao
+    basis, X, w, v = _structure(n_atoms, [(0, 0, 0, 1, 1, 2), (0, 0, 1)], [5.0, 4.0], n_r, n_ang)
+    ctx = nao.Context(0)
+    s = nao.build_batches(ctx, basis, X, w, max_batch, batcher=batcher)
+    H = s.integrate_h(v, precision=prec)
+    s.set_resident_basis(True)
+    e = rel_max(H, s.integrate_h(v, precision=prec))
+    s.set_resident_basis(False)
+    s.set_group_max(0)  # one unit per batch, no clusters, units that end inside a chunk
+    e1 = rel_max(H, s.integrate_h(v, precision=prec))
+    e64 = rel_max(H, s.integrate_h(v))
+    print("clusters against units %.2e, batches %.2e, FP64 %.2e" % (e, e1, e64), flush=True)
+    assert np.array_equal(H, H.T) and e <= 1e-12
+    tol = {"bf16x3": 3e-5, "bf16x6": 1e-6}[prec]
+    assert e1 <= tol and e64 <= tol
+    ctx.close()
