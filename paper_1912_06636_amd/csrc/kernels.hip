@@ -1729,23 +1729,23 @@ __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict
     }
 }
 
-// Density, split-BF16 MFMA: per item one 64-wide column tile J of a unit, K = 32 functions per
-// chunk; sixteen waves, wave w takes column block w % 4 and row blocks w / 4 + 4 q.  A (points x
-// functions) in LDS as [part][point][function], B (functions x columns) as [part][column][function],
-// two buffers.  The
-// FP32 sums move into FP64 after every 64-function tile; the row dot and the sums over tiles and
-// units are FP64.
-// Sixteen waves share one stage of A, split once for the 64 columns; parts are stored by 16 bytes
-// (they were stored by 2, to one buffer of padded rows: 64-atom block, three parts, 4.4 to 2.35 ms,
-// MFMA busy 18 %, VALU 39 %).
+// Density, split-BF16 MFMA: per item (NTile) one 64-wide column tile J of up to 128 rows of a unit,
+// K = 32 functions per chunk; eight waves, wave w takes column block w % 4 and row blocks w / 4 + 2 q.
+// A (points x functions) in LDS as [part][point][function], B (functions x columns) as
+// [part][column][function], two buffers.  The FP32 sums move into FP64 after every 64-function tile;
+// the row dot and the sums over tiles and units are FP64.
+// Bound by the splitting and the wait at the barrier of every chunk (one workgroup of 256 rows: MFMA
+// busy 18 %, VALU 39 %), so that two workgroups of 128 rows share a CU.  64-atom block, three parts:
+// 4.4 ms with parts stored by 2 bytes to one padded buffer, 2.35 by 16 bytes to two with permuted
+// slots, 2.22 with 128 rows.
 template <int NS>
-__global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
+__global__ __launch_bounds__(512, 4) void n_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
-    constexpr int RB = 4, RS = 4;
+    constexpr int RB = 4, RS = 2;
     constexpr int CPT = TILE / BK;  // chunks per tile (2)
-    __shared__ __attribute__((aligned(16))) __bf16 As[2][NS][MAX_UNIT_POINTS][BK];
+    __shared__ __attribute__((aligned(16))) __bf16 As[2][NS][NTILE_ROWS][BK];
     __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NS][TILE][BK];
-    __shared__ double red[4][MAX_UNIT_POINTS];
+    __shared__ double red[4][NTILE_ROWS];
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     const int cb = wave & 3, rh = wave >> 2;
     const int lr = lane & 15, lk = lane >> 4;
@@ -1754,30 +1754,28 @@ __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__
         if (b >= total) continue;
         const int s = find_segment(segs, n_segs, b, [](const DevSeg& g) { return g.item_prefix; });
         const DevSeg& sg = segs[s];
-        const NItem it = static_cast<const NItem*>(sg.items)[sg.item_begin + (b - sg.item_prefix)];
-        const DevUnit& u = sg.item_units[uni(it.unit)];
-        const int tj = uni(it.tj), np = uni(u.n_points), ld = uni(u.ld), m = uni(u.m);
-        if (np <= 0 || m <= 0) continue;
-        const int64_t out_offset = uni(u.out_offset), point_begin = uni(u.point_begin);
+        const NTile* it = static_cast<const NTile*>(sg.items) + (sg.item_begin + (b - sg.item_prefix));
+        const int tj = uni(it->tj), np = uni(it->n_rows), ld = uni(it->ld), m = uni(it->m);
+        const int64_t out_offset = uni(it->out_offset), point_begin = uni(it->point_begin);
         gp<const float> __restrict__ phi = gptr(static_cast<const float*>(sg.phi) + out_offset);
-        gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + uni(u.fn_begin));
+        gp<const int32_t> __restrict__ fn = gptr(sg.unit_fn + uni(it->fn_begin));
         gp<const double> __restrict__ D = gptr(sg.D);
         const int64_t ldd = uni(sg.ld);
         const int P = (np + 15) >> 4;
         const int J0 = tj * TILE, n_chunks = (tj + 1) * CPT;  // chunk c covers functions 32 c .. 32 c + 31
-        // staged by this thread: functions 8 (tid % 4) .. of row tid / 4, and functions 2 wave and
-        // 2 wave + 1 of column tid % 64
+        // staged by this thread: functions 8 (tid % 4) .. of row tid / 4, and functions 4 wave ..
+        // 4 wave + 3 of column tid % 64
         const int ar = tid >> 2, ag = tid & 3;
         const bool stages_a = wave < P;  // wave-uniform: 16 rows per wave
         gp<const float> a_row = phi + (int64_t)min(ar, np - 1) * ld + 8 * ag;
         const int cjd = J0 + lane;
         const int64_t gjd = fn[min(cjd, m - 1)];
         f4 pa[2];
-        double pd[2];
-        int32_t gcur[2], gnxt[2];
+        double pd[4];
+        int32_t gcur[4], gnxt[4];
         auto load_idx = [&](int c, int32_t* g) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) g[q] = uni(fn[min(BK * c + 2 * wave + q, m - 1)]);
+            for (int q = 0; q < 4; ++q) g[q] = uni(fn[min(BK * c + 4 * wave + q, m - 1)]);
         };
         auto fetch = [&](int c) {
             if (stages_a) {
@@ -1786,15 +1784,15 @@ __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__
             }
             const bool diag = c / CPT == tj;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const bool lower = diag && BK * c + 2 * wave + q > cjd;
+            for (int q = 0; q < 4; ++q) {
+                const bool lower = diag && BK * c + 4 * wave + q > cjd;
                 pd[q] = D[lower ? gjd * ldd + gcur[q] : (int64_t)gcur[q] * ldd + gjd];
             }
             load_idx(c + 1, gnxt);
         };
         auto stash = [&](int c, int buf) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) gcur[q] = gnxt[q];
+            for (int q = 0; q < 4; ++q) gcur[q] = gnxt[q];
             if (stages_a) {
                 u4 part[NS];
 #pragma unroll
@@ -1807,15 +1805,22 @@ __global__ __launch_bounds__(1024) void n_kernel_bf16(const DevSeg* __restrict__
 #pragma unroll
                 for (int t = 0; t < NS; ++t) *reinterpret_cast<u4*>(&As[buf][t][ar][bf16_slot(ar, ag)]) = part[t];
             }
-            uint32_t part[NS];
+            typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+            u2 part[NS];
             const bool diag = c / CPT == tj;
-            float d[2];
+            float d[4];
 #pragma unroll
-            for (int q = 0; q < 2; ++q) d[q] = BK * c + 2 * wave + q < m && cjd < m ? (float)(diag ? pd[q] : 2.0 * pd[q]) : 0.f;
-            split_bf16<NS>(d[0], d[1], part);
+            for (int q = 0; q < 4; ++q) d[q] = BK * c + 4 * wave + q < m && cjd < m ? (float)(diag ? pd[q] : 2.0 * pd[q]) : 0.f;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                uint32_t x[NS];
+                split_bf16<NS>(d[2 * q], d[2 * q + 1], x);
+#pragma unroll
+                for (int t = 0; t < NS; ++t) part[t][q] = x[t];
+            }
 #pragma unroll
             for (int t = 0; t < NS; ++t)
-                *reinterpret_cast<uint32_t*>(&Bs[buf][t][lane][bf16_slot(lane, wave >> 2) + 2 * (wave & 3)]) = part[t];
+                *reinterpret_cast<u2*>(&Bs[buf][t][lane][bf16_slot(lane, wave >> 1) + 4 * (wave & 1)]) = part[t];
         };
 
         f4 acc[RB];
@@ -1912,7 +1917,7 @@ hipError_t launch_n(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n_ite
     if (n_items <= 0 || n_segs <= 0) return hipSuccess;
     if (n_items > 0x7ffffff0) return hipErrorInvalidValue;
     const int lg = xcd_run(n_items, NRUN);
-    const dim3 g(grid_for(n_items, lg, max_grid)), b(1024);
+    const dim3 g(grid_for(n_items, lg, max_grid)), b(512);
     switch (mode) {
     case MODE_FP64: hipLaunchKernelGGL((n_tiles<double, NK_DENSITY>), g, dim3(256), 0, st, segs_dev, n_segs, n_items, lg); break;
     case MODE_FP32: hipLaunchKernelGGL((n_tiles<float, NK_DENSITY>), g, dim3(256), 0, st, segs_dev, n_segs, n_items, lg); break;

@@ -894,7 +894,7 @@ nao_status many_build(nao_ctx c, const nao_work* work, int64_t n_work, nao_preci
                 off = 0;
             }
             const bool wide = ham && s->h_tile == 128 && (prec == NAO_FP64 || prec == NAO_FP32);
-            DevSeg g = make_seg(s, b, ham, wide, cl, !ham && (prec == NAO_FP64 || prec == NAO_FP32));
+            DevSeg g = make_seg(s, b, ham, wide, cl, !ham);
             if (ham) {
                 g.wv = m->d_wv.as<double>() + m->wv_off[e];
                 g.H = const_cast<double*>(w.out);
@@ -1776,7 +1776,7 @@ static nao_status run_blocks(nao_system s, bool ham, nao_precision prec, const d
     for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
     const bool ovl = !res && blocks.size() > 1 && overlap_ready(c, need);
     for (size_t k = 0; k < blocks.size(); ++k) {
-        DevSeg g = make_seg(s, blocks[k], ham, wide, cl, !ham && (prec == NAO_FP64 || prec == NAO_FP32));
+        DevSeg g = make_seg(s, blocks[k], ham, wide, cl, !ham);
         if (ovl && (k & 1)) g.phi = c->scratch2;
         if (res) g.phi = static_cast<char*>(s->d_phi_res.p) + s->res_off[k] * (f32 ? sizeof(float) : sizeof(double));
         g.wv = wv;
