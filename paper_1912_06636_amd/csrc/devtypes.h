@@ -67,13 +67,13 @@ struct HItem {
     int16_t tj;
 };
 
-// Work item of the split-BF16 density kernel and the FP32 forces: one column tile of one unit.
+// Work item of the FP32 forces: one column tile of one unit.
 struct NItem {
     int32_t unit;
     int32_t tj;
 };
 
-// Work item of n_tiles: rows of one unit (at most NTILE_ROWS, whole row blocks of 16) and one column
+// Work item of the other density kernels: rows of one unit (at most NTILE_ROWS, whole row blocks of 16) and one column
 // tile.  It carries what the kernel needs of the unit, so that an item starts with one load.
 struct NTile {
     int64_t out_offset;   // of the first row within the block

@@ -1572,7 +1572,7 @@ __device__ inline int bf16_slot(int row, int g) { return 8 * (g ^ ((row >> 1) & 
 // one run and are split into bf16 parts at the stash.  The FP32 sums move into FP64 after every
 // chunk, so that a cluster's sums are those of its units and reach H by a half to a quarter of the
 // atomics; chunks that one of the tiles does not reach are left out.  FP64 atomics into the upper
-// triangle of H.  The splitting binds it (19 instructions beside every MFMA), then the atomics: three
+// triangle of H.  The splitting binds it (10 vector and 6 scalar instructions beside every MFMA), then the atomics: three
 // workgroups per CU, two values per conversion, scalar row addresses and w v; 64-atom block, three
 // parts, units alone 3.03 ms before and 2.81 after, over clusters 2.10 (MFMA busy 15 % at 2.81).
 template <int NS>
