@@ -759,19 +759,36 @@ void many_forget(nao_ctx c, const nao_system_s* sys)
 
 // Replace the context's basis scratch by one of at least `elems` values.  Captured launch plans
 // hold the old buffer's address, so they are dropped first (after the work in flight is done).
+// All systems of the context share the scratch: a refused growth leaves it as it was.
 nao_status grow_scratch(nao_ctx c, size_t elems)
 {
     if (elems <= c->scratch_elems) return NAO_OK;
+    const size_t bytes = elems * sizeof(double), held = c->scratch_elems * sizeof(double);
+    if (c->budget && c->used - held + bytes > c->budget) {
+        set_err(c, "HBM budget exceeded: need " + std::to_string(bytes) + " B of scratch, used " +
+                       std::to_string(c->used - held) + " of " + std::to_string(c->budget));
+        return NAO_ERR_BUDGET;
+    }
     many_forget(c, nullptr);
-    dev_free(c, c->scratch, c->scratch_elems * sizeof(double));
+    dev_free(c, c->scratch, held);
     c->scratch = nullptr;
     c->scratch_elems = 0;
     void* p = nullptr;
-    const nao_status st = dev_alloc(c, elems * sizeof(double), &p);
-    if (st != NAO_OK) return st;
+    const nao_status st = dev_alloc(c, bytes, &p);
+    const size_t got = st == NAO_OK ? elems : held / sizeof(double);
+    if (st != NAO_OK && held && dev_alloc(c, held, &p) != NAO_OK) return st;
     c->scratch = static_cast<double*>(p);
-    c->scratch_elems = elems;
-    return NAO_OK;
+    c->scratch_elems = got;
+    return st;
+}
+
+// The scratch holds the largest of an operation's blocks: every operation asks before it launches,
+// since the scratch has only the size that the last successful growth left.
+static nao_status scratch_for(nao_ctx c, const std::vector<Block>& blocks)
+{
+    size_t need = 0;
+    for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
+    return grow_scratch(c, need);
 }
 
 // Second stream, events and a second basis buffer of `elems` values for the overlapped block
@@ -1774,6 +1791,8 @@ static nao_status run_blocks(nao_system s, bool ham, nao_precision prec, const d
     const std::vector<Block>& blocks = cl ? s->cl_blocks : s->blocks;
     size_t need = 0;
     for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
+    nao_status st = res ? NAO_OK : scratch_for(c, blocks);
+    if (st != NAO_OK) return st;
     const bool ovl = !res && blocks.size() > 1 && overlap_ready(c, need);
     for (size_t k = 0; k < blocks.size(); ++k) {
         DevSeg g = make_seg(s, blocks[k], ham, wide, cl, !ham);
@@ -1790,7 +1809,7 @@ static nao_status run_blocks(nao_system s, bool ham, nao_precision prec, const d
                               c->stream));
     DevSeg* dseg = s->d_segs.as<DevSeg>();
     if (res && evaluate) s->res_kind = -1;  // marked valid only once every block is enqueued
-    nao_status st = block_loop(
+    st = block_loop(
         c, segs.size(), ovl, staged && evaluate ? (f32 ? "basis_f32" : "basis_f64") : nullptr, kname(ham, prec),
         [&](size_t k, hipStream_t q) { return launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->max_fn, s->mean_fn(), f32, q); },
         [&](size_t k) {
@@ -1993,6 +2012,7 @@ static nao_status integrate_h_with_l(nao_system s, const double* v, const double
     nao_status st;
     const int cl = use_clusters(s, prec);
     const std::vector<Block>& blocks = cl ? s->cl_blocks : s->blocks;
+    if ((st = scratch_for(c, blocks)) != NAO_OK) return st;
     if ((st = ensure_gscratch(s, 1, blocks)) != NAO_OK) return st;  // L: one value per basis value
     const bool has_a = a != nullptr && n > 0;
     const double* vd = v;
@@ -2093,6 +2113,7 @@ nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspa
     if ((D_space != NAO_MEM_HOST && D_space != NAO_MEM_DEVICE) || (out_space != NAO_MEM_HOST && out_space != NAO_MEM_DEVICE))
         return (set_err(c, "bad memspace"), NAO_ERR_INVALID_ARG);
     // gradients of one block's basis values: 3 per value
+    if ((st = scratch_for(c, s->blocks)) != NAO_OK) return st;
     if ((st = ensure_gscratch(s, 3, s->blocks)) != NAO_OK) return st;
     const double* Dd = D;
     if (D_space == NAO_MEM_HOST && nb > 0) {
@@ -2160,6 +2181,7 @@ nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, cons
     if (!F || (nb > 0 && (!D || !Q)) || (n > 0 && !v)) return (set_err(c, "NULL D, Q, v or F"), NAO_ERR_INVALID_ARG);
     if ((in_space != NAO_MEM_HOST && in_space != NAO_MEM_DEVICE) || (F_space != NAO_MEM_HOST && F_space != NAO_MEM_DEVICE))
         return (set_err(c, "bad memspace"), NAO_ERR_INVALID_ARG);
+    if ((st = scratch_for(c, s->blocks)) != NAO_OK) return st;
     if ((st = ensure_gscratch(s, 4, s->blocks)) != NAO_OK) return st;  // gradient and lap phi: 4 per basis value
     const double* Dd = D;
     const double* Qd = Q;

@@ -1,0 +1,193 @@
+// CPU check of the host runtime (runtime.cpp) over a HIP runtime whose memory is host memory
+// (fake_hip.h): under every budget that admits a sequence of calls, each launch stays inside live
+// allocations.  The argument names the scenario.  Built with sanitizers by tests/test_runtime_memory.py.
+#include <cmath>
+#include <cstdio>
+#include <functional>
+#include <random>
+#include <thread>
+
+#include "fake_hip.h"
+#include "nao.h"
+
+#define CHECK(cond)                                                                             \
+    do {                                                                                        \
+        if (!(cond)) {                                                                          \
+            std::fprintf(stderr, "CHECK failed at %s:%d: %s\n", __FILE__, __LINE__, #cond);      \
+            std::exit(1);                                                                       \
+        }                                                                                       \
+    } while (0)
+
+namespace {
+
+// Atoms on a line of cubes of 2.2 Angstrom, 14 or 28 functions each, random points around every atom.
+struct Structure {
+    std::vector<double> axyz, rmin, rcut, samples, xyz, w;
+    std::vector<int32_t> spc, shell_ptr{0}, shell_l, shell_rad;
+    nao_basis_desc d{};
+    int64_t nb = 0, np = 0;
+    Structure(int nx, int ny, int nz, double cutoff, int points_per_atom, int max_l, unsigned seed)
+    {
+        std::mt19937_64 rng(seed);
+        std::normal_distribution<double> g(0.0, 0.8);
+        for (int x = 0; x < nx; ++x)
+            for (int y = 0; y < ny; ++y)
+                for (int z = 0; z < nz; ++z) {
+                    const double at[3] = {2.2 * x, 2.2 * y, 2.2 * z};
+                    for (double q : at) axyz.push_back(q);
+                    spc.push_back(0);
+                    for (int k = 0; k < points_per_atom; ++k)
+                        for (double q : at) xyz.push_back(q + g(rng));
+                }
+        const int nk = 8;
+        int nf = 0;
+        for (int l : {0, 0, 1, 1, 2, 3})
+            if (l <= max_l) {
+                shell_l.push_back(l);
+                shell_rad.push_back((int32_t)rmin.size());
+                rmin.push_back(1e-3);
+                rcut.push_back(cutoff);
+                for (int k = 0; k < nk; ++k) samples.push_back(k + 1 < nk ? 1.0 : 0.0);
+                nf += 2 * l + 1;
+            }
+        shell_ptr.push_back((int32_t)shell_l.size());
+        np = (int64_t)xyz.size() / 3;
+        w.assign(np, 0.5);
+        nb = nf * (int64_t)spc.size();
+        d.n_atoms = (int64_t)spc.size();
+        d.atom_xyz = axyz.data();
+        d.atom_species = spc.data();
+        d.n_species = 1;
+        d.species_shell_ptr = shell_ptr.data();
+        d.shell_l = shell_l.data();
+        d.shell_radial = shell_rad.data();
+        d.n_radial = (int32_t)rmin.size();
+        d.n_knots = nk;
+        d.radial_rmin = rmin.data();
+        d.radial_rcut = rcut.data();
+        d.radial_samples = samples.data();
+    }
+};
+
+template <typename T> T* device(int64_t n)
+{
+    void* p = nullptr;
+    CHECK(hipMalloc(&p, sizeof(T) * n) == hipSuccess);
+    return static_cast<T*>(p);
+}
+
+// The caller's device buffers of a structure (not part of any context's budget).
+struct Buffers {
+    double *D, *Q, *H, *n, *gn, *v, *a, *F;
+    explicit Buffers(const Structure& s)
+        : D(device<double>(s.nb * s.nb)), Q(device<double>(s.nb * s.nb)), H(device<double>(s.nb * s.nb)), n(device<double>(s.np)),
+          gn(device<double>(3 * s.np)), v(device<double>(s.np)), a(device<double>(3 * s.np)), F(device<double>(3 * s.d.n_atoms))
+    {
+    }
+    ~Buffers()
+    {
+        for (double* p : {D, Q, H, n, gn, v, a, F}) CHECK(hipFree(p) == hipSuccess);
+    }
+};
+
+bool no_faults(const char* where)
+{
+    for (const auto& f : fake::faults) std::fprintf(stderr, "%s: %s\n", where, f.c_str());
+    return fake::faults.empty();
+}
+
+nao_status build(nao_ctx c, const Structure& s, nao_system* out) { return nao_build_batches(c, &s.d, s.np, s.xyz.data(), s.w.data(), 200, out); }
+
+// true when the call was accepted; a refusal for want of memory is the only other outcome
+bool took(nao_status st)
+{
+    if (st != NAO_OK && st != NAO_ERR_BUDGET && st != NAO_ERR_OUT_OF_MEMORY) std::fprintf(stderr, "status %d\n", (int)st);
+    CHECK(st == NAO_OK || st == NAO_ERR_BUDGET || st == NAO_ERR_OUT_OF_MEMORY);
+    return st == NAO_OK;
+}
+
+// Every operation with device arrays; the number that was accepted.
+int operations(nao_system s, const Buffers& b, nao_precision p)
+{
+    int k = 0;
+    k += took(nao_update_density(s, b.D, NAO_MEM_DEVICE, p, b.n, NAO_MEM_DEVICE, nullptr));
+    k += took(nao_integrate_h(s, b.v, NAO_MEM_DEVICE, p, b.H, NAO_MEM_DEVICE));
+    if (p <= NAO_FP32) {
+        k += took(nao_update_density_gradient(s, b.D, NAO_MEM_DEVICE, p, b.n, b.gn, NAO_MEM_DEVICE));
+        k += took(nao_integrate_h_gga(s, b.v, b.a, NAO_MEM_DEVICE, p, b.H, NAO_MEM_DEVICE));
+        k += took(nao_integrate_h_ks(s, b.v, b.a, NAO_MEM_DEVICE, p, b.H, NAO_MEM_DEVICE));
+        k += took(nao_pulay_forces(s, b.D, b.Q, b.v, NAO_MEM_DEVICE, p, b.F, NAO_MEM_DEVICE));
+    }
+    return k;
+}
+
+// `sequence` runs on a context of the given budget and returns how many of its calls were accepted.
+// Over budgets from `lo` (nothing fits) to beyond what it takes at most: no launch out of range.
+struct Sweep {
+    std::vector<size_t> budget;
+    std::vector<int> accepted, clusters;
+};
+Sweep sweep(const std::function<int(nao_ctx)>& sequence, int steps)
+{
+    auto once = [&](size_t budget, size_t* used, int* clusters) {
+        nao_ctx c = nullptr;
+        CHECK(nao_ctx_create(0, nullptr, budget, &c) == NAO_OK);
+        fake::cluster_launches = 0;
+        const int k = sequence(c);
+        if (clusters) *clusters = fake::cluster_launches;
+        if (used) CHECK(nao_ctx_memory(c, used, nullptr) == NAO_OK);
+        nao_ctx_destroy(c);
+        return k;
+    };
+    size_t most = 0;
+    Sweep r;
+    (void)once(0, &most, nullptr);
+    CHECK(no_faults("without a budget"));
+    most += most / 4;
+    for (int k = 0; k <= steps; ++k) {
+        const size_t b = most / 8 + (most - most / 8) * k / steps;
+        int clusters = 0;
+        r.accepted.push_back(once(b, nullptr, &clusters));
+        r.budget.push_back(b);
+        r.clusters.push_back(clusters);
+        if (!no_faults("under a budget")) {
+            std::fprintf(stderr, "budget %zu of %zu, %d calls accepted\n", b, most, r.accepted.back());
+            std::exit(1);
+        }
+    }
+    return r;
+}
+
+// An earlier system of the context needs more scratch than a later one, whose clusters need still
+// more: a refused growth must leave the scratch that the earlier one has.
+void scratch()
+{
+    const Structure A(9, 5, 3, 5.0, 75, 3, 1), B(8, 5, 3, 5.0, 75, 3, 2);
+    const Buffers a(A), b(B);
+    const Sweep r = sweep(
+        [&](nao_ctx c) {
+            nao_system sa = nullptr, sb = nullptr;
+            int k = 0;
+            if (!took(build(c, A, &sa))) return 0;
+            if (took(build(c, B, &sb))) k += 1 + operations(sb, b, NAO_FP64);
+            k += operations(sa, a, NAO_FP64) + operations(sa, a, NAO_FP32);
+            if (sb) k += operations(sb, b, NAO_BF16X6);
+            if (sb) nao_system_destroy(sb);
+            nao_system_destroy(sa);
+            return k;
+        },
+        60);
+    CHECK(r.clusters.back() > 0);
+}
+
+}  // namespace
+
+int main(int argc, char** argv)
+{
+    setenv("NAO_SCRATCH_MB", "512", 1);
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "scratch") scratch();
+    else return 2;
+    std::printf("%s: all ok\n", what.c_str());
+    return 0;
+}
