@@ -196,6 +196,19 @@ nao_status ensure(nao_ctx c, DevArray& a, size_t bytes)
     return s;
 }
 
+// ensure for an array that is in use already: a refused growth leaves it as it was.
+nao_status regrow(nao_ctx c, DevArray& a, size_t bytes)
+{
+    if (a.bytes >= bytes && a.p) return NAO_OK;
+    DevArray b;
+    const nao_status s = dev_alloc(c, bytes, &b.p);
+    if (s != NAO_OK) return s;
+    b.bytes = bytes;
+    dev_free(c, a.p, a.bytes);
+    a = b;
+    return NAO_OK;
+}
+
 // Launch-plan buffers come from a per-context pool: hipMalloc is slow and hipFree may wait
 // for the whole device, which would stall the work other streams have in flight.
 nao_status pool_take(nao_ctx c, DevArray& a, size_t bytes)
@@ -486,8 +499,8 @@ nao_status build_clusters(nao_system_s* s, const std::vector<Unit>& units, const
     size_t need = 0;
     for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
     if ((st = grow_scratch(c, need)) != NAO_OK) return st;
-    if ((st = ensure(c, s->d_wv, std::max(s->n_points, row) * sizeof(double))) != NAO_OK) return st;
-    if ((st = ensure(c, s->d_segs, std::max(s->blocks.size(), blocks.size()) * sizeof(DevSeg))) != NAO_OK) return st;
+    if ((st = regrow(c, s->d_wv, std::max(s->n_points, row) * sizeof(double))) != NAO_OK) return st;
+    if ((st = regrow(c, s->d_segs, std::max(s->blocks.size(), blocks.size()) * sizeof(DevSeg))) != NAO_OK) return st;
     HIP_TRY(c, hipStreamSynchronize(c->stream));  // host vectors above go out of scope
     s->cl_blocks = std::move(blocks);
     s->n_cl_subs = (int64_t)ds.size();

@@ -180,6 +180,44 @@ void scratch()
     CHECK(r.clusters.back() > 0);
 }
 
+// The last allocations of a build are the ones that the clusters want larger (w v, the segment
+// table): budgets and device limits a little below what the build takes.
+void arrays()
+{
+    const Structure A(8, 5, 3, 5.0, 75, 3, 2);
+    const Buffers a(A);
+    nao_ctx c = nullptr;
+    nao_system s = nullptr;
+    CHECK(nao_ctx_create(0, nullptr, 0, &c) == NAO_OK);
+    const size_t before = fake::device_used;
+    CHECK(build(c, A, &s) == NAO_OK);
+    size_t used = 0;
+    CHECK(nao_ctx_memory(c, &used, nullptr) == NAO_OK);
+    const size_t device = fake::device_used - before;
+    nao_system_destroy(s);
+    nao_ctx_destroy(c);
+    int built = 0, refused = 0;
+    for (int k = 0; k <= 240; ++k) {
+        const size_t less = (size_t)(k / 2) * 1024;
+        CHECK(nao_ctx_create(0, nullptr, k & 1 ? used - less : 0, &c) == NAO_OK);
+        fake::device_limit = k & 1 ? 0 : fake::device_used + device - less;
+        s = nullptr;
+        if (took(build(c, A, &s))) {
+            ++built;
+            operations(s, a, NAO_FP64);
+            operations(s, a, NAO_BF16X3);
+            nao_system_destroy(s);
+        } else {
+            ++refused;
+        }
+        fake::device_limit = 0;
+        nao_ctx_destroy(c);
+        CHECK(no_faults(k & 1 ? "under a budget" : "under a device limit"));
+    }
+    CHECK(built > 0);
+    std::printf("%d builds, %d refused\n", built, refused);
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -187,6 +225,7 @@ int main(int argc, char** argv)
     setenv("NAO_SCRATCH_MB", "512", 1);
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "scratch") scratch();
+    else if (what == "arrays") arrays();
     else return 2;
     std::printf("%s: all ok\n", what.c_str());
     return 0;
