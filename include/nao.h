@@ -196,7 +196,8 @@ nao_status nao_build_batches_ex(nao_ctx ctx, const nao_basis_desc* basis, int64_
                                 nao_batcher batcher, nao_system* out);
 /* Change the execution-group size (in points, 16..256; default 256) of a system; 0 runs
  * every batch as its own unit (no packing).  Results change only by floating-point
- * summation order. */
+ * summation order.  A size whose groups do not fit leaves the groups as they were (so does a
+ * refused nao_system_set_h_tile). */
 nao_status nao_system_set_group_max(nao_system sys, int32_t group_max);
 /* Keep the basis values of every block resident in device memory across operations
  * (enable = 1): nao_integrate_h and nao_update_density then evaluate them once per value type

@@ -298,6 +298,7 @@ struct nao_system_s {
     int32_t max_batch = 0;
     int32_t batcher = NAO_BATCH_OCTREE;
     int32_t group_max = MAX_UNIT_POINTS;
+    bool lost = false;      // no groups (see regroup)
     int32_t h_tile = TILE;  // width of the Hamiltonian kernel's tiles (64 or 128)
     std::vector<int64_t> perm, batch_ptr, atom_ptr;
     std::vector<int32_t> atoms;
@@ -633,7 +634,46 @@ nao_status build_groups(nao_system_s* s)
         if (st != NAO_ERR_BUDGET && st != NAO_ERR_OUT_OF_MEMORY) return st;
         if ((st = grow_scratch(c, need)) != NAO_OK) return st;
     }
-    return resident_layout(s);
+    return NAO_OK;
+}
+
+// Other groups or tiles of a system.  When they are refused, the groups that it had come back; should
+// even those no longer fit, the system is lost and its operations say so.
+nao_status regroup(nao_system_s* s, int32_t group_max, int32_t h_tile)
+{
+    const int32_t g0 = s->group_max, t0 = s->h_tile;
+    auto build = [&](int32_t g, int32_t t) {
+        s->group_max = g;
+        s->h_tile = t;
+        try {
+            return build_groups(s);
+        } catch (...) {
+            set_err(s->ctx, "internal error in the execution groups");
+            return NAO_ERR_INTERNAL;
+        }
+    };
+    const nao_status st = build(group_max, h_tile);
+    if (st == NAO_OK) {
+        s->lost = false;
+        return resident_layout(s);
+    }
+    std::string why;
+    {
+        std::lock_guard<std::mutex> lk(s->ctx->err_mu);
+        why = s->ctx->err;
+    }
+    s->lost = build(g0, t0) != NAO_OK;
+    const nao_status back = s->lost ? NAO_OK : resident_layout(s);
+    (void)back;  // refused: the resident mode is off
+    set_err(s->ctx, why);
+    return st;
+}
+
+// The operations' check of a system whose groups were lost (see regroup).
+nao_status check_groups(nao_system_s* s)
+{
+    if (!s->lost) return NAO_OK;
+    return (set_err(s->ctx, "the system has no execution groups since a change of groups that did not fit"), NAO_ERR_INTERNAL);
 }
 
 // Hamiltonian segments use the 128-wide items when wide is set (FP64 / FP32 on systems with
@@ -1600,13 +1640,7 @@ nao_status nao_system_set_group_max(nao_system s, int32_t group_max)
         return (set_err(s->ctx, "group_max must be 0 or in [16, 256]"), NAO_ERR_INVALID_ARG);
     HIP_TRY(s->ctx, hipStreamSynchronize(s->ctx->stream));
     many_forget(s->ctx, s);
-    s->group_max = group_max;
-    try {
-        return build_groups(s);
-    } catch (...) {
-        set_err(s->ctx, "internal error in nao_system_set_group_max");
-        return NAO_ERR_INTERNAL;
-    }
+    return regroup(s, group_max, s->h_tile);
 }
 
 nao_status nao_system_set_resident_basis(nao_system s, int enable)
@@ -1636,16 +1670,10 @@ nao_status nao_system_set_h_tile(nao_system s, int32_t h_tile)
     nao_status st = check_ctx(s->ctx);
     if (st != NAO_OK) return st;
     if (h_tile != 64 && h_tile != 128) return (set_err(s->ctx, "h_tile must be 64 or 128"), NAO_ERR_INVALID_ARG);
-    if (h_tile == s->h_tile) return NAO_OK;
+    if (h_tile == s->h_tile && !s->lost) return NAO_OK;
     HIP_TRY(s->ctx, hipStreamSynchronize(s->ctx->stream));
     many_forget(s->ctx, s);
-    s->h_tile = h_tile;
-    try {
-        return build_groups(s);
-    } catch (...) {
-        set_err(s->ctx, "internal error in nao_system_set_h_tile");
-        return NAO_ERR_INTERNAL;
-    }
+    return regroup(s, s->group_max, h_tile);
 }
 
 nao_status nao_system_info(nao_system s, int64_t* n_basis, int64_t* n_batches, int64_t* n_list, size_t* dev_bytes)
@@ -1841,6 +1869,7 @@ nao_status nao_integrate_h(nao_system s, const double* v, nao_memspace v_space, 
     nao_ctx c = s->ctx;
     nao_status st = check_ctx(c);
     if (st != NAO_OK) return st;
+    if ((st = check_groups(s)) != NAO_OK) return st;
     if ((st = check_prec(c, prec)) != NAO_OK) return st;
     if (!H || (s->n_points > 0 && !v)) return (set_err(c, "NULL v or H"), NAO_ERR_INVALID_ARG);
     if ((v_space != NAO_MEM_HOST && v_space != NAO_MEM_DEVICE) || (H_space != NAO_MEM_HOST && H_space != NAO_MEM_DEVICE))
@@ -1878,6 +1907,7 @@ nao_status nao_integrate_h_noalloc(nao_system s, const double* v, nao_precision 
     nao_ctx c = s->ctx;
     nao_status st = check_ctx(c);
     if (st != NAO_OK) return st;
+    if ((st = check_groups(s)) != NAO_OK) return st;
     if ((st = check_prec(c, prec)) != NAO_OK) return st;
     const int64_t n = s->n_points, nb = s->basis.n_basis;
     if (!H || (n > 0 && !v)) return (set_err(c, "NULL v or H"), NAO_ERR_INVALID_ARG);
@@ -1954,6 +1984,7 @@ nao_status nao_update_density(nao_system s, const double* D, nao_memspace D_spac
     nao_ctx c = s->ctx;
     nao_status st = check_ctx(c);
     if (st != NAO_OK) return st;
+    if ((st = check_groups(s)) != NAO_OK) return st;
     if ((st = check_prec(c, prec)) != NAO_OK) return st;
     const int64_t n = s->n_points, nb = s->basis.n_basis;
     if ((nb > 0 && !D) || (n > 0 && !nout)) return (set_err(c, "NULL D or n"), NAO_ERR_INVALID_ARG);
@@ -2095,6 +2126,7 @@ nao_status nao_integrate_h_gga(nao_system s, const double* v, const double* a, n
     nao_ctx c = s->ctx;
     nao_status st = check_ctx(c);
     if (st != NAO_OK) return st;
+    if ((st = check_groups(s)) != NAO_OK) return st;
     if (prec != NAO_FP64 && prec != NAO_FP32)
         return (set_err(c, "the Hamiltonian with a vector field runs in FP64 or FP32"), NAO_ERR_INVALID_ARG);
     return integrate_h_with_l(s, v, a, in_space, prec, H, H_space, EXTRA_GGA_L);
@@ -2107,6 +2139,7 @@ nao_status nao_integrate_h_ks(nao_system s, const double* v, const double* a, na
     nao_ctx c = s->ctx;
     nao_status st = check_ctx(c);
     if (st != NAO_OK) return st;
+    if ((st = check_groups(s)) != NAO_OK) return st;
     if (prec != NAO_FP64 && prec != NAO_FP32)
         return (set_err(c, "the Kohn-Sham Hamiltonian runs in FP64 or FP32"), NAO_ERR_INVALID_ARG);
     return integrate_h_with_l(s, v, a, in_space, prec, H, H_space, EXTRA_KS_L);
@@ -2119,6 +2152,7 @@ nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspa
     nao_ctx c = s->ctx;
     nao_status st = check_ctx(c);
     if (st != NAO_OK) return st;
+    if ((st = check_groups(s)) != NAO_OK) return st;
     if (prec != NAO_FP64 && prec != NAO_FP32)
         return (set_err(c, "the density gradient runs in FP64 or FP32"), NAO_ERR_INVALID_ARG);
     const int64_t n = s->n_points, nb = s->basis.n_basis;
@@ -2188,6 +2222,7 @@ nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, cons
     nao_ctx c = s->ctx;
     nao_status st = check_ctx(c);
     if (st != NAO_OK) return st;
+    if ((st = check_groups(s)) != NAO_OK) return st;
     if (prec != NAO_FP64 && prec != NAO_FP32)
         return (set_err(c, "the forces run in FP64 or FP32"), NAO_ERR_INVALID_ARG);
     const int64_t n = s->n_points, nb = s->basis.n_basis, na = s->basis.n_atoms;
@@ -2280,6 +2315,7 @@ nao_status nao_run_many(nao_ctx c, const nao_work* work, int64_t n_work, nao_pre
             return (set_err(c, "work entry with a system on another device"), NAO_ERR_INVALID_ARG);
         if (capture && w.sys->ctx != c)
             return (set_err(c, "graph capture needs every system to belong to the context"), NAO_ERR_INVALID_ARG);
+        if ((st = check_groups(w.sys)) != NAO_OK) return (set_err(c, "work entry whose system has no execution groups"), st);
         if (w.op != 0 && w.op != 1) return (set_err(c, "work op must be 0 (H) or 1 (density)"), NAO_ERR_INVALID_ARG);
         const bool need_in = w.op == 0 ? w.sys->n_points > 0 : w.sys->basis.n_basis > 0;
         if ((need_in && !w.in) || !w.out) return (set_err(c, "NULL work pointer"), NAO_ERR_INVALID_ARG);

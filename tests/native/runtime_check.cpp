@@ -218,6 +218,40 @@ void arrays()
     std::printf("%d builds, %d refused\n", built, refused);
 }
 
+// Other groups or tiles refused under a budget: the system keeps working, over the groups it had or
+// not at all.
+void regroup()
+{
+    const Structure A(8, 5, 3, 5.0, 75, 3, 2);
+    const Buffers a(A);
+    nao_ctx c = nullptr;
+    nao_system s = nullptr;
+    CHECK(nao_ctx_create(0, nullptr, 0, &c) == NAO_OK);
+    CHECK(build(c, A, &s) == NAO_OK);
+    size_t used = 0, other = 0;
+    CHECK(nao_ctx_memory(c, &used, nullptr) == NAO_OK);
+    CHECK(nao_system_set_group_max(s, 64) == NAO_OK);
+    CHECK(nao_ctx_memory(c, &other, nullptr) == NAO_OK);
+    nao_system_destroy(s);
+    nao_ctx_destroy(c);
+    const size_t top = std::max(used, other), bottom = top / 4 * 3;
+    int refused = 0;
+    for (int k = 0; k <= 120; ++k) {
+        CHECK(nao_ctx_create(0, nullptr, top - (top - bottom) * k / 120, &c) == NAO_OK);
+        if (took(build(c, A, &s))) {
+            refused += !took(nao_system_set_group_max(s, 64));
+            operations(s, a, NAO_FP64);
+            refused += !took(nao_system_set_h_tile(s, 128));
+            operations(s, a, NAO_FP32);
+            nao_system_destroy(s);
+        }
+        nao_ctx_destroy(c);
+        CHECK(no_faults("after a refused change"));
+    }
+    std::printf("%d changes refused\n", refused);
+    CHECK(refused > 0);
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -226,6 +260,7 @@ int main(int argc, char** argv)
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "scratch") scratch();
     else if (what == "arrays") arrays();
+    else if (what == "regroup") regroup();
     else return 2;
     std::printf("%s: all ok\n", what.c_str());
     return 0;

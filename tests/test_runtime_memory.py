@@ -25,7 +25,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["scratch", "arrays"])
+@pytest.mark.parametrize("scenario", ["scratch", "arrays", "regroup"])
 def test_launches_stay_in_live_memory(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and scenario + ": all ok" in r.stdout, r.stdout + r.stderr[-4000:]
