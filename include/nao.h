@@ -99,7 +99,10 @@ typedef struct {
  * Context.
  * nao_ctx_create: device = HIP ordinal; hip_stream = a hipStream_t to order work on, or
  * NULL for a stream the context creates; hbm_budget_bytes = cap on the device memory the
- * context allocates for all its systems (0 = no cap).  NAO_ERR_NOT_READY without a GPU.
+ * context allocates for all its systems (0 = no cap).  What the context holds beyond what its
+ * operations need (second forms of the execution groups that make the Hamiltonian faster, and
+ * scratch sized for them) is given back before an allocation is refused; a Hamiltonian without them
+ * differs by the order of its FP64 sums.  NAO_ERR_NOT_READY without a GPU.
  * ------------------------------------------------------------------------------------- */
 nao_status nao_ctx_create(int device, void* hip_stream, size_t hbm_budget_bytes, nao_ctx* out);
 /* Destroy every system and server of a context before the context itself. */

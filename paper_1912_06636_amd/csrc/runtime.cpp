@@ -7,6 +7,7 @@
 #include <cstring>
 #include <fstream>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -65,7 +66,7 @@ struct nao_ctx_s {
     hipEvent_t ev_start = nullptr;       // the context stream's work before the operation
     hipEvent_t ev_ready[2] = {};         // basis values of the last block of each buffer written
     hipEvent_t ev_done[2] = {};          // contraction of the last block of each buffer done
-    int n_systems = 0;
+    std::vector<struct nao_system_s*> systems;
     // per-kernel timing
     bool prof = false;
     struct Rec {
@@ -291,6 +292,13 @@ struct Block {
 
 }  // namespace
 
+// Launch plans of other contexts that use a system's clusters, which then stay (release_clusters may
+// run on the thread of the system's context while another thread drives that other context).
+struct ClusterGate {
+    std::mutex mu;
+    int plans = 0;
+};
+
 struct nao_system_s {
     nao_ctx ctx = nullptr;
     HostBasis basis;
@@ -320,6 +328,7 @@ struct nao_system_s {
     std::vector<Block> cl_blocks;
     int64_t n_cl_subs = 0, n_cl_rows = 0, n_cl_atoms = 0, n_cl_fn = 0, n_cl_mask = 0;
     DevArray d_cl_units, d_cl_subs, d_cl_atoms, d_cl_cols, d_cl_fn, d_cl_mask, d_cl_items;
+    std::shared_ptr<ClusterGate> gate = std::make_shared<ClusterGate>();
     DevArray d_wv, d_v, d_D, d_H, d_n, d_gn, d_a, d_wa, d_segs, d_Q, d_fb, d_atom_first, d_F;
     // resident basis values (opt-in): every block's values kept across operations
     bool resident = false;
@@ -332,8 +341,21 @@ struct nao_system_s {
 };
 
 nao_status grow_scratch(nao_ctx c, size_t elems);
+static bool release_clusters(nao_ctx c);
 
 namespace {
+
+bool refused(nao_status st) { return st == NAO_ERR_BUDGET || st == NAO_ERR_OUT_OF_MEMORY; }
+
+// Clusters are only a faster form: an operation that is refused memory runs again without them.
+template <typename F>
+nao_status with_room(nao_ctx c, F&& f)
+{
+    const nao_status st = f();
+    return refused(st) && release_clusters(c) ? f() : st;
+}
+template <typename F>
+nao_status with_room(nao_system_s* s, F&& f) { return s ? with_room(s->ctx, f) : f(); }
 
 size_t system_bytes(const nao_system_s* s)
 {
@@ -645,17 +667,23 @@ nao_status regroup(nao_system_s* s, int32_t group_max, int32_t h_tile)
     auto build = [&](int32_t g, int32_t t) {
         s->group_max = g;
         s->h_tile = t;
-        try {
-            return build_groups(s);
-        } catch (...) {
-            set_err(s->ctx, "internal error in the execution groups");
-            return NAO_ERR_INTERNAL;
-        }
+        return with_room(s->ctx, [&]() {
+            try {
+                return build_groups(s);
+            } catch (...) {
+                set_err(s->ctx, "internal error in the execution groups");
+                return NAO_ERR_INTERNAL;
+            }
+        });
     };
     const nao_status st = build(group_max, h_tile);
     if (st == NAO_OK) {
         s->lost = false;
-        return resident_layout(s);
+        const bool resident = s->resident;
+        return with_room(s->ctx, [&]() {
+            s->resident = resident;
+            return resident_layout(s);
+        });
     }
     std::string why;
     {
@@ -681,6 +709,7 @@ nao_status check_groups(nao_system_s* s)
 // clusters: over the system's clusters, 1 with columns by reach (FP64), 2 with ascending columns: a
 // pair's w v goes to the column that comes first and FP32 rounds the product, so FP32 and split-BF16
 // keep the order that the units have.
+// (g.phi is the caller's to set)
 DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = false, int clusters = 0, bool tiles = false)
 {
     DevSeg g{};
@@ -694,7 +723,6 @@ DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = fal
         g.unit_fn = s->d_cl_fn.as<int32_t>() + k * s->n_cl_fn;
         g.unit_mask = s->d_cl_mask.as<uint64_t>() + k * s->n_cl_mask;
         g.items = s->d_cl_items.p;
-        g.phi = s->ctx->scratch;
         g.ld = s->basis.n_basis;
         g.unit_begin = b.unit_begin;
         g.unit_count = b.unit_count;
@@ -709,7 +737,6 @@ DevSeg make_seg(const nao_system_s* s, const Block& b, bool ham, bool wide = fal
     g.unit_fn = s->d_unit_fn.as<int32_t>();
     g.unit_mask = s->d_unit_mask.as<uint64_t>();
     g.items = ham ? (wide ? (const void*)s->d_hw_items.p : (const void*)s->d_h_items.p) : (const void*)s->d_n_items.p;
-    g.phi = s->ctx->scratch;
     g.ld = s->basis.n_basis;
     g.unit_begin = b.unit_begin;
     g.unit_count = b.unit_count;
@@ -759,6 +786,8 @@ struct ManyPlan {
     std::vector<DevSeg> segs;
     std::vector<nao_work> entries;
     std::vector<int64_t> wv_off;  // per entry: offset into the w*v arena (H entries)
+    std::vector<int> clusters;    // per entry: over the system's clusters, and in which order (make_seg)
+    std::vector<std::shared_ptr<ClusterGate>> gates;  // of the systems of other contexts among those
     nao_precision prec = NAO_FP64;
     bool overlap = false;  // odd chunks in the second buffer, basis launches on the second stream
     DevArray d_segs, d_wv;
@@ -774,6 +803,10 @@ void many_free(nao_ctx c, ManyPlan* m)
     if (m->graph) (void)hipGraphDestroy(m->graph);
     pool_give(c, m->d_segs);
     pool_give(c, m->d_wv);
+    for (auto& g : m->gates) {
+        std::lock_guard<std::mutex> lk(g->mu);
+        --g->plans;
+    }
     delete m;
 }
 
@@ -835,12 +868,49 @@ nao_status grow_scratch(nao_ctx c, size_t elems)
     return st;
 }
 
-// The scratch holds the largest of an operation's blocks: every operation asks before it launches,
-// since the scratch has only the size that the last successful growth left.
-static nao_status scratch_for(nao_ctx c, const std::vector<Block>& blocks)
+// Gives back what the context holds for clusters: their tables, and the scratch buffers, which grow
+// again to what the next operation needs.  True when there was anything.
+static bool release_clusters(nao_ctx c)
 {
+    bool any = false;
+    size_t units = 0;
+    for (nao_system_s* s : c->systems) {
+        for (const Block& b : s->blocks) units = std::max(units, (size_t)b.phi_elems);
+        if (s->cl_blocks.empty()) continue;
+        many_forget(c, s);  // before the lock: it frees plans, which takes other systems' locks
+        std::lock_guard<std::mutex> lk(s->gate->mu);
+        if (s->gate->plans) continue;
+        drop_clusters(s);
+        for (DevArray* a : {&s->d_wv, &s->d_segs}) {  // sized for the clusters; every operation asks for its own
+            dev_free(c, a->p, a->bytes);
+            *a = DevArray();
+        }
+        any = true;
+    }
+    if (!any && c->scratch_elems <= units) return false;
+    many_forget(c, nullptr);
+    if (c->stream2) (void)hipStreamSynchronize(c->stream2);
+    dev_free(c, c->scratch, c->scratch_elems * sizeof(double));
+    dev_free(c, c->scratch2, c->scratch2_elems * sizeof(double));
+    dev_free(c, c->gscratch, c->gscratch_bytes);
+    dev_free(c, c->gscratch2, c->gscratch2_bytes);
+    c->scratch = c->scratch2 = nullptr;
+    c->gscratch = c->gscratch2 = nullptr;
+    c->scratch_elems = c->scratch2_elems = c->gscratch_bytes = c->gscratch2_bytes = 0;
+    return true;
+}
+
+// The scratch holds the largest of an operation's blocks: every operation asks before it launches,
+// since the scratch has only the size that the last successful growth left.  The same goes for the
+// segment table and, for `rows` values, for w v.
+static nao_status scratch_for(nao_system_s* s, const std::vector<Block>& blocks, int64_t rows)
+{
+    nao_ctx c = s->ctx;
     size_t need = 0;
     for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
+    nao_status st;
+    if ((st = ensure(c, s->d_segs, std::max<size_t>(1, blocks.size()) * sizeof(DevSeg))) != NAO_OK) return st;
+    if (rows > 0 && (st = ensure(c, s->d_wv, rows * sizeof(double))) != NAO_OK) return st;
     return grow_scratch(c, need);
 }
 
@@ -930,22 +1000,36 @@ static nao_status block_loop(nao_ctx c, size_t n_blocks, bool ovl, const char* b
 
 namespace {
 
-nao_status many_build(nao_ctx c, const nao_work* work, int64_t n_work, nao_precision prec, ManyPlan* m)
+// The clusters that an entry of a plan runs over (0: none), held until the plan is freed.
+int plan_clusters(nao_ctx c, nao_system_s* s, nao_precision prec, ManyPlan* m)
+{
+    if (s->ctx == c) return use_clusters(s, prec);  // dropped only after the context's plans
+    std::lock_guard<std::mutex> lk(s->gate->mu);
+    const int cl = use_clusters(s, prec);
+    if (cl) {
+        ++s->gate->plans;
+        m->gates.push_back(s->gate);
+    }
+    return cl;
+}
+
+nao_status many_build(nao_ctx c, const nao_work* work, int64_t n_work, nao_precision prec, bool clusters, ManyPlan* m)
 {
     m->prec = prec;
     m->entries.assign(work, work + n_work);
     int64_t wv_total = 0;
     for (const nao_work& w : m->entries) {
         m->wv_off.push_back(wv_total);
-        if (w.op == 0) wv_total += use_clusters(w.sys, prec) ? w.sys->n_cl_rows : w.sys->n_points;
+        m->clusters.push_back(w.op == 0 && clusters ? plan_clusters(c, w.sys, prec, m) : 0);
+        if (w.op == 0) wv_total += m->clusters.back() ? w.sys->n_cl_rows : w.sys->n_points;
     }
     nao_status st = pool_take(c, m->d_wv, std::max<int64_t>(1, wv_total) * sizeof(double));
     if (st != NAO_OK) return st;
     // the scratch must hold the largest block of every system (systems may come from other
     // contexts on this device)
     int64_t need = 0;
-    for (const nao_work& w : m->entries)
-        for (const Block& b : w.op == 0 && use_clusters(w.sys, prec) ? w.sys->cl_blocks : w.sys->blocks)
+    for (size_t e = 0; e < m->entries.size(); ++e)
+        for (const Block& b : m->clusters[e] ? m->entries[e].sys->cl_blocks : m->entries[e].sys->blocks)
             need = std::max(need, b.phi_elems);
     if ((st = grow_scratch(c, (size_t)need)) != NAO_OK) return st;
     // one segment per (entry, block); consecutive segments share a chunk while their basis
@@ -957,7 +1041,7 @@ nao_status many_build(nao_ctx c, const nao_work* work, int64_t n_work, nao_preci
         const nao_work& w = m->entries[e];
         nao_system_s* s = w.sys;
         const bool ham = w.op == 0;
-        const int cl = ham ? use_clusters(s, prec) : 0;
+        const int cl = m->clusters[e];
         for (const Block& b : cl ? s->cl_blocks : s->blocks) {
             if (off + b.phi_elems > (int64_t)c->scratch_elems && off > 0) {
                 chunks.emplace_back();
@@ -1038,7 +1122,7 @@ nao_status many_enqueue(nao_ctx c, ManyPlan* m)
         nao_system_s* s = w.sys;
         if (w.op == 0) {
             LAUNCH(c, "fill", launch_fill(w.out, s->basis.n_basis * s->basis.n_basis, 0.0, c->stream));
-            LAUNCH(c, "wv", use_clusters(s, m->prec)
+            LAUNCH(c, "wv", m->clusters[e]
                                 ? launch_wv_rows(s->d_cl_subs.as<DevUnit>(), s->n_cl_subs, s->d_pw.as<double>(),
                                                  s->d_perm.as<int32_t>(), w.in, m->d_wv.as<double>() + m->wv_off[e], c->stream)
                                 : launch_wv(s->d_pw.as<double>(), s->d_perm.as<int32_t>(), w.in,
@@ -1094,7 +1178,7 @@ nao_status many_enqueue(nao_ctx c, ManyPlan* m)
     return NAO_OK;
 }
 
-nao_status run_many_impl(nao_ctx c, const nao_work* work, int64_t n_work, nao_precision prec, bool capture)
+nao_status run_many_impl(nao_ctx c, const nao_work* work, int64_t n_work, nao_precision prec, bool capture, bool clusters)
 {
     many_retire(c, false);
     std::vector<const void*> key;
@@ -1114,7 +1198,7 @@ nao_status run_many_impl(nao_ctx c, const nao_work* work, int64_t n_work, nao_pr
     }
     ManyPlan* m = new ManyPlan();
     m->key = key;
-    nao_status st = many_build(c, work, n_work, prec, m);
+    nao_status st = many_build(c, work, n_work, prec, clusters, m);
     if (st != NAO_OK) {
         many_free(c, m);
         return st;
@@ -1175,7 +1259,10 @@ nao_status run_many_impl(nao_ctx c, const nao_work* work, int64_t n_work, nao_pr
 
 namespace nao {
 
-nao_status ctx_alloc(nao_ctx c, size_t bytes, void** out) { return dev_alloc(c, bytes, out); }
+nao_status ctx_alloc(nao_ctx c, size_t bytes, void** out)
+{
+    return with_room(c, [&]() { return dev_alloc(c, bytes, out); });
+}
 void ctx_free(nao_ctx c, void* p, size_t bytes) { dev_free(c, p, bytes); }
 hipStream_t ctx_stream(nao_ctx c) { return c->stream; }
 int ctx_device(nao_ctx c) { return c->device; }
@@ -1598,37 +1685,41 @@ nao_status nao_build_batches_ex(nao_ctx c, const nao_basis_desc* basis, int64_t 
     for (int64_t k = 0; k < n_points; ++k)
         if (!std::isfinite(point_w[k]) || point_w[k] < 0.0)
             return (set_err(c, "point weights must be finite and >= 0"), NAO_ERR_INVALID_ARG);
-    nao_system s = nullptr;
-    try {
-        s = new nao_system_s();
-        s->ctx = c;
-        why = load_basis(basis, s->basis);
-        if (!why.empty()) {
-            delete s;
-            set_err(c, why);
-            return NAO_ERR_INVALID_ARG;
+    return with_room(c, [&]() {
+        nao_system s = nullptr;
+        nao_status got = NAO_OK;
+        try {
+            c->systems.reserve(c->systems.size() + 1);
+            s = new nao_system_s();
+            s->ctx = c;
+            const std::string bad = load_basis(basis, s->basis);
+            if (!bad.empty()) {
+                delete s;
+                set_err(c, bad);
+                return NAO_ERR_INVALID_ARG;
+            }
+            s->n_points = n_points;
+            s->max_batch = max_batch;
+            s->batcher = batcher;
+            got = setup_system(s, point_xyz, point_w);
+        } catch (const std::bad_alloc&) {
+            set_err(c, "host allocation failed");
+            got = NAO_ERR_OUT_OF_MEMORY;
+        } catch (...) {
+            set_err(c, "internal error in nao_build_batches");
+            got = NAO_ERR_INTERNAL;
         }
-        s->n_points = n_points;
-        s->max_batch = max_batch;
-        s->batcher = batcher;
-        st = setup_system(s, point_xyz, point_w);
-    } catch (const std::bad_alloc&) {
-        set_err(c, "host allocation failed");
-        st = NAO_ERR_OUT_OF_MEMORY;
-    } catch (...) {
-        set_err(c, "internal error in nao_build_batches");
-        st = NAO_ERR_INTERNAL;
-    }
-    if (st != NAO_OK) {
-        if (s) {
-            free_all(s);
-            delete s;
+        if (got != NAO_OK) {
+            if (s) {
+                free_all(s);
+                delete s;
+            }
+            return got;
         }
-        return st;
-    }
-    c->n_systems++;
-    *out = s;
-    return NAO_OK;
+        c->systems.push_back(s);
+        *out = s;
+        return NAO_OK;
+    });
 }
 
 nao_status nao_system_set_group_max(nao_system s, int32_t group_max)
@@ -1659,9 +1750,10 @@ nao_status nao_system_set_resident_basis(nao_system s, int enable)
         s->res_off.clear();
         return NAO_OK;
     }
-    s->resident = true;
-    st = resident_layout(s);
-    return st;  // the allocation's own message says what did not fit
+    return with_room(s->ctx, [&]() {
+        s->resident = true;
+        return resident_layout(s);  // the allocation's own message says what did not fit
+    });
 }
 
 nao_status nao_system_set_h_tile(nao_system s, int32_t h_tile)
@@ -1726,13 +1818,14 @@ void nao_system_destroy(nao_system s)
     many_forget(s->ctx, s);
     (void)hipStreamSynchronize(s->ctx->stream);
     free_all(s);
-    s->ctx->n_systems--;
+    auto& all = s->ctx->systems;
+    all.erase(std::remove(all.begin(), all.end(), s), all.end());
     delete s;
 }
 
 // ------------------------------------------------------------------------------ basis values
 
-nao_status nao_eval_basis(nao_system s, int64_t b0, int64_t b1, double* phi, nao_memspace phi_space,
+static nao_status eval_basis_once(nao_system s, int64_t b0, int64_t b1, double* phi, nao_memspace phi_space,
                           int64_t* phi_ptr)
 {
     if (!s) return (g_thread_error = "system is NULL", NAO_ERR_INVALID_ARG);
@@ -1801,6 +1894,12 @@ nao_status nao_eval_basis(nao_system s, int64_t b0, int64_t b1, double* phi, nao
     return NAO_OK;
 }
 
+nao_status nao_eval_basis(nao_system s, int64_t b0, int64_t b1, double* phi, nao_memspace phi_space,
+                          int64_t* phi_ptr)
+{
+    return with_room(s, [&]() { return eval_basis_once(s, b0, b1, phi, phi_space, phi_ptr); });
+}
+
 // ------------------------------------------------------------------------------ contractions
 
 static nao_status check_prec(nao_ctx c, nao_precision p)
@@ -1832,12 +1931,12 @@ static nao_status run_blocks(nao_system s, bool ham, nao_precision prec, const d
     const std::vector<Block>& blocks = cl ? s->cl_blocks : s->blocks;
     size_t need = 0;
     for (const Block& b : blocks) need = std::max(need, (size_t)b.phi_elems);
-    nao_status st = res ? NAO_OK : scratch_for(c, blocks);
+    nao_status st = res ? ensure(c, s->d_segs, std::max<size_t>(1, blocks.size()) * sizeof(DevSeg)) : scratch_for(s, blocks, 0);
     if (st != NAO_OK) return st;
     const bool ovl = !res && blocks.size() > 1 && overlap_ready(c, need);
     for (size_t k = 0; k < blocks.size(); ++k) {
         DevSeg g = make_seg(s, blocks[k], ham, wide, cl, !ham);
-        if (ovl && (k & 1)) g.phi = c->scratch2;
+        g.phi = ovl && (k & 1) ? c->scratch2 : c->scratch;
         if (res) g.phi = static_cast<char*>(s->d_phi_res.p) + s->res_off[k] * (f32 ? sizeof(float) : sizeof(double));
         g.wv = wv;
         g.D = D;
@@ -1862,7 +1961,7 @@ static nao_status run_blocks(nao_system s, bool ham, nao_precision prec, const d
     return NAO_OK;
 }
 
-nao_status nao_integrate_h(nao_system s, const double* v, nao_memspace v_space, nao_precision prec, double* H,
+static nao_status integrate_h_once(nao_system s, const double* v, nao_memspace v_space, nao_precision prec, double* H,
                            nao_memspace H_space)
 {
     if (!s) return (g_thread_error = "system is NULL", NAO_ERR_INVALID_ARG);
@@ -1886,8 +1985,9 @@ nao_status nao_integrate_h(nao_system s, const double* v, nao_memspace v_space, 
         if ((st = ensure(c, s->d_H, std::max<int64_t>(1, nb * nb) * sizeof(double))) != NAO_OK) return st;
         Hd = s->d_H.as<double>();
     }
-    LAUNCH(c, "fill", launch_fill(Hd, nb * nb, 0.0, c->stream));
     const bool cl = use_clusters(s, prec) && !(s->resident && s->d_phi_res.p && s->res_off.size() == s->blocks.size());
+    if ((st = ensure(c, s->d_wv, std::max<int64_t>(1, cl ? s->n_cl_rows : n) * sizeof(double))) != NAO_OK) return st;
+    LAUNCH(c, "fill", launch_fill(Hd, nb * nb, 0.0, c->stream));
     LAUNCH(c, "wv", cl ? launch_wv_rows(s->d_cl_subs.as<DevUnit>(), s->n_cl_subs, s->d_pw.as<double>(), s->d_perm.as<int32_t>(),
                                         vd, s->d_wv.as<double>(), c->stream)
                        : launch_wv(s->d_pw.as<double>(), s->d_perm.as<int32_t>(), vd, s->d_wv.as<double>(), n, c->stream));
@@ -1899,6 +1999,12 @@ nao_status nao_integrate_h(nao_system s, const double* v, nao_memspace v_space, 
     }
     if (v_space == NAO_MEM_HOST) HIP_TRY(c, hipStreamSynchronize(c->stream));
     return NAO_OK;
+}
+
+nao_status nao_integrate_h(nao_system s, const double* v, nao_memspace v_space, nao_precision prec, double* H,
+                           nao_memspace H_space)
+{
+    return with_room(s, [&]() { return integrate_h_once(s, v, v_space, prec, H, H_space); });
 }
 
 nao_status nao_integrate_h_noalloc(nao_system s, const double* v, nao_precision prec, double* H)
@@ -1977,7 +2083,7 @@ nao_status nao_integrate_h_noalloc(nao_system s, const double* v, nao_precision 
     return NAO_OK;
 }
 
-nao_status nao_update_density(nao_system s, const double* D, nao_memspace D_space, nao_precision prec, double* nout,
+static nao_status update_density_once(nao_system s, const double* D, nao_memspace D_space, nao_precision prec, double* nout,
                               nao_memspace n_space, double* n_electrons)
 {
     if (!s) return (g_thread_error = "system is NULL", NAO_ERR_INVALID_ARG);
@@ -2013,6 +2119,12 @@ nao_status nao_update_density(nao_system s, const double* D, nao_memspace D_spac
         HIP_TRY(c, hipMemcpyAsync(nout, nd, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     if (n_space == NAO_MEM_HOST || n_electrons || D_space == NAO_MEM_HOST) HIP_TRY(c, hipStreamSynchronize(c->stream));
     return NAO_OK;
+}
+
+nao_status nao_update_density(nao_system s, const double* D, nao_memspace D_space, nao_precision prec, double* nout,
+                              nao_memspace n_space, double* n_electrons)
+{
+    return with_room(s, [&]() { return update_density_once(s, D, D_space, prec, nout, n_space, n_electrons); });
 }
 
 // Extra per-block scratch beside the basis values: `per_value` FP64 slots per basis value.
@@ -2056,7 +2168,7 @@ static nao_status integrate_h_with_l(nao_system s, const double* v, const double
     nao_status st;
     const int cl = use_clusters(s, prec);
     const std::vector<Block>& blocks = cl ? s->cl_blocks : s->blocks;
-    if ((st = scratch_for(c, blocks)) != NAO_OK) return st;
+    if ((st = scratch_for(s, blocks, n)) != NAO_OK) return st;
     if ((st = ensure_gscratch(s, 1, blocks)) != NAO_OK) return st;  // L: one value per basis value
     const bool has_a = a != nullptr && n > 0;
     const double* vd = v;
@@ -2090,6 +2202,7 @@ static nao_status integrate_h_with_l(nao_system s, const double* v, const double
         g.wv = s->d_wv.as<double>();
         g.wa = has_a ? s->d_wa.as<double>() : nullptr;
         g.H = Hd;
+        g.phi = c->scratch;
         g.gphi = c->gscratch;
         g.plane = b.phi_elems;
         if (ovl && (segs.size() & 1)) {
@@ -2119,7 +2232,7 @@ static nao_status integrate_h_with_l(nao_system s, const double* v, const double
     return NAO_OK;
 }
 
-nao_status nao_integrate_h_gga(nao_system s, const double* v, const double* a, nao_memspace in_space,
+static nao_status integrate_h_gga_once(nao_system s, const double* v, const double* a, nao_memspace in_space,
                                nao_precision prec, double* H, nao_memspace H_space)
 {
     if (!s) return (g_thread_error = "system is NULL", NAO_ERR_INVALID_ARG);
@@ -2132,7 +2245,13 @@ nao_status nao_integrate_h_gga(nao_system s, const double* v, const double* a, n
     return integrate_h_with_l(s, v, a, in_space, prec, H, H_space, EXTRA_GGA_L);
 }
 
-nao_status nao_integrate_h_ks(nao_system s, const double* v, const double* a, nao_memspace in_space,
+nao_status nao_integrate_h_gga(nao_system s, const double* v, const double* a, nao_memspace in_space,
+                               nao_precision prec, double* H, nao_memspace H_space)
+{
+    return with_room(s, [&]() { return integrate_h_gga_once(s, v, a, in_space, prec, H, H_space); });
+}
+
+static nao_status integrate_h_ks_once(nao_system s, const double* v, const double* a, nao_memspace in_space,
                               nao_precision prec, double* H, nao_memspace H_space)
 {
     if (!s) return (g_thread_error = "system is NULL", NAO_ERR_INVALID_ARG);
@@ -2145,7 +2264,13 @@ nao_status nao_integrate_h_ks(nao_system s, const double* v, const double* a, na
     return integrate_h_with_l(s, v, a, in_space, prec, H, H_space, EXTRA_KS_L);
 }
 
-nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspace D_space, nao_precision prec,
+nao_status nao_integrate_h_ks(nao_system s, const double* v, const double* a, nao_memspace in_space,
+                              nao_precision prec, double* H, nao_memspace H_space)
+{
+    return with_room(s, [&]() { return integrate_h_ks_once(s, v, a, in_space, prec, H, H_space); });
+}
+
+static nao_status update_density_gradient_once(nao_system s, const double* D, nao_memspace D_space, nao_precision prec,
                                        double* nout, double* gout, nao_memspace out_space)
 {
     if (!s) return (g_thread_error = "system is NULL", NAO_ERR_INVALID_ARG);
@@ -2160,7 +2285,7 @@ nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspa
     if ((D_space != NAO_MEM_HOST && D_space != NAO_MEM_DEVICE) || (out_space != NAO_MEM_HOST && out_space != NAO_MEM_DEVICE))
         return (set_err(c, "bad memspace"), NAO_ERR_INVALID_ARG);
     // gradients of one block's basis values: 3 per value
-    if ((st = scratch_for(c, s->blocks)) != NAO_OK) return st;
+    if ((st = scratch_for(s, s->blocks, 0)) != NAO_OK) return st;
     if ((st = ensure_gscratch(s, 3, s->blocks)) != NAO_OK) return st;
     const double* Dd = D;
     if (D_space == NAO_MEM_HOST && nb > 0) {
@@ -2187,6 +2312,7 @@ nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspa
         g.D = Dd;
         g.n = nd;
         g.gn = gd;
+        g.phi = c->scratch;
         g.gphi = c->gscratch;
         g.plane = b.phi_elems;
         if (ovl && (segs.size() & 1)) {
@@ -2215,7 +2341,13 @@ nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspa
     return NAO_OK;
 }
 
-nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, const double* v, nao_memspace in_space,
+nao_status nao_update_density_gradient(nao_system s, const double* D, nao_memspace D_space, nao_precision prec,
+                                       double* nout, double* gout, nao_memspace out_space)
+{
+    return with_room(s, [&]() { return update_density_gradient_once(s, D, D_space, prec, nout, gout, out_space); });
+}
+
+static nao_status pulay_forces_once(nao_system s, const double* D, const double* Q, const double* v, nao_memspace in_space,
                             nao_precision prec, double* F, nao_memspace F_space)
 {
     if (!s) return (g_thread_error = "system is NULL", NAO_ERR_INVALID_ARG);
@@ -2229,7 +2361,7 @@ nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, cons
     if (!F || (nb > 0 && (!D || !Q)) || (n > 0 && !v)) return (set_err(c, "NULL D, Q, v or F"), NAO_ERR_INVALID_ARG);
     if ((in_space != NAO_MEM_HOST && in_space != NAO_MEM_DEVICE) || (F_space != NAO_MEM_HOST && F_space != NAO_MEM_DEVICE))
         return (set_err(c, "bad memspace"), NAO_ERR_INVALID_ARG);
-    if ((st = scratch_for(c, s->blocks)) != NAO_OK) return st;
+    if ((st = scratch_for(s, s->blocks, n)) != NAO_OK) return st;
     if ((st = ensure_gscratch(s, 4, s->blocks)) != NAO_OK) return st;  // gradient and lap phi: 4 per basis value
     const double* Dd = D;
     const double* Qd = Q;
@@ -2270,6 +2402,7 @@ nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, cons
         g.Q = Qd;
         g.wv = s->d_wv.as<double>();
         g.fb = s->d_fb.as<double>();
+        g.phi = c->scratch;
         g.gphi = c->gscratch;
         g.plane = b.phi_elems;
         if (ovl && (segs.size() & 1)) {
@@ -2297,6 +2430,12 @@ nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, cons
         HIP_TRY(c, hipMemcpyAsync(F, Fd, 3 * na * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     if (F_space == NAO_MEM_HOST || in_space == NAO_MEM_HOST) HIP_TRY(c, hipStreamSynchronize(c->stream));
     return NAO_OK;
+}
+
+nao_status nao_pulay_forces(nao_system s, const double* D, const double* Q, const double* v, nao_memspace in_space,
+                            nao_precision prec, double* F, nao_memspace F_space)
+{
+    return with_room(s, [&]() { return pulay_forces_once(s, D, Q, v, in_space, prec, F, F_space); });
 }
 
 nao_status nao_run_many(nao_ctx c, const nao_work* work, int64_t n_work, nao_precision prec, void* hip_stream,
@@ -2336,7 +2475,11 @@ nao_status nao_run_many(nao_ctx c, const nao_work* work, int64_t n_work, nao_pre
         c->stream = user;
     }
     try {
-        st = run_many_impl(c, work, n_work, prec, capture);
+        st = run_many_impl(c, work, n_work, prec, capture, true);
+        if (refused(st)) {  // without any clusters, those of other contexts' systems included
+            (void)release_clusters(c);
+            st = run_many_impl(c, work, n_work, prec, capture, false);
+        }
         for (int64_t k = 0; st == NAO_OK && k < n_work; ++k) {
             const nao_work& w = work[k];
             if (!w.n_electrons) continue;
@@ -2495,14 +2638,18 @@ extern "C" nao_status nao_system_autotune(nao_system s, nao_precision prec, cons
     };
     const double* vin = v;
     const double* Din = D;
-    if (space == NAO_MEM_HOST) {
-        if ((st = upload(c, dv, v, np * sizeof(double))) != NAO_OK) return release(), st;
-        if ((st = upload(c, dD, D, nb * nb * sizeof(double))) != NAO_OK) return release(), st;
-        vin = dv.as<double>();
-        Din = dD.as<double>();
-    }
-    if ((st = ensure(c, dH, std::max<int64_t>(1, nb * nb) * sizeof(double))) != NAO_OK) return release(), st;
-    if ((st = ensure(c, dn, std::max<int64_t>(1, np) * sizeof(double))) != NAO_OK) return release(), st;
+    st = with_room(c, [&]() {
+        nao_status got;
+        if (space == NAO_MEM_HOST) {
+            if ((got = upload(c, dv, v, np * sizeof(double))) != NAO_OK) return got;
+            if ((got = upload(c, dD, D, nb * nb * sizeof(double))) != NAO_OK) return got;
+            vin = dv.as<double>();
+            Din = dD.as<double>();
+        }
+        if ((got = ensure(c, dH, std::max<int64_t>(1, nb * nb) * sizeof(double))) != NAO_OK) return got;
+        return ensure(c, dn, std::max<int64_t>(1, np) * sizeof(double));
+    });
+    if (st != NAO_OK) return release(), st;
     std::vector<std::pair<int, int>> cand;
     const bool dense = prec == NAO_FP64 || prec == NAO_FP32;
     for (int gm : {256, 192, 128})

@@ -4,6 +4,7 @@
 // fake::faults.  Captured launches are checked again whenever their graph is launched.
 #pragma once
 
+#include <atomic>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -24,8 +25,8 @@ std::map<uintptr_t, size_t> live;
 std::vector<std::string> faults;
 size_t device_limit = 0;          // bytes that hipMalloc gives out at most (0 = no limit)
 size_t device_used = 0;
-int launches = 0;                 // contraction launches
-int cluster_launches = 0;         // ... of them over clusters
+std::atomic<int> launches{0};      // contraction launches
+std::atomic<int> cluster_launches{0};  // ... of them over clusters
 std::vector<std::function<void()>>* capturing = nullptr;
 
 inline void fault(const std::string& m)

@@ -218,38 +218,163 @@ void arrays()
     std::printf("%d builds, %d refused\n", built, refused);
 }
 
-// Other groups or tiles refused under a budget: the system keeps working, over the groups it had or
-// not at all.
+// Other groups or tiles refused for want of device memory: the system keeps working over the groups it
+// had, or, where not even those come back, refuses its operations.
 void regroup()
 {
     const Structure A(8, 5, 3, 5.0, 75, 3, 2);
     const Buffers a(A);
-    nao_ctx c = nullptr;
-    nao_system s = nullptr;
-    CHECK(nao_ctx_create(0, nullptr, 0, &c) == NAO_OK);
-    CHECK(build(c, A, &s) == NAO_OK);
-    size_t used = 0, other = 0;
-    CHECK(nao_ctx_memory(c, &used, nullptr) == NAO_OK);
-    CHECK(nao_system_set_group_max(s, 64) == NAO_OK);
-    CHECK(nao_ctx_memory(c, &other, nullptr) == NAO_OK);
-    nao_system_destroy(s);
-    nao_ctx_destroy(c);
-    const size_t top = std::max(used, other), bottom = top / 4 * 3;
-    int refused = 0;
-    for (int k = 0; k <= 120; ++k) {
-        CHECK(nao_ctx_create(0, nullptr, top - (top - bottom) * k / 120, &c) == NAO_OK);
-        if (took(build(c, A, &s))) {
-            refused += !took(nao_system_set_group_max(s, 64));
-            operations(s, a, NAO_FP64);
-            refused += !took(nao_system_set_h_tile(s, 128));
-            operations(s, a, NAO_FP32);
-            nao_system_destroy(s);
+    int refused = 0, lost = 0;
+    for (int k = 0; k <= 60; ++k) {
+        nao_ctx c = nullptr;
+        nao_system s = nullptr;
+        CHECK(nao_ctx_create(0, nullptr, 0, &c) == NAO_OK);
+        const size_t before = fake::device_used;
+        CHECK(build(c, A, &s) == NAO_OK);
+        operations(s, a, NAO_FP64);
+        fake::device_limit = before + (fake::device_used - before) * k / 60;
+        refused += !took(nao_system_set_group_max(s, 64));
+        refused += !took(nao_system_set_h_tile(s, 128));
+        fake::device_limit = 0;
+        if (nao_integrate_h(s, a.v, NAO_MEM_DEVICE, NAO_FP64, a.H, NAO_MEM_DEVICE) == NAO_ERR_INTERNAL) {
+            ++lost;
+            CHECK(nao_update_density(s, a.D, NAO_MEM_DEVICE, NAO_FP64, a.n, NAO_MEM_DEVICE, nullptr) == NAO_ERR_INTERNAL);
+            CHECK(nao_system_set_group_max(s, 128) == NAO_OK);  // memory is there again
         }
+        CHECK(operations(s, a, NAO_FP64) == 6 && operations(s, a, NAO_FP32) == 6);
+        nao_system_destroy(s);
         nao_ctx_destroy(c);
         CHECK(no_faults("after a refused change"));
     }
-    std::printf("%d changes refused\n", refused);
+    std::printf("%d changes refused, %d systems lost\n", refused, lost);
     CHECK(refused > 0);
+}
+
+// Clusters are a faster form and no more: what is accepted at some budget is accepted at every larger
+// one, and the smallest budgets that take a Hamiltonian take it over the units.
+void budget()
+{
+    const Structure A(8, 5, 3, 5.0, 75, 3, 2), B(6, 4, 3, 5.0, 60, 3, 3);
+    const Buffers a(A), b(B);
+    std::vector<double> D(A.nb * A.nb), H(A.nb * A.nb), n(A.np), v(A.np);
+    struct Call {
+        const char* name;
+        bool hamiltonian;
+        std::function<nao_status(nao_system)> f;
+    };
+    nao_ctx ctx = nullptr;
+    const Call calls[] = {
+        {"H", true, [&](nao_system s) { return nao_integrate_h(s, a.v, NAO_MEM_DEVICE, NAO_FP64, a.H, NAO_MEM_DEVICE); }},
+        {"H host", true, [&](nao_system s) { return nao_integrate_h(s, v.data(), NAO_MEM_HOST, NAO_FP32, H.data(), NAO_MEM_HOST); }},
+        {"density host", false, [&](nao_system s) { return nao_update_density(s, D.data(), NAO_MEM_HOST, NAO_FP64, n.data(), NAO_MEM_HOST, nullptr); }},
+        {"gradient", false, [&](nao_system s) { return nao_update_density_gradient(s, a.D, NAO_MEM_DEVICE, NAO_FP64, a.n, a.gn, NAO_MEM_DEVICE); }},
+        {"GGA", true, [&](nao_system s) { return nao_integrate_h_gga(s, a.v, a.a, NAO_MEM_DEVICE, NAO_FP64, a.H, NAO_MEM_DEVICE); }},
+        {"KS", true, [&](nao_system s) { return nao_integrate_h_ks(s, a.v, nullptr, NAO_MEM_DEVICE, NAO_FP64, a.H, NAO_MEM_DEVICE); }},
+        {"forces", false, [&](nao_system s) { return nao_pulay_forces(s, a.D, a.Q, a.v, NAO_MEM_DEVICE, NAO_FP64, a.F, NAO_MEM_DEVICE); }},
+        {"resident", false, [&](nao_system s) { return nao_system_set_resident_basis(s, 1); }},
+        {"second system", false, [&](nao_system) {
+             nao_system t = nullptr;
+             const nao_status st = build(ctx, B, &t);
+             if (st == NAO_OK) nao_system_destroy(t);
+             return st;
+         }},
+        {"run_many", true, [&](nao_system s) {
+             const nao_work w[] = {{s, 0, a.v, a.H, nullptr}, {s, 1, a.D, a.n, nullptr}};
+             return nao_run_many(ctx, w, 2, NAO_FP64, nullptr, 0);
+         }},
+        {"captured run_many", true, [&](nao_system s) {
+             const nao_work w[] = {{s, 0, a.v, a.H, nullptr}, {s, 1, a.D, a.n, nullptr}};
+             for (int k = 0; k < 2; ++k)
+                 if (const nao_status st = nao_run_many(ctx, w, 2, NAO_FP64, nullptr, NAO_RUN_CAPTURE_GRAPH)) return st;
+             return NAO_OK;
+         }},
+    };
+    for (const Call& q : calls) {
+        auto once = [&](size_t limit, size_t* used, int* clusters) {
+            CHECK(nao_ctx_create(0, nullptr, limit, &ctx) == NAO_OK);
+            nao_system s = nullptr;
+            bool ok = false;
+            fake::cluster_launches = 0;
+            if (took(build(ctx, A, &s))) {
+                ok = took(q.f(s));
+                operations(s, a, NAO_FP64);  // whatever the call did: in range
+                nao_system_destroy(s);
+            }
+            if (clusters) *clusters = fake::cluster_launches;
+            if (used) CHECK(nao_ctx_memory(ctx, used, nullptr) == NAO_OK);
+            nao_ctx_destroy(ctx);
+            CHECK(no_faults(q.name));
+            return ok;
+        };
+        size_t most = 0;
+        CHECK(once(0, &most, nullptr));
+        most *= 2;
+        int accepted = 0, over_units = 0, over_clusters = 0;
+        const int steps = 40;
+        for (int k = 0; k <= steps; ++k) {
+            int clusters = 0;
+            const bool ok = once(most / 16 + (most - most / 16) / steps * k, nullptr, &clusters);
+            if (accepted && !ok) {
+                std::fprintf(stderr, "%s: accepted at budget step %d, refused at %d\n", q.name, k - 1, k);
+                std::exit(1);
+            }
+            accepted += ok;
+            if (ok && q.hamiltonian) (clusters ? over_clusters : over_units) += 1;
+        }
+        std::printf("%s: %d of %d budgets accept, %d with clusters\n", q.name, accepted, steps + 1, over_clusters);
+        CHECK(accepted > 0 && accepted <= steps);
+        if (q.hamiltonian) CHECK(over_units > 0 && over_clusters > 0);
+    }
+}
+
+// What a server does: one thread builds and releases systems of a context whose budget is tight, so
+// that clusters are given back, while another runs a system of it through a context of its own.
+void serve()
+{
+    const Structure A(8, 5, 3, 5.0, 75, 3, 2), B(8, 5, 3, 5.0, 60, 3, 3);
+    const Buffers a(A);
+    nao_ctx home = nullptr, slot = nullptr;
+    nao_system s = nullptr, t = nullptr;
+    CHECK(nao_ctx_create(0, nullptr, 0, &home) == NAO_OK);
+    CHECK(build(home, A, &s) == NAO_OK);
+    size_t one = 0;
+    CHECK(nao_ctx_memory(home, &one, nullptr) == NAO_OK);
+    nao_system_destroy(s);
+    nao_ctx_destroy(home);
+    int all = 0, clustered = 0;
+    for (int k = 0; k < 24; ++k) {
+        CHECK(nao_ctx_create(0, nullptr, one / 2 + one * k / 32, &home) == NAO_OK);
+        if (!took(build(home, A, &s))) {
+            nao_ctx_destroy(home);
+            continue;
+        }
+        CHECK(nao_ctx_create(0, nullptr, 0, &slot) == NAO_OK);
+        fake::cluster_launches = 0;
+        std::atomic<bool> stop{false};
+        std::atomic<int> runs{0};
+        std::thread builder([&]() {
+            while (runs < 2) std::this_thread::yield();
+            for (int j = 0; j < 3; ++j)
+                if (took(build(home, B, &t))) nao_system_destroy(t);
+            stop = true;
+        });
+        while (!stop || runs < 4) {
+            const nao_work w[] = {{s, 1, a.D, a.n, nullptr}, {s, 0, a.v, a.H, nullptr}};
+            CHECK(nao_run_many(slot, w, 2, NAO_FP64, nullptr, 0) == NAO_OK);
+            CHECK(nao_ctx_synchronize(slot) == NAO_OK);  // retires the plan
+            ++runs;
+        }
+        builder.join();
+        CHECK(no_faults("run beside builds"));
+        all += runs;
+        clustered += fake::cluster_launches;
+        nao_ctx_destroy(slot);
+        nao_system_destroy(s);
+        nao_ctx_destroy(home);
+        CHECK(no_faults("at the end"));
+    }
+    std::printf("%d runs, %d with clusters\n", all, clustered);
+    CHECK(clustered > 0 && clustered < all);
 }
 
 }  // namespace
@@ -261,6 +386,8 @@ int main(int argc, char** argv)
     if (what == "scratch") scratch();
     else if (what == "arrays") arrays();
     else if (what == "regroup") regroup();
+    else if (what == "budget") budget();
+    else if (what == "serve") serve();
     else return 2;
     std::printf("%s: all ok\n", what.c_str());
     return 0;

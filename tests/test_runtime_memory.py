@@ -12,20 +12,32 @@ CSRC = os.path.join(ROOT, "paper_1912_06636_amd", "csrc")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 
-@pytest.fixture(scope="module")
-def program(tmp_path_factory):
+def _build(directory, sanitizers):
     if shutil.which("g++") is None or not os.path.isdir(os.path.join(ROCM, "include", "hip")):
         pytest.skip("needs g++ and the HIP headers")
-    exe = str(tmp_path_factory.mktemp("runtime") / "runtime_check")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-ffp-contract=off", "-D__HIP_PLATFORM_AMD__",
-                    "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+    exe = str(directory / "runtime_check")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-ffp-contract=off", "-D__HIP_PLATFORM_AMD__"] + sanitizers + [
                     "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-isystem", os.path.join(ROCM, "include"),
                     os.path.join(ROOT, "tests", "native", "runtime_check.cpp"),
                     os.path.join(CSRC, "runtime.cpp"), os.path.join(CSRC, "plan.cpp"), "-o", exe, "-lpthread"], check=True)
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["scratch", "arrays", "regroup"])
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    return _build(tmp_path_factory.mktemp("runtime"), ["-fsanitize=undefined", "-fno-sanitize-recover=all"])
+
+
+@pytest.mark.parametrize("scenario", ["scratch", "arrays", "regroup", "budget", "serve"])
 def test_launches_stay_in_live_memory(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and scenario + ": all ok" in r.stdout, r.stdout + r.stderr[-4000:]
+
+
+def test_clusters_given_back_beside_a_run(tmp_path):
+    """The same beside another thread's launches, under ThreadSanitizer."""
+    r = subprocess.run([_build(tmp_path, ["-fsanitize=thread"]), "serve"], capture_output=True, text=True, timeout=300,
+                       env=dict(os.environ, TSAN_OPTIONS="halt_on_error=1"))
+    if "unexpected memory mapping" in r.stderr:
+        pytest.skip("ThreadSanitizer runtime does not support this kernel's memory layout")
+    assert r.returncode == 0 and "serve: all ok" in r.stdout, r.stdout + r.stderr[-4000:]
