@@ -322,6 +322,11 @@ nao_status nao_integrate_h_gga(nao_system sys, const double* v, const double* a,
  * a [n_points][3] (nullable: no field) in caller point order, both in in_space; H as for
  * nao_integrate_h.  precision: NAO_FP64 or NAO_FP32.  Needs device scratch for one L value per
  * basis value of a block (as much as the basis scratch).
+ * A v or a that is not finite at a point makes H_ij non-finite for every pair of functions that both
+ * reach the point (lie within their atom's largest cutoff); pairs of which neither does take nothing
+ * from it; other pairs of the same execution group may be non-finite too.  (For nao_integrate_h only
+ * the first holds.  A D_ij that is not finite makes n non-finite at every point that both functions
+ * reach, and may do so at others of the group.)
  * ------------------------------------------------------------------------------------- */
 nao_status nao_integrate_h_ks(nao_system sys, const double* v, const double* a, nao_memspace in_space,
                               nao_precision precision, double* H, nao_memspace H_space);

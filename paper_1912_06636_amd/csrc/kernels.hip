@@ -311,19 +311,19 @@ __global__ __launch_bounds__(64 * basis_waves(EX), basis_waves(EX) / 4) void bas
             Pair q{};
             const double dx = gptr(S->px)[p] - ax, dy = gptr(S->py)[p] - ay, dz = gptr(S->pz)[p] - az;
             q.d2 = dist2_exact(dx, dy, dz);
-            if (GGA || KS) q.hwv = 0.5 * gptr(sg.wv)[p];
-            if (field) {
-                gp<const double> wa = gptr(sg.wa) + 3 * p;
-                q.wax = wa[0], q.way = wa[1], q.waz = wa[2];
-            }
-            if (KS) q.qw = 0.25 * gptr(S->pw)[p];
-            if (LAPL) {
-                q.hwv = gptr(sg.wv)[p];
-                q.qw = 0.5 * gptr(S->pw)[p];
-            }
-            q.near = q.d2 < arc2;  // else every value of the pair is zero
+            q.near = q.d2 < arc2;  // else every value of the pair is zero, whatever w v is at the point
             q.z = 1.0;
             if (q.near) {
+                if (GGA || KS) q.hwv = 0.5 * gptr(sg.wv)[p];
+                if (field) {
+                    gp<const double> wa = gptr(sg.wa) + 3 * p;
+                    q.wax = wa[0], q.way = wa[1], q.waz = wa[2];
+                }
+                if (KS) q.qw = 0.25 * gptr(S->pw)[p];
+                if (LAPL) {
+                    q.hwv = gptr(sg.wv)[p];
+                    q.qw = 0.5 * gptr(S->pw)[p];
+                }
                 q.r = sqrt(q.d2);
                 if (q.r > 0.0) {
                     q.ir = 1.0 / q.r;
