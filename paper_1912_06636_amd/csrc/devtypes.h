@@ -13,6 +13,13 @@ constexpr int MAX_UNIT_POINTS = 256;  // largest execution group the contraction
 constexpr int NTILE_ROWS = 128;       // rows of a density item (8 row blocks)
 constexpr int MAX_CLUSTER_ROWS = 960; // largest Hamiltonian cluster (60 chunks: masks have 64 bits, and
                                       // four FP64 workgroups with w v of 960 rows fill a CU's LDS)
+// The density kernels address D by unsigned 32-bit byte offsets up to this many functions (N_b^2 * 8
+// bytes reach 2^32), and row by row beyond.
+constexpr int64_t D_OFFSET_MAX_BASIS = 23170;
+constexpr uint32_t d_offset(int row, int64_t n_basis, int col)
+{
+    return (uint32_t)row * (uint32_t)(n_basis * 8) + (uint32_t)col * 8u;
+}
 constexpr int MAX_SPLINE_LDS = 8192;  // doubles of spline table staged in LDS (64 KiB)
 
 // One structure's resident device state, as seen by the kernels.

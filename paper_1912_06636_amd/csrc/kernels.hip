@@ -1102,8 +1102,7 @@ __global__ __launch_bounds__(256, 4) void n_tiles(const DevSeg* __restrict__ seg
         // pairs of neighbours (atoms with an even number of functions) and D to lie within 32-bit offsets
         const int ldd8 = (int)(ldd * 8);
         const int cp = J0 + 2 * (lane & 31), gp0 = fn[min(cp, m - 1)], gp1 = fn[min(cp + 1, m - 1)];
-        const bool pairs = ldd <= 23170 && __all(cp + 1 >= m || gp1 == gp0 + 1);
-        const int voff_p = gp0 * 8;
+        const bool pairs = ldd <= D_OFFSET_MAX_BASIS && __all(cp + 1 >= m || gp1 == gp0 + 1);
         // else by 4 bytes per lane, half of a row per wave load: columns J0 + 32 q + lane / 2
         int voff_d[2];
         int64_t row_j[FULL || !F64 ? 2 : 1];  // byte offsets of those columns' own rows (diagonal tile)
@@ -1194,7 +1193,7 @@ __global__ __launch_bounds__(256, 4) void n_tiles(const DevSeg* __restrict__ seg
                         }
                     } else if (pairs && (TRI || !tile_diag(k0))) {
 #pragma unroll
-                        for (int t = 0; t < KR / 2; ++t) load16_to_lds(rd, bt + t * 1024, nx_k[t] * ldd8 + voff_p, 0);
+                        for (int t = 0; t < KR / 2; ++t) load16_to_lds(rd, bt + t * 1024, (int)d_offset(nx_k[t], ldd, gp0), 0);
                     } else {
 #pragma unroll
                         for (int t = 0; t < KR; ++t) {
