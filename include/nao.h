@@ -223,7 +223,7 @@ nao_status nao_system_set_h_tile(nao_system sys, int32_t h_tile);
  * D in `space`) at `precision` for each candidate (Hamiltonian tile width 64 / 128, execution
  * groups of 256 / 192 / 128 points; 64-wide only for split-BF16), keeps the fastest and
  * applies it.  The choice is cached in a JSON file ($NAO_TUNE_CACHE, default
- * $HOME/.cache/nao_tune.json) keyed by device, precision and the system's shape class
+ * $HOME/.cache/nao_tune.json) keyed by device, kernel version, precision and the system's shape class
  * (work-weighted mean list length and mean batch size of its octree batches); a cached class
  * is applied without timing unless NAO_TUNE_FORCE is set.  Outputs (nullable): the chosen
  * h_tile and group_max, and the best measured milliseconds (-1 when taken from the cache). */

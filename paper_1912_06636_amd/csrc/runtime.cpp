@@ -2561,7 +2561,11 @@ void tune_save(const std::map<std::string, std::pair<int, int>>& c)
     std::rename(tmp.c_str(), path.c_str());
 }
 
-// Shape class of a system: device, precision, work-weighted mean list length and mean batch
+// Raised with every change of kernels or execution forms that moves the best choice (2: the Hamiltonian
+// over clusters, which 128-wide tiles do without): choices cached by other kernels are not taken.
+constexpr int TUNE_VERSION = 2;
+
+// Shape class of a system: device, kernels, precision, work-weighted mean list length and mean batch
 // size of its batches (both bucketed), batch-size limit.
 std::string tune_key(nao_system s, nao_precision prec)
 {
@@ -2585,7 +2589,7 @@ std::string tune_key(nao_system s, nao_precision prec)
     const int mclass = bm > 0 ? (int)std::lround(bm2 / bm / 32.0) * 32 : 0;
     const int bclass = nb > 0 ? (int)std::lround(pts / nb / 8.0) * 8 : 0;
     static const char* pn[] = {"fp64", "fp32", "bf16x3", "bf16x6"};
-    return dev + "/" + pn[prec] + "/m" + std::to_string(mclass) + "/b" + std::to_string(bclass) + "/max" +
+    return dev + "/k" + std::to_string(TUNE_VERSION) + "/" + pn[prec] + "/m" + std::to_string(mclass) + "/b" + std::to_string(bclass) + "/max" +
            std::to_string(s->max_batch);
 }
 

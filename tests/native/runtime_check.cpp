@@ -3,6 +3,7 @@
 // allocations.  The argument names the scenario.  Built with sanitizers by tests/test_runtime_memory.py.
 #include <cmath>
 #include <cstdio>
+#include <fstream>
 #include <functional>
 #include <random>
 #include <thread>
@@ -377,6 +378,37 @@ void serve()
     CHECK(clustered > 0 && clustered < all);
 }
 
+// A choice cached by the kernels of an earlier version (no version in its key) is not taken.
+void tune(const char* path)
+{
+    const Structure A(3, 2, 2, 5.0, 40, 2, 4);
+    const Buffers a(A);
+    setenv("NAO_TUNE_CACHE", path, 1);
+    nao_ctx c = nullptr;
+    nao_system s = nullptr;
+    CHECK(nao_ctx_create(0, nullptr, 0, &c) == NAO_OK && build(c, A, &s) == NAO_OK);
+    int32_t tile = 0, groups = 0;
+    double ms = 0.0;
+    auto run = [&](uint32_t flags) {
+        CHECK(nao_system_autotune(s, NAO_FP64, a.v, a.D, NAO_MEM_DEVICE, flags, &tile, &groups, &ms) == NAO_OK);
+        return ms >= 0.0;  // timed, not taken from the file
+    };
+    CHECK(run(NAO_TUNE_FORCE) && !run(0));
+    std::ifstream in(path);
+    std::string line, key;
+    while (std::getline(in, line))
+        if (line.find("fp64") != std::string::npos) key = line.substr(line.find('"') + 1, line.rfind('"') - line.find('"') - 1);
+    CHECK(!key.empty());
+    const size_t v = key.find("/k");
+    if (v != std::string::npos) key.erase(v, key.find('/', v + 1) - v);
+    std::ofstream(path) << "{\n  \"" << key << "\": [128, 128]\n}\n";
+    CHECK(run(0) && tile == 64 && groups == 256);
+    CHECK(!run(0) && tile == 64);  // the new choice joined the file
+    nao_system_destroy(s);
+    nao_ctx_destroy(c);
+    CHECK(no_faults("autotune"));
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -388,6 +420,7 @@ int main(int argc, char** argv)
     else if (what == "regroup") regroup();
     else if (what == "budget") budget();
     else if (what == "serve") serve();
+    else if (what == "tune") tune(argc > 2 ? argv[2] : "/tmp/nao_tune_check.json");
     else return 2;
     std::printf("%s: all ok\n", what.c_str());
     return 0;

@@ -34,6 +34,11 @@ def test_launches_stay_in_live_memory(program, scenario):
     assert r.returncode == 0 and scenario + ": all ok" in r.stdout, r.stdout + r.stderr[-4000:]
 
 
+def test_cached_choices_of_other_kernels_are_not_taken(program, tmp_path):
+    r = subprocess.run([program, "tune", str(tmp_path / "tune.json")], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "tune: all ok" in r.stdout, r.stdout + r.stderr[-4000:]
+
+
 def test_clusters_given_back_beside_a_run(tmp_path):
     """The same beside another thread's launches, under ThreadSanitizer."""
     r = subprocess.run([_build(tmp_path, ["-fsanitize=thread"]), "serve"], capture_output=True, text=True, timeout=300,
