@@ -176,15 +176,19 @@ __device__ inline void ylm_grad_one(int lm, double x, double y, double z, double
 // Basis evaluation
 constexpr int BASIS_ATOMS = 192;   // atoms of a unit staged in LDS
 constexpr int BASIS_SHELLS = 128;  // shells of a system staged in LDS
-constexpr int BASIS_SLICES = 2, BASIS_SLICES_PAIRS = 4;  // work items per unit (point slices), rows staged or not
+constexpr int BASIS_SLICES = 2, BASIS_SLICES_PAIRS = 4;  // work items per unit (point slices), rows staged or not, or
+constexpr int BASIS_SLICES_PLANES = 8;                   // not and with gradients
 // waves of a workgroup, as many as its registers allow a CU
 constexpr int basis_waves(int extra)
 {
     return extra == EXTRA_NONE ? 16 : extra == EXTRA_GRAD ? 12 : 8;
 }
 constexpr int BASIS_LDS = 160 * 1024, BASIS_STATIC = 13312;  // LDS of a CU, and the kernel's static arrays
-constexpr int64_t BASIS_ROWS_UNITS = 512;
-constexpr int BASIS_ROWS_BYTES = 96;
+// The lines of launch_basis' rule
+constexpr double BASIS_ROWS_PAIRS = 4096, BASIS_ROWS_PAIRS_GRAD = 2816;  // atoms of all units together
+constexpr double BASIS_ROWS_BYTES = 96;        // bytes per atom and plane
+constexpr double BASIS_ROWS_GLOBAL_FN = 12;    // functions per atom, spline table in global memory
+constexpr double BASIS_PLANES_FN = 12;         // functions per atom, eight slices
 
 // N consecutive values of one lane, 16 bytes per store (values are only aligned to their own size).
 template <int N, typename T> __device__ inline void store_run(gp<T> dst, const T* v)
@@ -220,9 +224,9 @@ template <int N, typename T> __device__ inline void store_run(gp<T> dst, const T
 //   and three gradients: 9.7 ms at 2.9 TB/s; staged 5.1 ms at 5.4 TB/s, a fill writes 6.4).  One plane at
 //   a time, a wave's LDS being 64 pairs of one plane, which recomputes the radial functions per plane
 //   (8 % VALU before, the arithmetic is not what bounds).  Values alone: 3.9 to 3.0 ms (FP64, 14
-//   functions per atom), 7.0 to 4.4 ms (slab of 100, FP32, 29 functions).
+//   functions per atom), 7.0 to 4.4 ms (slab of 100, FP32, 28 functions).
 //   pairs: every lane stores its own.  Less work per value where the runs are short, see launch_basis.
-template <typename T, bool SPLINE_LDS, int EX>
+template <typename T, bool SPLINE_LDS, int EX, bool ROWS>
 __global__ __launch_bounds__(64 * basis_waves(EX), basis_waves(EX) / 4) void basis_kernel(const DevSeg* __restrict__ segs, int n_segs,
                                                                                            int64_t total, int lg, int slices, int spline_lds, int run)
 {
@@ -312,18 +316,20 @@ __global__ __launch_bounds__(64 * basis_waves(EX), basis_waves(EX) / 4) void bas
             const double dx = gptr(S->px)[p] - ax, dy = gptr(S->py)[p] - ay, dz = gptr(S->pz)[p] - az;
             q.d2 = dist2_exact(dx, dy, dz);
             q.near = q.d2 < arc2;  // else every value of the pair is zero, whatever w v is at the point
+            // (read for every pair: behind the test the reads would start later, 193 against 205 us)
+            if (GGA || KS) q.hwv = 0.5 * gptr(sg.wv)[p];
+            if (field) {
+                gp<const double> wa = gptr(sg.wa) + 3 * p;
+                q.wax = wa[0], q.way = wa[1], q.waz = wa[2];
+            }
+            if (KS) q.qw = 0.25 * gptr(S->pw)[p];
+            if (LAPL) {
+                q.hwv = gptr(sg.wv)[p];
+                q.qw = 0.5 * gptr(S->pw)[p];
+            }
+            if (!q.near) q.hwv = q.wax = q.way = q.waz = 0.0;
             q.z = 1.0;
             if (q.near) {
-                if (GGA || KS) q.hwv = 0.5 * gptr(sg.wv)[p];
-                if (field) {
-                    gp<const double> wa = gptr(sg.wa) + 3 * p;
-                    q.wax = wa[0], q.way = wa[1], q.waz = wa[2];
-                }
-                if (KS) q.qw = 0.25 * gptr(S->pw)[p];
-                if (LAPL) {
-                    q.hwv = gptr(sg.wv)[p];
-                    q.qw = 0.5 * gptr(S->pw)[p];
-                }
                 q.r = sqrt(q.d2);
                 if (q.r > 0.0) {
                     q.ir = 1.0 / q.r;
@@ -460,20 +466,27 @@ __global__ __launch_bounds__(64 * basis_waves(EX), basis_waves(EX) / 4) void bas
                 }
             }
         };
-        // A wave takes 16 neighbouring atoms of four points, plane by plane: every lane puts the values
-        // of its pair where they belong in the run of columns that the 16 atoms have in each row, and
-        // the runs are copied out by 16 bytes per lane from 64-byte boundaries
+        // A wave takes 16 neighbouring atoms of four points, plane by plane: every lane puts the values of
+        // its pair where they belong in the run of columns that the atoms have in each row, and the runs
+        // are copied out by 16 bytes per lane from 64-byte boundaries.  Where the unit's atoms split evenly
+        // into parts of 12 or fewer the wave takes such a part of five or more points: 16 left 11 of 16
+        // lanes idle with five atoms (6-atom slab, FP64, a value and three gradients: 400 to 264 us; 45
+        // atoms: 4.6 to 4.0 ms).
         auto rows_staged = [&]() {
             constexpr int V = 16 / (int)sizeof(T), SEG = 64 / (int)sizeof(T);
             typedef T vec __attribute__((ext_vector_type(V)));
             const int lane = tid & 63, wave = uni(tid >> 6), waves = (int)blockDim.x >> 6;
             T* win = reinterpret_cast<T*>(lds_spline + spline_lds) + wave * 4 * run;
-            const int parts = (na + 15) >> 4, tasks = (row1 - row0 + 3) / 4 * parts;
+            const int parts = (na + 15) >> 4, even = (na + parts - 1) / max(parts, 1), per = even <= 12 ? max(even, 1) : 16;
+            // a row of the window: `per` atoms from up to a segment on (run is that of 16)
+            const int wrow = ((run - SEG) / 16 * per + V - 1) / V * V + SEG, R = min(64 / per, 4 * run / wrow);
+            const int rl = lane / per, al = lane - rl * per;
+            const int tasks = (row1 - row0 + R - 1) / R * parts;
             for (int task = wave; task < tasks; task += waves) {
-                const int part = task % parts, rowb = row0 + 4 * (task / parts);
-                const int c0 = uni(s_aspc[16 * part][1]), c1 = part + 1 < parts ? uni(s_aspc[16 * part + 16][1]) : u.m;
-                const int ai = 16 * part + (lane & 15), rl = lane >> 4;
-                const bool mine = ai < na && rowb + rl < row1;
+                const int part = task % parts, rowb = row0 + R * (task / parts);
+                const int c0 = uni(s_aspc[per * part][1]), c1 = part + 1 < parts ? uni(s_aspc[per * part + per][1]) : u.m;
+                const int ai = per * part + al;
+                const bool mine = ai < na && rl < R && rowb + rl < row1;
                 const int pl = min(rowb + rl, row1 - 1), aj = min(ai, na - 1);
                 const Pair q = pair_at(u.point_begin + pl, s_atom[aj][0], s_atom[aj][1], s_atom[aj][2], s_atom[aj][3]);
                 const int sp = s_aspc[aj][0];
@@ -483,7 +496,7 @@ __global__ __launch_bounds__(64 * basis_waves(EX), basis_waves(EX) / 4) void bas
                     gp<T> dst = plane(decltype(which)::value) + (int64_t)rowb * u.ld + c0;
                     // values by which a row's run starts past a 64-byte boundary
                     auto past = [&](int r) { return (int)(reinterpret_cast<uintptr_t>(dst + (int64_t)r * u.ld) / sizeof(T)) & (SEG - 1); };
-                    T* at = win + rl * run + past(rl) + (s_aspc[aj][1] - c0);
+                    T* at = win + rl * wrow + past(rl) + (s_aspc[aj][1] - c0);
                     Knot g{};
                     for (int j = sh0; j < sh1; ++j) {
                         const int sh = s_shell[j], l = sh & 3;
@@ -501,12 +514,13 @@ __global__ __launch_bounds__(64 * basis_waves(EX), basis_waves(EX) / 4) void bas
                     // the wave's own LDS writes are performed before its later reads (in order)
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                     __builtin_amdgcn_wave_barrier();
-                    const int n_rows = min(4, row1 - rowb);
-                    for (int r = 0; r < n_rows; ++r) {
+                    const int n_rows = min(R, row1 - rowb);
+                    // row r by `step` lanes, the first of them at its value i0
+                    auto copy_row = [&](int r, int i0, int step) {
                         const int b0 = past(r), b1 = b0 + c1 - c0;
-                        const T* src = win + r * run;
+                        const T* src = win + r * wrow;
                         gp<T> to = dst + (int64_t)r * u.ld - b0;
-                        for (int i = lane * V; i < b1; i += 64 * V) {
+                        for (int i = i0; i < b1; i += step) {
                             vec x = *reinterpret_cast<const vec*>(src + i);
                             if (!any) x = vec(T(0));
                             if (i >= b0 && i + V <= b1) {
@@ -517,15 +531,26 @@ __global__ __launch_bounds__(64 * basis_waves(EX), basis_waves(EX) / 4) void bas
                                     if (i + k >= b0 && i + k < b1) to[i + k] = x[k];
                             }
                         }
+                    };
+                    if (R <= 4) {
+                        for (int r = 0; r < n_rows; ++r) copy_row(r, lane * V, 64 * V);
+                    } else {  // short runs: 2, 4, ... rows at a time
+                        int lg = 2;
+                        while (lg < 6 && V << lg < c1 - c0 + SEG - V) ++lg;
+                        for (int r = lane >> lg; r < n_rows; r += 64 >> lg) copy_row(r, (lane & ((1 << lg) - 1)) * V, V << lg);
                     }
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                 });
             }
         };
-        if (run > 0 && staged) rows_staged();
-        else if (staged) pairs(std::true_type{});
-        else pairs(std::false_type{});
+        if constexpr (ROWS) {
+            if (staged) rows_staged();
+            else pairs(std::false_type{});
+        } else {
+            if (staged) pairs(std::true_type{});
+            else pairs(std::false_type{});
+        }
         if (slice == slices - 1 && u.n_rows > u.n_points) {  // padding rows of a cluster's unit
             const int64_t z0 = (int64_t)u.n_points * u.ld, z1 = (int64_t)u.n_rows * u.ld;
             for (int64_t q = z0 + tid; q < z1; q += blockDim.x) each_plane([&](auto which) { plane(decltype(which)::value)[q] = T(0); });
@@ -552,11 +577,11 @@ static unsigned grid_for(int64_t n, int lg, int64_t max_grid)
     return (unsigned)span;
 }
 
-hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int spline_lds, int max_fn, double mean_fn,
+hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int spline_lds, const BasisShape& shape,
                         bool fp32_out, hipStream_t st, int64_t max_grid, int extra)
 {
     if (n_units <= 0 || n_segs <= 0) return hipSuccess;
-    if (n_units > 0x7ffffff0 / BASIS_SLICES_PAIRS || spline_lds < 0 || spline_lds > MAX_SPLINE_LDS || max_fn < 0)
+    if (n_units > 0x7ffffff0 / BASIS_SLICES_PLANES || spline_lds < 0 || spline_lds > MAX_SPLINE_LDS || shape.max_fn < 0)
         return hipErrorInvalidValue;
     if (extra != EXTRA_NONE && extra != EXTRA_GRAD && extra != EXTRA_GGA_L && extra != EXTRA_KS_L &&
         extra != EXTRA_GRAD_H)
@@ -570,17 +595,32 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
     }
     const int cus = std::max(1, n_cu.load());
     // Rows are staged where the LDS left by the spline table holds those of four waves or more, and
-    // where their longer way pays: not in launches too small to fill the chip (8 atoms, 130 units: 14 us
-    // by pairs, 20 staged), not for short runs (9.5 FP64 functions per atom: 0.25 against 0.28 ms; 14
-    // FP32 ones: 0.72 against 0.77; 14 FP64 ones: 1.5 by rows against 2.2), and not for L in FP32, two
-    // planes with the arithmetic of four (2.0 against 2.3 ms).
+    // where their longer way pays (all figures FP64 unless said; rows against pairs, us):
+    //   - not in launches of little work, counted by the atoms of all units.  Values: 5 atoms and 28
+    //     functions each, 510 units (2,500 atoms) 66 against 46; 8 atoms, 472 units (3,700) 54 against
+    //     58; 10 atoms, 590 units (5,600) 68 against 73; 14 atoms 114 against 136.  L: 3,700 121 against
+    //     112, 10,700 266 against 258, 45-atom slab 2.5 ms against 4.0.  Gradients gain earlier: 2,100
+    //     atoms 119 against 124, 3,700 163 against 227, but 2,500 of 28 functions 187 against 140;
+    //   - not for short runs: 5 functions per atom 100 against 63, 9.5 of them 0.28 ms against 0.25; 14
+    //     FP32 ones 0.77 against 0.72;
+    //   - with the table in global memory and 14 functions per atom FP32 gradients gain all the same:
+    //     36 radial functions, 60 atoms, 2.9 ms against 4.2;
+    //   - not for L in FP32, two planes with the arithmetic of four (2.3 ms against 2.0).
+    // Pairs with gradients store a plane at a time.  Where four slices of every unit are more than run
+    // at once, eight leave a shorter last round (4 atoms 72 to 63, 6 atoms 150 to 124; where they all
+    // run at once 27 against 31 with eight), but not where an atom's functions are few (5: 139 against 150).
     const int size = fp32_out ? sizeof(float) : sizeof(double), most = basis_waves(extra);
     const int64_t table = 8 * (int64_t)spline_lds, room = BASIS_LDS - BASIS_STATIC - table;
-    const int64_t run = 16 * (int64_t)max_fn + 64 / size;
+    const int64_t run = 16 * (int64_t)shape.max_fn + 64 / size;
     const int fit = (int)std::min<int64_t>(most, room / (4 * run * size));
-    const bool rows = fit >= 4 && n_units >= BASIS_ROWS_UNITS && mean_fn * size >= BASIS_ROWS_BYTES &&
+    const bool grad = extra == EXTRA_GRAD || extra == EXTRA_GRAD_H;
+    const double pairs = n_units * shape.mean_atoms, bytes = shape.mean_fn * size;
+    const bool rows = fit >= 4 && pairs >= (grad ? BASIS_ROWS_PAIRS_GRAD : BASIS_ROWS_PAIRS) &&
+                      (bytes >= BASIS_ROWS_BYTES || (grad && table == 0 && shape.mean_fn >= BASIS_ROWS_GLOBAL_FN)) &&
                       !(fp32_out && (extra == EXTRA_GGA_L || extra == EXTRA_KS_L));
-    const int waves = rows ? fit : 4, slices = rows ? BASIS_SLICES : BASIS_SLICES_PAIRS;
+    const int64_t at_once = cus * std::max<int64_t>(1, std::min<int64_t>(most / 4, BASIS_LDS / (table + BASIS_STATIC)));
+    const bool fine = grad && shape.mean_fn >= BASIS_PLANES_FN && n_units * BASIS_SLICES_PAIRS > at_once;
+    const int waves = rows ? fit : 4, slices = rows ? BASIS_SLICES : fine ? BASIS_SLICES_PLANES : BASIS_SLICES_PAIRS;
     const int64_t n_items = n_units * slices;
     const size_t lds = (size_t)(table + (rows ? waves * 4 * run * size : 0));
     // as many workgroups as fit the chip at once (LDS and registers): each takes many items and
@@ -595,18 +635,14 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
     if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
     const uint64_t bit = 1ull << (dev & 63);
     if (!(attrs_set.load() & bit)) {
-#define NAO_BASIS_FNS(TT)                                                                                          \
-    reinterpret_cast<const void*>(&basis_kernel<TT, true, EXTRA_NONE>),                                          \
-        reinterpret_cast<const void*>(&basis_kernel<TT, false, EXTRA_NONE>),                                     \
-        reinterpret_cast<const void*>(&basis_kernel<TT, true, EXTRA_GRAD>),                                      \
-        reinterpret_cast<const void*>(&basis_kernel<TT, false, EXTRA_GRAD>),                                     \
-        reinterpret_cast<const void*>(&basis_kernel<TT, true, EXTRA_GGA_L>),                                     \
-        reinterpret_cast<const void*>(&basis_kernel<TT, false, EXTRA_GGA_L>),                                    \
-        reinterpret_cast<const void*>(&basis_kernel<TT, true, EXTRA_KS_L>),                                      \
-        reinterpret_cast<const void*>(&basis_kernel<TT, false, EXTRA_KS_L>),                                     \
-        reinterpret_cast<const void*>(&basis_kernel<TT, true, EXTRA_GRAD_H>),                                  \
-        reinterpret_cast<const void*>(&basis_kernel<TT, false, EXTRA_GRAD_H>)
-        const void* fns[] = {NAO_BASIS_FNS(float), NAO_BASIS_FNS(double)};
+#define NAO_BASIS_FNS(TT, EE)                                                                                     \
+    reinterpret_cast<const void*>(&basis_kernel<TT, true, EE, true>), reinterpret_cast<const void*>(&basis_kernel<TT, false, EE, true>), \
+        reinterpret_cast<const void*>(&basis_kernel<TT, true, EE, false>), reinterpret_cast<const void*>(&basis_kernel<TT, false, EE, false>)
+#define NAO_BASIS_TYPE(TT)                                                                                        \
+    NAO_BASIS_FNS(TT, EXTRA_NONE), NAO_BASIS_FNS(TT, EXTRA_GRAD), NAO_BASIS_FNS(TT, EXTRA_GGA_L),                 \
+        NAO_BASIS_FNS(TT, EXTRA_KS_L), NAO_BASIS_FNS(TT, EXTRA_GRAD_H)
+        const void* fns[] = {NAO_BASIS_TYPE(float), NAO_BASIS_TYPE(double)};
+#undef NAO_BASIS_TYPE
 #undef NAO_BASIS_FNS
         for (const void* f : fns) {
             const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, BASIS_LDS - BASIS_STATIC);
@@ -614,10 +650,15 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
         }
         attrs_set.fetch_or(bit);
     }
-#define NAO_BASIS_LAUNCH(TT, EE)                                                                                 \
-    do {                                                                                                       \
-        if (staged) hipLaunchKernelGGL((basis_kernel<TT, true, EE>), g, b, lds, st, segs_dev, n_segs, n_items, 2, slices, spline_lds, rows ? (int)run : 0); \
-        else hipLaunchKernelGGL((basis_kernel<TT, false, EE>), g, b, lds, st, segs_dev, n_segs, n_items, 2, slices, 0, rows ? (int)run : 0);  \
+#define NAO_BASIS_ROWS(TT, SS, EE)                                                                                \
+    do {                                                                                                          \
+        if (rows) hipLaunchKernelGGL((basis_kernel<TT, SS, EE, true>), g, b, lds, st, segs_dev, n_segs, n_items, 2, slices, spline_lds, (int)run); \
+        else hipLaunchKernelGGL((basis_kernel<TT, SS, EE, false>), g, b, lds, st, segs_dev, n_segs, n_items, 2, slices, spline_lds, 0); \
+    } while (0)
+#define NAO_BASIS_LAUNCH(TT, EE)                                                                                  \
+    do {                                                                                                          \
+        if (staged) NAO_BASIS_ROWS(TT, true, EE);                                                                 \
+        else NAO_BASIS_ROWS(TT, false, EE);                                                                       \
     } while (0)
 #define NAO_BASIS_EXTRA(TT)                                           \
     do {                                                              \
@@ -631,16 +672,9 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
     else NAO_BASIS_EXTRA(double);
 #undef NAO_BASIS_EXTRA
 #undef NAO_BASIS_LAUNCH
+#undef NAO_BASIS_ROWS
     return hipGetLastError();
 }
-
-
-
-
-
-
-
-
 
 // ------------------------------------------------------------------------------------------
 // Contractions with one value per lane per operand: FP64 (v_mfma_f64_16x16x4f64) and FP32

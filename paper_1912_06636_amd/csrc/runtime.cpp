@@ -336,8 +336,7 @@ struct nao_system_s {
     std::vector<int64_t> res_off;   // element offset of every block
     DevArray d_phi_res;
     int spline_lds = 0;  // doubles of spline table staged in LDS by the basis kernel (0 = not staged)
-    int max_fn = 0;      // functions of the atom that has most
-    double mean_fn() const { return basis.n_atoms > 0 ? (double)basis.n_basis / (double)basis.n_atoms : 0.0; }
+    BasisShape shape;    // what the rule of the basis launch asks for
 };
 
 nao_status grow_scratch(nao_ctx c, size_t elems);
@@ -628,6 +627,7 @@ nao_status build_groups(nao_system_s* s)
     if (cur.unit_count) s->blocks.push_back(cur);
     item_first.push_back((int64_t)hitems.size());
     s->n_units = (int64_t)units.size();
+    s->shape.mean_atoms = units.empty() ? 0.0 : (double)uat.size() / (double)units.size();
     s->n_h_items = (int64_t)hitems.size();
     s->n_n_items = (int64_t)nitems.size();
     if (hitems.size() > 0x7fffffffu) return (set_err(c, "too many work items"), NAO_ERR_INTERNAL);
@@ -1133,18 +1133,23 @@ nao_status many_enqueue(nao_ctx c, ManyPlan* m)
     }
     const DevSeg* d = m->d_segs.as<DevSeg>();
     // stage the spline tables in LDS only if every system's table fits
-    int lds = 0, max_fn = 0;
+    int lds = 0;
+    BasisShape shape;
     int64_t n_fn = 0, n_at = 0;
+    double units = 0.0, unit_atoms = 0.0;
     bool all_fit = true;
     for (const nao_work& w : m->entries) {
         all_fit = all_fit && w.sys->spline_lds > 0;
         lds = std::max(lds, w.sys->spline_lds);
-        max_fn = std::max(max_fn, w.sys->max_fn);
+        shape.max_fn = std::max(shape.max_fn, w.sys->shape.max_fn);
         n_fn += w.sys->basis.n_basis;
         n_at += w.sys->basis.n_atoms;
+        units += (double)w.sys->n_units;
+        unit_atoms += (double)w.sys->n_units * w.sys->shape.mean_atoms;
     }
     if (!all_fit) lds = 0;
-    const double mean_fn = n_at > 0 ? (double)n_fn / (double)n_at : 0.0;
+    shape.mean_fn = n_at > 0 ? (double)n_fn / (double)n_at : 0.0;
+    shape.mean_atoms = units > 0.0 ? unit_atoms / units : 0.0;
     // with overlap, as in run_blocks: chunk k's basis launch on the second stream after the
     // contraction of chunk k - 2 (the last reader of its buffer), its contractions after it (the
     // fork and join are events, which a captured graph records as dependencies)
@@ -1159,12 +1164,12 @@ nao_status many_enqueue(nao_ctx c, ManyPlan* m)
         if (ovl) {
             if (ki >= 2) HIP_TRY(c, hipStreamWaitEvent(c->stream2, c->ev_done[buf], 0));
             LAUNCH_ON(c, f32 ? "basis_f32" : "basis_f64", c->stream2,
-                      launch_basis(d + k.all_off, (int)k.all_n, k.units, lds, max_fn, mean_fn, f32, c->stream2, grid));
+                      launch_basis(d + k.all_off, (int)k.all_n, k.units, lds, shape, f32, c->stream2, grid));
             HIP_TRY(c, hipEventRecord(c->ev_ready[buf], c->stream2));
             HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_ready[buf], 0));
         } else if (staged) {
             LAUNCH(c, f32 ? "basis_f32" : "basis_f64",
-                   launch_basis(d + k.all_off, (int)k.all_n, k.units, lds, max_fn, mean_fn, f32, c->stream, grid));
+                   launch_basis(d + k.all_off, (int)k.all_n, k.units, lds, shape, f32, c->stream, grid));
         }
         for (int t = 0; t < 2; ++t)
             if (k.h_n[t])
@@ -1611,7 +1616,8 @@ static nao_status setup_system(nao_system s, const double* xyz, const double* w)
     std::vector<double> spl = spline_knots(B);
     s->spline_lds = spl.size() <= (size_t)MAX_SPLINE_LDS ? (int)spl.size() : 0;
     for (size_t a = 0; a + 1 < B.atom_first.size(); ++a)
-        s->max_fn = std::max(s->max_fn, (int)(B.atom_first[a + 1] - B.atom_first[a]));
+        s->shape.max_fn = std::max(s->shape.max_fn, (int)(B.atom_first[a + 1] - B.atom_first[a]));
+    s->shape.mean_fn = B.n_atoms > 0 ? (double)B.n_basis / (double)B.n_atoms : 0.0;
     nao_status st;
 #define UP(arr, vec) \
     if ((st = upload(c, s->arr, (vec).data(), (vec).size() * sizeof((vec)[0]))) != NAO_OK) return st
@@ -1885,7 +1891,9 @@ static nao_status eval_basis_once(nao_system s, int64_t b0, int64_t b1, double* 
     g.unit_count = (int64_t)du.size();
     g.unit_prefix = 0;
     if ((st = upload(c, t_seg, &g, sizeof(DevSeg))) != NAO_OK) return cleanup(), st;
-    hipError_t e = launch_basis(t_seg.as<DevSeg>(), 1, (int64_t)du.size(), s->spline_lds, s->max_fn, s->mean_fn(), false, c->stream);
+    BasisShape shape = s->shape;
+    shape.mean_atoms = (double)uat.size() / (double)du.size();
+    hipError_t e = launch_basis(t_seg.as<DevSeg>(), 1, (int64_t)du.size(), s->spline_lds, shape, false, c->stream);
     if (e == hipSuccess && phi_space == NAO_MEM_HOST)
         e = hipMemcpyAsync(phi, out, (size_t)total * sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -1951,7 +1959,7 @@ static nao_status run_blocks(nao_system s, bool ham, nao_precision prec, const d
     if (res && evaluate) s->res_kind = -1;  // marked valid only once every block is enqueued
     st = block_loop(
         c, segs.size(), ovl, staged && evaluate ? (f32 ? "basis_f32" : "basis_f64") : nullptr, kname(ham, prec),
-        [&](size_t k, hipStream_t q) { return launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->max_fn, s->mean_fn(), f32, q); },
+        [&](size_t k, hipStream_t q) { return launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->shape, f32, q); },
         [&](size_t k) {
             return ham ? launch_h(mode, dseg + k, 1, segs[k].item_count, c->stream, 0, wide ? 128 : TILE)
                        : launch_n(mode, dseg + k, 1, segs[k].item_count, c->stream);
@@ -2075,7 +2083,7 @@ nao_status nao_integrate_h_noalloc(nao_system s, const double* v, nao_precision 
         HIP_TRY(c, hipMemcpyAsync(base, segs.data(), segs.size() * sizeof(DevSeg), hipMemcpyHostToDevice, c->stream));
         const DevSeg* dseg = reinterpret_cast<const DevSeg*>(base);
         for (size_t k = 0; k < segs.size(); ++k) {
-            HIP_TRY(c, launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->max_fn, s->mean_fn(), prec != NAO_FP64, c->stream));
+            HIP_TRY(c, launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->shape, prec != NAO_FP64, c->stream));
             HIP_TRY(c, launch_h(mode, dseg + k, 1, segs[k].item_count, c->stream, 0, TILE));
         }
     }
@@ -2219,7 +2227,7 @@ static nao_status integrate_h_with_l(nao_system s, const double* v, const double
         const char* hname = ks ? (f32 ? "hks_f32" : "hks_f64") : (f32 ? "hgga_f32" : "hgga_f64");
         st = block_loop(
             c, segs.size(), ovl, bname, hname,
-            [&](size_t k, hipStream_t q) { return launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->max_fn, s->mean_fn(), f32, q, 0, extra); },
+            [&](size_t k, hipStream_t q) { return launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->shape, f32, q, 0, extra); },
             [&](size_t k) { return launch_h_gga(mode, dseg + k, 1, segs[k].item_count, c->stream); });
         if (st != NAO_OK) return st;
     }
@@ -2328,7 +2336,7 @@ static nao_status update_density_gradient_once(nao_system s, const double* D, na
         st = block_loop(
             c, segs.size(), ovl, f32 ? "basis_grad_f32" : "basis_grad_f64", f32 ? "ngrad_f32" : "ngrad_f64",
             [&](size_t k, hipStream_t q) {
-                return launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->max_fn, s->mean_fn(), f32, q, 0, EXTRA_GRAD);
+                return launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->shape, f32, q, 0, EXTRA_GRAD);
             },
             [&](size_t k) { return launch_n_grad(mode, dseg + k, 1, segs[k].item_count, c->stream); });
         if (st != NAO_OK) return st;
@@ -2420,7 +2428,7 @@ static nao_status pulay_forces_once(nao_system s, const double* D, const double*
         st = block_loop(
             c, segs.size(), ovl, f32 ? "basis_gradlap_f32" : "basis_gradlap_f64", f32 ? "nforce_f32" : "nforce_f64",
             [&](size_t k, hipStream_t q) {
-                return launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->max_fn, s->mean_fn(), f32, q, 0, EXTRA_GRAD_H);
+                return launch_basis(dseg + k, 1, segs[k].unit_count, s->spline_lds, s->shape, f32, q, 0, EXTRA_GRAD_H);
             },
             [&](size_t k) { return launch_n_force(mode, dseg + k, 1, segs[k].item_count, c->stream); });
         if (st != NAO_OK) return st;

@@ -154,7 +154,7 @@ inline void check_n(const DevSeg* segs, int n, bool f32, int planes, bool force)
 // ------------------------------------------------------------------------------ launchers
 namespace nao {
 
-hipError_t launch_basis(const DevSeg* s, int n, int64_t, int, int, double, bool f32, hipStream_t, int64_t, int extra)
+hipError_t launch_basis(const DevSeg* s, int n, int64_t, int, const BasisShape&, bool f32, hipStream_t, int64_t, int extra)
 {
     return fake::run([=] { fake::check_basis(s, n, f32, extra); });
 }
