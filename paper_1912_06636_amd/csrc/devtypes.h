@@ -22,6 +22,10 @@ constexpr uint32_t d_offset(int row, int64_t n_basis, int col)
 }
 constexpr int MAX_SPLINE_LDS = 8192;  // doubles of spline table staged in LDS (64 KiB)
 
+// Copies of the force sums fb[N_b][3], one after the other, one per XCD: the items of a small structure
+// all add to the same few of them, whose lines else move between the L2s of the XCDs.
+constexpr int64_t FORCE_COPIES = 8;
+
 // One structure's resident device state, as seen by the kernels.
 struct DevSys {
     const double* px;                  // batch-ordered point coordinates [n_points]
@@ -117,7 +121,7 @@ struct DevSeg {
     double* gn;              // density gradient [n_points][3], caller order
     const double* wa;        // batch-ordered w*a, 3 per point (Hamiltonian with a vector field)
     const double* Q;         // energy-weighted density matrix (forces), row-major, ld = n_basis
-    double* fb;              // per-function force accumulator [n_basis][3] (forces)
+    double* fb;              // per-function force accumulators [FORCE_COPIES][n_basis][3] (forces)
     int64_t ld;              // n_basis
     int64_t unit_begin, unit_count, unit_prefix;
     int64_t item_begin, item_count, item_prefix;
@@ -161,8 +165,8 @@ hipError_t launch_h_gga(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n
 // fb[j] += sum_p grad phi_pj [((w v Phi - w lap Phi / 2) D)_pj - w_p (Phi Q)_pj]; gphi and hphi
 // from the basis launch with EXTRA_GRAD_H, wv batch-ordered w*v.
 hipError_t launch_n_force(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t n_items, hipStream_t st);
-// F[a] = 2 sum over the functions i of atom a (atom_first[a] <= i < atom_first[a + 1]) of fb[i].
-hipError_t launch_force_atoms(const double* fb, const int64_t* atom_first, int64_t n_atoms, double* F,
+// F[a] = 2 sum over the functions i of atom a (atom_first[a] <= i < atom_first[a + 1]) and the copies of fb[i].
+hipError_t launch_force_atoms(const double* fb, const int64_t* atom_first, int64_t n_atoms, int64_t n_basis, double* F,
                               hipStream_t st);
 hipError_t launch_wa(const double* pw, const int32_t* perm, const double* a_caller, double* wa, int64_t n_points,
                      hipStream_t st);

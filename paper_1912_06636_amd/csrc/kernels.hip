@@ -1383,7 +1383,7 @@ __global__ __launch_bounds__(256, 4) void n_tiles(const DevSeg* __restrict__ seg
             __syncthreads();
             const int k = threadIdx.x / TILE, col = threadIdx.x % TILE;
             if (k < 3 && J0 + col < m)
-                gadd(gptr(sg.fb) + 3 * (int64_t)fn[J0 + col] + k, red[k * TILE + col]);
+                gadd(gptr(sg.fb) + 3 * (v_ % FORCE_COPIES * ldd + fn[J0 + col]) + k, red[k * TILE + col]);
         } else {
             constexpr int NQ = KIND == NK_GRADIENT ? 4 : 1;
             const char* ph = reinterpret_cast<const char*>(phi);
@@ -1551,7 +1551,7 @@ __global__ __launch_bounds__(1024) void n_force_f32(const DevSeg* __restrict__ s
         if (tid < 3 * TILE) {
             const int k = tid / TILE, col = tid % TILE;
             if (J0 + col < m)
-                gadd(gptr(sg.fb) + 3 * (int64_t)fn[J0 + col] + k,
+                gadd(gptr(sg.fb) + 3 * (v_ % FORCE_COPIES * ldd + fn[J0 + col]) + k,
                      (red[k][0][col] + red[k][1][col]) + (red[k][2][col] + red[k][3][col]));
         }
         __syncthreads();  // red is rewritten by the next item
@@ -2012,24 +2012,31 @@ __global__ void fill_kernel(double* __restrict__ p, int64_t n, double value)
         p[i] = value;
 }
 
-__global__ void force_atoms_kernel(const double* __restrict__ fb, const int64_t* __restrict__ atom_first,
-                                   int64_t n_atoms, double* __restrict__ F)
+// One wave per atom: the copies' sums of its functions, then over the lanes.
+__global__ __launch_bounds__(64) void force_atoms_kernel(const double* __restrict__ fb, const int64_t* __restrict__ atom_first,
+                                                         int64_t n_basis, double* __restrict__ F)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 3 * n_atoms) return;
-    const int64_t a = i / 3, k = i - 3 * a;
-    double v = 0.0;
-    for (int64_t j = atom_first[a]; j < atom_first[a + 1]; ++j) v += fb[3 * j + k];
-    F[i] = 2.0 * v;
+    const int64_t a = blockIdx.x, j0 = atom_first[a], nf = atom_first[a + 1] - j0;
+    double v[3] = {};
+    for (int64_t e = threadIdx.x; e < FORCE_COPIES * nf; e += 64) {
+        const double* f = fb + 3 * (e % FORCE_COPIES * n_basis + j0 + e / FORCE_COPIES);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k] += f[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) v[k] += __shfl_xor(v[k], m);
+        if (threadIdx.x == 0) F[3 * a + k] = 2.0 * v[k];
+    }
 }
 
-hipError_t launch_force_atoms(const double* fb, const int64_t* atom_first, int64_t n_atoms, double* F,
+hipError_t launch_force_atoms(const double* fb, const int64_t* atom_first, int64_t n_atoms, int64_t n_basis, double* F,
                               hipStream_t st)
 {
     if (n_atoms <= 0) return hipSuccess;
-    const int64_t blocks = (3 * n_atoms + 255) / 256;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(force_atoms_kernel, dim3((unsigned)blocks), dim3(256), 0, st, fb, atom_first, n_atoms, F);
+    if (n_atoms > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(force_atoms_kernel, dim3((unsigned)n_atoms), dim3(64), 0, st, fb, atom_first, n_basis, F);
     return hipGetLastError();
 }
 

@@ -2389,7 +2389,8 @@ static nao_status pulay_forces_once(nao_system s, const double* D, const double*
             vd = s->d_v.as<double>();
         }
     }
-    if ((st = ensure(c, s->d_fb, std::max<int64_t>(1, 3 * nb) * sizeof(double))) != NAO_OK) return st;
+    const int64_t fb_len = 3 * nb * FORCE_COPIES;
+    if ((st = ensure(c, s->d_fb, std::max<int64_t>(1, fb_len) * sizeof(double))) != NAO_OK) return st;
     if ((st = ensure(c, s->d_atom_first, (na + 1) * sizeof(int64_t))) != NAO_OK) return st;
     HIP_TRY(c, hipMemcpyAsync(s->d_atom_first.p, s->basis.atom_first.data(), (na + 1) * sizeof(int64_t),
                               hipMemcpyHostToDevice, c->stream));
@@ -2398,7 +2399,7 @@ static nao_status pulay_forces_once(nao_system s, const double* D, const double*
         if ((st = ensure(c, s->d_F, std::max<int64_t>(1, 3 * na) * sizeof(double))) != NAO_OK) return st;
         Fd = s->d_F.as<double>();
     }
-    LAUNCH(c, "fill", launch_fill(s->d_fb.as<double>(), 3 * nb, 0.0, c->stream));
+    LAUNCH(c, "fill", launch_fill(s->d_fb.as<double>(), fb_len, 0.0, c->stream));
     LAUNCH(c, "wv", launch_wv(s->d_pw.as<double>(), s->d_perm.as<int32_t>(), vd, s->d_wv.as<double>(), n, c->stream));
     const Mode mode = exec_mode(c, prec);
     const bool f32 = prec != NAO_FP64;
@@ -2433,7 +2434,7 @@ static nao_status pulay_forces_once(nao_system s, const double* D, const double*
             [&](size_t k) { return launch_n_force(mode, dseg + k, 1, segs[k].item_count, c->stream); });
         if (st != NAO_OK) return st;
     }
-    LAUNCH(c, "force_atoms", launch_force_atoms(s->d_fb.as<double>(), s->d_atom_first.as<int64_t>(), na, Fd, c->stream));
+    LAUNCH(c, "force_atoms", launch_force_atoms(s->d_fb.as<double>(), s->d_atom_first.as<int64_t>(), na, nb, Fd, c->stream));
     if (F_space == NAO_MEM_HOST && na > 0)
         HIP_TRY(c, hipMemcpyAsync(F, Fd, 3 * na * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     if (F_space == NAO_MEM_HOST || in_space == NAO_MEM_HOST) HIP_TRY(c, hipStreamSynchronize(c->stream));

@@ -123,7 +123,7 @@ inline void check_n(const DevSeg* segs, int n, bool f32, int planes, bool force)
     for (int s = 0; s < n; ++s) {
         const DevSeg g = segs[s];
         if (!system_ok(g) || !range(g.D, g.ld * g.ld * 8, "D")) return;
-        if (force ? !range(g.fb, g.ld * 24, "force sums") || !range(g.Q, g.ld * g.ld * 8, "Q") : !range(g.n, g.sys->n_points * 8, "n")) return;
+        if (force ? !range(g.fb, FORCE_COPIES * g.ld * 24, "force sums") || !range(g.Q, g.ld * g.ld * 8, "Q") : !range(g.n, g.sys->n_points * 8, "n")) return;
         if (planes == 3 && !force && !range(g.gn, g.sys->n_points * 24, "grad n")) return;
         if (force && f32) {
             if (!range(static_cast<const NItem*>(g.items) + g.item_begin, g.item_count * sizeof(NItem), "column tiles")) return;
@@ -178,10 +178,10 @@ hipError_t launch_n_force(Mode m, const DevSeg* s, int n, int64_t, hipStream_t)
 {
     return fake::run([=] { fake::check_n(s, n, m != MODE_FP64, 3, true); });
 }
-hipError_t launch_force_atoms(const double* fb, const int64_t* first, int64_t n, double* F, hipStream_t)
+hipError_t launch_force_atoms(const double* fb, const int64_t* first, int64_t n, int64_t nb, double* F, hipStream_t)
 {
     return fake::run([=] {
-        if (fake::range(first, (n + 1) * 8, "atom_first")) fake::range(fb, first[n] * 24, "force sums");
+        if (fake::range(first, (n + 1) * 8, "atom_first")) fake::range(fb, FORCE_COPIES * first[n] * 24, "force sums");
         fake::range(F, 24 * n, "F");
     });
 }

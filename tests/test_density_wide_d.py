@@ -17,6 +17,19 @@ CSRC = os.path.join(ROOT, "paper_1912_06636_amd", "csrc")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 
+def far_structure(n_atoms):
+    """Atoms of 10 functions far from the points and from each other, but for the first two and the last
+    two: (basis, basis of those four, points, weights, the four's functions in the whole basis)."""
+    near = np.array([0, 1, n_atoms - 2, n_atoms - 1])
+    xyz = np.zeros((n_atoms, 3))
+    xyz[:, 0] = 200.0 + 10.0 * np.arange(n_atoms)
+    xyz[near] = [[0.0, 0.0, 0.0], [1.7, 0.4, 0.0], [0.3, 2.1, 0.2], [1.1, 0.9, 1.6]]
+    full = g.make_basis(xyz, np.zeros(n_atoms, np.int32), [(0, 1, 1, 1)], [4.0], 11, 5)
+    four = dict(full, atom_xyz=xyz[near].copy(), atom_species=np.zeros(4, np.int32))
+    X = np.random.default_rng(1).normal(0.8, 1.4, size=(700, 3))
+    return full, four, X, np.full(len(X), 0.1), (10 * near[:, None] + np.arange(10)).ravel()
+
+
 @pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(os.path.join(ROCM, "include", "hip")), reason="needs g++ and the HIP headers")
 def test_offsets(tmp_path):
     exe = str(tmp_path / "offset_check")
@@ -33,18 +46,9 @@ def test_offsets(tmp_path):
 def test_density_of_a_wide_matrix(n_atoms):
     import torch
     from paper_1912_06636_amd import nao
-    shells, rcut = [(0, 1, 1, 1)], [4.0]
-    near = np.array([0, 1, n_atoms - 2, n_atoms - 1])
-    xyz = np.zeros((n_atoms, 3))
-    xyz[:, 0] = 200.0 + 10.0 * np.arange(n_atoms)  # far from the points and from each other
-    xyz[near] = [[0.0, 0.0, 0.0], [1.7, 0.4, 0.0], [0.3, 2.1, 0.2], [1.1, 0.9, 1.6]]
-    full = g.make_basis(xyz, np.zeros(n_atoms, np.int32), shells, rcut, 11, 5)
-    four = dict(full, atom_xyz=xyz[near].copy(), atom_species=np.zeros(4, np.int32))
-    X = np.random.default_rng(1).normal(0.8, 1.4, size=(700, 3))
-    w = np.full(len(X), 0.1)
+    full, four, X, w, fn = far_structure(n_atoms)
     C = np.random.default_rng(2).normal(size=(40, 9))
     D4 = C @ C.T
-    fn = (10 * near[:, None] + np.arange(10)).ravel()
     nb = 10 * n_atoms
     D = torch.zeros(nb, nb, dtype=torch.float64, device="cuda")
     ix = torch.from_numpy(fn).cuda()
