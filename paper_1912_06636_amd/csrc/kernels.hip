@@ -132,17 +132,8 @@ __device__ inline void ylm_l(double x, double y, double z, double* Y)
     }
 }
 
-// All harmonics up to lmax (<= 3), index l^2 + l + m.
-__device__ inline void real_ylm(double x, double y, double z, int lmax, double* Y)
-{
-    ylm_l<0>(x, y, z, Y);
-    if (lmax >= 1) ylm_l<1>(x, y, z, Y + 1);
-    if (lmax >= 2) ylm_l<2>(x, y, z, Y + 4);
-    if (lmax >= 3) ylm_l<3>(x, y, z, Y + 9);
-}
-
-// Partial derivatives of the harmonic polynomials of real_ylm (index lm) with respect to the
-// three components of the unit vector, taken as independent variables.
+// Partial derivatives of the harmonic polynomials of ylm_l (index lm = l^2 + l + m) with respect to
+// the three components of the unit vector, taken as independent variables.
 __device__ inline void ylm_grad_one(int lm, double x, double y, double z, double* g)
 {
     const double c1 = 0.48860251190291992, c2a = 1.0925484305920792, c2b = 0.31539156525252005;
@@ -217,7 +208,8 @@ template <int N, typename T> __device__ inline void store_run(gp<T> dst, const T
 // unit's points.  The unit's atoms (position, cutoff, species, first column) and the system's shell
 // tables (l, radial function and its parameters) are staged in LDS first, so that a pair's chain of
 // table lookups stays on chip; a unit or system larger than the staging arrays reads them from global
-// memory instead.  Two ways to the rows of the block:
+// memory instead.  Two ways to the rows of the block, in kernels of their own (ROWS; in one kernel they
+// cost each other registers, up to 5 % of the pairs' time):
 //   rows_staged: the values go to LDS first, in the place that they have in the row, and leave in full
 //   64-byte segments.  A lane that stores its own pair's values makes an L2 request of 12 to 22 bytes
 //   out of every 16-byte store, and the L2s, not HBM, bound the launch (100-atom block, FP64, a value

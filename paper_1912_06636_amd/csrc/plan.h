@@ -77,8 +77,8 @@ void make_groups(const HostBasis& b, const std::vector<int64_t>& batch_ptr,
                  std::vector<int32_t>& unit_cols);
 
 // Hamiltonian clusters: runs of consecutive units contracted as one, over the union of their
-// atoms.  Every unit's rows start at a multiple of 16 within its cluster (row_off), the last ones up
-// to the next multiple are padding.
+// atoms.  Every unit's rows start at a multiple of 16 within its cluster, the last ones up to the
+// next multiple are padding.
 struct Cluster {
     int32_t unit_begin, unit_count;
     int32_t n_rows;       // a multiple of 16

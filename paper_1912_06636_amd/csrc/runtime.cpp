@@ -428,8 +428,11 @@ void drop_clusters(nao_system_s* s)
 // of a cluster adds its 4,096 sums to H once for two to four units, whose sums would otherwise
 // each cost as many atomics (they bound the FP32 kernel: a 100-atom slab's 14.4 ms fell to 7.5
 // without them).  Columns of the same cluster differ in how many points reach them, which the
-// masks turn into work left out.  Only while enough items remain to fill the chip: 256 CUs take
-// 1,024 tile pairs at a time.
+// masks turn into work left out.  Only while CLUSTER_ITEMS tile pairs remain: 256 CUs take 1,024 at a
+// time, and six rounds keep the last one short.  The line is on the safe side: basis and Hamiltonian
+// launches over units and over clusters of 512 and 960 rows take 203, 193 and 209 us at 3,200 tile
+// pairs of units (12 atoms, FP64), 625, 538 and 552 at 10,300 (27 atoms), 1,200, 1,126 and 1,135 at
+// 27,400 (34 atoms); FP32 at 59,400 (slab of 30) 1,989, 1,437 and 1,420.
 nao_status build_clusters(nao_system_s* s, const std::vector<Unit>& units, const std::vector<int32_t>& uat)
 {
     nao_ctx c = s->ctx;
