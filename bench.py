@@ -380,6 +380,8 @@ def main():
         if "n_" + sfx in cands:
             t = cands["n_" + sfx][1]
             roofline["kernels"]["n_" + sfx]["frac_half_credit"] = round(credit_n_half / (t * 1e-3) / 1e12 / peak, 4)
+            if dom == "n_" + sfx:  # the full credit counts a product of which half is executed
+                roofline["frac_half_credit"] = roofline["kernels"][dom]["frac_half_credit"]
         roofline["kernels_alone"] = {k: {"launches": c, "ms": round(t, 3),
                                          "frac": round(credit[k] / (t * 1e-3) / 1e12 / peak, 4)}
                                      for k, (c, t) in prof_alone.items() if k in credit}
