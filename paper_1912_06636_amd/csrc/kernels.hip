@@ -73,6 +73,8 @@ static int xcd_run(int64_t total, int most)
 }
 constexpr int HRUN = 5;  // tile pairs (28 of a unit with 7 tiles): 16 to 64 measure alike, 512 a few percent slower
 constexpr int NRUN = 4;  // column tiles (7 to 11 of a unit): runs of 4 cost the 375-atom slab 4 %, 64 gain nothing
+constexpr int FRUN = 2;  // of the FP32 forces, whose workgroups hold a CU alone: runs of 4 or 8 measure alike,
+                         // 16 cost a 64-atom slab on a small grid 10 % (3.46 against 3.13 ms)
 
 // Lane-uniform values kept in scalar registers: FP64 and FP32 MFMA do not issue beside vector
 // instructions (measured: 69 and 31 cycles per MFMA alone, about 3 more for every vector
@@ -1971,7 +1973,7 @@ hipError_t launch_n_force(Mode mode, const DevSeg* segs_dev, int n_segs, int64_t
 {
     if (n_items <= 0 || n_segs <= 0) return hipSuccess;
     if (n_items > 0x7ffffff0) return hipErrorInvalidValue;
-    const int lg = xcd_run(n_items, NRUN);
+    const int lg = xcd_run(n_items, mode == MODE_FP32 ? FRUN : NRUN);
     const dim3 g(grid_for(n_items, lg, 0)), b(1024);
     switch (mode) {
     case MODE_FP64: hipLaunchKernelGGL((n_tiles<double, NK_FORCE>), g, dim3(256), 0, st, segs_dev, n_segs, n_items, lg); break;
