@@ -178,10 +178,11 @@ constexpr int basis_waves(int extra)
 }
 constexpr int BASIS_LDS = 160 * 1024, BASIS_STATIC = 13312;  // LDS of a CU, and the kernel's static arrays
 // The lines of launch_basis' rule
-constexpr double BASIS_ROWS_PAIRS = 4096, BASIS_ROWS_PAIRS_GRAD = 2816;  // atoms of all units together
-constexpr double BASIS_ROWS_BYTES = 96;        // bytes per atom and plane
+constexpr double BASIS_ROWS_PAIRS = 4096, BASIS_ROWS_PAIRS_GRAD = 2048, BASIS_ROWS_PAIRS_FEW = 2816;  // atoms of all units together
+constexpr double BASIS_ROWS_FEW_ATOMS = 6;     // atoms per unit
+constexpr double BASIS_ROWS_BYTES = 96, BASIS_ROWS_BYTES_GRAD = 64;  // bytes per atom and plane
 constexpr double BASIS_ROWS_GLOBAL_FN = 12;    // functions per atom, spline table in global memory
-constexpr double BASIS_PLANES_FN = 12;         // functions per atom, eight slices
+constexpr double BASIS_PLANES_FN = 8;          // functions per atom, eight slices
 
 // N consecutive values of one lane, 16 bytes per store (values are only aligned to their own size).
 template <int N, typename T> __device__ inline void store_run(gp<T> dst, const T* v)
@@ -593,24 +594,27 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
     //   - not in launches of little work, counted by the atoms of all units.  Values: 5 atoms and 28
     //     functions each, 510 units (2,500 atoms) 66 against 46; 8 atoms, 472 units (3,700) 54 against
     //     58; 10 atoms, 590 units (5,600) 68 against 73; 14 atoms 114 against 136.  L: 3,700 121 against
-    //     112, 10,700 266 against 258, 45-atom slab 2.5 ms against 4.0.  Gradients gain earlier: 2,100
-    //     atoms 119 against 124, 3,700 163 against 227, but 2,500 of 28 functions 187 against 140;
+    //     112, 10,700 266 against 258, 45-atom slab 2.5 ms against 4.0.  Gradients gain earlier: 1,100
+    //     atoms 84 against 64, 2,100 119 against 124, 2,300 189 against 207, 3,700 163 against 227; units
+    //     of 5 atoms later: 2,500 187 against 140, 3,000 264 against 319;
     //   - not for short runs: 5 functions per atom 100 against 63, 9.5 of them 0.28 ms against 0.25; 14
-    //     FP32 ones 0.77 against 0.72;
+    //     FP32 ones 0.77 against 0.72.  Gradients: 5 functions 115 against 72, 9.5 0.80 ms against 1.37;
+    //     14 FP32 ones 402 against 299;
     //   - with the table in global memory and 14 functions per atom FP32 gradients gain all the same:
     //     36 radial functions, 60 atoms, 2.9 ms against 4.2;
     //   - not for L in FP32, two planes with the arithmetic of four (2.3 ms against 2.0).
     // Pairs with gradients store a plane at a time.  Where four slices of every unit are more than run
-    // at once, eight leave a shorter last round (4 atoms 72 to 63, 6 atoms 150 to 124; where they all
-    // run at once 27 against 31 with eight), but not where an atom's functions are few (5: 139 against 150).
+    // at once, eight leave a shorter last round (4 atoms 72 to 63, FP32 594 to 526 for 9.5 functions per
+    // atom; where they all run at once 27 against 31 with eight), but not for 5 functions (139 against 150).
     const int size = fp32_out ? sizeof(float) : sizeof(double), most = basis_waves(extra);
     const int64_t table = 8 * (int64_t)spline_lds, room = BASIS_LDS - BASIS_STATIC - table;
     const int64_t run = 16 * (int64_t)shape.max_fn + 64 / size;
     const int fit = (int)std::min<int64_t>(most, room / (4 * run * size));
     const bool grad = extra == EXTRA_GRAD || extra == EXTRA_GRAD_H;
     const double pairs = n_units * shape.mean_atoms, bytes = shape.mean_fn * size;
-    const bool rows = fit >= 4 && pairs >= (grad ? BASIS_ROWS_PAIRS_GRAD : BASIS_ROWS_PAIRS) &&
-                      (bytes >= BASIS_ROWS_BYTES || (grad && table == 0 && shape.mean_fn >= BASIS_ROWS_GLOBAL_FN)) &&
+    const double least = !grad ? BASIS_ROWS_PAIRS : shape.mean_atoms < BASIS_ROWS_FEW_ATOMS ? BASIS_ROWS_PAIRS_FEW : BASIS_ROWS_PAIRS_GRAD;
+    const bool rows = fit >= 4 && pairs >= least &&
+                      (bytes >= (grad ? BASIS_ROWS_BYTES_GRAD : BASIS_ROWS_BYTES) || (grad && table == 0 && shape.mean_fn >= BASIS_ROWS_GLOBAL_FN)) &&
                       !(fp32_out && (extra == EXTRA_GGA_L || extra == EXTRA_KS_L));
     const int64_t at_once = cus * std::max<int64_t>(1, std::min<int64_t>(most / 4, BASIS_LDS / (table + BASIS_STATIC)));
     const bool fine = grad && shape.mean_fn >= BASIS_PLANES_FN && n_units * BASIS_SLICES_PAIRS > at_once;
