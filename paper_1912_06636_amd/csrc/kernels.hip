@@ -169,8 +169,8 @@ __device__ inline void ylm_grad_one(int lm, double x, double y, double z, double
 // Basis evaluation
 constexpr int BASIS_ATOMS = 192;   // atoms of a unit staged in LDS
 constexpr int BASIS_SHELLS = 128;  // shells of a system staged in LDS
-constexpr int BASIS_SLICES = 2, BASIS_SLICES_PAIRS = 4;  // work items per unit (point slices), rows staged or not, or
-constexpr int BASIS_SLICES_PLANES = 8;                   // not and with gradients
+// work items per unit (point slices): rows staged, pairs, and pairs with gradients
+constexpr int BASIS_SLICES = 2, BASIS_SLICES_PAIRS = 4, BASIS_SLICES_PLANES = 8;
 // waves of a workgroup, as many as its registers allow a CU
 constexpr int basis_waves(int extra)
 {
@@ -178,8 +178,8 @@ constexpr int basis_waves(int extra)
 }
 constexpr int BASIS_LDS = 160 * 1024, BASIS_STATIC = 13312;  // LDS of a CU, and the kernel's static arrays
 // The lines of launch_basis' rule
-constexpr double BASIS_ROWS_PAIRS = 4096, BASIS_ROWS_PAIRS_GRAD = 2048, BASIS_ROWS_PAIRS_FEW = 2816;  // atoms of all units together
-constexpr double BASIS_ROWS_FEW_ATOMS = 6;     // atoms per unit
+constexpr double BASIS_ROWS_PAIRS = 4096, BASIS_ROWS_PAIRS_GRAD = 2048;  // atoms of all units together
+constexpr double BASIS_ROWS_FEW_ATOMS = 6, BASIS_ROWS_PAIRS_FEW = 2816;  // atoms per unit, and of all then (gradients)
 constexpr double BASIS_ROWS_BYTES = 96, BASIS_ROWS_BYTES_GRAD = 64;  // bytes per atom and plane
 constexpr double BASIS_ROWS_GLOBAL_FN = 12;    // functions per atom, spline table in global memory
 constexpr double BASIS_PLANES_FN = 8;          // functions per atom, eight slices
@@ -576,7 +576,7 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
                         bool fp32_out, hipStream_t st, int64_t max_grid, int extra)
 {
     if (n_units <= 0 || n_segs <= 0) return hipSuccess;
-    if (n_units > 0x7ffffff0 / BASIS_SLICES_PLANES || spline_lds < 0 || spline_lds > MAX_SPLINE_LDS || shape.max_fn < 0)
+    if (n_units > 0x7ffffff0 / BASIS_SLICES_PAIRS || spline_lds < 0 || spline_lds > MAX_SPLINE_LDS || shape.max_fn < 0)
         return hipErrorInvalidValue;
     if (extra != EXTRA_NONE && extra != EXTRA_GRAD && extra != EXTRA_GGA_L && extra != EXTRA_KS_L &&
         extra != EXTRA_GRAD_H)
@@ -617,7 +617,8 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
                       (bytes >= (grad ? BASIS_ROWS_BYTES_GRAD : BASIS_ROWS_BYTES) || (grad && table == 0 && shape.mean_fn >= BASIS_ROWS_GLOBAL_FN)) &&
                       !(fp32_out && (extra == EXTRA_GGA_L || extra == EXTRA_KS_L));
     const int64_t at_once = cus * std::max<int64_t>(1, std::min<int64_t>(most / 4, BASIS_LDS / (table + BASIS_STATIC)));
-    const bool fine = grad && shape.mean_fn >= BASIS_PLANES_FN && n_units * BASIS_SLICES_PAIRS > at_once;
+    const bool fine = grad && shape.mean_fn >= BASIS_PLANES_FN && n_units * BASIS_SLICES_PAIRS > at_once &&
+                      n_units <= 0x7ffffff0 / BASIS_SLICES_PLANES;
     const int waves = rows ? fit : 4, slices = rows ? BASIS_SLICES : fine ? BASIS_SLICES_PLANES : BASIS_SLICES_PAIRS;
     const int64_t n_items = n_units * slices;
     const size_t lds = (size_t)(table + (rows ? waves * 4 * run * size : 0));
