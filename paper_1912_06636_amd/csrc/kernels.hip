@@ -178,7 +178,7 @@ constexpr int basis_waves(int extra)
 }
 constexpr int BASIS_LDS = 160 * 1024, BASIS_STATIC = 13312;  // LDS of a CU, and the kernel's static arrays
 // The lines of launch_basis' rule
-constexpr double BASIS_ROWS_PAIRS = 4096, BASIS_ROWS_PAIRS_GRAD = 2048;  // atoms of all units together
+constexpr double BASIS_ROWS_PAIRS = 4096, BASIS_ROWS_PAIRS_GRAD = 1536;  // atoms of all units together
 constexpr double BASIS_ROWS_FEW_ATOMS = 6, BASIS_ROWS_PAIRS_FEW = 2816;  // atoms per unit, and of all then (gradients)
 constexpr double BASIS_ROWS_BYTES = 96, BASIS_ROWS_BYTES_GRAD = 64;  // bytes per atom and plane
 constexpr double BASIS_ROWS_GLOBAL_FN = 12;    // functions per atom, spline table in global memory
@@ -595,8 +595,8 @@ hipError_t launch_basis(const DevSeg* segs_dev, int n_segs, int64_t n_units, int
     //     functions each, 510 units (2,500 atoms) 66 against 46; 8 atoms, 472 units (3,700) 54 against
     //     58; 10 atoms, 590 units (5,600) 68 against 73; 14 atoms 114 against 136.  L: 3,700 121 against
     //     112, 10,700 266 against 258, 45-atom slab 2.5 ms against 4.0.  Gradients gain earlier: 1,100
-    //     atoms 84 against 64, 2,100 119 against 124, 2,300 189 against 207, 3,700 163 against 227; units
-    //     of 5 atoms later: 2,500 187 against 140, 3,000 264 against 319;
+    //     atoms 84 against 64, 1,700 88 against 116, 2,300 189 against 207, 3,700 163 against 227; units
+    //     of 5 atoms later: 1,900 188 against 172, 2,500 187 against 140, 3,000 264 against 319;
     //   - not for short runs: 5 functions per atom 100 against 63, 9.5 of them 0.28 ms against 0.25; 14
     //     FP32 ones 0.77 against 0.72.  Gradients: 5 functions 115 against 72, 9.5 0.80 ms against 1.37;
     //     14 FP32 ones 402 against 299;
@@ -1604,9 +1604,9 @@ __device__ inline int bf16_slot(int row, int g) { return 8 * (g ^ ((row >> 1) & 
 // one run and are split into bf16 parts at the stash.  The FP32 sums move into FP64 after every
 // chunk, so that a cluster's sums are those of its units and reach H by a half to a quarter of the
 // atomics; chunks that one of the tiles does not reach are left out.  FP64 atomics into the upper
-// triangle of H.  The splitting binds it (10 vector and 6 scalar instructions beside every MFMA), then the atomics: three
+// triangle of H.  The splitting binds it (8 vector and 6 scalar instructions beside every MFMA), then the atomics: three
 // workgroups per CU, two values per conversion, scalar row addresses and w v; 64-atom block, three
-// parts, units alone 3.03 ms before and 2.81 after, over clusters 2.10 (MFMA busy 15 % at 2.81).
+// parts, units alone 3.03 ms before and 2.81 after (MFMA busy 15 %), over clusters 2.10 (23 %).
 template <int NS>
 __global__ __launch_bounds__(256, 3) void h_kernel_bf16(const DevSeg* __restrict__ segs, int n_segs, int64_t total, int lg)
 {
