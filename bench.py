@@ -34,9 +34,9 @@ KERNELS_SRC = os.path.join(ROOT, "paper_1912_06636_amd", "csrc", "kernels.hip")
 # --no-cpu-baseline --no-plain --serve-seconds 0 --calibrate-copy 1024", each counter scaled by
 # its reading of the 1 GiB plain copy made in that run.  Valid only for the kernel source it was
 # taken on (sha256).
-TRAFFIC = {"sha256": "c2c7a9de02dbfb3c597dac27a00b80bb0f5384c1f912a099fc7f171c45fffe70",
+TRAFFIC = {"sha256": "0112e96e7f22670348124fee38bc3b37c6d01b6ad3cc93fcc923dc9bd45c3ee2",
            "workload": "slab375", "precision": "fp64", "h_tile": 64, "group_max": 256,
-           "bytes_per_launch": {"n_f64": 15.686e9, "h_f64": 9.871e9}}
+           "bytes_per_launch": {"n_f64": 15.658e9, "h_f64": 9.836e9}}
 WORKLOADS = {
     "slab375": (4, "375-atom layered slab, 28 NAO/atom (10,500 basis functions, l<=3, 6 A cutoff), "
                    "60x434 grid/atom = 9,765,000 points, octree batches <= 256"),
